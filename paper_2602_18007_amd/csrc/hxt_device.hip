@@ -94,12 +94,19 @@ int env_int(const char *name, int dflt)
     return (s && *s) ? std::atoi(s) : dflt;
 }
 
-// Cache hints.  Tensors are streamed once: non-temporal.  The packed buffer is written by
-// pack and read back soon after (by the wire, or by unpack here): it stays cacheable while it
-// can still be in the 256 MB last-level cache when it is re-read, and becomes non-temporal
-// too for larger messages (measured: 56 MiB pack->unpack 21.1 us per kernel cacheable vs 22.7
-// non-temporal; 1.7 GB 625 us vs 586 us).  HXT_NT_USER / HXT_NT_PACKED (0/1) override.
-constexpr uint64_t kCacheablePackedLimit = uint64_t(128) << 20;
+// Cache hints, chosen per launch from the bytes it moves (HXT_NT_USER / HXT_NT_PACKED, 0 or 1, override).
+//   Packed side, stores: written through to the last-level cache, where the wire or hxt_unpack reads them
+//     (store_packed16).  Better than non-temporal stores up to 1 GiB (pack + unpack with sums: 128 MiB 81 against 92 us,
+//     288 MiB 171 against 197, 512 MiB 338 against 356); above, nothing of the buffer's start is left when it is read
+//     and non-temporal stores are as good or better (1.7 GB pack + accumulate 1407 against 1401 us).
+//   Packed side, loads: cacheable up to 64 MiB, non-temporal above, where keeping what has been read only pushes out
+//     what is still to be read (128 MiB 82.5 -> 80.7 us, 256 MiB 160 -> 152, 288 MiB 219 -> 171; 64 MiB 43.8 against 44.1).
+//   Tensor side, loads: cacheable while the tensors, the packed buffer and the receiver's tensors fit the 256 MB
+//     last-level cache together (messages up to 32 MiB: 16 MiB 15.1 -> 14.0 us, 32 MiB 24.9 -> 23.4), non-temporal
+//     above (112 MiB 76 -> 71 us).  Stores: non-temporal (a tensor is written once, whole).
+constexpr uint64_t kCacheablePackedLoads = uint64_t(64) << 20;
+constexpr uint64_t kWrittenThroughLimit = uint64_t(1) << 30;
+constexpr uint64_t kCacheableTensorLoads = uint64_t(32) << 20;
 
 struct Tuning {
     int nt_user, nt_packed;        // -1 = automatic
@@ -111,22 +118,25 @@ const Tuning &tuning()
     return t;
 }
 
-inline bool packed_nontemporal(uint64_t packed_bytes)
+// hint: HXT_OPT_PACKED_HINT of the plan that decides; bytes: packed bytes of the launch; load: it reads the packed side.
+inline bool packed_nontemporal(int hint, uint64_t bytes, bool load)
 {
-    const int o = tuning().nt_packed;
-    return o >= 0 ? o != 0 : packed_bytes > kCacheablePackedLimit;
+    return hint >= 0 ? hint != 0 : bytes > (load ? kCacheablePackedLoads : kWrittenThroughLimit);
 }
 
-inline bool packed_nontemporal(const hxt_plan_t &pl)
+inline bool packed_nontemporal(const hxt_plan_t &pl, bool load) { return packed_nontemporal(pl.nt_packed, pl.p.C * pl.p.B, load); }
+
+// load: the launch reads the tensors and writes the packed buffer.
+inline bool user_nontemporal(uint64_t bytes, bool load)
 {
-    return pl.nt_packed >= 0 ? pl.nt_packed != 0 : packed_nontemporal(pl.p.C * pl.p.B);
+    const int o = tuning().nt_user;
+    return o >= 0 ? o != 0 : !load || bytes > kCacheableTensorLoads;
 }
 
 // Calls f.template operator()<NTU, NTP>() for the chosen cache hints.
 template <typename F>
-void with_hints(bool nt_packed, F &&f)
+void with_hints(bool nt_user, bool nt_packed, F &&f)
 {
-    const bool nt_user = tuning().nt_user != 0;
     if (nt_user) {
         if (nt_packed) f.template operator()<true, true>();
         else f.template operator()<true, false>();
@@ -134,6 +144,13 @@ void with_hints(bool nt_packed, F &&f)
         if (nt_packed) f.template operator()<false, true>();
         else f.template operator()<false, false>();
     }
+}
+
+// The hints of one plan's launch.
+template <bool UNPACK, typename F>
+void with_hints(const hxt_plan_t &pl, F &&f)
+{
+    with_hints(user_nontemporal(pl.p.C * pl.p.B, !UNPACK), packed_nontemporal(pl, UNPACK), f);
 }
 
 // The streaming copies are launched with 32 KiB of (unused) dynamic LDS per workgroup, which caps residency at 5
@@ -153,17 +170,18 @@ inline size_t residency_cap_lds()
 }
 
 template <int DIR, bool CSUM>
-void launch_uniform(const UniformArgs &a, uint32_t tiles, bool nt_packed, hipStream_t st)
+void launch_uniform(const UniformArgs &a, uint32_t tiles, uint64_t bytes, int hint, hipStream_t st)
 {
     const size_t lds = residency_cap_lds();
-    with_hints(nt_packed, [&]<bool NTU, bool NTP>() { k_uniform<DIR, CSUM, NTU, NTP><<<tiles, kThreads, lds, st>>>(a); });
+    // (a mixed launch has one hint for both directions: as for loads, which it wants cacheable while they are small)
+    with_hints(user_nontemporal(bytes, DIR == DIR_PACK), packed_nontemporal(hint, bytes, DIR != DIR_PACK), [&]<bool NTU, bool NTP>() { k_uniform<DIR, CSUM, NTU, NTP><<<tiles, kThreads, lds, st>>>(a); });
 }
 
 template <bool UNPACK, bool CSUM>
 void launch_contig(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const SumCtx &cx,
                    hipStream_t st)
 {
-    with_hints(packed_nontemporal(pl), [&]<bool NTU, bool NTP>() {
+    with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
         k_contig<UNPACK, CSUM, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, b, packed, cx);
     });
 }
@@ -172,7 +190,7 @@ template <bool UNPACK, bool CSUM>
 void launch_rows(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const SumCtx &cx,
                  hipStream_t st)
 {
-    with_hints(packed_nontemporal(pl), [&]<bool NTU, bool NTP>() {
+    with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
         k_rows<UNPACK, CSUM, NTU, NTP><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
                                                                      g.tensor_base, b, packed, cx);
     });
@@ -192,7 +210,7 @@ void launch_transpose(const hxt_plan_t &pl, uint32_t first, uint32_t count, int 
         default: k_transpose<uint64_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
         }
     };
-    if (packed_nontemporal(pl)) go.template operator()<true>();
+    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
     else go.template operator()<false>();
 }
 
@@ -211,7 +229,7 @@ void launch_transpose_span(const hxt_plan_t &pl, uint32_t first, uint32_t count,
         default: k_transpose_span<uint64_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
         }
     };
-    if (packed_nontemporal(pl)) go.template operator()<true>();
+    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
     else go.template operator()<false>();
 }
 
@@ -230,7 +248,7 @@ void launch_generic(const hxt_plan_t &pl, uint32_t first, uint32_t count, uint32
         default: k_generic<uint64_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, cx); break;
         }
     };
-    if (packed_nontemporal(pl)) go.template operator()<true>();
+    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
     else go.template operator()<false>();
 }
 
@@ -365,7 +383,7 @@ int run_copy(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums,
         a.n = 1;
         a.it[0] = UniformItem{p.geom, base, packed, cx, 0, UNPACK};
         if (reinterpret_cast<uintptr_t>(base) % 16 == 0)
-            launch_uniform<UNPACK ? DIR_UNPACK : DIR_PACK, CSUM>(a, p.geom.ntiles, packed_nontemporal(pl), st);
+            launch_uniform<UNPACK ? DIR_UNPACK : DIR_PACK, CSUM>(a, p.geom.ntiles, p.C * p.B, pl.nt_packed, st);
         else                                             // element aligned only: narrower accesses on the tensor side
             k_uniform_any<UNPACK, CSUM><<<p.geom.ntiles, kThreads, 0, st>>>(a);
         HXT_HIP(hipGetLastError());
@@ -391,7 +409,7 @@ int run_copy(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums,
             k_rows_any<UNPACK, CSUM><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
                                                                    g.tensor_base, b, packed, cx);
         } else if (g.kernel == K_ROWS_SPLIT) {
-            if (packed_nontemporal(pl))
+            if (packed_nontemporal(pl, UNPACK))
                 k_rows_split<UNPACK, CSUM, true><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
                                                                                g.tensor_base, b, packed, cx);
             else
@@ -432,7 +450,6 @@ int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t 
         if (rc != HXT_OK) return rc;
         cx.sum_bits = pl.sum_bits_table;
     }
-    const bool ntp = packed_nontemporal(pl);
     if (p.uniform) {
         const TensorPlan &tp = p.tensors[p.uniform_tensor];
         UniformArgs a;
@@ -443,7 +460,7 @@ int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t 
         a.it[0] = UniformItem{p.geom, static_cast<uint8_t *>(ptrs[p.uniform_tensor]), packed, cx, 0,
                               tp.dtype == HXT_F32 ? 1u : 0u};
         if (reinterpret_cast<uintptr_t>(ptrs[p.uniform_tensor]) % 16 == 0)
-            with_hints(ntp, [&]<bool NTU, bool NTP>() {
+            with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
                 k_uniform_accumulate<CSUM, NTU, NTP><<<p.geom.ntiles, kThreads, 0, st>>>(a);
             });
         else
@@ -463,7 +480,7 @@ int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t 
             if (p.tensors[g.tensor_base + i].bytes && reinterpret_cast<uintptr_t>(b.p[i]) % 16) aligned = false;
         }
         if (aligned)
-            with_hints(ntp, [&]<bool NTU, bool NTP>() {
+            with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
                 k_contig_accumulate<CSUM, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles,
                                                                                   b, kinds, packed, cx);
             });
@@ -684,9 +701,8 @@ int run_batch(int n, const hxt_plan_t *const *plans, void *const *const *tensors
         }
         constexpr int DIR = UNPACK ? DIR_UNPACK : DIR_PACK;
         // cache hint of the launch: the first message's plan decides if it has been told to, else the bytes of the launch
-        const bool ntp = plans[i]->nt_packed >= 0 ? plans[i]->nt_packed != 0 : packed_nontemporal(bytes);
-        if (sm) launch_uniform<DIR, true>(a, uint32_t(tiles), ntp, st);
-        else launch_uniform<DIR, false>(a, uint32_t(tiles), ntp, st);
+        if (sm) launch_uniform<DIR, true>(a, uint32_t(tiles), bytes, plans[i]->nt_packed, st);
+        else launch_uniform<DIR, false>(a, uint32_t(tiles), bytes, plans[i]->nt_packed, st);
         HXT_HIP(hipGetLastError());
         i = j;
     }
@@ -709,7 +725,7 @@ int run_sum2(const hxt_plan_t *plan, const void *packed, int mode, void *out, co
     SlotsLock lock(pl.slots_mu);
     if ((rc = claim_slots(pl, mode == SUM2_VERIFY ? (chain ? OP_SUM2_RECV_B : OP_SUM2_RECV) : (chain ? OP_SUM2_SEND_B : OP_SUM2_SEND), st, cx, nullptr)) != HXT_OK) return rc;
     const uint8_t *pk = static_cast<const uint8_t *>(packed);
-    const bool ntp = packed_nontemporal(pl);
+    const bool ntp = packed_nontemporal(pl, true);
     auto launch = [&]<int MODE>() {
         TagWork w = work;
         w.sum_bits = pl.sum_bits_geom;
@@ -765,7 +781,7 @@ int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *
         std::memset(&a, 0, sizeof a);
         a.n = 1;
         a.it[0] = UniformTagItem{p.geom, base, pk, out, cx.acc, cx.stride, cx.fan, w, 0};
-        with_hints(packed_nontemporal(pl), [&]<bool NTU, bool NTP>() {
+        with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
             k_uniform_tag<UNPACK, MODE, NTU, NTP><<<p.geom.ntiles, kThreads, 0, st>>>(a);
         });
         HXT_HIP(hipGetLastError());
@@ -778,7 +794,7 @@ int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *
         BasePtrs b;
         std::memset(&b, 0, sizeof b);
         for (uint32_t i = 0; i < g.n_tensors; ++i) b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
-        with_hints(packed_nontemporal(pl), [&]<bool NTU, bool NTP>() {
+        with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
             k_contig_tag<UNPACK, MODE, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, b, pk,
                                                                                p.geom, out, cx.acc, cx.stride, cx.fan, w);
         });
@@ -851,8 +867,7 @@ int run_tag_batch(int n, const hxt_plan_t *const *plans, void *const *const *ten
             bytes += pj.p.C * pj.p.B;
             ++j;
         }
-        const bool ntp = plans[i]->nt_packed >= 0 ? plans[i]->nt_packed != 0 : packed_nontemporal(bytes);
-        with_hints(ntp, [&]<bool NTU, bool NTP>() { k_uniform_tag<UNPACK, MODE, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a); });
+        with_hints(user_nontemporal(bytes, !UNPACK), packed_nontemporal(plans[i]->nt_packed, bytes, UNPACK), [&]<bool NTU, bool NTP>() { k_uniform_tag<UNPACK, MODE, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a); });
         HXT_HIP(hipGetLastError());
         i = j;
     }
@@ -903,7 +918,6 @@ int fused_direct_stream(hxt_plan_t &pl, const hxt_exchange_t &x, hipStream_t sp,
 {
     const Plan &p = pl.p;
     const size_t T = p.tensors.size();
-    const bool nt_packed = packed_nontemporal(pl);
     SlotsLock lock(pl.slots_mu);
     for (int k = 0; k <= x.n_messages; ++k) {
         UniformArgs a;
@@ -927,8 +941,8 @@ int fused_direct_stream(hxt_plan_t &pl, const hxt_exchange_t &x, hipStream_t sp,
         if (k > 0) rc = add(k - 1, true);
         if (rc == HXT_OK && k < x.n_messages) rc = add(k, false);
         if (rc != HXT_OK) return rc;
-        if (x.send_sums) launch_uniform<DIR_MIXED, true>(a, tiles, nt_packed, sp);
-        else launch_uniform<DIR_MIXED, false>(a, tiles, nt_packed, sp);
+        if (x.send_sums) launch_uniform<DIR_MIXED, true>(a, tiles, p.C * p.B, pl.nt_packed, sp);
+        else launch_uniform<DIR_MIXED, false>(a, tiles, p.C * p.B, pl.nt_packed, sp);
         HXT_HIP(hipGetLastError());
     }
     if (su != sp || ss != sp) {
@@ -1293,8 +1307,7 @@ int hxt_unpack_accumulate_batch(int n, const hxt_plan_t *const *plans, const voi
             bytes += pj.p.C * pj.p.B;
             ++j;
         }
-        const bool ntp = plans[i]->nt_packed >= 0 ? plans[i]->nt_packed != 0 : packed_nontemporal(bytes);
-        with_hints(ntp, [&]<bool NTU, bool NTP>() {
+        with_hints(user_nontemporal(bytes, false), packed_nontemporal(plans[i]->nt_packed, bytes, true), [&]<bool NTU, bool NTP>() {
             if (sm) k_uniform_accumulate<true, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a);
             else k_uniform_accumulate<false, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a);
         });
@@ -1469,10 +1482,10 @@ int hxt_pack_noalloc(const void *src, size_t message_bytes, int n_lanes, size_t 
     a.it[0].cx = cx;
     a.it[0].first_tile = 0;
     a.it[0].unpack = 0;
-    const bool ntp = packed_nontemporal(uint64_t(g.C) * g.B);
+    const uint64_t bytes = uint64_t(g.C) * g.B;
     if (reinterpret_cast<uintptr_t>(user) % 16 == 0) {
-        if (sums) launch_uniform<DIR_PACK, true>(a, g.ntiles, ntp, st);
-        else launch_uniform<DIR_PACK, false>(a, g.ntiles, ntp, st);
+        if (sums) launch_uniform<DIR_PACK, true>(a, g.ntiles, bytes, tuning().nt_packed, st);
+        else launch_uniform<DIR_PACK, false>(a, g.ntiles, bytes, tuning().nt_packed, st);
     } else if (sums) {
         k_uniform_any<false, true><<<g.ntiles, kThreads, 0, st>>>(a);
     } else {
@@ -1494,7 +1507,7 @@ int hxt_checksum(const hxt_plan_t *plan, const void *packed, uint64_t *sums, voi
     if ((rc = claim_slots(pl, OP_CHECKSUM, st, cx, sums)) != HXT_OK) return rc;
     cx.sum_bits = pl.sum_bits_geom;
     const uint8_t *pk = static_cast<const uint8_t *>(packed);
-    if (packed_nontemporal(pl))
+    if (packed_nontemporal(pl, true))
         k_checksum<true><<<pl.p.geom.ntiles, kThreads, 0, st>>>(pl.p.geom, pk, cx);
     else
         k_checksum<false><<<pl.p.geom.ntiles, kThreads, 0, st>>>(pl.p.geom, pk, cx);
