@@ -153,6 +153,19 @@ void with_hints(const hxt_plan_t &pl, F &&f)
     with_hints(user_nontemporal(pl.p.C * pl.p.B, !UNPACK), packed_nontemporal(pl, UNPACK), f);
 }
 
+// The same for the strided kernels, whose stores to the tensors are always non-temporal: a receiving launch has one hint.
+template <bool UNPACK, typename F>
+void with_strided_hints(const hxt_plan_t &pl, F &&f)
+{
+    const bool ntp = packed_nontemporal(pl, UNPACK);
+    if constexpr (UNPACK) {
+        if (ntp) f.template operator()<true, true>();
+        else f.template operator()<true, false>();
+    } else {
+        with_hints(user_nontemporal(pl.p.C * pl.p.B, true), ntp, f);
+    }
+}
+
 // The streaming copies are launched with 32 KiB of (unused) dynamic LDS per workgroup, which caps residency at 5
 // workgroups per CU instead of 8: with 8 the memory system holds twice the bytes it needs to stay busy, every
 // request queues for longer and the launch's tail grows.  Measured per launch, all-cold, checks on: k_uniform on
@@ -202,16 +215,14 @@ void launch_transpose(const hxt_plan_t &pl, uint32_t first, uint32_t count, int 
 {
     const Tile *tiles = pl.d_tiles + first;
     const uint32_t *ct = pl.d_chunk_tiles;
-    auto go = [&]<bool NTP>() {
+    with_strided_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
         switch (esize) {
-        case 1: k_transpose<uint8_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
-        case 2: k_transpose<uint16_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
-        case 4: k_transpose<uint32_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
-        default: k_transpose<uint64_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
+        case 1: k_transpose<uint8_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
+        case 2: k_transpose<uint16_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
+        case 4: k_transpose<uint32_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
+        default: k_transpose<uint64_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
         }
-    };
-    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
-    else go.template operator()<false>();
+    });
 }
 
 template <bool UNPACK, bool CSUM>
@@ -221,16 +232,14 @@ void launch_transpose_span(const hxt_plan_t &pl, uint32_t first, uint32_t count,
     const Tile *tiles = pl.d_tiles + first;
     const uint32_t *ct = pl.d_chunk_tiles, *inc = pl.d_inc;
     const ChunkGeom &g = pl.p.geom;
-    auto go = [&]<bool NTP>() {
+    with_strided_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
         switch (esize) {
-        case 1: k_transpose_span<uint8_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
-        case 2: k_transpose_span<uint16_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
-        case 4: k_transpose_span<uint32_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
-        default: k_transpose_span<uint64_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
+        case 1: k_transpose_span<uint8_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
+        case 2: k_transpose_span<uint16_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
+        case 4: k_transpose_span<uint32_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
+        default: k_transpose_span<uint64_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
         }
-    };
-    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
-    else go.template operator()<false>();
+    });
 }
 
 template <bool UNPACK, bool CSUM>

@@ -83,6 +83,7 @@ struct ChunkGeom {
     uint32_t ntiles;     // (C - 1) * tpc + tiles of the last chunk
     uint32_t last_tiles; // tiles of the last chunk
     FastDiv div_tpc, div_k;
+    FastDiv div_b256;    // division by B / 256 (of stream offsets / 256, below 2^31)
 };
 
 struct TileSpan {

@@ -106,6 +106,37 @@ __device__ __forceinline__ void store_packed_elem(E *p, E v)
     else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// 16 bytes at any address: the hardware takes misaligned vector accesses, and 64 lanes of them next to each other
+// still cost little more than aligned ones.
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+
+template <bool NT>
+__device__ __forceinline__ u32x4 load16_any(const uint8_t *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(p));
+    else return *reinterpret_cast<const u32x4_any *>(p);
+}
+
+template <bool NT>
+__device__ __forceinline__ void store16_any(uint8_t *p, u32x4 v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any *>(p));
+    else *reinterpret_cast<u32x4_any *>(p) = v;
+}
+
+// The first n elements of a vector, one at a time.
+template <typename E>
+__device__ __forceinline__ void store_elems(uint8_t *p, u32x4 v, uint32_t n)
+{
+    union {
+        u32x4 x;
+        E e[16 / sizeof(E)];
+    } o{v};
+#pragma unroll
+    for (uint32_t q = 0; q < 16 / sizeof(E); ++q)
+        if (q < n) reinterpret_cast<E *>(p)[q] = o.e[q];
+}
+
 // Vector v of a span of nvec (>= 1) vectors, zeros beyond its end.  The load itself is unconditional (the
 // index is clamped into the span): the loads of an unrolled round are then all issued before the first
 // of them is waited for, where guarded loads are waited for one by one.
@@ -119,6 +150,43 @@ __device__ __forceinline__ u32x4 load16_or_zero(const u32x4 *s, uint32_t v, uint
 __device__ __forceinline__ uint64_t words_sum(u32x4 v)
 {
     return (uint64_t(v.x) + uint64_t(v.y)) + (uint64_t(v.z) + uint64_t(v.w));
+}
+
+// The sum of the packed words that 16 bytes at packed position pos contribute to: byte k weighs 256^((pos + k) mod 4),
+// so a vector that starts inside a word is summed as words rotated by its phase.
+__device__ __forceinline__ uint64_t rotated_sum(u32x4 v, uint32_t pos)
+{
+    const uint32_t by = 8 * (pos & 3u);
+    return words_sum(u32x4{__builtin_rotateleft32(v.x, by), __builtin_rotateleft32(v.y, by), __builtin_rotateleft32(v.z, by),
+                           __builtin_rotateleft32(v.w, by)});
+}
+
+// Bytes [from, to) of a vector, zeros elsewhere.
+__device__ __forceinline__ u32x4 keep_bytes(u32x4 v, uint32_t from, uint32_t to)
+{
+    auto below = [](uint32_t word, uint32_t k) {         // mask of the bytes of a word that lie below byte k of the vector
+        const uint32_t lo = 4 * word;
+        return k <= lo ? 0u : (k >= lo + 4 ? ~0u : (1u << (8 * (k - lo))) - 1u);
+    };
+    return u32x4{v.x & below(0, to) & ~below(0, from), v.y & below(1, to) & ~below(1, from),
+                 v.z & below(2, to) & ~below(2, from), v.w & below(3, to) & ~below(3, from)};
+}
+
+// Sum over the 16 lanes of a DPP row, in its last lane (the others hold partial sums).  Inactive lanes count as zero.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint64_t dpp_plus(uint64_t v)
+{
+    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(v)), CTRL, ROWS, 0xF, false));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(v >> 32)), CTRL, ROWS, 0xF, false));
+    return v + (uint64_t(hi) << 32 | lo);
+}
+
+__device__ __forceinline__ uint64_t row16_sum(uint64_t v)
+{
+    v = dpp_plus<0x111>(v);                              // row_shr 1, 2, 4, 8
+    v = dpp_plus<0x112>(v);
+    v = dpp_plus<0x114>(v);
+    return dpp_plus<0x118>(v);
 }
 
 // One arrival at an accumulator slot that expects `expected` of them: adds `value` and reports
@@ -765,9 +833,6 @@ __global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict_
     if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
 }
 
-// ---- transpose: logical inner dimension strided, the one before it contiguous ----
-// A tile is ni x nj elements (at most 128 x 128 for 1- and 2-byte elements, 64 x 64 otherwise).  Storage is read/written along i, the packed
-// stream along j, both coalesced; the swap of roles goes through a padded LDS tile.
 template <typename E>
 __device__ __forceinline__ uint64_t elem_weighted(E v, uint64_t packed_pos)
 {
@@ -778,306 +843,300 @@ __device__ __forceinline__ uint64_t elem_weighted(E v, uint64_t packed_pos)
     }
 }
 
-// Vector path of the transpose: src has R rows of Cc contiguous elements, dst gets Cc rows of R
-// contiguous elements, dst[c][r] = src[r][c]; R and Cc are multiples of V = 16 / sizeof(E) and
-// every row start is 16-byte aligned.  16-byte global loads along src rows land in LDS rows of
-// T elements whose 16-byte slots are XOR-swizzled with the row group, so that the V element
-// reads that assemble one dst vector (same column, V consecutive rows) and the other lanes'
-// reads of the same instruction fall into distinct banks; then 16-byte global stores along dst
-// rows.  The sum is taken on whichever side is the packed buffer.
-// FULL: the tile is T x T, so every index computation folds to shifts and masks and each thread moves exactly
-// T * T / (V * kThreads) vectors per phase, all of whose global loads are issued before the first LDS store
-// (measured with counters: with run-time extents the kernel was bound by its integer divisions, not by memory).
-// Where the rows of a tile lie on the packed side, and where their sums go.
+// ---- transpose: logical inner dimension strided, the one before it contiguous ----
+// A tile is ni x nj elements (at most T x T: 128 x 128 for 1- and 2-byte elements, 64 x 64 otherwise).  The tensor
+// stores nj rows of ni contiguous elements, the packed stream has ni rows of nj.  A thread loads a block of V x V
+// elements (V = 16 bytes' worth: V rows of one vector each), transposes it in registers and leaves V vectors in LDS;
+// after the barrier the tile's rows leave LDS as whole vectors, 16 lanes (256 contiguous bytes) to a row.  So LDS is
+// touched by 16-byte accesses only, once each way; gathering elements out of it instead kept the LDS pipe busy for
+// about 1.7 us of a 14 us launch (64 two-byte reads per thread).  32 MiB of bf16, pack + unpack: 27.3 -> 24.4 us (a plain copy of the same bytes: 24.1).
+// Vectors need no alignment beyond the element's: the hardware takes misaligned 16-byte accesses, and even with both
+// row pitches odd (bf16, pitches of 8198 bytes) they beat element accesses, 30 against 31-38 us per pair.
+template <typename E>
+struct TransposeShape {
+    static constexpr uint32_t T = transpose_tile(sizeof(E)), V = 16 / sizeof(E);
+    static constexpr uint32_t NB = T / V;                        // vectors per tile row, blocks per tile side
+    static constexpr uint32_t BLOCKS = NB * NB;
+};
+
+// x[r] holds V elements of source row r; afterwards x[c] holds the V elements of source column c.
+template <typename E>
+__device__ __forceinline__ void transpose_block(u32x4 (&x)[16 / sizeof(E)])
+{
+    constexpr int V = 16 / sizeof(E);
+    u32x4 y[V];
+    if constexpr (sizeof(E) == 8) {
+        y[0] = u32x4{x[0].x, x[0].y, x[1].x, x[1].y};
+        y[1] = u32x4{x[0].z, x[0].w, x[1].z, x[1].w};
+    } else if constexpr (sizeof(E) == 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y[c] = u32x4{x[0][c], x[1][c], x[2][c], x[3][c]};
+    } else if constexpr (sizeof(E) == 2) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t a = x[2 * q][c], b = x[2 * q + 1][c];
+                y[2 * c][q] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+                y[2 * c + 1][q] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+            }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t lo01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x05010400u);       // bytes 0 0' 1 1'
+                const uint32_t hi01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x07030602u);       // bytes 2 2' 3 3'
+                const uint32_t lo23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x05010400u);
+                const uint32_t hi23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x07030602u);
+                y[4 * c][q] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+                y[4 * c + 1][q] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+                y[4 * c + 2][q] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+                y[4 * c + 3][q] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i) x[i] = y[i];
+}
+
+// Where the rows of a tile lie on the packed side.
 // PitchRows: a tile inside one chunk, rows a fixed pitch apart, one sum for the tile.
 struct PitchRows {
-    uint8_t *base;
+    static constexpr bool kSpan = false;
+    uint8_t *base;                 // element (0, 0) of the tile
     uint64_t pitch;
+    uint32_t pos;                  // low bits of its position in the packed buffer (for the phase of sums)
     __device__ __forceinline__ uint8_t *at(uint32_t row, uint32_t byte) const { return base + row * pitch + byte; }
-    __device__ __forceinline__ void count(uint32_t, uint32_t, uint64_t s, uint64_t &acc) const { acc += s; }
+    __device__ __forceinline__ uint32_t position(uint32_t row, uint32_t byte) const { return pos + row * uint32_t(pitch) + byte; }
 };
-// SpanRows: every row placed on its own (k_transpose_span keeps the placement in LDS): bytes below first_b[row]
-// lie p0[row] into the packed buffer, the rest p1[row]; a vector's sum goes to the partial sum of its chunk.
+// SpanRows: every row placed on its own (k_transpose_span keeps the placement in LDS): bytes below first[row] lie from
+// p0[row] on in the packed buffer, the rest at p1[row]; sums go to the partial sum of the chunk they fall into.
 struct SpanRows {
+    static constexpr bool kSpan = true;
     uint8_t *packed;
     const uint64_t *p0, *p1;
-    const uint32_t *first_b, *entry;
+    const uint32_t *first, *entry, *low;
     unsigned long long *part;
+    bool may_cross;                // a vector may straddle a chunk border (rows are not 16-byte aligned against it)
     __device__ __forceinline__ uint8_t *at(uint32_t row, uint32_t byte) const
     {
-        return packed + (byte < first_b[row] ? p0[row] : p1[row]) + byte;
+        return packed + (byte < first[row] ? p0[row] : p1[row]) + byte;
     }
-    __device__ __forceinline__ void count(uint32_t row, uint32_t byte, uint64_t s, uint64_t &) const
+    __device__ __forceinline__ uint32_t position(uint32_t row, uint32_t byte) const { return low[row] + byte; }
+    __device__ __forceinline__ bool crosses(uint32_t row, uint32_t byte) const
     {
-        __hip_atomic_fetch_add(&part[entry[row] + (byte < first_b[row] ? 0u : 1u)], (unsigned long long)s, __ATOMIC_RELAXED,
+        return may_cross && byte < first[row] && byte + 16 > first[row];
+    }
+    __device__ __forceinline__ void count(uint32_t row, bool second, uint64_t s) const
+    {
+        __hip_atomic_fetch_add(&part[entry[row] + (second ? 1u : 0u)], (unsigned long long)s, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 };
 
-// user / user_pitch: the tensor side (rows of the tile as the tensor stores them); pk: the packed side.
-// SRC_IS_PACKED: unpack (packed rows are the source), else pack.
-template <typename E, bool SRC_IS_PACKED, bool CSUM, bool NTP, int UA, bool FULL, class PK>
-__device__ __forceinline__ uint64_t transpose_vec(uint8_t *user, uint64_t user_pitch, uint32_t R_in, uint32_t Cc_in,
-                                                  const PK &pk, uint8_t *lds)
+// The elements of a vector on the packed side that straddles a chunk border (bytes below `first` of the row lie from
+// `before` on, the rest from `after` on), one at a time.
+template <typename E, bool NTP>
+__device__ __forceinline__ void store_crossing(uint8_t *before, uint8_t *after, uint32_t first, uint32_t byte, uint32_t n, u32x4 v)
 {
-    constexpr uint32_t T = transpose_tile(sizeof(E)), V = 16 / sizeof(E), ROWB = T * sizeof(E), NV = T / V;
-    const uint32_t R = FULL ? T : R_in, Cc = FULL ? T : Cc_in;
-    uint64_t acc = 0;
-    const uint32_t nvs = Cc / V;                           // vectors per src row
-    auto load_src = [&](uint32_t v, uint32_t &slot) {
-        const uint32_t r = v / nvs, cv = v - r * nvs;
-        slot = r * ROWB + ((cv ^ ((r / V) % NV)) * 16);
-        // the user tensor is streamed once (non-temporal) and may be only UA-byte aligned; the packed side as the plan says
-        if constexpr (SRC_IS_PACKED) return load16<NTP>(reinterpret_cast<const u32x4 *>(pk.at(r, cv * 16)));
-        else return load_user<UA, true>(user + r * user_pitch + cv * 16);
-    };
-    auto count_src = [&](uint32_t v, const u32x4 &x) {     // after the loads, so that none of them waits for a sum
-        if constexpr (CSUM && SRC_IS_PACKED) {
-            const uint32_t r = v / nvs, cv = v - r * nvs;
-            pk.count(r, cv * 16, words_sum(x), acc);
-        }
-    };
-    if constexpr (FULL) {
-        constexpr uint32_t PER = T * T / (V * kThreads);   // 8 vectors per thread (4 for 1-byte elements)
-        u32x4 x[PER];
-        uint32_t slot[PER];
+    constexpr uint32_t ES = sizeof(E);
 #pragma unroll
-        for (uint32_t u = 0; u < PER; ++u) x[u] = load_src(threadIdx.x + u * kThreads, slot[u]);
+    for (uint32_t q = 0; q < 16 / ES; ++q) {
+        const uint32_t at = byte + q * ES;
+        const E e = E(ES == 8 ? uint64_t(v[q * ES / 4]) | uint64_t(v[(q * ES / 4 + 1) & 3]) << 32 : uint64_t(v[q * ES / 4]) >> (8 * (q * ES & 3)));
+        if (q < n) store_packed_elem<NTP>(reinterpret_cast<E *>((at < first ? before : after) + at), e);
+    }
+}
+
+template <typename E>
+__device__ __forceinline__ u32x4 load_crossing(const uint8_t *before, const uint8_t *after, uint32_t first, uint32_t byte)
+{
+    union {
+        E e[16 / sizeof(E)];
+        u32x4 x;
+    } o;
 #pragma unroll
-        for (uint32_t u = 0; u < PER; ++u) {
-            count_src(threadIdx.x + u * kThreads, x[u]);
-            *reinterpret_cast<u32x4 *>(lds + slot[u]) = x[u];
-        }
+    for (uint32_t q = 0; q < 16 / sizeof(E); ++q) {
+        const uint32_t at = byte + q * uint32_t(sizeof(E));
+        o.e[q] = *reinterpret_cast<const E *>((at < first ? before : after) + at);
+    }
+    return o.x;
+}
+
+// Adds the sum of a vector of packed bytes (n of them from byte `skip` on count) to the tile's sum, or to the partial sum
+// of its chunk.  SpanRows: called by all lanes of a wave, the 16 lanes of a DPP row holding vectors of one tile row
+// (live: this lane's vector counts); the row is summed across those lanes first, so that one lane goes to LDS.
+template <typename E, class Rows>
+__device__ __forceinline__ void count_packed(const Rows &rows, uint32_t row, uint32_t byte, u32x4 v, uint32_t skip, uint32_t n,
+                                             bool live, uint64_t &acc)
+{
+    const u32x4 kept = live ? keep_bytes(v, skip, n) : u32x4{0, 0, 0, 0};
+    if constexpr (!Rows::kSpan) {
+        acc += rotated_sum(kept, rows.position(row, byte));
     } else {
-        for (uint32_t v = threadIdx.x; v < R * nvs; v += kThreads) {
-            uint32_t slot;
-            const u32x4 x = load_src(v, slot);
-            count_src(v, x);
-            *reinterpret_cast<u32x4 *>(lds + slot) = x;
+        const uint32_t border = rows.first[row];
+        const bool crossing = rows.crosses(row, byte);
+        if (crossing && live) {                          // split at the border: rare, and only where rows are misaligned
+            const uint32_t before = border - byte;
+            rows.count(row, false, rotated_sum(keep_bytes(kept, 0, before), rows.position(row, byte)));
+            rows.count(row, true, rotated_sum(keep_bytes(kept, before, 16), rows.position(row, byte)));
+        }
+        const uint64_t s = crossing ? 0 : rotated_sum(kept, rows.position(row, byte));
+        constexpr bool kGrouped = TransposeShape<E>::NB % 16 == 0;
+        const bool whole = border >= TransposeShape<E>::T * uint32_t(sizeof(E));     // the row meets no border in this tile
+        if constexpr (kGrouped) {
+            const uint64_t total = row16_sum(s);
+            if (whole && (threadIdx.x & 15) == 15) rows.count(row, false, total);
+            if (!whole && s) rows.count(row, byte >= border, s);
+        } else {
+            if (s) rows.count(row, byte >= border, s);
+        }
+    }
+}
+
+// Moves one tile.  Source rows are the tensor's (pack) or the packed side's (unpack): nb rows of na elements.
+// place() puts into LDS what `rows` reads there; a pack does that while its loads from the tensor are on their way.
+// fetch() asks for what the caller needs at the end.
+template <typename E, bool UNPACK, bool CSUM, bool NTU, bool NTP, bool FULL, class Rows, class Place, class Fetch>
+__device__ __forceinline__ uint64_t transpose_tile_vectors(uint8_t *user, uint64_t user_pitch, uint32_t na_in, uint32_t nb_in,
+                                                           const Rows &rows, u32x4 *lds, Place &&place, Fetch &&fetch)
+{
+    using Sh = TransposeShape<E>;
+    constexpr uint32_t T = Sh::T, V = Sh::V, NB = Sh::NB, ES = sizeof(E);
+    constexpr uint32_t PER = Sh::BLOCKS < uint32_t(kThreads) ? 1 : Sh::BLOCKS / kThreads;      // blocks per thread
+    const uint32_t na = FULL ? T : na_in, nb = FULL ? T : nb_in;
+    auto slot_of = [](uint32_t row, uint32_t slot) { return row * NB + (slot ^ ((row / V) & (NB - 1))); };
+    uint64_t acc = 0;
+    if constexpr (Rows::kSpan && UNPACK) {
+        place();
+        __syncthreads();
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t id = threadIdx.x + k * kThreads, la = id & (NB - 1), lb = id / NB;
+        const uint32_t a0 = la * V, b0 = lb * V;
+        constexpr bool kAll = FULL && Sh::BLOCKS >= uint32_t(kThreads);      // every thread has a whole block
+        const bool live = kAll || (id < Sh::BLOCKS && a0 < na && b0 < nb);
+        auto row_of = [&](uint32_t r) { return kAll ? b0 + r : min(b0 + r, nb - 1); };
+        // The last block of a row that is no multiple of V starts early enough to end with it (its first columns are
+        // then moved twice, with the same values); rows beyond the tile repeat the last one.
+        const uint32_t as = FULL || a0 + V <= na ? a0 : (na >= V ? na - V : 0);
+        const bool narrow = !FULL && na < V;
+        u32x4 x[V];
+        if (live && !narrow) {
+#pragma unroll
+            for (uint32_t r = 0; r < V; ++r) {
+                const uint32_t b = row_of(r);
+                if constexpr (!UNPACK) {
+                    x[r] = load16_any<NTU>(user + b * user_pitch + as * ES);
+                } else if constexpr (!Rows::kSpan) {
+                    x[r] = load16_any<NTP>(rows.at(b, as * ES));
+                } else {
+                    // (a vector across a chunk border is read from the 16 bytes that end there, and put right below)
+                    const uint32_t byte = rows.crosses(b, as * ES) ? rows.first[b] - 16u : as * ES;
+                    x[r] = load16_any<NTP>(rows.packed + (as * ES < rows.first[b] ? rows.p0[b] : rows.p1[b]) + int32_t(byte));
+                }
+            }
+            if constexpr (UNPACK && Rows::kSpan) {
+                if (rows.may_cross)
+#pragma unroll
+                    for (uint32_t r = 0; r < V; ++r) {
+                        const uint32_t b = row_of(r);
+                        if (rows.crosses(b, as * ES)) x[r] = load_crossing<E>(rows.packed + rows.p0[b], rows.packed + rows.p1[b], rows.first[b], as * ES);
+                    }
+            }
+        } else if (live) {                               // fewer than V columns in the whole tile
+#pragma unroll
+            for (uint32_t r = 0; r < V; ++r) {
+                const uint32_t b = row_of(r);
+                union {
+                    E e[V];
+                    u32x4 v;
+                } o{};
+#pragma unroll
+                for (uint32_t q = 0; q < V; ++q)
+                    if (q < na) {
+                        if constexpr (!UNPACK) o.e[q] = *reinterpret_cast<const E *>(user + b * user_pitch + q * ES);
+                        else o.e[q] = *reinterpret_cast<const E *>(rows.at(b, q * ES));
+                    }
+                x[r] = o.v;
+            }
+        }
+        if constexpr (CSUM && UNPACK) {
+            const uint32_t skip = (a0 - as) * ES, n = narrow ? na * ES : 16;
+#pragma unroll
+            for (uint32_t r = 0; r < V; ++r)
+                count_packed<E>(rows, row_of(r), as * ES, x[r], FULL ? 0 : skip, FULL ? 16 : n,
+                                live && (kAll || b0 + r < nb), acc);
+        }
+        if (k == 0) {
+            if constexpr (!UNPACK) place();
+            fetch();
+        }
+        if (live) {
+            transpose_block<E>(x);
+#pragma unroll
+            for (uint32_t c = 0; c < V; ++c)
+                if (!narrow || c < na) lds[slot_of(as + c, lb)] = x[c];
         }
     }
     __syncthreads();
-    // dst vectors are handed out with 8 consecutive vectors of one dst row (128 contiguous bytes) fastest,
-    // then the dst row: a half-wave then reads 8 row groups x 4 columns from LDS, which the swizzle spreads
-    // over all 32 banks (16 row groups of one column pair would hit each bank twice).
-    const uint32_t nvd = R / V;                            // vectors per dst row
-    const uint32_t full8 = nvd >> 3, rem = nvd & 7, main = Cc * 8 * full8;
-    auto move_dst = [&](uint32_t v) {
-        uint32_t c, dv;
-        if (FULL || v < main) {                            // a full tile's dst rows are whole groups of 8 vectors
-            const uint32_t b = v / (Cc * 8), w = v - b * (Cc * 8);
-            c = w >> 3;
-            dv = b * 8 + (w & 7);
-        } else if constexpr (!FULL) {
-            const uint32_t w = v - main;
-            c = w / rem;
-            dv = full8 * 8 + (w - c * rem);
-        }
-        union {
-            E e[V];
-            u32x4 x;
-        } o;
 #pragma unroll
-        for (uint32_t q = 0; q < V; ++q) {
-            const uint32_t r = dv * V + q;
-            o.e[q] = *reinterpret_cast<const E *>(lds + r * ROWB + (((c / V) ^ ((r / V) % NV)) * 16) + (c % V) * sizeof(E));
+    for (uint32_t k = 0; k < T * NB / kThreads; ++k) {
+        const uint32_t id = threadIdx.x + k * kThreads, row = id / NB, slot = id & (NB - 1);
+        const bool live = FULL || (row < na && slot * V < nb);
+        const uint32_t r = FULL ? row : min(row, na - 1), n = FULL ? V : min(V, nb - min(slot * V, nb));
+        const u32x4 v = lds[slot_of(r, slot)];
+        if constexpr (CSUM && !UNPACK) count_packed<E>(rows, r, slot * 16, v, 0, n * ES, live, acc);
+        if (!live) continue;
+        if constexpr (UNPACK) {
+            uint8_t *to = user + r * user_pitch + slot * 16;
+            if (FULL || n == V) store16_any<true>(to, v);
+            else store_elems<E>(to, v, n);
+        } else if constexpr (!Rows::kSpan) {
+            uint8_t *to = rows.at(r, slot * 16);
+            if (FULL || n == V) store_packed16<NTP>(reinterpret_cast<u32x4 *>(to), v);
+            else store_elems<E>(to, v, n);
+        } else {
+            if ((FULL || n == V) && !rows.crosses(r, slot * 16)) store_packed16<NTP>(reinterpret_cast<u32x4 *>(rows.at(r, slot * 16)), v);
+            else store_crossing<E, NTP>(rows.packed + rows.p0[r], rows.packed + rows.p1[r], rows.first[r], slot * 16, n, v);
         }
-        if constexpr (CSUM && !SRC_IS_PACKED) pk.count(c, dv * 16, words_sum(o.x), acc);
-        if constexpr (SRC_IS_PACKED) store_user<UA, true>(user + c * user_pitch + dv * 16, o.x);
-        else store_packed16<NTP>(reinterpret_cast<u32x4 *>(pk.at(c, dv * 16)), o.x);
-    };
-    if constexpr (FULL) {
-        static_assert(NV % 8 == 0, "a full tile's dst rows must be whole groups of 8 vectors");
-        constexpr uint32_t PER = T * T / (V * kThreads);
-#pragma unroll
-        for (uint32_t u = 0; u < PER; ++u) move_dst(threadIdx.x + u * kThreads);
-    } else {
-        for (uint32_t v = threadIdx.x; v < Cc * nvd; v += kThreads) move_dst(v);
     }
     return acc;
 }
 
-template <typename E, bool UNPACK, bool CSUM, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__ tiles,
-                                                        const uint32_t *__restrict__ chunk_tiles, BasePtrs bases,
-                                                        uint8_t *__restrict__ packed, SumCtx cx)
+// The tensor's fast direction has a stride of a few elements (es bytes from element to element): element by element,
+// through an LDS tile padded by one element.  Thread (tx, ty) holds elements of packed row tx only while it is on the
+// tensor side and sums them there: sum(row, v, j) for element j of its row.  Eight global loads per thread are issued
+// before the first of them is needed (row and column numbers are clamped into the tile, so the loads need no guard).
+template <typename E, bool UNPACK, bool NTP, class Rows, class Sum>
+__device__ __forceinline__ void transpose_tile_elements(uint8_t *user, uint64_t user_pitch, uint32_t es, uint32_t ni, uint32_t nj,
+                                                        const Rows &rows, uint8_t *lds_raw, Sum &&sum)
 {
-    constexpr uint32_t T = transpose_tile(sizeof(E)), V = 16 / sizeof(E);
-    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[T * (T + 1) * sizeof(E)];
-    const Tile t = tiles[blockIdx.x];
-    uint8_t *user = bases.p[t.tensor] + t.src_off;
-    uint8_t *pk = packed + t.packed_off;
-    const uint32_t ni = t.n0, nj = t.n1;
-    uint64_t acc = 0;
-    const uint32_t es = t.estep;                       // tensor side: bytes from element i to element i + 1 (sizeof(E) or more)
-    const bool vec_ok = es == sizeof(E) && ((ni | nj) % V) == 0 && ((reinterpret_cast<uintptr_t>(pk) | t.a | t.b) % 16) == 0;
-    if (vec_ok) {
-        // storage: nj rows (pitch a) of ni contiguous elements; packed: ni rows (pitch b) of nj elements.  Every
-        // storage row of the tile is off a 16-byte boundary by the same amount (the pitch is a multiple of 16).
-        auto run = [&]<int UA, bool FULL = false>() {
-            const PitchRows rows{pk, t.b};
-            if constexpr (!UNPACK) return transpose_vec<E, false, CSUM, NTP, UA, FULL>(user, t.a, nj, ni, rows, lds_raw);
-            else return transpose_vec<E, true, CSUM, NTP, UA, FULL>(user, t.a, ni, nj, rows, lds_raw);
-        };
-        const uint32_t mis = uint32_t(reinterpret_cast<uintptr_t>(user)) & 15u;
-        if (mis == 0 && ni == T && nj == T) acc = run.template operator()<16, true>();      // the common case
-        else if (mis == 0) acc = run.template operator()<16>();
-        else if ((mis & 3u) == 0) acc = run.template operator()<4>();
-        else if ((mis & 1u) == 0) acc = run.template operator()<2>();
-        else acc = run.template operator()<1>();
-    } else {
-        // Element by element (extents or pitches that are not multiples of 16 bytes, or a tensor side whose
-        // fast direction has a stride of a few elements instead of one).  Eight global loads
-        // per thread are issued before the first of them is needed (the row number is clamped into the
-        // tile, so the loads need no guard of their own).
-        E(*lds)[T + 1] = reinterpret_cast<E(*)[T + 1]>(lds_raw);
-        const uint32_t tx = threadIdx.x & (T - 1), ty = threadIdx.x / T;
-        constexpr uint32_t TY = kThreads / T, U = 8;
-        if constexpr (!UNPACK) {
-            if (tx < ni)
-                for (uint32_t j0 = ty; j0 < nj; j0 += TY * U) {
-                    E v[U];
-#pragma unroll
-                    for (uint32_t u = 0; u < U; ++u)
-                        v[u] = __builtin_nontemporal_load(reinterpret_cast<const E *>(user + uint64_t(min(j0 + u * TY, nj - 1)) * t.a + tx * es));
-#pragma unroll
-                    for (uint32_t u = 0; u < U; ++u)
-                        if (j0 + u * TY < nj) lds[j0 + u * TY][tx] = v[u];
-                }
-            __syncthreads();
-            if (tx < nj)
-                for (uint32_t i = ty; i < ni; i += TY) {
-                    const E v = lds[tx][i];
-                    const uint64_t pos = i * t.b + tx * sizeof(E);
-                    store_packed_elem<NTP>(reinterpret_cast<E *>(pk + pos), v);
-                    if constexpr (CSUM) acc += elem_weighted(v, t.packed_off + pos);
-                }
-        } else {
-            if (tx < nj)
-                for (uint32_t i0 = ty; i0 < ni; i0 += TY * U) {
-                    E v[U];
-#pragma unroll
-                    for (uint32_t u = 0; u < U; ++u)
-                        v[u] = load_elem<NTP>(reinterpret_cast<const E *>(pk + uint64_t(min(i0 + u * TY, ni - 1)) * t.b + tx * sizeof(E)));
-#pragma unroll
-                    for (uint32_t u = 0; u < U; ++u) {
-                        const uint32_t i = i0 + u * TY;
-                        if (i < ni) {
-                            lds[tx][i] = v[u];
-                            if constexpr (CSUM) acc += elem_weighted(v[u], t.packed_off + i * t.b + tx * sizeof(E));
-                        }
-                    }
-                }
-            __syncthreads();
-            if (tx < ni)
-                for (uint32_t j = ty; j < nj; j += TY)
-                    __builtin_nontemporal_store(lds[j][tx], reinterpret_cast<E *>(user + j * t.a + tx * es));
-        }
-    }
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
-// ---- transpose whose tiles span chunks -------------------------------------------
-// For matrices whose packed rows are long against the chunk: a tile is a full block of the logical matrix
-// (so that every memory burst of the tensor side is used whole) and row i of it starts at stream byte
-// s0 + i * b, wherever that falls; a tile row is shorter than a chunk, so it meets at most one chunk
-// border.  Thread i first places row i (its chunk, the packed address of its first byte, how many of its
-// columns lie before the border and where the rest go) and leaves that in LDS, so that the copy loop only
-// reads it back.  Checksums are taken on the tensor side, where a thread holds elements of one row only, and
-// added to the tile's per-chunk partial sums in LDS; at the end one thread per chunk touched makes that
-// chunk's arrival (inc holds the tile's chunks, ascending, and the ordinal of each arrival).
-template <typename E, bool UNPACK, bool CSUM, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restrict__ tiles,
-                                                             const uint32_t *__restrict__ chunk_tiles,
-                                                             const uint32_t *__restrict__ inc, ChunkGeom g,
-                                                             BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
-{
-    constexpr uint32_t T = transpose_tile(sizeof(E));
-    constexpr uint32_t TY = kThreads / T, MAXC = 2 * T + 2;
-    static_assert(T <= kThreads, "one thread places one row");
-    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[T * (T + 1) * sizeof(E)];
-    __shared__ unsigned long long part[MAXC];          // partial sum per chunk touched
-    __shared__ uint32_t touched[MAXC];                 // those chunks
-    // per row: packed offset of column j is row_p0 + j * sizeof(E) for j < row_first, row_p1 + j * sizeof(E) from there on
-    __shared__ uint64_t row_p0[T], row_p1[T];
-    __shared__ uint32_t row_first[T], row_at[T], row_low[T];   // row_at: entry of the row's first chunk; row_low: low bits of
-                                                               // its first byte's position (for the weights of the sum)
-    const Tile t = tiles[blockIdx.x];
-    uint8_t *user = bases.p[t.tensor] + t.src_off;
-    const uint32_t ni = t.n0, nj = t.n1, es = t.estep, n_inc = t.ordinal;
-    const uint32_t *my = inc + 2 * size_t(t.chunk);
+    constexpr uint32_t T = TransposeShape<E>::T, TY = kThreads / T, U = 8;
     E(*lds)[T + 1] = reinterpret_cast<E(*)[T + 1]>(lds_raw);
-    const uint32_t tx = threadIdx.x & (T - 1);
-    const uint32_t ty = threadIdx.x / T;
-    for (uint32_t i = threadIdx.x; i < n_inc; i += kThreads) {
-        touched[i] = my[2 * i];
-        part[i] = 0;
-    }
-    __syncthreads();
-    if (threadIdx.x < ni) {                             // place row threadIdx.x
-        const uint64_t B = g.B, s = t.packed_off + uint64_t(threadIdx.x) * t.b;
-        const uint64_t c = s / B, rem = s - c * B;
-        uint32_t lo = 0, hi = n_inc - 1;                // the entry that names chunk c (it is there)
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) / 2;
-            if (touched[mid] < uint32_t(c)) lo = mid + 1;
-            else hi = mid;
-        }
-        auto chunk_base = [&](uint64_t ch) {
-            const uint32_t slot = fast_div(uint32_t(ch), g.div_k), lane = uint32_t(ch) - slot * g.k;
-            return (uint64_t(lane) * g.q + (lane < g.r ? lane : g.r) + slot) * B;
-        };
-        const uint64_t room = B - rem;                  // bytes of chunk c from the row's start on
-        const uint32_t first = room >= uint64_t(nj) * sizeof(E) ? nj : uint32_t(room / sizeof(E));
-        row_at[threadIdx.x] = lo;
-        row_first[threadIdx.x] = first;
-        row_low[threadIdx.x] = uint32_t(rem) & 3u;
-        row_p0[threadIdx.x] = chunk_base(c) + rem;
-        row_p1[threadIdx.x] = first < nj ? chunk_base(c + 1) + rem - B : 0;     // (+ j * sizeof(E) >= B - rem for those columns)
-    }
-    __syncthreads();
-    // The tensor side of the tile: thread (tx, ty) moves columns ty, ty + TY, ... of row tx between the tensor and
-    // LDS, and while it holds them adds them to the row's sums (the part before the chunk border and the part
-    // after it), which go to the tile's per-chunk partial sums: no reduction across lanes.
-    constexpr uint32_t U = 8;
+    const uint32_t tx = threadIdx.x & (T - 1), ty = threadIdx.x / T;
     auto tensor_side = [&]() {
         if (tx >= ni) return;
-        const uint32_t first = row_first[tx], low = row_low[tx];
-        unsigned long long a0 = 0, a1 = 0;
-        auto count = [&](E v, uint32_t j) {
-            const unsigned long long w = elem_weighted(v, uint64_t(low) + uint64_t(j) * sizeof(E));
-            if (j < first) a0 += w;
-            else a1 += w;
-        };
-        if constexpr (!UNPACK) {
-            for (uint32_t j0 = ty; j0 < nj; j0 += TY * U) {
-                E v[U];
+        for (uint32_t j0 = ty; j0 < nj; j0 += TY * U) {
+            E v[U];
 #pragma unroll
-                for (uint32_t u = 0; u < U; ++u)
-                    v[u] = __builtin_nontemporal_load(reinterpret_cast<const E *>(user + uint64_t(min(j0 + u * TY, nj - 1)) * t.a + tx * es));
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t j = min(j0 + u * TY, nj - 1);
+                if constexpr (!UNPACK) v[u] = __builtin_nontemporal_load(reinterpret_cast<const E *>(user + j * user_pitch + tx * es));
+                else v[u] = lds[j][tx];
+            }
 #pragma unroll
-                for (uint32_t u = 0; u < U; ++u)
-                    if (j0 + u * TY < nj) {
-                        lds[j0 + u * TY][tx] = v[u];
-                        if constexpr (CSUM) count(v[u], j0 + u * TY);
-                    }
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t j = j0 + u * TY;
+                if (j < nj) {
+                    if constexpr (!UNPACK) lds[j][tx] = v[u];
+                    else __builtin_nontemporal_store(v[u], reinterpret_cast<E *>(user + j * user_pitch + tx * es));
+                    sum(tx, v[u], j);
+                }
             }
-        } else {
-            for (uint32_t j = ty; j < nj; j += TY) {
-                const E v = lds[j][tx];
-                __builtin_nontemporal_store(v, reinterpret_cast<E *>(user + j * t.a + tx * es));
-                if constexpr (CSUM) count(v, j);
-            }
-        }
-        if constexpr (CSUM) {
-            const uint32_t at = row_at[tx];
-            if (a0) __hip_atomic_fetch_add(&part[at], a0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (a1) __hip_atomic_fetch_add(&part[at + 1], a1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     };
-    // The packed side, rows ty, ty + TY, ...: pack stores what is in LDS, unpack fills it.  The loads of an unpack
-    // need no guard (a row beyond the tile repeats the last one, lanes beyond its width shadow its last column),
-    // so all U of a round are in flight before the first is used.
     auto packed_side = [&]() {
         const uint32_t txc = min(tx, nj - 1);
         for (uint32_t i0 = ty; i0 < ni; i0 += TY * U) {
@@ -1085,9 +1144,7 @@ __global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restr
             E v[U];
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t i = min(i0 + u * TY, ni - 1);
-                const uint64_t off = (txc < row_first[i] ? row_p0[i] : row_p1[i]) + uint64_t(txc) * sizeof(E);
-                p[u] = reinterpret_cast<E *>(packed + off);
+                p[u] = reinterpret_cast<E *>(rows.at(min(i0 + u * TY, ni - 1), txc * uint32_t(sizeof(E))));
                 if constexpr (UNPACK) v[u] = load_elem<NTP>(p[u]);
             }
 #pragma unroll
@@ -1100,25 +1157,7 @@ __global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restr
             }
         }
     };
-    // 16-byte vectors on both sides when every extent, pitch and row start allows it (then a row's chunk border
-    // falls between two vectors too); the tensor side may be less than 16-byte aligned as a whole.
-    constexpr uint32_t V = 16 / sizeof(E);
-    const bool vec_ok = es == sizeof(E) && ((ni | nj) % V) == 0 && ((t.packed_off | t.a | t.b) % 16) == 0;
-    if (vec_ok) {
-        const SpanRows rows{packed, row_p0, row_p1, row_first, row_at, part};    // row_first in bytes: see below
-        if (threadIdx.x < ni) row_first[threadIdx.x] *= uint32_t(sizeof(E));     // (its own entry: no other thread reads it yet)
-        __syncthreads();
-        auto run = [&]<int UA, bool FULL = false>() {
-            if constexpr (!UNPACK) transpose_vec<E, false, CSUM, NTP, UA, FULL>(user, t.a, nj, ni, rows, lds_raw);
-            else transpose_vec<E, true, CSUM, NTP, UA, FULL>(user, t.a, ni, nj, rows, lds_raw);
-        };
-        const uint32_t mis = uint32_t(reinterpret_cast<uintptr_t>(user)) & 15u;
-        if (mis == 0 && ni == T && nj == T) run.template operator()<16, true>();
-        else if (mis == 0) run.template operator()<16>();
-        else if ((mis & 3u) == 0) run.template operator()<4>();
-        else if ((mis & 1u) == 0) run.template operator()<2>();
-        else run.template operator()<1>();
-    } else if constexpr (!UNPACK) {
+    if constexpr (!UNPACK) {
         tensor_side();
         __syncthreads();
         packed_side();
@@ -1127,10 +1166,134 @@ __global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restr
         __syncthreads();
         tensor_side();
     }
+}
+
+template <typename E>
+constexpr uint32_t transpose_lds_bytes() { return TransposeShape<E>::T * (TransposeShape<E>::T + 1) * sizeof(E); }
+
+template <typename E, bool UNPACK, bool CSUM, bool NTU, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__ tiles,
+                                                        const uint32_t *__restrict__ chunk_tiles, BasePtrs bases,
+                                                        uint8_t *__restrict__ packed, SumCtx cx)
+{
+    constexpr uint32_t T = TransposeShape<E>::T;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
+    const Tile t = tiles[blockIdx.x];
+    uint8_t *user = bases.p[t.tensor] + t.src_off;
+    const uint32_t ni = t.n0, nj = t.n1;
+    const PitchRows rows{packed + t.packed_off, t.b, uint32_t(t.packed_off)};
+    u32x4 *lds = reinterpret_cast<u32x4 *>(lds_raw);
+    const uint32_t na = UNPACK ? nj : ni, nb = UNPACK ? ni : nj;
+    uint64_t acc = 0;
+    if (t.estep != sizeof(E))
+        transpose_tile_elements<E, UNPACK, NTP>(user, t.a, t.estep, ni, nj, rows, lds_raw, [&](uint32_t i, E v, uint32_t j) {
+            if constexpr (CSUM) acc += elem_weighted(v, rows.position(i, j * sizeof(E)));
+        });
+    else if (ni == T && nj == T)
+        acc = transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, true>(user, t.a, na, nb, rows, lds, [] {}, [] {});
+    else
+        acc = transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, false>(user, t.a, na, nb, rows, lds, [] {}, [] {});
+    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
+}
+
+// ---- transpose whose tiles span chunks -------------------------------------------
+// For matrices whose packed rows are long against the chunk: a tile is a full block of the logical matrix
+// (so that every memory burst of the tensor side is used whole) and row i of it starts at stream byte
+// s0 + i * b, wherever that falls; a tile row is shorter than a chunk, so it meets at most one chunk
+// border.  Thread i places row i (its chunk, the packed address of its first byte, how many of its
+// bytes lie before the border and where the rest go) and leaves that in LDS, so that the copy only
+// reads it back.  Placing takes no division and no memory access but for rows farther apart than a chunk is long, and
+// what the commit at the end reads is loaded at the start.  Sums go to the tile's per-chunk partial sums in LDS; at the
+// end one thread per chunk touched makes that chunk's arrival (inc holds the tile's chunks, ascending, and the ordinal
+// of each arrival).
+// [256, 65536] bf16 (8 packed rows per 1 MiB chunk), pack + unpack: 33.0 -> 26.0 us.
+template <typename E, bool UNPACK, bool CSUM, bool NTU, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restrict__ tiles,
+                                                             const uint32_t *__restrict__ chunk_tiles,
+                                                             const uint32_t *__restrict__ inc, ChunkGeom g,
+                                                             BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
+{
+    constexpr uint32_t T = TransposeShape<E>::T, MAXC = 2 * T + 2;
+    static_assert(T <= kThreads, "one thread places one row");
+    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
+    __shared__ unsigned long long part[MAXC];          // partial sum per chunk touched
+    // per row: packed offset of byte x is row_p0 + x for x < row_first, row_p1 + x from there on (row_first is a whole
+    // tile row or more where the row meets no border); row_at: entry of the row's first chunk; row_low: low bits of
+    // its first byte's position (for the weights of the sum)
+    __shared__ uint64_t row_p0[T], row_p1[T];
+    __shared__ uint32_t row_first[T], row_at[T], row_low[T];
+    const Tile t = tiles[blockIdx.x];
+    uint8_t *user = bases.p[t.tensor] + t.src_off;
+    const uint32_t ni = t.n0, nj = t.n1, n_inc = t.ordinal;
+    const uint32_t *my = inc + 2 * size_t(t.chunk);
+    uint32_t my_chunk = 0, my_ordinal = 0, my_expected = 0;      // this thread's arrival at the end
+    auto fetch = [&]() {                                // asked for behind the tile's own loads, so that it is there then
+        if (!CSUM || threadIdx.x >= n_inc) return;
+        my_chunk = my[2 * threadIdx.x];
+        my_ordinal = my[2 * threadIdx.x + 1];
+        my_expected = chunk_tiles[my_chunk];
+    };
+    auto place = [&]() {                                // row threadIdx.x; the partial sums start at zero
+        for (uint32_t i = threadIdx.x; i < n_inc; i += kThreads) part[i] = 0;
+        if (threadIdx.x >= ni) return;
+        // (s / B in units of 256 bytes: tensor starts and chunks are multiples of that, and no message comes near 2^39 bytes)
+        const uint64_t B = g.B, s0 = t.packed_off, s = s0 + uint64_t(threadIdx.x) * t.b;
+        const uint32_t c = fast_div(uint32_t(s >> 8), g.div_b256), c0 = fast_div(uint32_t(s0 >> 8), g.div_b256);
+        const uint64_t rem = s - uint64_t(c) * B;
+        uint32_t at = c - c0;                           // rows no farther apart than a chunk is long meet every chunk in turn
+        if (t.b > B) {                                  // else: look for the entry that names chunk c (it is there)
+            uint32_t lo = 0, hi = n_inc - 1;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) / 2;
+                if (my[2 * mid] < c) lo = mid + 1;
+                else hi = mid;
+            }
+            at = lo;
+        }
+        auto chunk_base = [&](uint32_t ch) {
+            const uint32_t slot = fast_div(ch, g.div_k), lane = ch - slot * g.k;
+            return (uint64_t(lane) * g.q + (lane < g.r ? lane : g.r) + slot) * B;
+        };
+        const uint64_t room = B - rem;                  // bytes of chunk c from the row's start on
+        const bool whole = room >= uint64_t(nj) * sizeof(E);
+        row_at[threadIdx.x] = at;
+        row_first[threadIdx.x] = whole ? T * uint32_t(sizeof(E)) : uint32_t(room);
+        row_low[threadIdx.x] = uint32_t(rem) & 3u;
+        row_p0[threadIdx.x] = chunk_base(c) + rem;
+        row_p1[threadIdx.x] = whole ? 0 : chunk_base(c + 1) + rem - B;          // (+ x >= B - rem for those bytes)
+    };
+    const SpanRows rows{packed, row_p0, row_p1, row_first, row_at, row_low, part, ((t.packed_off | t.b) & 15u) != 0};
+    u32x4 *lds = reinterpret_cast<u32x4 *>(lds_raw);
+    const uint32_t na = UNPACK ? nj : ni, nb = UNPACK ? ni : nj;
+    if (t.estep != sizeof(E)) {
+        // one thread holds elements of one row: the part before the chunk border and the part after it are summed in
+        // registers and go to LDS once
+        unsigned long long a0 = 0, a1 = 0;
+        place();
+        fetch();
+        __syncthreads();
+        transpose_tile_elements<E, UNPACK, NTP>(user, t.a, t.estep, ni, nj, rows, lds_raw, [&](uint32_t i, E v, uint32_t j) {
+            if constexpr (CSUM) {
+                const unsigned long long w = elem_weighted(v, rows.position(i, j * sizeof(E)));
+                if (j * sizeof(E) < row_first[i]) a0 += w;
+                else a1 += w;
+            }
+        });
+        if constexpr (CSUM) {
+            const uint32_t tx = threadIdx.x & (T - 1);
+            if (a0) rows.count(tx, false, a0);
+            if (a1) rows.count(tx, true, a1);
+        }
+    } else if (ni == T && nj == T) {
+        transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, true>(user, t.a, na, nb, rows, lds, place, fetch);
+    } else {
+        transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, false>(user, t.a, na, nb, rows, lds, place, fetch);
+    }
     if constexpr (CSUM) {
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < n_inc; i += kThreads)
-            commit_total(part[i], touched[i], my[2 * i + 1], chunk_tiles[touched[i]], cx);
+        if (threadIdx.x < n_inc) commit_total(part[threadIdx.x], my_chunk, my_ordinal, my_expected, cx);
+        for (uint32_t i = threadIdx.x + kThreads; i < n_inc; i += kThreads)
+            commit_total(part[i], my[2 * i], my[2 * i + 1], chunk_tiles[my[2 * i]], cx);
     }
 }
 
