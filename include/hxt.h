@@ -139,8 +139,6 @@ int hxt_plan_destroy(hxt_plan_t *plan); /* NULL is allowed */
  *      it while packed_bytes <= 1 GiB, loads are cacheable up to 64 MiB; non-temporal above;
  *    0 always cacheable;  1 always non-temporal (every byte goes to and comes from HBM).
  *   The environment variable HXT_NT_PACKED (0/1), read when a plan is created, sets the initial value.
- *   Exception: the slower kernel variants taken when a tensor's base pointer is not 16-byte aligned
- *   keep both sides cacheable whatever the hint.
  * HXT_OPT_STAGE_D2H: how hxt_stage_d2h* and the CPU-forwarding path of hxt_exchange_stream move
  *   the packed buffer to pinned host memory.
  *    0 (default) a copy command (hipMemcpyAsync: the runtime picks a DMA engine or a blit kernel of
@@ -175,9 +173,7 @@ int hxt_plan_tensor_unpack_safe(const hxt_plan_t *plan, int t);
 int hxt_plan_tensor_kind(const hxt_plan_t *plan, int t);
 
 /* ---- step 2: pack (Section 2.2: user buffer -> chunk buffer, device to device)
- * src: host array of n_tensors device base pointers (element aligned; a tensor
- *   whose base is not 16-byte aligned is served by the same kernel with narrower
- *   accesses on its side).
+ * src: host array of n_tensors device base pointers (element aligned).
  * packed: device, >= packed_bytes, 256-byte aligned.  Every chunk's padded bytes
  *   are written (pad = 0); nothing else.
  * sums: NULL, or device array of num_chunks uint64 that receives the send-side
@@ -243,7 +239,7 @@ int hxt_unpack_accumulate(const hxt_plan_t *plan, const void *packed, void *cons
                           uint64_t *sums, void *stream);
 
 /* The same for n messages at once, like hxt_unpack_batch: messages that are one contiguous
- * 16-byte aligned tensor each share kernel launches (up to 4 per launch), the others are
+ * tensor each share kernel launches (up to 4 per launch), the others are
  * enqueued one by one; results are those of n hxt_unpack_accumulate calls.  sums: NULL, or an
  * array of n entries each NULL or a device array of that plan's num_chunks values; a plan may
  * appear twice only if at most one of its entries asks for sums (HXT_EINVAL otherwise).
@@ -257,7 +253,7 @@ int hxt_unpack_accumulate_batch(int n, const hxt_plan_t *const *plans, const voi
  * the backward gradient of another).  These calls take n independent messages, each
  * with its own plan, tensors, packed buffer and (optional) checksum array, and give
  * exactly the result of n hxt_pack / hxt_unpack calls on `stream` in order, but
- * messages that consist of one contiguous 16-byte aligned tensor share kernel
+ * messages that consist of one contiguous tensor share kernel
  * launches (up to 4 per launch), which removes per-launch ramp-up for small messages.
  * plans[i], src[i] / dst[i] (array of that plan's tensor pointers) and packed[i] as
  * in the single-message calls; sums may be NULL, and sums[i] may be NULL.
@@ -399,7 +395,7 @@ int hxt_verify(const hxt_plan_t *plan, const void *packed, const hxt_chunk_tag_t
                uint32_t micro_batch, uint32_t *status, void *stream);
 
 /* The same, fused into the copies (no extra pass over the message when all its tensors
- * are contiguous and 16-byte aligned: one activation, or a bucket of gradients; otherwise
+ * are contiguous: one activation, or a bucket of gradients; otherwise
  * the two passes run one after the other on the stream, with identical results):
  * hxt_pack_seal = hxt_pack + hxt_seal,
  * hxt_unpack_verify = hxt_verify + hxt_unpack.  The destination is written whatever the
@@ -414,7 +410,7 @@ int hxt_unpack_verify(const hxt_plan_t *plan, const void *packed, const hxt_chun
  * Code under HIP graph capture, tight serving loops and harnesses that forbid allocation
  * cannot create a plan (hxt_plan* allocates device memory).  hxt_pack_noalloc is hxt_pack for
  * a message that is ONE contiguous tensor of message_bytes bytes at `src` (device, any
- * alignment; 16-byte aligned is the fast path), with the same layout contract, the same
+ * alignment), with the same layout contract, the same
  * packed bytes and the same checksums as hxt_pack on hxt_plan({message_bytes}, NULL, 1,
  * HXT_U8, n_lanes, chunk_bytes).  It needs no plan, and neither it nor anything it calls
  * allocates host or device memory: the geometry is computed on the stack, and the checksum
@@ -437,7 +433,7 @@ int hxt_pack_noalloc(const void *src, size_t message_bytes, int n_lanes, size_t 
 
 /* The fused tag calls for several messages at once, as hxt_pack_batch / hxt_unpack_batch are for
  * the plain sums: exactly the result of n hxt_pack_seal / hxt_unpack_verify calls on `stream` in
- * order; messages that consist of one contiguous 16-byte aligned tensor share launches (up to 4 per
+ * order; messages that consist of one contiguous tensor share launches (up to 4 per
  * launch).  seq[i], micro_batch[i], tags[i], status[i] belong to message i.  HXT_EINVAL also if a
  * plan appears twice.  Nothing is enqueued on error. */
 int hxt_pack_seal_batch(int n, const hxt_plan_t *const *plans, const void *const *const *src,

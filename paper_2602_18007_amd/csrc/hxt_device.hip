@@ -391,32 +391,18 @@ int run_copy(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums,
         std::memset(&a, 0, sizeof a);
         a.n = 1;
         a.it[0] = UniformItem{p.geom, base, packed, cx, 0, UNPACK};
-        if (reinterpret_cast<uintptr_t>(base) % 16 == 0)
-            launch_uniform<UNPACK ? DIR_UNPACK : DIR_PACK, CSUM>(a, p.geom.ntiles, p.C * p.B, pl.nt_packed, st);
-        else                                             // element aligned only: narrower accesses on the tensor side
-            k_uniform_any<UNPACK, CSUM><<<p.geom.ntiles, kThreads, 0, st>>>(a);
+        launch_uniform<UNPACK ? DIR_UNPACK : DIR_PACK, CSUM>(a, p.geom.ntiles, p.C * p.B, pl.nt_packed, st);
         HXT_HIP(hipGetLastError());
         return HXT_OK;
     }
     for (const Group &g : p.groups) {
         BasePtrs b;
         std::memset(&b, 0, sizeof b);
-        bool fast_ok = true;
-        for (uint32_t i = 0; i < g.n_tensors; ++i) {
-            const TensorPlan &tp = p.tensors[g.tensor_base + i];
-            uint8_t *base = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
-            b.p[i] = base;
-            if (tp.bytes && tp.kind == g.kernel && reinterpret_cast<uintptr_t>(base) % 16) fast_ok = false;
-        }
-        if (g.kernel == K_CONTIG && fast_ok) {
+        for (uint32_t i = 0; i < g.n_tensors; ++i) b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
+        if (g.kernel == K_CONTIG) {
             launch_contig<UNPACK, CSUM>(pl, g, b, packed, cx, st);
-        } else if (g.kernel == K_CONTIG) {               // some base is element aligned only
-            k_contig_any<UNPACK, CSUM><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, b, packed, cx);
-        } else if (g.kernel == K_ROWS && fast_ok) {
-            launch_rows<UNPACK, CSUM>(pl, g, b, packed, cx, st);
         } else if (g.kernel == K_ROWS) {
-            k_rows_any<UNPACK, CSUM><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                   g.tensor_base, b, packed, cx);
+            launch_rows<UNPACK, CSUM>(pl, g, b, packed, cx, st);
         } else if (g.kernel == K_ROWS_SPLIT) {
             if (packed_nontemporal(pl, UNPACK))
                 k_rows_split<UNPACK, CSUM, true><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
@@ -446,7 +432,7 @@ int run_copy(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums,
     return HXT_OK;
 }
 
-// Receive and accumulate: contiguous bf16 / f32 tensors with 16-byte aligned bases only.
+// Receive and accumulate: contiguous bf16 / f32 tensors.
 template <bool CSUM>
 int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums, hipStream_t st)
 {
@@ -468,12 +454,9 @@ int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t 
         // `unpack` carries the element kind here: 1 = f32, 0 = bf16
         a.it[0] = UniformItem{p.geom, static_cast<uint8_t *>(ptrs[p.uniform_tensor]), packed, cx, 0,
                               tp.dtype == HXT_F32 ? 1u : 0u};
-        if (reinterpret_cast<uintptr_t>(ptrs[p.uniform_tensor]) % 16 == 0)
-            with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
-                k_uniform_accumulate<CSUM, NTU, NTP><<<p.geom.ntiles, kThreads, 0, st>>>(a);
-            });
-        else
-            k_uniform_accumulate_any<CSUM><<<p.geom.ntiles, kThreads, 0, st>>>(a);
+        with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
+            k_uniform_accumulate<CSUM, NTU, NTP><<<p.geom.ntiles, kThreads, 0, st>>>(a);
+        });
         HXT_HIP(hipGetLastError());
         return HXT_OK;
     }
@@ -482,20 +465,14 @@ int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t 
         ElemKinds kinds;
         std::memset(&b, 0, sizeof b);
         std::memset(&kinds, 0, sizeof kinds);
-        bool aligned = true;
         for (uint32_t i = 0; i < g.n_tensors; ++i) {
             b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
             kinds.f32[i] = p.tensors[g.tensor_base + i].dtype == HXT_F32;
-            if (p.tensors[g.tensor_base + i].bytes && reinterpret_cast<uintptr_t>(b.p[i]) % 16) aligned = false;
         }
-        if (aligned)
-            with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
-                k_contig_accumulate<CSUM, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles,
-                                                                                  b, kinds, packed, cx);
-            });
-        else
-            k_contig_accumulate_any<CSUM><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, b, kinds,
-                                                                        packed, cx);
+        with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
+            k_contig_accumulate<CSUM, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles,
+                                                                              b, kinds, packed, cx);
+        });
         HXT_HIP(hipGetLastError());
     }
     return HXT_OK;
@@ -652,7 +629,7 @@ int stage(const hxt_plan_t *plan, int lane, int64_t first_slot, int64_t n_slots,
     return HXT_OK;
 }
 
-// Batch: the messages that the uniform kernel can take (one contiguous 16-byte aligned tensor,
+// Batch: the messages that the uniform kernel can take (one contiguous tensor,
 // same checksum choice) are fused, up to kMaxBatch per launch; the rest go one by one.
 template <bool UNPACK>
 int run_batch(int n, const hxt_plan_t *const *plans, void *const *const *tensors, void *const *packed,
@@ -676,8 +653,7 @@ int run_batch(int n, const hxt_plan_t *const *plans, void *const *const *tensors
         uint64_t *sm = sums ? sums[i] : nullptr;
         auto fusable = [&](int j) {
             const Plan &q = plans[j]->p;
-            return q.C != 0 && q.uniform && reinterpret_cast<uintptr_t>(tensors[j][q.uniform_tensor]) % 16 == 0 &&
-                   ((sums ? sums[j] : nullptr) != nullptr) == (sm != nullptr);
+            return q.C != 0 && q.uniform && ((sums ? sums[j] : nullptr) != nullptr) == (sm != nullptr);
         };
         if (p.C == 0) {
             ++i;
@@ -749,7 +725,7 @@ int run_sum2(const hxt_plan_t *plan, const void *packed, int mode, void *out, co
 }
 
 // pack + seal (UNPACK = false) or unpack + verify (UNPACK = true).  One pass for a message that is one
-// contiguous, 16-byte aligned tensor; otherwise the copy and the pair-of-sums pass one after the other
+// contiguous tensor; otherwise the copy and the pair-of-sums pass one after the other
 // on the stream, which gives the same bytes, tags and masks.
 template <bool UNPACK>
 int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *out, const TagWork &work, void *stream,
@@ -768,10 +744,7 @@ int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t *pk = static_cast<uint8_t *>(packed);
     uint8_t *base = p.uniform ? static_cast<uint8_t *>(ptrs[p.uniform_tensor]) : nullptr;
-    bool aligned = true;                                 // every live tensor's base on a 16-byte boundary
-    for (size_t i = 0; i < p.tensors.size(); ++i)
-        aligned = aligned && (p.tensors[i].bytes == 0 || reinterpret_cast<uintptr_t>(ptrs[i]) % 16 == 0);
-    const bool one_pass = aligned && (p.uniform || p.all_contig);
+    const bool one_pass = p.uniform || p.all_contig;
     if (!one_pass) {
         if (UNPACK) {                                    // check what arrived, then scatter it
             if ((rc = run_sum2(plan, packed, MODE, out, work, stream, chain)) != HXT_OK) return rc;
@@ -812,7 +785,7 @@ int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *
     return HXT_OK;
 }
 
-// Batched pack + seal / unpack + verify: messages that are one contiguous 16-byte aligned tensor share
+// Batched pack + seal / unpack + verify: messages that are one contiguous tensor share
 // launches (up to kMaxBatch each), the rest go one by one.
 template <bool UNPACK>
 int run_tag_batch(int n, const hxt_plan_t *const *plans, void *const *const *tensors, void *const *packed,
@@ -846,7 +819,7 @@ int run_tag_batch(int n, const hxt_plan_t *const *plans, void *const *const *ten
         };
         auto fusable = [&](int j) {
             const Plan &q = plans[j]->p;
-            return q.C != 0 && q.uniform && reinterpret_cast<uintptr_t>(tensors[j][q.uniform_tensor]) % 16 == 0;
+            return q.C != 0 && q.uniform;
         };
         if (!fusable(i)) {
             int rc;
@@ -1257,7 +1230,7 @@ int hxt_unpack_accumulate(const hxt_plan_t *plan, const void *packed, void *cons
     return sums ? run_accumulate<true>(pl, dst, pk, sums, st) : run_accumulate<false>(pl, dst, pk, nullptr, st);
 }
 
-// Batched receive-and-accumulate: messages that are one contiguous 16-byte aligned tensor share launches of
+// Batched receive-and-accumulate: messages that are one contiguous tensor share launches of
 // up to kMaxBatch (same checksum choice within a launch); the rest go one by one.
 int hxt_unpack_accumulate_batch(int n, const hxt_plan_t *const *plans, const void *const *packed,
                                 void *const *const *dst, uint64_t *const *sums, void *stream)
@@ -1281,8 +1254,7 @@ int hxt_unpack_accumulate_batch(int n, const hxt_plan_t *const *plans, const voi
         uint64_t *sm = sums ? sums[i] : nullptr;
         auto fusable = [&](int j) {
             const Plan &q = plans[j]->p;
-            return q.C != 0 && q.uniform && reinterpret_cast<uintptr_t>(dst[j][q.uniform_tensor]) % 16 == 0 &&
-                   ((sums ? sums[j] : nullptr) != nullptr) == (sm != nullptr);
+            return q.C != 0 && q.uniform && ((sums ? sums[j] : nullptr) != nullptr) == (sm != nullptr);
         };
         if (p.C == 0) {
             ++i;
@@ -1492,14 +1464,8 @@ int hxt_pack_noalloc(const void *src, size_t message_bytes, int n_lanes, size_t 
     a.it[0].first_tile = 0;
     a.it[0].unpack = 0;
     const uint64_t bytes = uint64_t(g.C) * g.B;
-    if (reinterpret_cast<uintptr_t>(user) % 16 == 0) {
-        if (sums) launch_uniform<DIR_PACK, true>(a, g.ntiles, bytes, tuning().nt_packed, st);
-        else launch_uniform<DIR_PACK, false>(a, g.ntiles, bytes, tuning().nt_packed, st);
-    } else if (sums) {
-        k_uniform_any<false, true><<<g.ntiles, kThreads, 0, st>>>(a);
-    } else {
-        k_uniform_any<false, false><<<g.ntiles, kThreads, 0, st>>>(a);
-    }
+    if (sums) launch_uniform<DIR_PACK, true>(a, g.ntiles, bytes, tuning().nt_packed, st);
+    else launch_uniform<DIR_PACK, false>(a, g.ntiles, bytes, tuning().nt_packed, st);
     HXT_HIP(hipGetLastError());
     return HXT_OK;
 }

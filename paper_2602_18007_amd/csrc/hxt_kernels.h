@@ -257,53 +257,10 @@ __device__ __forceinline__ void chunk_commit(uint64_t acc, uint32_t chunk, uint3
 // Copy `bytes` contiguous bytes between a user tensor and the packed buffer (pack: user ->
 // packed, unpack: packed -> user) in 16-byte vectors, UNROLL independent loads in flight per
 // thread before the first store; a last partial vector goes byte by byte.  NTU / NTP mark
-// the user-side / packed-side accesses non-temporal; UA is the alignment of `user`.
-// (The two blocks below are the user-side access helpers and the copy itself.)
-// 16 bytes of a user tensor that is only UA-byte aligned (UA = 16, 4, 2 or 1): the vector is put
-// together from / taken apart into naturally aligned pieces, so no access is misaligned and none
-// touches a byte outside the 16.
-template <int UA, bool NT>
-__device__ __forceinline__ u32x4 load_user(const uint8_t *p)
-{
-    if constexpr (UA == 16) {
-        return load16<NT>(reinterpret_cast<const u32x4 *>(p));
-    } else if constexpr (UA == 4) {
-        const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
-        return u32x4{q[0], q[1], q[2], q[3]};
-    } else if constexpr (UA == 2) {
-        const uint16_t *q = reinterpret_cast<const uint16_t *>(p);
-        return u32x4{q[0] | uint32_t(q[1]) << 16, q[2] | uint32_t(q[3]) << 16, q[4] | uint32_t(q[5]) << 16,
-                     q[6] | uint32_t(q[7]) << 16};
-    } else {
-        uint32_t w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[i] = p[4 * i] | uint32_t(p[4 * i + 1]) << 8 | uint32_t(p[4 * i + 2]) << 16 | uint32_t(p[4 * i + 3]) << 24;
-        return u32x4{w[0], w[1], w[2], w[3]};
-    }
-}
-
-template <int UA, bool NT>
-__device__ __forceinline__ void store_user(uint8_t *p, u32x4 v)
-{
-    if constexpr (UA == 16) {
-        store16<NT>(reinterpret_cast<u32x4 *>(p), v);
-    } else if constexpr (UA == 4) {
-        uint32_t *q = reinterpret_cast<uint32_t *>(p);
-        q[0] = v.x, q[1] = v.y, q[2] = v.z, q[3] = v.w;
-    } else if constexpr (UA == 2) {
-        uint16_t *q = reinterpret_cast<uint16_t *>(p);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) q[2 * i] = uint16_t(w[i]), q[2 * i + 1] = uint16_t(w[i] >> 16);
-    } else {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 16; ++i) p[i] = uint8_t(w[i >> 2] >> (8 * (i & 3)));
-    }
-}
-
-template <bool UNPACK, bool CSUM, bool NTU, bool NTP, int UA = 16>
+// the user-side / packed-side accesses non-temporal.  The tensor may start at any address: with a base that is only
+// element aligned the same instructions cost 4 % (32 MiB, pack + unpack: 20.9 us aligned, 21.7 us one or two bytes
+// off; putting vectors together from narrower aligned accesses took 24.0).
+template <bool UNPACK, bool CSUM, bool NTU, bool NTP>
 __device__ __forceinline__ uint64_t copy_span(uint8_t *user, uint8_t *pk, uint32_t bytes)
 {
     const uint32_t nvec = bytes >> 4;
@@ -311,10 +268,10 @@ __device__ __forceinline__ uint64_t copy_span(uint8_t *user, uint8_t *pk, uint32
     const uint32_t full = nvec / STEP * STEP;            // uniform: blocks that need no bounds checks
     auto load = [&](uint32_t v) {
         if constexpr (UNPACK) return load16<NTP>(reinterpret_cast<const u32x4 *>(pk) + v);
-        else return load_user<UA, NTU>(user + (size_t(v) << 4));
+        else return load16_any<NTU>(user + (size_t(v) << 4));
     };
     auto store = [&](uint32_t v, u32x4 r) {
-        if constexpr (UNPACK) store_user<UA, NTU>(user + (size_t(v) << 4), r);
+        if constexpr (UNPACK) store16_any<NTU>(user + (size_t(v) << 4), r);
         else store_packed16<NTP>(reinterpret_cast<u32x4 *>(pk) + v, r);
     };
     uint64_t acc = 0;
@@ -375,10 +332,10 @@ __device__ __forceinline__ u32x4 add_vec(u32x4 old, u32x4 in)
     else return u32x4{add_bf16x2(old.x, in.x), add_bf16x2(old.y, in.y), add_bf16x2(old.z, in.z), add_bf16x2(old.w, in.w)};
 }
 
-// Adds `bytes` arriving contiguous bytes at pk to the tensor bytes at user (both 16-byte aligned
-// except for a last partial vector, which goes element by element).  Returns the checksum
+// Adds `bytes` arriving contiguous bytes at pk to the tensor bytes at user (element aligned; a last partial vector goes
+// element by element).  Returns the checksum
 // contribution of the packed bytes read.
-template <bool F32, bool CSUM, bool NTU, bool NTP, int UA = 16>
+template <bool F32, bool CSUM, bool NTU, bool NTP>
 __device__ __forceinline__ uint64_t accumulate_span(uint8_t *user, const uint8_t *pk, uint32_t bytes)
 {
     const u32x4 *in = reinterpret_cast<const u32x4 *>(pk);
@@ -392,18 +349,18 @@ __device__ __forceinline__ uint64_t accumulate_span(uint8_t *user, const uint8_t
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             a[u] = load16<NTP>(in + v + u * kThreads);
-            b[u] = load_user<UA, NTU>(user + (size_t(v + u * kThreads) << 4));
+            b[u] = load16_any<NTU>(user + (size_t(v + u * kThreads) << 4));
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            store_user<UA, NTU>(user + (size_t(v + u * kThreads) << 4), add_vec<F32>(b[u], a[u]));
+            store16_any<NTU>(user + (size_t(v + u * kThreads) << 4), add_vec<F32>(b[u], a[u]));
             if constexpr (CSUM) acc += words_sum(a[u]);
         }
     }
     for (uint32_t v = full + threadIdx.x; v < nvec; v += kThreads) {
         const u32x4 a = load16<NTP>(in + v);
         uint8_t *at = user + (size_t(v) << 4);
-        store_user<UA, NTU>(at, add_vec<F32>(load_user<UA, NTU>(at), a));
+        store16_any<NTU>(at, add_vec<F32>(load16_any<NTU>(at), a));
         if constexpr (CSUM) acc += words_sum(a);
     }
     constexpr uint32_t ES = F32 ? 4 : 2;
@@ -508,48 +465,6 @@ __global__ __launch_bounds__(kThreads) void k_contig(const Tile *__restrict__ ti
     if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
 }
 
-// ---- contiguous tensors whose base pointer is only element aligned -------------------
-// The same copies with the user side accessed in pieces of its actual alignment (4, 2 or 1 bytes;
-// the packed side stays 16 bytes wide).  Separate kernels, so that the aligned ones keep their
-// register budget.
-template <bool UNPACK, bool CSUM>
-__device__ __forceinline__ uint64_t copy_span_any(uint8_t *user, uint8_t *pk, uint32_t bytes)
-{
-    const uint32_t mis = uint32_t(reinterpret_cast<uintptr_t>(user)) & 15u;          // the same for the whole workgroup
-    if (mis == 0) return copy_span<UNPACK, CSUM, false, false, 16>(user, pk, bytes);
-    if ((mis & 3u) == 0) return copy_span<UNPACK, CSUM, false, false, 4>(user, pk, bytes);
-    if ((mis & 1u) == 0) return copy_span<UNPACK, CSUM, false, false, 2>(user, pk, bytes);
-    return copy_span<UNPACK, CSUM, false, false, 1>(user, pk, bytes);
-}
-
-template <bool UNPACK, bool CSUM>
-__global__ __launch_bounds__(kThreads) void k_uniform_any(UniformArgs a)
-{
-    const UniformItem &it = a.it[0];
-    const ChunkGeom &g = it.g;
-    const TileSpan t = locate_tile(g, blockIdx.x);
-    const uint64_t left = g.N > t.stream_off ? g.N - t.stream_off : 0;
-    const uint32_t data = left < t.len ? uint32_t(left) : t.len;
-    uint8_t *pk = it.packed + t.packed_off;
-    uint64_t acc = copy_span_any<UNPACK, CSUM>(it.user + t.stream_off, pk, data);
-    if (data < t.len) acc += pad_span<UNPACK, CSUM>(pk + data, t.len - data, data);
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, t.expected, it.cx);
-}
-
-template <bool UNPACK, bool CSUM>
-__global__ __launch_bounds__(kThreads) void k_contig_any(const Tile *__restrict__ tiles,
-                                                         const uint32_t *__restrict__ chunk_tiles, BasePtrs bases,
-                                                         uint8_t *__restrict__ packed, SumCtx cx)
-{
-    const Tile t = tiles[blockIdx.x];
-    uint64_t acc;
-    if (t.kind == K_ZERO)
-        acc = pad_span<UNPACK, CSUM>(packed + t.packed_off, t.n0, uint32_t(t.packed_off));
-    else
-        acc = copy_span_any<UNPACK, CSUM>(bases.p[t.tensor] + t.src_off, packed + t.packed_off, t.n0);
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
 // ---- receive and accumulate: the uniform and the table-driven contiguous kernels -----
 template <bool CSUM, bool NTU, bool NTP>
 __global__ __launch_bounds__(kThreads) void k_uniform_accumulate(UniformArgs a)
@@ -570,48 +485,6 @@ __global__ __launch_bounds__(kThreads) void k_uniform_accumulate(UniformArgs a)
     if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, t.expected, it.cx);
 }
 
-// The same for destinations whose base is only element aligned.
-template <bool F32, bool CSUM>
-__device__ __forceinline__ uint64_t accumulate_span_any(uint8_t *user, const uint8_t *pk, uint32_t bytes)
-{
-    const uint32_t mis = uint32_t(reinterpret_cast<uintptr_t>(user)) & 15u;
-    if (mis == 0) return accumulate_span<F32, CSUM, false, false, 16>(user, pk, bytes);
-    if ((mis & 3u) == 0) return accumulate_span<F32, CSUM, false, false, 4>(user, pk, bytes);
-    return accumulate_span<F32, CSUM, false, false, 2>(user, pk, bytes);      // bf16 on an odd element
-}
-
-template <bool CSUM>
-__global__ __launch_bounds__(kThreads) void k_uniform_accumulate_any(UniformArgs a)
-{
-    const UniformItem &it = a.it[0];
-    const ChunkGeom &g = it.g;
-    const TileSpan t = locate_tile(g, blockIdx.x);
-    const uint64_t left = g.N > t.stream_off ? g.N - t.stream_off : 0;
-    const uint32_t data = left < t.len ? uint32_t(left) : t.len;
-    uint8_t *pk = it.packed + t.packed_off;
-    uint64_t acc = it.unpack ? accumulate_span_any<true, CSUM>(it.user + t.stream_off, pk, data)
-                             : accumulate_span_any<false, CSUM>(it.user + t.stream_off, pk, data);
-    if (data < t.len) acc += pad_span<true, CSUM>(pk + data, t.len - data, data);
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, t.expected, it.cx);
-}
-
-template <bool CSUM>
-__global__ __launch_bounds__(kThreads) void k_contig_accumulate_any(const Tile *__restrict__ tiles,
-                                                                    const uint32_t *__restrict__ chunk_tiles,
-                                                                    BasePtrs bases, ElemKinds kinds,
-                                                                    uint8_t *__restrict__ packed, SumCtx cx)
-{
-    const Tile t = tiles[blockIdx.x];
-    uint64_t acc;
-    if (t.kind == K_ZERO)
-        acc = pad_span<true, CSUM>(packed + t.packed_off, t.n0, uint32_t(t.packed_off));
-    else if (kinds.f32[t.tensor])
-        acc = accumulate_span_any<true, CSUM>(bases.p[t.tensor] + t.src_off, packed + t.packed_off, t.n0);
-    else
-        acc = accumulate_span_any<false, CSUM>(bases.p[t.tensor] + t.src_off, packed + t.packed_off, t.n0);
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
 template <bool CSUM, bool NTU, bool NTP>
 __global__ __launch_bounds__(kThreads) void k_contig_accumulate(const Tile *__restrict__ tiles,
                                                                 const uint32_t *__restrict__ chunk_tiles,
@@ -630,9 +503,9 @@ __global__ __launch_bounds__(kThreads) void k_contig_accumulate(const Tile *__re
 }
 
 // ---- rows: innermost dimension contiguous, outer dimensions strided -------------
-// A 16-byte vector never straddles a run (run length and strides are multiples of 16).
+// A 16-byte vector never straddles a run (run length and strides are multiples of 16; the base need not be).
 // Logical byte -> (row, column) and row -> outer indices use multiply-shift division.
-template <bool UNPACK, bool CSUM, bool NTU, bool NTP, int UA>
+template <bool UNPACK, bool CSUM, bool NTU, bool NTP>
 __device__ __forceinline__ uint64_t rows_tile(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
     const uint32_t row_bytes = td.row_bytes;
@@ -660,14 +533,14 @@ __device__ __forceinline__ uint64_t rows_tile(const Tile &t, const TensorDev &td
             off[u] = o;
             if (v < nvec) {
                 if constexpr (UNPACK) r[u] = load16<NTP>(reinterpret_cast<const u32x4 *>(pk + (uint64_t(v) << 4)));
-                else r[u] = load_user<UA, NTU>(user + o);
+                else r[u] = load16_any<NTU>(user + o);
             }
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const uint32_t v = v0 + u * kThreads;
             if (v < nvec) {
-                if constexpr (UNPACK) store_user<UA, NTU>(user + off[u], r[u]);
+                if constexpr (UNPACK) store16_any<NTU>(user + off[u], r[u]);
                 else store_packed16<NTP>(reinterpret_cast<u32x4 *>(pk + (uint64_t(v) << 4)), r[u]);
                 if constexpr (CSUM) acc += words_sum(r[u]);
             }
@@ -683,28 +556,8 @@ __global__ __launch_bounds__(kThreads) void k_rows(const Tile *__restrict__ tile
                                                    BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
 {
     const Tile t = tiles[blockIdx.x];
-    const uint64_t acc = rows_tile<UNPACK, CSUM, NTU, NTP, 16>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor],
+    const uint64_t acc = rows_tile<UNPACK, CSUM, NTU, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor],
                                                                packed + t.packed_off);
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
-// The same gather when a base pointer is only element aligned (all strides are multiples of 16 bytes, so
-// every vector of a tensor is off by the same amount): narrower accesses on the tensor side.
-template <bool UNPACK, bool CSUM>
-__global__ __launch_bounds__(kThreads) void k_rows_any(const Tile *__restrict__ tiles,
-                                                       const uint32_t *__restrict__ chunk_tiles,
-                                                       const TensorDev *__restrict__ tensors, uint32_t tensor_base,
-                                                       BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
-{
-    const Tile t = tiles[blockIdx.x];
-    const TensorDev &td = tensors[tensor_base + t.tensor];
-    uint8_t *user = bases.p[t.tensor], *pk = packed + t.packed_off;
-    const uint32_t mis = uint32_t(reinterpret_cast<uintptr_t>(user)) & 15u;
-    uint64_t acc;
-    if (mis == 0) acc = rows_tile<UNPACK, CSUM, false, false, 16>(t, td, user, pk);
-    else if ((mis & 3u) == 0) acc = rows_tile<UNPACK, CSUM, false, false, 4>(t, td, user, pk);
-    else if ((mis & 1u) == 0) acc = rows_tile<UNPACK, CSUM, false, false, 2>(t, td, user, pk);
-    else acc = rows_tile<UNPACK, CSUM, false, false, 1>(t, td, user, pk);
     if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
 }
 
@@ -1676,13 +1529,14 @@ struct Partial2 {
 template <bool UNPACK, bool NTU, bool NTP>
 __device__ __forceinline__ Sums2 copy_span2(uint8_t *user, uint8_t *pk, uint32_t bytes)
 {
-    constexpr bool NTL = UNPACK ? NTP : NTU;
-    auto store = [](u32x4 *p, u32x4 v) {
-        if constexpr (UNPACK) store16<NTU>(p, v);
-        else store_packed16<NTP>(p, v);
+    auto load = [&](uint32_t v) {
+        if constexpr (UNPACK) return load16<NTP>(reinterpret_cast<const u32x4 *>(pk) + v);
+        else return load16_any<NTU>(user + (size_t(v) << 4));
     };
-    const u32x4 *s = reinterpret_cast<const u32x4 *>(UNPACK ? pk : user);
-    u32x4 *d = reinterpret_cast<u32x4 *>(UNPACK ? user : pk);
+    auto store = [&](uint32_t v, u32x4 r) {
+        if constexpr (UNPACK) store16_any<NTU>(user + (size_t(v) << 4), r);
+        else store_packed16<NTP>(reinterpret_cast<u32x4 *>(pk) + v, r);
+    };
     const uint32_t nvec = bytes >> 4;
     constexpr uint32_t STEP = kThreads * kUnroll;
     const uint32_t full = nvec / STEP * STEP;
@@ -1692,11 +1546,11 @@ __device__ __forceinline__ Sums2 copy_span2(uint8_t *user, uint8_t *pk, uint32_t
     for (; v < full; v += STEP, n0 += kUnroll) {
         u32x4 r[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) r[u] = load16<NTL>(s + v + u * kThreads);
+        for (int u = 0; u < kUnroll; ++u) r[u] = load(v + u * kThreads);
         uint64_t blockS = 0, blockN = 0, blockI = 0;     // this block's sum_u S_u, sum_u u * S_u, sum_u I_u
 #pragma unroll
         for (int u = kUnroll - 1; u >= 0; --u) {
-            store(d + v + u * kThreads, r[u]);
+            store(v + u * kThreads, r[u]);
             const uint64_t zw = uint64_t(r[u].z) + r[u].w, yzw = zw + r[u].y;
             blockN += blockS;                            // after the loop: sum_u u * S_u
             blockS += yzw + r[u].x;
@@ -1707,8 +1561,8 @@ __device__ __forceinline__ Sums2 copy_span2(uint8_t *user, uint8_t *pk, uint32_t
         p.I += blockI;
     }
     for (; v < nvec; v += kThreads, ++n0) {
-        const u32x4 r = load16<NTL>(s + v);
-        store(d + v, r);
+        const u32x4 r = load(v);
+        store(v, r);
         p.add(r, n0);
     }
     Sums2 acc{p.S, uint64_t(4 * threadIdx.x + 1) * p.S + 4ull * kThreads * p.nS + p.I};
