@@ -394,9 +394,7 @@ int hxt_seal(const hxt_plan_t *plan, const void *packed, uint64_t seq, uint32_t 
 int hxt_verify(const hxt_plan_t *plan, const void *packed, const hxt_chunk_tag_t *tags, uint64_t seq,
                uint32_t micro_batch, uint32_t *status, void *stream);
 
-/* The same, fused into the copies (no extra pass over the message when all its tensors
- * are contiguous: one activation, or a bucket of gradients; otherwise
- * the two passes run one after the other on the stream, with identical results):
+/* The same, fused into the copies (no extra pass over the message, whatever its views):
  * hxt_pack_seal = hxt_pack + hxt_seal,
  * hxt_unpack_verify = hxt_verify + hxt_unpack.  The destination is written whatever the
  * verdict; the caller reads `status` before using it.  Arguments as in those calls. */

@@ -3,13 +3,16 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libhxt.so")
-SOURCES = [os.path.join(PKG, "csrc", "hxt_device.hip"), os.path.join(PKG, "csrc", "hxt_plan.cpp")]
-HEADERS = [os.path.join(PKG, "csrc", "hxt_internal.h"), os.path.join(PKG, "csrc", "hxt_kernels.h"),
-           os.path.join(ROOT, "include", "hxt.h")]
+SOURCES = [os.path.join(PKG, "csrc", f) for f in ("hxt_device.hip", "hxt_transpose.hip", "hxt_transpose_span.hip", "hxt_message_pack.hip",
+                                                      "hxt_message_unpack.hip", "hxt_plan.cpp")]
+HEADERS = [os.path.join(PKG, "csrc", f) for f in ("hxt_internal.h", "hxt_kernels.h", "hxt_launch.h")] + \
+          [os.path.join(ROOT, "include", "hxt.h")]
 
 
 def hipcc() -> str:
@@ -19,14 +22,13 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def command() -> list:
-    return [
-        hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-shared",
-        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-Wall", "-Wextra", "-Wno-unused-parameter",
-        "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
-        "-o", LIB, *SOURCES,
-    ]
+FLAGS = ["-O3", "-std=c++20", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-Wall", "-Wextra", "-Wno-unused-parameter",
+         "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc")]
+
+
+def compile_one(src: str, obj: str) -> None:
+    subprocess.run([hipcc(), "--offload-arch=gfx950", *FLAGS, "-c", "-o", obj, src], check=True)
 
 
 def stale() -> bool:
@@ -38,7 +40,10 @@ def stale() -> bool:
 
 def build(force: bool = True) -> str:
     if force or stale():
-        subprocess.run(command(), check=True)
+        with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(len(SOURCES)) as pool:
+            objs = [os.path.join(tmp, os.path.basename(s) + ".o") for s in SOURCES]
+            list(pool.map(compile_one, SOURCES, objs))
+            subprocess.run([hipcc(), "--offload-arch=gfx950", "-shared", "-o", LIB, *objs], check=True)
     return LIB
 
 

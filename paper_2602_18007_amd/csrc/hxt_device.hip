@@ -19,6 +19,7 @@
 
 #include "hxt_internal.h"
 #include "hxt_kernels.h"
+#include "hxt_launch.h"
 
 using namespace hxt;
 
@@ -72,6 +73,56 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 
+// ---- small kernels ------------------------------------------------------------------
+
+// A few KiB of chunk tags between device memory and pinned host memory (either direction; the pinned
+// buffer is addressed directly over the host link).  A kernel rather than a DMA copy: a launch costs
+// less than the fixed overhead of a copy command, and the DMA queues keep only the large staging copies.
+__global__ __launch_bounds__(kThreads) void k_copy_tags(u32x4 *__restrict__ to, const u32x4 *__restrict__ from, uint32_t nvec)
+{
+    for (uint32_t v = blockIdx.x * kThreads + threadIdx.x; v < nvec; v += gridDim.x * kThreads) to[v] = from[v];
+}
+
+// Plain copy of nvec 16-byte vectors by a small grid (grid-stride), for staging between device memory and
+// pinned host memory over the host link: a few dozen workgroups keep the link busy and leave the rest of the
+// chip to other kernels.  The device side is streamed (non-temporal), four vectors in flight per thread.
+__global__ __launch_bounds__(kThreads) void k_stage_copy(u32x4 *__restrict__ to, const u32x4 *__restrict__ from, uint64_t nvec)
+{
+    const uint64_t step = uint64_t(gridDim.x) * kThreads;
+    uint64_t v = uint64_t(blockIdx.x) * kThreads + threadIdx.x;
+    for (; v + 3 * step < nvec; v += 4 * step) {
+        u32x4 r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = __builtin_nontemporal_load(from + v + u * step);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) __builtin_nontemporal_store(r[u], to + v + u * step);
+    }
+    for (; v < nvec; v += step) __builtin_nontemporal_store(__builtin_nontemporal_load(from + v), to + v);
+}
+
+// Zero-fill of nvec 16-byte vectors (a kernel, so that it can be recorded where a memset node cannot).
+__global__ __launch_bounds__(kThreads) void k_fill_zero(u32x4 *__restrict__ p, uint32_t nvec)
+{
+    for (uint32_t v = blockIdx.x * kThreads + threadIdx.x; v < nvec; v += gridDim.x * kThreads) p[v] = u32x4{0, 0, 0, 0};
+}
+
+// status[C] = number of chunks of status[0 .. C) that were rejected.  One workgroup.
+__global__ __launch_bounds__(kThreads) void k_count_rejected(uint32_t *status, uint32_t C)
+{
+    __shared__ uint32_t part[kThreads / 64];
+    uint32_t n = 0;
+    for (uint32_t c = threadIdx.x; c < C; c += kThreads) n += status[c] != 0;
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_down(n, o, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t total = 0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) total += part[w];
+        status[C] = total;
+    }
+}
+
 // ---- host side --------------------------------------------------------------------
 
 thread_local int g_last_hip = 0;
@@ -108,6 +159,14 @@ constexpr uint64_t kCacheablePackedLoads = uint64_t(64) << 20;
 constexpr uint64_t kWrittenThroughLimit = uint64_t(1) << 30;
 constexpr uint64_t kCacheableTensorLoads = uint64_t(32) << 20;
 
+// Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack +
+// unpack, launches of their own against one launch: bundles of four kinds 0.8 MB 38.7 -> 17.9 us, 7 MB 40.0 -> 18.5 us,
+// with tags 48.5 -> 22.9 us, 17 MB with tags 64.0 -> 40.8 us, 34 MB 46.6 -> 40.9 us.  Where all but one launch is pads
+// the gain is one short launch each way, and k_message's residency (3 or 4 workgroups per CU) costs more than that on
+// large messages: 4.5 MB 23.2 -> 20.0 us, 7.5 MB 26.8 -> 23.6 us, but 17.5 MB 32.4 -> 33.6, 60 MB 102 -> 110 us.
+constexpr uint64_t kOneLaunchLimit = uint64_t(64) << 20;
+constexpr uint64_t kOneLaunchForTwoLimit = uint64_t(8) << 20;
+
 struct Tuning {
     int nt_user, nt_packed;        // -1 = automatic
     Tuning() : nt_user(env_int("HXT_NT_USER", -1)), nt_packed(env_int("HXT_NT_PACKED", -1)) {}
@@ -133,37 +192,13 @@ inline bool user_nontemporal(uint64_t bytes, bool load)
     return o >= 0 ? o != 0 : !load || bytes > kCacheableTensorLoads;
 }
 
-// Calls f.template operator()<NTU, NTP>() for the chosen cache hints.
-template <typename F>
-void with_hints(bool nt_user, bool nt_packed, F &&f)
-{
-    if (nt_user) {
-        if (nt_packed) f.template operator()<true, true>();
-        else f.template operator()<true, false>();
-    } else {
-        if (nt_packed) f.template operator()<false, true>();
-        else f.template operator()<false, false>();
-    }
-}
+using hxt::with_hints;
 
 // The hints of one plan's launch.
 template <bool UNPACK, typename F>
 void with_hints(const hxt_plan_t &pl, F &&f)
 {
     with_hints(user_nontemporal(pl.p.C * pl.p.B, !UNPACK), packed_nontemporal(pl, UNPACK), f);
-}
-
-// The same for the strided kernels, whose stores to the tensors are always non-temporal: a receiving launch has one hint.
-template <bool UNPACK, typename F>
-void with_strided_hints(const hxt_plan_t &pl, F &&f)
-{
-    const bool ntp = packed_nontemporal(pl, UNPACK);
-    if constexpr (UNPACK) {
-        if (ntp) f.template operator()<true, true>();
-        else f.template operator()<true, false>();
-    } else {
-        with_hints(user_nontemporal(pl.p.C * pl.p.B, true), ntp, f);
-    }
 }
 
 // The streaming copies are launched with 32 KiB of (unused) dynamic LDS per workgroup, which caps residency at 5
@@ -190,71 +225,43 @@ void launch_uniform(const UniformArgs &a, uint32_t tiles, uint64_t bytes, int hi
     with_hints(user_nontemporal(bytes, DIR == DIR_PACK), packed_nontemporal(hint, bytes, DIR != DIR_PACK), [&]<bool NTU, bool NTP>() { k_uniform<DIR, CSUM, NTU, NTP><<<tiles, kThreads, lds, st>>>(a); });
 }
 
-template <bool UNPACK, bool CSUM>
-void launch_contig(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const SumCtx &cx,
+template <bool UNPACK, int CHECK>
+void launch_contig(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck,
                    hipStream_t st)
 {
     with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
-        k_contig<UNPACK, CSUM, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, b, packed, cx);
+        if constexpr (CHECK == CHECK_TAGS)
+            k_contig_tag<UNPACK, UNPACK ? SUM2_VERIFY : SUM2_SEAL, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(
+                pl.d_tiles + g.first, pl.d_chunk_tiles, b, packed, ck.g, ck.out, ck.cx.acc, ck.cx.stride, ck.cx.fan, ck.work);
+        else
+            k_contig<UNPACK, CHECK == CHECK_SUMS, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(
+                pl.d_tiles + g.first, pl.d_chunk_tiles, b, packed, ck.cx);
     });
 }
 
-template <bool UNPACK, bool CSUM>
-void launch_rows(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const SumCtx &cx,
+template <bool UNPACK, int CHECK>
+void launch_rows(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck,
                  hipStream_t st)
 {
     with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
-        k_rows<UNPACK, CSUM, NTU, NTP><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                     g.tensor_base, b, packed, cx);
+        k_rows<UNPACK, CHECK, NTU, NTP><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
+                                                                     g.tensor_base, b, packed, ck);
     });
 }
 
-template <bool UNPACK, bool CSUM>
-void launch_transpose(const hxt_plan_t &pl, uint32_t first, uint32_t count, int esize, const BasePtrs &b,
-                      uint8_t *packed, const SumCtx &cx, hipStream_t st)
-{
-    const Tile *tiles = pl.d_tiles + first;
-    const uint32_t *ct = pl.d_chunk_tiles;
-    with_strided_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
-        switch (esize) {
-        case 1: k_transpose<uint8_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
-        case 2: k_transpose<uint16_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
-        case 4: k_transpose<uint32_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
-        default: k_transpose<uint64_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, b, packed, cx); break;
-        }
-    });
-}
-
-template <bool UNPACK, bool CSUM>
-void launch_transpose_span(const hxt_plan_t &pl, uint32_t first, uint32_t count, int esize, const BasePtrs &b,
-                           uint8_t *packed, const SumCtx &cx, hipStream_t st)
-{
-    const Tile *tiles = pl.d_tiles + first;
-    const uint32_t *ct = pl.d_chunk_tiles, *inc = pl.d_inc;
-    const ChunkGeom &g = pl.p.geom;
-    with_strided_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
-        switch (esize) {
-        case 1: k_transpose_span<uint8_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
-        case 2: k_transpose_span<uint16_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
-        case 4: k_transpose_span<uint32_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
-        default: k_transpose_span<uint64_t, UNPACK, CSUM, NTU, NTP><<<count, kThreads, 0, st>>>(tiles, ct, inc, g, b, packed, cx); break;
-        }
-    });
-}
-
-template <bool UNPACK, bool CSUM>
+template <bool UNPACK, int CHECK>
 void launch_generic(const hxt_plan_t &pl, uint32_t first, uint32_t count, uint32_t tensor_base, int esize,
-                    const BasePtrs &b, uint8_t *packed, const SumCtx &cx, hipStream_t st)
+                    const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck, hipStream_t st)
 {
     const Tile *tiles = pl.d_tiles + first;
     const uint32_t *ct = pl.d_chunk_tiles;
     const TensorDev *td = pl.d_tensors;
     auto go = [&]<bool NTP>() {
         switch (esize) {
-        case 1: k_generic<uint8_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, cx); break;
-        case 2: k_generic<uint16_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, cx); break;
-        case 4: k_generic<uint32_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, cx); break;
-        default: k_generic<uint64_t, UNPACK, CSUM, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, cx); break;
+        case 1: k_generic<uint8_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
+        case 2: k_generic<uint16_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
+        case 4: k_generic<uint32_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
+        default: k_generic<uint64_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
         }
     };
     if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
@@ -371,6 +378,63 @@ int scratch_on_device(uint8_t **out)
     return HXT_OK;
 }
 
+// One launch per group of the plan (the strided kernels: one per element size in it).  The chunks' accumulators carry
+// over from one launch to the next.
+template <bool UNPACK, int CHECK>
+int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckArgs<CHECK> &ck, hipStream_t st)
+{
+    const Plan &p = pl.p;
+    const Hints hints{user_nontemporal(p.C * p.B, !UNPACK), packed_nontemporal(pl, UNPACK)};
+    if (p.launches > 1 && p.tensors.size() <= size_t(kMaxGroupTensors) && !hints.packed && tuning().nt_user < 0 &&
+        p.L <= (p.launches > 2 ? kOneLaunchLimit : kOneLaunchForTwoLimit)) {
+        MessageArgs a;
+        std::memset(&a, 0, sizeof a);
+        for (size_t i = 0; i < p.tensors.size(); ++i) a.bases.p[i] = static_cast<uint8_t *>(ptrs[i]);
+        for (const Group &g : p.groups) {
+            a.first[a.n] = g.first;
+            a.base[a.n++] = g.tensor_base;
+        }
+        launch_message<UNPACK, CHECK>(pl.d_tiles, uint32_t(p.tiles.size()), pl.d_chunk_tiles, pl.d_tensors, pl.d_inc, p.geom, a, packed, ck, st);
+        HXT_HIP(hipGetLastError());
+        return HXT_OK;
+    }
+    for (const Group &g : p.groups) {
+        BasePtrs b;
+        std::memset(&b, 0, sizeof b);
+        for (uint32_t i = 0; i < g.n_tensors; ++i) b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
+        if (g.kernel == K_CONTIG) {
+            launch_contig<UNPACK, CHECK>(pl, g, b, packed, ck, st);
+        } else if (g.kernel == K_ROWS) {
+            launch_rows<UNPACK, CHECK>(pl, g, b, packed, ck, st);
+        } else if (g.kernel == K_ROWS_SPLIT) {
+            if (packed_nontemporal(pl, UNPACK))
+                k_rows_split<UNPACK, CHECK, true><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
+                                                                               g.tensor_base, b, packed, ck);
+            else
+                k_rows_split<UNPACK, CHECK, false><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
+                                                                                g.tensor_base, b, packed, ck);
+        } else {
+            // The transpose and per-element kernels are instantiated per element size: issue one
+            // launch per run of tiles whose tensors share it (host table, same order as on the device).
+            uint32_t i = 0;
+            while (i < g.count) {
+                const int es = p.tensors[g.tensor_base + p.tiles[g.first + i].tensor].esize;
+                uint32_t j = i + 1;
+                while (j < g.count && p.tensors[g.tensor_base + p.tiles[g.first + j].tensor].esize == es) ++j;
+                if (g.kernel == K_TRANSPOSE)
+                    launch_transpose<UNPACK, CHECK>(hints, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, b, packed, ck, st);
+                else if (g.kernel == K_TRANSPOSE_SPAN)
+                    launch_transpose_span<UNPACK, CHECK>(hints, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, pl.d_inc, p.geom, b, packed, ck, st);
+                else
+                    launch_generic<UNPACK, CHECK>(pl, g.first + i, j - i, g.tensor_base, es, b, packed, ck, st);
+                i = j;
+            }
+        }
+        HXT_HIP(hipGetLastError());
+    }
+    return HXT_OK;
+}
+
 template <bool UNPACK, bool CSUM>
 int run_copy(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums, hipStream_t st, int chain = 0)
 {
@@ -395,41 +459,7 @@ int run_copy(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums,
         HXT_HIP(hipGetLastError());
         return HXT_OK;
     }
-    for (const Group &g : p.groups) {
-        BasePtrs b;
-        std::memset(&b, 0, sizeof b);
-        for (uint32_t i = 0; i < g.n_tensors; ++i) b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
-        if (g.kernel == K_CONTIG) {
-            launch_contig<UNPACK, CSUM>(pl, g, b, packed, cx, st);
-        } else if (g.kernel == K_ROWS) {
-            launch_rows<UNPACK, CSUM>(pl, g, b, packed, cx, st);
-        } else if (g.kernel == K_ROWS_SPLIT) {
-            if (packed_nontemporal(pl, UNPACK))
-                k_rows_split<UNPACK, CSUM, true><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                               g.tensor_base, b, packed, cx);
-            else
-                k_rows_split<UNPACK, CSUM, false><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                                g.tensor_base, b, packed, cx);
-        } else {
-            // The transpose and per-element kernels are instantiated per element size: issue one
-            // launch per run of tiles whose tensors share it (host table, same order as on the device).
-            uint32_t i = 0;
-            while (i < g.count) {
-                const int es = p.tensors[g.tensor_base + p.tiles[g.first + i].tensor].esize;
-                uint32_t j = i + 1;
-                while (j < g.count && p.tensors[g.tensor_base + p.tiles[g.first + j].tensor].esize == es) ++j;
-                if (g.kernel == K_TRANSPOSE)
-                    launch_transpose<UNPACK, CSUM>(pl, g.first + i, j - i, es, b, packed, cx, st);
-                else if (g.kernel == K_TRANSPOSE_SPAN)
-                    launch_transpose_span<UNPACK, CSUM>(pl, g.first + i, j - i, es, b, packed, cx, st);
-                else
-                    launch_generic<UNPACK, CSUM>(pl, g.first + i, j - i, g.tensor_base, es, b, packed, cx, st);
-                i = j;
-            }
-        }
-        HXT_HIP(hipGetLastError());
-    }
-    return HXT_OK;
+    return run_groups<UNPACK, CSUM ? CHECK_SUMS : CHECK_NONE>(pl, ptrs, packed, CheckArgs<CSUM ? CHECK_SUMS : CHECK_NONE>{cx}, st);
 }
 
 // Receive and accumulate: contiguous bf16 / f32 tensors.
@@ -724,9 +754,8 @@ int run_sum2(const hxt_plan_t *plan, const void *packed, int mode, void *out, co
     return HXT_OK;
 }
 
-// pack + seal (UNPACK = false) or unpack + verify (UNPACK = true).  One pass for a message that is one
-// contiguous tensor; otherwise the copy and the pair-of-sums pass one after the other
-// on the stream, which gives the same bytes, tags and masks.
+// pack + seal (UNPACK = false) or unpack + verify (UNPACK = true) in one pass over the message: every copy kernel
+// takes both sums on the way.
 template <bool UNPACK>
 int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *out, const TagWork &work, void *stream,
                  int chain = 0)
@@ -744,15 +773,6 @@ int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t *pk = static_cast<uint8_t *>(packed);
     uint8_t *base = p.uniform ? static_cast<uint8_t *>(ptrs[p.uniform_tensor]) : nullptr;
-    const bool one_pass = p.uniform || p.all_contig;
-    if (!one_pass) {
-        if (UNPACK) {                                    // check what arrived, then scatter it
-            if ((rc = run_sum2(plan, packed, MODE, out, work, stream, chain)) != HXT_OK) return rc;
-            return run_copy<true, false>(pl, ptrs, pk, nullptr, st, chain);
-        }
-        if ((rc = run_copy<false, false>(pl, ptrs, pk, nullptr, st, chain)) != HXT_OK) return rc;
-        return run_sum2(plan, packed, MODE, out, work, stream, chain);
-    }
     SumCtx cx{nullptr, nullptr, 0, 0, 1, 0};
     SlotsLock lock(pl.slots_mu);
     if ((rc = claim_slots(pl, UNPACK ? (chain ? OP_SUM2_RECV_B : OP_SUM2_RECV) : (chain ? OP_SUM2_SEND_B : OP_SUM2_SEND), st, cx, nullptr)) != HXT_OK) return rc;
@@ -769,20 +789,8 @@ int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *
         HXT_HIP(hipGetLastError());
         return HXT_OK;
     }
-    // contiguous tensors of a multi-tensor message: the table-driven copy with both sums taken on the way; the
-    // chunks' accumulators carry over from one launch group to the next
     w.sum_bits = pl.sum_bits_table;
-    for (const Group &g : p.groups) {
-        BasePtrs b;
-        std::memset(&b, 0, sizeof b);
-        for (uint32_t i = 0; i < g.n_tensors; ++i) b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
-        with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
-            k_contig_tag<UNPACK, MODE, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, b, pk,
-                                                                               p.geom, out, cx.acc, cx.stride, cx.fan, w);
-        });
-        HXT_HIP(hipGetLastError());
-    }
-    return HXT_OK;
+    return run_groups<UNPACK, CHECK_TAGS>(pl, ptrs, pk, CheckArgs<CHECK_TAGS>{cx, p.geom, out, w}, st);
 }
 
 // Batched pack + seal / unpack + verify: messages that are one contiguous tensor share

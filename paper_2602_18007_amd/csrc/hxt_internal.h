@@ -167,7 +167,7 @@ struct Plan {
     ChunkGeom geom;                      // closed-form geometry of the packed stream
     bool uniform = false;                // the message is one contiguous tensor: geom alone describes the copy
     uint32_t uniform_tensor = 0;         // index of that tensor
-    bool all_contig = false;             // every launch group is a contiguous copy (zero pads included)
+    uint32_t launches = 0;               // launches the groups take, one per group and element size
 
     uint64_t chunk_padded(uint64_t c) const;
     uint64_t chunk_packed_off(uint64_t c) const { return lane_off[c % k] + (c / k) * B; }

@@ -502,809 +502,7 @@ __global__ __launch_bounds__(kThreads) void k_contig_accumulate(const Tile *__re
     if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
 }
 
-// ---- rows: innermost dimension contiguous, outer dimensions strided -------------
-// A 16-byte vector never straddles a run (run length and strides are multiples of 16; the base need not be).
-// Logical byte -> (row, column) and row -> outer indices use multiply-shift division.
-template <bool UNPACK, bool CSUM, bool NTU, bool NTP>
-__device__ __forceinline__ uint64_t rows_tile(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
-{
-    const uint32_t row_bytes = td.row_bytes;
-    const uint64_t row0 = t.src_off / row_bytes;                    // uniform
-    const uint32_t col0 = uint32_t(t.src_off - row0 * row_bytes);
-    const int outer = td.ndim - 1;
-    const uint32_t nvec = t.n0 >> 4;
-    uint64_t acc = 0;
-    for (uint32_t v0 = threadIdx.x; v0 < nvec; v0 += kThreads * kUnroll) {
-        u32x4 r[kUnroll];
-        uint64_t off[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const uint32_t v = v0 + u * kThreads;
-            const uint32_t x = col0 + (v << 4);
-            const uint32_t dr = fast_div(x, td.row_div);
-            uint32_t row = uint32_t(row0) + dr;
-            uint64_t o = x - dr * row_bytes;
-            for (int d = outer - 1; d > 0; --d) {
-                const uint32_t q = fast_div(row, td.dim_div[d]);
-                o += uint64_t(row - q * uint32_t(td.shape[d])) * uint64_t(td.stride_b[d]);
-                row = q;
-            }
-            o += uint64_t(row) * uint64_t(td.stride_b[0]);
-            off[u] = o;
-            if (v < nvec) {
-                if constexpr (UNPACK) r[u] = load16<NTP>(reinterpret_cast<const u32x4 *>(pk + (uint64_t(v) << 4)));
-                else r[u] = load16_any<NTU>(user + o);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const uint32_t v = v0 + u * kThreads;
-            if (v < nvec) {
-                if constexpr (UNPACK) store16_any<NTU>(user + off[u], r[u]);
-                else store_packed16<NTP>(reinterpret_cast<u32x4 *>(pk + (uint64_t(v) << 4)), r[u]);
-                if constexpr (CSUM) acc += words_sum(r[u]);
-            }
-        }
-    }
-    return acc;
-}
-
-template <bool UNPACK, bool CSUM, bool NTU, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_rows(const Tile *__restrict__ tiles,
-                                                   const uint32_t *__restrict__ chunk_tiles,
-                                                   const TensorDev *__restrict__ tensors, uint32_t tensor_base,
-                                                   BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
-{
-    const Tile t = tiles[blockIdx.x];
-    const uint64_t acc = rows_tile<UNPACK, CSUM, NTU, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor],
-                                                               packed + t.packed_off);
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
-// ---- rows whose length or pitch is not a multiple of 16 bytes ----------------------
-// Still a gather of contiguous runs (of 16 bytes or more), but a 16-byte vector of the packed stream may end
-// one run and begin the next, and the tensor side is only G-byte aligned (G = 8, 4, 2 or 1).
-// Work is dealt in pieces of G bytes, consecutive lanes taking consecutive pieces of the tile: a wave's access
-// is then contiguous on the packed side and contiguous within each run on the tensor side (64 lanes x 4 bytes
-// = 256 bytes per instruction), whatever the run length; each piece finds its run with one multiply-shift
-// division and the run's storage offset from the outer indices.
-template <int G> struct PieceOf;
-template <> struct PieceOf<8> { using type = uint64_t; };
-template <> struct PieceOf<4> { using type = uint32_t; };
-template <> struct PieceOf<2> { using type = uint16_t; };
-template <> struct PieceOf<1> { using type = uint8_t; };
-
-// TWO_D: the view has two dims (the usual padded-pitch matrix) and needs no index decomposition: run
-// row0 + dr starts (row0 + dr) * pitch into the storage, so byte x of the tile's first run sits at
-// x + dr * (pitch - run length) from that run's start.  Otherwise the run's storage offset comes from
-// its outer indices, divided out with the dims held in registers (the loop stores through byte
-// pointers, which may alias the descriptor, so anything read through it inside the loop would be
-// read again for every piece).  With pieces of 1 or 2 bytes the loads of a round are unconditional
-// (the piece number is clamped into the tile): guarded, the compiler waits for each load before it
-// goes on to the next guard, and 16 loads one after the other cost 1.8-2.4 times the time.  With pieces
-// of 4 or 8 bytes the guarded loads are issued without such waits, interleaved with the address
-// arithmetic, and that order measures 10 % faster than eight loads in one burst.
-template <bool UNPACK, bool CSUM, bool NTP, int G, bool TWO_D>
-__device__ __forceinline__ uint64_t rows_split_tile(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
-{
-    using P = typename PieceOf<G>::type;
-    const uint32_t row_bytes = td.row_bytes;
-    const FastDiv row_div = td.row_div;
-    const uint64_t row0 = t.src_off / row_bytes;                    // uniform
-    const uint32_t col0 = uint32_t(t.src_off - row0 * row_bytes);
-    const uint32_t npiece = t.n0 / G;
-    constexpr int U = G == 8 ? 8 : 16;                              // pieces in flight per thread: a 16 KiB tile in one go
-    constexpr int D = TWO_D ? 1 : HXT_MAX_DIMS - 1;                 // dims outside the run
-    const int outer = TWO_D ? 1 : td.ndim - 1;
-    uint32_t shape[D], mul[D], shift[D];
-    uint64_t stride[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        shape[d] = 1, mul[d] = 0, shift[d] = 0, stride[d] = 0;
-        if (d < outer) {
-            shape[d] = uint32_t(td.shape[d]);
-            mul[d] = td.dim_div[d].mul;
-            shift[d] = td.dim_div[d].shift;
-            stride[d] = uint64_t(td.stride_b[d]);
-        }
-    }
-    uint8_t *const first_run = user + row0 * stride[0];             // uniform
-    const int64_t slack = int64_t(stride[0]) - int64_t(row_bytes);
-    auto user_piece = [&](uint32_t i) {                             // piece i of the tile -> its place in storage
-        const uint32_t x = col0 + i * G;
-        const uint32_t dr = fast_div(x, row_div);
-        if constexpr (TWO_D) {
-            return reinterpret_cast<P *>(first_run + (int64_t(x) + int64_t(dr) * slack));
-        } else {
-            uint32_t row = uint32_t(row0) + dr;
-            uint64_t o = 0;
-#pragma unroll
-            for (int d = D - 1; d > 0; --d) {
-                if (d < outer) {
-                    const uint32_t q = fast_div(row, FastDiv{mul[d], shift[d]});
-                    o += uint64_t(row - q * shape[d]) * stride[d];
-                    row = q;
-                }
-            }
-            return reinterpret_cast<P *>(user + o + uint64_t(row) * stride[0] + (x - dr * row_bytes));
-        }
-    };
-    P *pieces = reinterpret_cast<P *>(pk);
-    uint64_t acc = 0;
-    const uint32_t last = npiece - 1;
-    for (uint32_t i0 = threadIdx.x; i0 < npiece; i0 += kThreads * U) {
-        P r[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if constexpr (G >= 4) {
-                const uint32_t i = i0 + u * kThreads;
-                r[u] = 0;
-                if (i < npiece) {
-                    if constexpr (UNPACK) r[u] = load_elem<NTP>(pieces + i);
-                    else r[u] = __builtin_nontemporal_load(user_piece(i));
-                }
-            } else {
-                const uint32_t i = min(i0 + u * kThreads, last);
-                if constexpr (UNPACK) r[u] = load_elem<NTP>(pieces + i);
-                else r[u] = __builtin_nontemporal_load(user_piece(i));
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t i = i0 + u * kThreads;
-            if (i < npiece) {
-                if constexpr (UNPACK) __builtin_nontemporal_store(r[u], user_piece(i));
-                else store_packed_elem<NTP>(pieces + i, r[u]);
-                if constexpr (CSUM && G == 8) acc += (uint64_t(r[u]) & 0xFFFFFFFFull) + (uint64_t(r[u]) >> 32);
-                if constexpr (CSUM && G < 8) acc += uint64_t(r[u]) << (8 * ((i * G) & 3));
-            }
-        }
-    }
-    return acc;
-}
-
-template <bool UNPACK, bool CSUM, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict__ tiles,
-                                                         const uint32_t *__restrict__ chunk_tiles,
-                                                         const TensorDev *__restrict__ tensors, uint32_t tensor_base,
-                                                         BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
-{
-    const Tile t = tiles[blockIdx.x];
-    const TensorDev &td = tensors[tensor_base + t.tensor];
-    uint8_t *user = bases.p[t.tensor], *pk = packed + t.packed_off;
-    // widest piece that is naturally aligned everywhere: low bits of the base address, the run length and the pitches
-    const uint32_t low = (uint32_t(reinterpret_cast<uintptr_t>(user)) | td.low_or) & 15u;
-    auto run = [&]<int G>() {
-        return td.ndim == 2 ? rows_split_tile<UNPACK, CSUM, NTP, G, true>(t, td, user, pk)
-                            : rows_split_tile<UNPACK, CSUM, NTP, G, false>(t, td, user, pk);
-    };
-    uint64_t acc;
-    if ((low & 7u) == 0) acc = run.template operator()<8>();
-    else if ((low & 3u) == 0) acc = run.template operator()<4>();
-    else if ((low & 1u) == 0) acc = run.template operator()<2>();
-    else acc = run.template operator()<1>();
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
-template <typename E>
-__device__ __forceinline__ uint64_t elem_weighted(E v, uint64_t packed_pos)
-{
-    if constexpr (sizeof(E) == 8) {
-        return uint64_t(uint32_t(v)) + uint64_t(uint32_t(uint64_t(v) >> 32));
-    } else {
-        return uint64_t(v) << (8 * (packed_pos & 3));
-    }
-}
-
-// ---- transpose: logical inner dimension strided, the one before it contiguous ----
-// A tile is ni x nj elements (at most T x T: 128 x 128 for 1- and 2-byte elements, 64 x 64 otherwise).  The tensor
-// stores nj rows of ni contiguous elements, the packed stream has ni rows of nj.  A thread loads a block of V x V
-// elements (V = 16 bytes' worth: V rows of one vector each), transposes it in registers and leaves V vectors in LDS;
-// after the barrier the tile's rows leave LDS as whole vectors, 16 lanes (256 contiguous bytes) to a row.  So LDS is
-// touched by 16-byte accesses only, once each way; gathering elements out of it instead kept the LDS pipe busy for
-// about 1.7 us of a 14 us launch (64 two-byte reads per thread).  32 MiB of bf16, pack + unpack: 27.3 -> 24.4 us (a plain copy of the same bytes: 24.1).
-// Vectors need no alignment beyond the element's: the hardware takes misaligned 16-byte accesses, and even with both
-// row pitches odd (bf16, pitches of 8198 bytes) they beat element accesses, 30 against 31-38 us per pair.
-template <typename E>
-struct TransposeShape {
-    static constexpr uint32_t T = transpose_tile(sizeof(E)), V = 16 / sizeof(E);
-    static constexpr uint32_t NB = T / V;                        // vectors per tile row, blocks per tile side
-    static constexpr uint32_t BLOCKS = NB * NB;
-};
-
-// x[r] holds V elements of source row r; afterwards x[c] holds the V elements of source column c.
-template <typename E>
-__device__ __forceinline__ void transpose_block(u32x4 (&x)[16 / sizeof(E)])
-{
-    constexpr int V = 16 / sizeof(E);
-    u32x4 y[V];
-    if constexpr (sizeof(E) == 8) {
-        y[0] = u32x4{x[0].x, x[0].y, x[1].x, x[1].y};
-        y[1] = u32x4{x[0].z, x[0].w, x[1].z, x[1].w};
-    } else if constexpr (sizeof(E) == 4) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) y[c] = u32x4{x[0][c], x[1][c], x[2][c], x[3][c]};
-    } else if constexpr (sizeof(E) == 2) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t a = x[2 * q][c], b = x[2 * q + 1][c];
-                y[2 * c][q] = __builtin_amdgcn_perm(b, a, 0x05040100u);
-                y[2 * c + 1][q] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-            }
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t lo01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x05010400u);       // bytes 0 0' 1 1'
-                const uint32_t hi01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x07030602u);       // bytes 2 2' 3 3'
-                const uint32_t lo23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x05010400u);
-                const uint32_t hi23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x07030602u);
-                y[4 * c][q] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
-                y[4 * c + 1][q] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
-                y[4 * c + 2][q] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
-                y[4 * c + 3][q] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-            }
-    }
-#pragma unroll
-    for (int i = 0; i < V; ++i) x[i] = y[i];
-}
-
-// Where the rows of a tile lie on the packed side.
-// PitchRows: a tile inside one chunk, rows a fixed pitch apart, one sum for the tile.
-struct PitchRows {
-    static constexpr bool kSpan = false;
-    uint8_t *base;                 // element (0, 0) of the tile
-    uint64_t pitch;
-    uint32_t pos;                  // low bits of its position in the packed buffer (for the phase of sums)
-    __device__ __forceinline__ uint8_t *at(uint32_t row, uint32_t byte) const { return base + row * pitch + byte; }
-    __device__ __forceinline__ uint32_t position(uint32_t row, uint32_t byte) const { return pos + row * uint32_t(pitch) + byte; }
-};
-// SpanRows: every row placed on its own (k_transpose_span keeps the placement in LDS): bytes below first[row] lie from
-// p0[row] on in the packed buffer, the rest at p1[row]; sums go to the partial sum of the chunk they fall into.
-struct SpanRows {
-    static constexpr bool kSpan = true;
-    uint8_t *packed;
-    const uint64_t *p0, *p1;
-    const uint32_t *first, *entry, *low;
-    unsigned long long *part;
-    bool may_cross;                // a vector may straddle a chunk border (rows are not 16-byte aligned against it)
-    __device__ __forceinline__ uint8_t *at(uint32_t row, uint32_t byte) const
-    {
-        return packed + (byte < first[row] ? p0[row] : p1[row]) + byte;
-    }
-    __device__ __forceinline__ uint32_t position(uint32_t row, uint32_t byte) const { return low[row] + byte; }
-    __device__ __forceinline__ bool crosses(uint32_t row, uint32_t byte) const
-    {
-        return may_cross && byte < first[row] && byte + 16 > first[row];
-    }
-    __device__ __forceinline__ void count(uint32_t row, bool second, uint64_t s) const
-    {
-        __hip_atomic_fetch_add(&part[entry[row] + (second ? 1u : 0u)], (unsigned long long)s, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-};
-
-// The elements of a vector on the packed side that straddles a chunk border (bytes below `first` of the row lie from
-// `before` on, the rest from `after` on), one at a time.
-template <typename E, bool NTP>
-__device__ __forceinline__ void store_crossing(uint8_t *before, uint8_t *after, uint32_t first, uint32_t byte, uint32_t n, u32x4 v)
-{
-    constexpr uint32_t ES = sizeof(E);
-#pragma unroll
-    for (uint32_t q = 0; q < 16 / ES; ++q) {
-        const uint32_t at = byte + q * ES;
-        const E e = E(ES == 8 ? uint64_t(v[q * ES / 4]) | uint64_t(v[(q * ES / 4 + 1) & 3]) << 32 : uint64_t(v[q * ES / 4]) >> (8 * (q * ES & 3)));
-        if (q < n) store_packed_elem<NTP>(reinterpret_cast<E *>((at < first ? before : after) + at), e);
-    }
-}
-
-template <typename E>
-__device__ __forceinline__ u32x4 load_crossing(const uint8_t *before, const uint8_t *after, uint32_t first, uint32_t byte)
-{
-    union {
-        E e[16 / sizeof(E)];
-        u32x4 x;
-    } o;
-#pragma unroll
-    for (uint32_t q = 0; q < 16 / sizeof(E); ++q) {
-        const uint32_t at = byte + q * uint32_t(sizeof(E));
-        o.e[q] = *reinterpret_cast<const E *>((at < first ? before : after) + at);
-    }
-    return o.x;
-}
-
-// Adds the sum of a vector of packed bytes (n of them from byte `skip` on count) to the tile's sum, or to the partial sum
-// of its chunk.  SpanRows: called by all lanes of a wave, the 16 lanes of a DPP row holding vectors of one tile row
-// (live: this lane's vector counts); the row is summed across those lanes first, so that one lane goes to LDS.
-template <typename E, class Rows>
-__device__ __forceinline__ void count_packed(const Rows &rows, uint32_t row, uint32_t byte, u32x4 v, uint32_t skip, uint32_t n,
-                                             bool live, uint64_t &acc)
-{
-    const u32x4 kept = live ? keep_bytes(v, skip, n) : u32x4{0, 0, 0, 0};
-    if constexpr (!Rows::kSpan) {
-        acc += rotated_sum(kept, rows.position(row, byte));
-    } else {
-        const uint32_t border = rows.first[row];
-        const bool crossing = rows.crosses(row, byte);
-        if (crossing && live) {                          // split at the border: rare, and only where rows are misaligned
-            const uint32_t before = border - byte;
-            rows.count(row, false, rotated_sum(keep_bytes(kept, 0, before), rows.position(row, byte)));
-            rows.count(row, true, rotated_sum(keep_bytes(kept, before, 16), rows.position(row, byte)));
-        }
-        const uint64_t s = crossing ? 0 : rotated_sum(kept, rows.position(row, byte));
-        constexpr bool kGrouped = TransposeShape<E>::NB % 16 == 0;
-        const bool whole = border >= TransposeShape<E>::T * uint32_t(sizeof(E));     // the row meets no border in this tile
-        if constexpr (kGrouped) {
-            const uint64_t total = row16_sum(s);
-            if (whole && (threadIdx.x & 15) == 15) rows.count(row, false, total);
-            if (!whole && s) rows.count(row, byte >= border, s);
-        } else {
-            if (s) rows.count(row, byte >= border, s);
-        }
-    }
-}
-
-// Moves one tile.  Source rows are the tensor's (pack) or the packed side's (unpack): nb rows of na elements.
-// place() puts into LDS what `rows` reads there; a pack does that while its loads from the tensor are on their way.
-// fetch() asks for what the caller needs at the end.
-template <typename E, bool UNPACK, bool CSUM, bool NTU, bool NTP, bool FULL, class Rows, class Place, class Fetch>
-__device__ __forceinline__ uint64_t transpose_tile_vectors(uint8_t *user, uint64_t user_pitch, uint32_t na_in, uint32_t nb_in,
-                                                           const Rows &rows, u32x4 *lds, Place &&place, Fetch &&fetch)
-{
-    using Sh = TransposeShape<E>;
-    constexpr uint32_t T = Sh::T, V = Sh::V, NB = Sh::NB, ES = sizeof(E);
-    constexpr uint32_t PER = Sh::BLOCKS < uint32_t(kThreads) ? 1 : Sh::BLOCKS / kThreads;      // blocks per thread
-    const uint32_t na = FULL ? T : na_in, nb = FULL ? T : nb_in;
-    auto slot_of = [](uint32_t row, uint32_t slot) { return row * NB + (slot ^ ((row / V) & (NB - 1))); };
-    uint64_t acc = 0;
-    if constexpr (Rows::kSpan && UNPACK) {
-        place();
-        __syncthreads();
-    }
-#pragma unroll
-    for (uint32_t k = 0; k < PER; ++k) {
-        const uint32_t id = threadIdx.x + k * kThreads, la = id & (NB - 1), lb = id / NB;
-        const uint32_t a0 = la * V, b0 = lb * V;
-        constexpr bool kAll = FULL && Sh::BLOCKS >= uint32_t(kThreads);      // every thread has a whole block
-        const bool live = kAll || (id < Sh::BLOCKS && a0 < na && b0 < nb);
-        auto row_of = [&](uint32_t r) { return kAll ? b0 + r : min(b0 + r, nb - 1); };
-        // The last block of a row that is no multiple of V starts early enough to end with it (its first columns are
-        // then moved twice, with the same values); rows beyond the tile repeat the last one.
-        const uint32_t as = FULL || a0 + V <= na ? a0 : (na >= V ? na - V : 0);
-        const bool narrow = !FULL && na < V;
-        u32x4 x[V];
-        if (live && !narrow) {
-#pragma unroll
-            for (uint32_t r = 0; r < V; ++r) {
-                const uint32_t b = row_of(r);
-                if constexpr (!UNPACK) {
-                    x[r] = load16_any<NTU>(user + b * user_pitch + as * ES);
-                } else if constexpr (!Rows::kSpan) {
-                    x[r] = load16_any<NTP>(rows.at(b, as * ES));
-                } else {
-                    // (a vector across a chunk border is read from the 16 bytes that end there, and put right below)
-                    const uint32_t byte = rows.crosses(b, as * ES) ? rows.first[b] - 16u : as * ES;
-                    x[r] = load16_any<NTP>(rows.packed + (as * ES < rows.first[b] ? rows.p0[b] : rows.p1[b]) + int32_t(byte));
-                }
-            }
-            if constexpr (UNPACK && Rows::kSpan) {
-                if (rows.may_cross)
-#pragma unroll
-                    for (uint32_t r = 0; r < V; ++r) {
-                        const uint32_t b = row_of(r);
-                        if (rows.crosses(b, as * ES)) x[r] = load_crossing<E>(rows.packed + rows.p0[b], rows.packed + rows.p1[b], rows.first[b], as * ES);
-                    }
-            }
-        } else if (live) {                               // fewer than V columns in the whole tile
-#pragma unroll
-            for (uint32_t r = 0; r < V; ++r) {
-                const uint32_t b = row_of(r);
-                union {
-                    E e[V];
-                    u32x4 v;
-                } o{};
-#pragma unroll
-                for (uint32_t q = 0; q < V; ++q)
-                    if (q < na) {
-                        if constexpr (!UNPACK) o.e[q] = *reinterpret_cast<const E *>(user + b * user_pitch + q * ES);
-                        else o.e[q] = *reinterpret_cast<const E *>(rows.at(b, q * ES));
-                    }
-                x[r] = o.v;
-            }
-        }
-        if constexpr (CSUM && UNPACK) {
-            const uint32_t skip = (a0 - as) * ES, n = narrow ? na * ES : 16;
-#pragma unroll
-            for (uint32_t r = 0; r < V; ++r)
-                count_packed<E>(rows, row_of(r), as * ES, x[r], FULL ? 0 : skip, FULL ? 16 : n,
-                                live && (kAll || b0 + r < nb), acc);
-        }
-        if (k == 0) {
-            if constexpr (!UNPACK) place();
-            fetch();
-        }
-        if (live) {
-            transpose_block<E>(x);
-#pragma unroll
-            for (uint32_t c = 0; c < V; ++c)
-                if (!narrow || c < na) lds[slot_of(as + c, lb)] = x[c];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t k = 0; k < T * NB / kThreads; ++k) {
-        const uint32_t id = threadIdx.x + k * kThreads, row = id / NB, slot = id & (NB - 1);
-        const bool live = FULL || (row < na && slot * V < nb);
-        const uint32_t r = FULL ? row : min(row, na - 1), n = FULL ? V : min(V, nb - min(slot * V, nb));
-        const u32x4 v = lds[slot_of(r, slot)];
-        if constexpr (CSUM && !UNPACK) count_packed<E>(rows, r, slot * 16, v, 0, n * ES, live, acc);
-        if (!live) continue;
-        if constexpr (UNPACK) {
-            uint8_t *to = user + r * user_pitch + slot * 16;
-            if (FULL || n == V) store16_any<true>(to, v);
-            else store_elems<E>(to, v, n);
-        } else if constexpr (!Rows::kSpan) {
-            uint8_t *to = rows.at(r, slot * 16);
-            if (FULL || n == V) store_packed16<NTP>(reinterpret_cast<u32x4 *>(to), v);
-            else store_elems<E>(to, v, n);
-        } else {
-            if ((FULL || n == V) && !rows.crosses(r, slot * 16)) store_packed16<NTP>(reinterpret_cast<u32x4 *>(rows.at(r, slot * 16)), v);
-            else store_crossing<E, NTP>(rows.packed + rows.p0[r], rows.packed + rows.p1[r], rows.first[r], slot * 16, n, v);
-        }
-    }
-    return acc;
-}
-
-// The tensor's fast direction has a stride of a few elements (es bytes from element to element): element by element,
-// through an LDS tile padded by one element.  Thread (tx, ty) holds elements of packed row tx only while it is on the
-// tensor side and sums them there: sum(row, v, j) for element j of its row.  Eight global loads per thread are issued
-// before the first of them is needed (row and column numbers are clamped into the tile, so the loads need no guard).
-template <typename E, bool UNPACK, bool NTP, class Rows, class Sum>
-__device__ __forceinline__ void transpose_tile_elements(uint8_t *user, uint64_t user_pitch, uint32_t es, uint32_t ni, uint32_t nj,
-                                                        const Rows &rows, uint8_t *lds_raw, Sum &&sum)
-{
-    constexpr uint32_t T = TransposeShape<E>::T, TY = kThreads / T, U = 8;
-    E(*lds)[T + 1] = reinterpret_cast<E(*)[T + 1]>(lds_raw);
-    const uint32_t tx = threadIdx.x & (T - 1), ty = threadIdx.x / T;
-    auto tensor_side = [&]() {
-        if (tx >= ni) return;
-        for (uint32_t j0 = ty; j0 < nj; j0 += TY * U) {
-            E v[U];
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t j = min(j0 + u * TY, nj - 1);
-                if constexpr (!UNPACK) v[u] = __builtin_nontemporal_load(reinterpret_cast<const E *>(user + j * user_pitch + tx * es));
-                else v[u] = lds[j][tx];
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t j = j0 + u * TY;
-                if (j < nj) {
-                    if constexpr (!UNPACK) lds[j][tx] = v[u];
-                    else __builtin_nontemporal_store(v[u], reinterpret_cast<E *>(user + j * user_pitch + tx * es));
-                    sum(tx, v[u], j);
-                }
-            }
-        }
-    };
-    auto packed_side = [&]() {
-        const uint32_t txc = min(tx, nj - 1);
-        for (uint32_t i0 = ty; i0 < ni; i0 += TY * U) {
-            E *p[U];
-            E v[U];
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                p[u] = reinterpret_cast<E *>(rows.at(min(i0 + u * TY, ni - 1), txc * uint32_t(sizeof(E))));
-                if constexpr (UNPACK) v[u] = load_elem<NTP>(p[u]);
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t i = i0 + u * TY;
-                if (i < ni && tx < nj) {
-                    if constexpr (UNPACK) lds[tx][i] = v[u];
-                    else store_packed_elem<NTP>(p[u], lds[tx][i]);
-                }
-            }
-        }
-    };
-    if constexpr (!UNPACK) {
-        tensor_side();
-        __syncthreads();
-        packed_side();
-    } else {
-        packed_side();
-        __syncthreads();
-        tensor_side();
-    }
-}
-
-template <typename E>
-constexpr uint32_t transpose_lds_bytes() { return TransposeShape<E>::T * (TransposeShape<E>::T + 1) * sizeof(E); }
-
-template <typename E, bool UNPACK, bool CSUM, bool NTU, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__ tiles,
-                                                        const uint32_t *__restrict__ chunk_tiles, BasePtrs bases,
-                                                        uint8_t *__restrict__ packed, SumCtx cx)
-{
-    constexpr uint32_t T = TransposeShape<E>::T;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
-    const Tile t = tiles[blockIdx.x];
-    uint8_t *user = bases.p[t.tensor] + t.src_off;
-    const uint32_t ni = t.n0, nj = t.n1;
-    const PitchRows rows{packed + t.packed_off, t.b, uint32_t(t.packed_off)};
-    u32x4 *lds = reinterpret_cast<u32x4 *>(lds_raw);
-    const uint32_t na = UNPACK ? nj : ni, nb = UNPACK ? ni : nj;
-    uint64_t acc = 0;
-    if (t.estep != sizeof(E))
-        transpose_tile_elements<E, UNPACK, NTP>(user, t.a, t.estep, ni, nj, rows, lds_raw, [&](uint32_t i, E v, uint32_t j) {
-            if constexpr (CSUM) acc += elem_weighted(v, rows.position(i, j * sizeof(E)));
-        });
-    else if (ni == T && nj == T)
-        acc = transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, true>(user, t.a, na, nb, rows, lds, [] {}, [] {});
-    else
-        acc = transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, false>(user, t.a, na, nb, rows, lds, [] {}, [] {});
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
-// ---- transpose whose tiles span chunks -------------------------------------------
-// For matrices whose packed rows are long against the chunk: a tile is a full block of the logical matrix
-// (so that every memory burst of the tensor side is used whole) and row i of it starts at stream byte
-// s0 + i * b, wherever that falls; a tile row is shorter than a chunk, so it meets at most one chunk
-// border.  Thread i places row i (its chunk, the packed address of its first byte, how many of its
-// bytes lie before the border and where the rest go) and leaves that in LDS, so that the copy only
-// reads it back.  Placing takes no division and no memory access but for rows farther apart than a chunk is long, and
-// what the commit at the end reads is loaded at the start.  Sums go to the tile's per-chunk partial sums in LDS; at the
-// end one thread per chunk touched makes that chunk's arrival (inc holds the tile's chunks, ascending, and the ordinal
-// of each arrival).
-// [256, 65536] bf16 (8 packed rows per 1 MiB chunk), pack + unpack: 33.0 -> 26.0 us.
-template <typename E, bool UNPACK, bool CSUM, bool NTU, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restrict__ tiles,
-                                                             const uint32_t *__restrict__ chunk_tiles,
-                                                             const uint32_t *__restrict__ inc, ChunkGeom g,
-                                                             BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
-{
-    constexpr uint32_t T = TransposeShape<E>::T, MAXC = 2 * T + 2;
-    static_assert(T <= kThreads, "one thread places one row");
-    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
-    __shared__ unsigned long long part[MAXC];          // partial sum per chunk touched
-    // per row: packed offset of byte x is row_p0 + x for x < row_first, row_p1 + x from there on (row_first is a whole
-    // tile row or more where the row meets no border); row_at: entry of the row's first chunk; row_low: low bits of
-    // its first byte's position (for the weights of the sum)
-    __shared__ uint64_t row_p0[T], row_p1[T];
-    __shared__ uint32_t row_first[T], row_at[T], row_low[T];
-    const Tile t = tiles[blockIdx.x];
-    uint8_t *user = bases.p[t.tensor] + t.src_off;
-    const uint32_t ni = t.n0, nj = t.n1, n_inc = t.ordinal;
-    const uint32_t *my = inc + 2 * size_t(t.chunk);
-    uint32_t my_chunk = 0, my_ordinal = 0, my_expected = 0;      // this thread's arrival at the end
-    auto fetch = [&]() {                                // asked for behind the tile's own loads, so that it is there then
-        if (!CSUM || threadIdx.x >= n_inc) return;
-        my_chunk = my[2 * threadIdx.x];
-        my_ordinal = my[2 * threadIdx.x + 1];
-        my_expected = chunk_tiles[my_chunk];
-    };
-    auto place = [&]() {                                // row threadIdx.x; the partial sums start at zero
-        for (uint32_t i = threadIdx.x; i < n_inc; i += kThreads) part[i] = 0;
-        if (threadIdx.x >= ni) return;
-        // (s / B in units of 256 bytes: tensor starts and chunks are multiples of that, and no message comes near 2^39 bytes)
-        const uint64_t B = g.B, s0 = t.packed_off, s = s0 + uint64_t(threadIdx.x) * t.b;
-        const uint32_t c = fast_div(uint32_t(s >> 8), g.div_b256), c0 = fast_div(uint32_t(s0 >> 8), g.div_b256);
-        const uint64_t rem = s - uint64_t(c) * B;
-        uint32_t at = c - c0;                           // rows no farther apart than a chunk is long meet every chunk in turn
-        if (t.b > B) {                                  // else: look for the entry that names chunk c (it is there)
-            uint32_t lo = 0, hi = n_inc - 1;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) / 2;
-                if (my[2 * mid] < c) lo = mid + 1;
-                else hi = mid;
-            }
-            at = lo;
-        }
-        auto chunk_base = [&](uint32_t ch) {
-            const uint32_t slot = fast_div(ch, g.div_k), lane = ch - slot * g.k;
-            return (uint64_t(lane) * g.q + (lane < g.r ? lane : g.r) + slot) * B;
-        };
-        const uint64_t room = B - rem;                  // bytes of chunk c from the row's start on
-        const bool whole = room >= uint64_t(nj) * sizeof(E);
-        row_at[threadIdx.x] = at;
-        row_first[threadIdx.x] = whole ? T * uint32_t(sizeof(E)) : uint32_t(room);
-        row_low[threadIdx.x] = uint32_t(rem) & 3u;
-        row_p0[threadIdx.x] = chunk_base(c) + rem;
-        row_p1[threadIdx.x] = whole ? 0 : chunk_base(c + 1) + rem - B;          // (+ x >= B - rem for those bytes)
-    };
-    const SpanRows rows{packed, row_p0, row_p1, row_first, row_at, row_low, part, ((t.packed_off | t.b) & 15u) != 0};
-    u32x4 *lds = reinterpret_cast<u32x4 *>(lds_raw);
-    const uint32_t na = UNPACK ? nj : ni, nb = UNPACK ? ni : nj;
-    if (t.estep != sizeof(E)) {
-        // one thread holds elements of one row: the part before the chunk border and the part after it are summed in
-        // registers and go to LDS once
-        unsigned long long a0 = 0, a1 = 0;
-        place();
-        fetch();
-        __syncthreads();
-        transpose_tile_elements<E, UNPACK, NTP>(user, t.a, t.estep, ni, nj, rows, lds_raw, [&](uint32_t i, E v, uint32_t j) {
-            if constexpr (CSUM) {
-                const unsigned long long w = elem_weighted(v, rows.position(i, j * sizeof(E)));
-                if (j * sizeof(E) < row_first[i]) a0 += w;
-                else a1 += w;
-            }
-        });
-        if constexpr (CSUM) {
-            const uint32_t tx = threadIdx.x & (T - 1);
-            if (a0) rows.count(tx, false, a0);
-            if (a1) rows.count(tx, true, a1);
-        }
-    } else if (ni == T && nj == T) {
-        transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, true>(user, t.a, na, nb, rows, lds, place, fetch);
-    } else {
-        transpose_tile_vectors<E, UNPACK, CSUM, NTU, NTP, false>(user, t.a, na, nb, rows, lds, place, fetch);
-    }
-    if constexpr (CSUM) {
-        __syncthreads();
-        if (threadIdx.x < n_inc) commit_total(part[threadIdx.x], my_chunk, my_ordinal, my_expected, cx);
-        for (uint32_t i = threadIdx.x + kThreads; i < n_inc; i += kThreads)
-            commit_total(part[i], my[2 * i], my[2 * i + 1], chunk_tiles[my[2 * i]], cx);
-    }
-}
-
-// ---- generic: any strides, one element at a time -------------------------------
-// Every element's address is recomputed from its logical index.  Only used for views the
-// other kernels do not take (no dimension with stride one, or runs shorter than 16 bytes).
-// The elements [e0, e0 + nel) of one tensor, every dim within reach of the multiply-shift division.
-// ND > 0: the tensor has exactly ND merged dims; ND == 0: any number, read from the descriptor.
-// The dims are copied into registers first: the loop below stores through byte pointers, which
-// may alias anything, so values read through the descriptor inside it would be read again for
-// every element.  Consecutive lanes take consecutive elements, U of them in flight per thread:
-// a wave's access is contiguous on the packed side and as dense on the tensor side as the view
-// allows.  The loads of a round are unconditional (the index is clamped into the tile), so that
-// all of them are issued before the first is waited for; only the stores are guarded.
-template <typename E, bool UNPACK, bool CSUM, bool NTP, int ND>
-__device__ __forceinline__ uint64_t generic_span(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p)
-{
-    constexpr int D = ND ? ND : HXT_MAX_DIMS;
-    const int nd = ND ? ND : td.ndim;
-    uint32_t shape[D], mul[D], shift[D], first[D];
-    uint64_t stride[D];
-    {
-        uint64_t idx = e0;                                  // coordinates of the span's first element
-#pragma unroll
-        for (int d = D - 1; d >= 0; --d) {
-            shape[d] = 1, mul[d] = 0, shift[d] = 0, first[d] = 0, stride[d] = 0;
-            if (d < nd) {
-                shape[d] = uint32_t(td.shape[d]);
-                mul[d] = td.dim_div[d].mul;
-                shift[d] = td.dim_div[d].shift;
-                stride[d] = uint64_t(td.stride_b[d]);
-                const uint64_t q = idx / uint64_t(td.shape[d]);
-                first[d] = uint32_t(idx - q * uint64_t(td.shape[d]));
-                idx = q;
-            }
-        }
-    }
-    // An element's coordinates are the first element's plus its number within the span, carried from
-    // the last dim upwards in 32 bits (a span has fewer than 2^30 elements and so has every dim).
-    auto locate = [&](uint32_t el) -> E * {
-        uint64_t off = 0;
-        uint32_t x = el;
-#pragma unroll
-        for (int d = D - 1; d > 0; --d) {
-            if (d < nd) {
-                x += first[d];
-                const uint32_t q = fast_div(x, FastDiv{mul[d], shift[d]});
-                off += uint64_t(x - q * shape[d]) * stride[d];
-                x = q;
-            }
-        }
-        off += uint64_t(x + first[0]) * stride[0];
-        return reinterpret_cast<E *>(user + off);
-    };
-    constexpr int U = 8;
-    uint64_t acc = 0;
-    const uint32_t last = nel - 1;
-    for (uint32_t e1 = threadIdx.x; e1 < nel; e1 += kThreads * U) {
-        E val[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t el = min(e1 + u * kThreads, last);
-            if constexpr (UNPACK) val[u] = load_elem<NTP>(p + el);
-            else val[u] = load_elem<true>(locate(el));
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t el = e1 + u * kThreads;
-            if (el < nel) {
-                if constexpr (UNPACK) store_elem<true>(locate(el), val[u]);
-                else store_packed_elem<NTP>(p + el, val[u]);
-                if constexpr (CSUM) acc += elem_weighted(val[u], uint64_t(el) * sizeof(E));
-            }
-        }
-    }
-    return acc;
-}
-
-// The same for tensors with a dim beyond the reach of the multiply-shift division: every element's
-// index is divided out in 64 bits.
-template <typename E, bool UNPACK, bool CSUM, bool NTP>
-__device__ __noinline__ uint64_t generic_span_wide(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p)
-{
-    const int nd = td.ndim;
-    uint64_t acc = 0;
-    for (uint32_t el = threadIdx.x; el < nel; el += kThreads) {
-        uint64_t idx = e0 + el, off = 0;
-        for (int d = nd - 1; d >= 0; --d) {
-            const uint64_t q = idx / uint64_t(td.shape[d]);
-            off += (idx - q * uint64_t(td.shape[d])) * uint64_t(td.stride_b[d]);
-            idx = q;
-        }
-        E *at = reinterpret_cast<E *>(user + off);
-        E v;
-        if constexpr (UNPACK) {
-            v = load_elem<NTP>(p + el);
-            store_elem<true>(at, v);
-        } else {
-            v = load_elem<true>(at);
-            store_packed_elem<NTP>(p + el, v);
-        }
-        if constexpr (CSUM) acc += elem_weighted(v, uint64_t(el) * sizeof(E));
-    }
-    return acc;
-}
-
-template <typename E, bool UNPACK, bool CSUM, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_generic(const Tile *__restrict__ tiles,
-                                                      const uint32_t *__restrict__ chunk_tiles,
-                                                      const TensorDev *__restrict__ tensors, uint32_t tensor_base,
-                                                      BasePtrs bases, uint8_t *__restrict__ packed, SumCtx cx)
-{
-    const Tile t = tiles[blockIdx.x];
-    uint64_t acc = 0;
-    if (t.kind == K_ZERO) {
-        acc = pad_span<UNPACK, CSUM>(packed + t.packed_off, t.n0, uint32_t(t.packed_off));
-    } else {
-        const TensorDev &td = tensors[tensor_base + t.tensor];
-        uint8_t *user = bases.p[t.tensor];
-        E *p = reinterpret_cast<E *>(packed + t.packed_off);
-        const uint32_t nel = t.n0 / sizeof(E);
-        const uint64_t e0 = t.src_off / sizeof(E);
-        if (nel == 0) {
-        } else if (!td.all_div) {
-            acc = generic_span_wide<E, UNPACK, CSUM, NTP>(td, e0, nel, user, p);
-        } else {
-            switch (td.ndim) {
-            case 1: acc = generic_span<E, UNPACK, CSUM, NTP, 1>(td, e0, nel, user, p); break;
-            case 2: acc = generic_span<E, UNPACK, CSUM, NTP, 2>(td, e0, nel, user, p); break;
-            case 3: acc = generic_span<E, UNPACK, CSUM, NTP, 3>(td, e0, nel, user, p); break;
-            case 4: acc = generic_span<E, UNPACK, CSUM, NTP, 4>(td, e0, nel, user, p); break;
-            default: acc = generic_span<E, UNPACK, CSUM, NTP, 0>(td, e0, nel, user, p); break;
-            }
-        }
-    }
-    if constexpr (CSUM) chunk_commit(acc, t.chunk, t.ordinal, chunk_tiles[t.chunk], cx);
-}
-
-// ---- stand-alone checksum of packed chunks (closed-form geometry, no table) ----------
-template <bool NTP>
-__global__ __launch_bounds__(kThreads) void k_checksum(ChunkGeom g, const uint8_t *__restrict__ packed, SumCtx cx)
-{
-    const TileSpan t = locate_tile(g, blockIdx.x);
-    const u32x4 *s = reinterpret_cast<const u32x4 *>(packed + t.packed_off);
-    const uint32_t nvec = t.len >> 4;
-    uint64_t acc = 0;
-    for (uint32_t v = threadIdx.x; v < nvec; v += kThreads * kUnroll) {
-        u32x4 r[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            r[u] = load16_or_zero<NTP>(s, v + u * kThreads, nvec);
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) acc += words_sum(r[u]);
-    }
-    chunk_commit(acc, t.chunk, t.ordinal, t.expected, cx);
-}
-
-// ---- stand-alone strong check: plain sum and position-weighted sum of every chunk -------
+// ---- strong check: plain sum and position-weighted sum of every chunk -----------------
 // out[2c] = sum of the chunk's words, out[2c+1] = sum of (j+1) * word j, both mod 2^64.
 // A logical accumulator is a pair of slots (2s: plain sum and arrival count, 2s+1: weighted
 // sum); the ticket is taken after both additions have returned.  Same two-level fan-out as
@@ -1338,12 +536,6 @@ __device__ __forceinline__ bool pair_arrive(uint8_t *acc, uint32_t stride, size_
     return true;
 }
 
-// Word j of the chunk sits at tile word i = j - j0.  A thread's vectors start at tile words
-// 4 * (tid + 256 * n), n = 0, 1, ...; with S_n the sum of vector n's words and I_n = y + 2z + 3w,
-//   sum (j+1) w_j = (j0 + 4 tid + 1) * sum_n S_n + 1024 * sum_n n S_n + sum_n I_n,
-// so the loop needs additions only (sum_n n S_n is kept as a running suffix sum) and each
-// thread multiplies once.
-//
 // MODE says what the workgroup that completes a chunk does with the two sums:
 //   SUMS   out = uint64[2C]: writes the pair.
 //   SEAL   out = C tags: writes the chunk's 64-byte tag (hxt_chunk_tag_t) at its packed-slot index.
@@ -1371,22 +563,26 @@ __device__ __forceinline__ uint64_t tag_place(const ChunkGeom &g, uint32_t c)   
     return uint64_t(lane) * g.q + (lane < g.r ? lane : g.r) + slot;
 }
 
-__device__ __forceinline__ TagRegs prefetch_tag(int mode, const ChunkGeom &g, uint32_t chunk, const TagWork &w)
+__device__ __forceinline__ TagRegs load_tag(const ChunkGeom &g, uint32_t chunk, const TagWork &w)
 {
     TagRegs t{};
-    if (mode == SUM2_VERIFY && threadIdx.x == 0) {
-        const u32x4 *tag = reinterpret_cast<const u32x4 *>(w.tags + tag_place(g, chunk) * 64);
+    if (!w.tags) return t;                               // nothing to compare with: a tag is being written
+    const u32x4 *tag = reinterpret_cast<const u32x4 *>(w.tags + tag_place(g, chunk) * 64);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) t.r[i] = tag[i];
-    }
+    for (int i = 0; i < 4; ++i) t.r[i] = tag[i];
     return t;
 }
 
-__device__ __forceinline__ void finish_chunk(int mode, const ChunkGeom &g, const TileSpan &t, uint64_t sum,
+__device__ __forceinline__ TagRegs prefetch_tag(int mode, const ChunkGeom &g, uint32_t chunk, const TagWork &w)
+{
+    if (mode == SUM2_VERIFY && threadIdx.x == 0) return load_tag(g, chunk, w);
+    return TagRegs{};
+}
+
+__device__ __forceinline__ void finish_chunk(int mode, const ChunkGeom &g, uint32_t c, uint64_t sum,
                                              uint64_t wsum, void *out, const TagWork &w, const TagRegs &got,
                                              uint8_t *acc, uint32_t stride, uint32_t fan)
 {
-    const uint32_t c = t.chunk;
     if (mode == SUM2_SUMS) {
         uint64_t *o = static_cast<uint64_t *>(out);
         o[2 * size_t(c)] = sum;
@@ -1433,6 +629,26 @@ __device__ __forceinline__ void finish_chunk(int mode, const ChunkGeom &g, const
     static_cast<uint32_t *>(out)[g.C] = uint32_t(total);
 }
 
+// One arrival, made by one thread (as commit_total): the one that completes the chunk finishes it with the received
+// tag that tag() returns.
+template <class GetTag>
+__device__ __forceinline__ void pair_commit_total(int mode, const ChunkGeom &g, uint32_t chunk, uint32_t ordinal, uint32_t expected,
+                                                  unsigned long long a, unsigned long long b, void *out, uint8_t *acc,
+                                                  uint32_t stride, uint32_t fan, const TagWork &work, GetTag &&tag)
+{
+    const size_t top = size_t(g.C) * fan + chunk;
+    bool last;
+    if (fan == 1 || expected < 2 * fan) {
+        last = pair_arrive(acc, stride, top, a, b, expected, work.sum_bits);
+    } else {
+        const uint32_t sub = ordinal & (fan - 1);
+        const uint32_t share = expected / fan + (sub < (expected & (fan - 1)) ? 1u : 0u);
+        last = pair_arrive(acc, stride, size_t(chunk) * fan + sub, a, b, share, work.sum_bits) &&
+               pair_arrive(acc, stride, top, a, b, fan, work.sum_bits);
+    }
+    if (last) finish_chunk(mode, g, chunk, a, b, out, work, tag(), acc, stride, fan);
+}
+
 // Workgroup-wide: reduces every thread's (a, b), adds the pair to the chunk's accumulators (two-level
 // fan-out as in chunk_commit); the workgroup that completes the chunk finishes it.
 __device__ __forceinline__ void pair_commit(int mode, const ChunkGeom &g, const TileSpan &t, unsigned long long a,
@@ -1457,56 +673,10 @@ __device__ __forceinline__ void pair_commit(int mode, const ChunkGeom &g, const 
             a += part[0][w];
             b += part[1][w];
         }
-        const size_t top = size_t(g.C) * fan + t.chunk;
-        bool last;
-        if (fan == 1 || t.expected < 2 * fan) {
-            last = pair_arrive(acc, stride, top, a, b, t.expected, work.sum_bits);
-        } else {
-            const uint32_t sub = t.ordinal & (fan - 1);
-            const uint32_t share = t.expected / fan + (sub < (t.expected & (fan - 1)) ? 1u : 0u);
-            last = pair_arrive(acc, stride, size_t(t.chunk) * fan + sub, a, b, share, work.sum_bits) &&
-                   pair_arrive(acc, stride, top, a, b, fan, work.sum_bits);
-        }
-        if (last) finish_chunk(mode, g, t, a, b, out, work, got, acc, stride, fan);
+        pair_commit_total(mode, g, t.chunk, t.ordinal, t.expected, a, b, out, acc, stride, fan, work, [&] { return got; });
     }
 }
 
-template <int MODE, bool NTP>
-__global__ __launch_bounds__(kThreads) void k_checksum2(ChunkGeom g, const uint8_t *__restrict__ packed,
-                                                        void *__restrict__ out, uint8_t *acc, uint32_t stride,
-                                                        uint32_t fan, TagWork work)
-{
-    const TileSpan t = locate_tile(g, blockIdx.x);
-    const TagRegs got = prefetch_tag(MODE, g, t.chunk, work);
-    const u32x4 *s = reinterpret_cast<const u32x4 *>(packed + t.packed_off);
-    const uint64_t j0 = (t.stream_off - uint64_t(t.chunk) * g.B) >> 2;
-    const uint32_t nvec = t.len >> 4;
-    uint64_t S = 0, nS = 0, I = 0;          // sum_n S_n, sum_n n*S_n, sum_n I_n
-    uint64_t n0 = 0;                         // n of the current block of vectors
-    for (uint32_t v = threadIdx.x; v < nvec; v += kThreads * kUnroll, n0 += kUnroll) {
-        u32x4 r[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            r[u] = load16_or_zero<NTP>(s, v + u * kThreads, nvec);
-        uint64_t blockS = 0, blockN = 0;     // this block's sum_u S_u and sum_u u*S_u
-#pragma unroll
-        for (int u = kUnroll - 1; u >= 0; --u) {
-            const uint64_t zw = uint64_t(r[u].z) + r[u].w;
-            const uint64_t yzw = zw + r[u].y;
-            blockN += blockS;                // after the loop: sum_u u * S_u
-            blockS += yzw + r[u].x;
-            I += yzw + zw + r[u].w;
-        }
-        S += blockS;
-        nS += blockN + n0 * blockS;
-    }
-    pair_commit(MODE, g, t, S, (j0 + 4ull * threadIdx.x + 1) * S + 4ull * kThreads * nS + I, out, acc, stride, fan, work, got);
-}
-
-// ---- pack + seal and unpack + verify in one pass (messages that are one contiguous tensor) ----
-// The copy of k_uniform with both sums of the packed words taken on the way, so that tags cost no
-// extra pass over the message.  Weights are tile-local here (word i of the tile weighs i + 1);
-// the tile's position in its chunk is applied once per workgroup.
 struct Sums2 {
     uint64_t s, w;
 };
@@ -1597,6 +767,1052 @@ __device__ __forceinline__ Sums2 pad_span2(uint8_t *pk, uint32_t bytes, uint64_t
     return acc;
 }
 
+template <typename E>
+__device__ __forceinline__ uint64_t elem_weighted(E v, uint64_t packed_pos)
+{
+    if constexpr (sizeof(E) == 8) {
+        return uint64_t(uint32_t(v)) + uint64_t(uint32_t(uint64_t(v) >> 32));
+    } else {
+        return uint64_t(v) << (8 * (packed_pos & 3));
+    }
+}
+
+// ---- what a copy checks on the way ------------------------------------------------
+// NONE: nothing.  SUMS: the plain sum of every chunk.  TAGS: both sums, sealed into a tag by a pack and compared with
+// the received tag by an unpack, so that tags cost no pass of their own whatever the views of the message.
+enum Check { CHECK_NONE = 0, CHECK_SUMS = 1, CHECK_TAGS = 2 };
+
+template <int CHECK>
+struct CheckArgs {
+    SumCtx cx;
+};
+
+template <>
+struct CheckArgs<CHECK_TAGS> {
+    SumCtx cx;             // the pair-of-sums slots; cx.sums is not used
+    ChunkGeom g;
+    void *out;             // pack: the message's tags; unpack: its status words
+    TagWork work;
+};
+
+template <bool UNPACK, int CHECK>
+__device__ __forceinline__ TagRegs prefetch_check(const CheckArgs<CHECK> &ck, uint32_t chunk)
+{
+    if constexpr (CHECK == CHECK_TAGS) return prefetch_tag(UNPACK ? SUM2_VERIFY : SUM2_SEAL, ck.g, chunk, ck.work);
+    else return TagRegs{};
+}
+
+// Workgroup-wide: the tile's sums (weights counted from the chunk's first word) go to its chunk.
+template <bool UNPACK, int CHECK>
+__device__ __forceinline__ void commit_tile(Sums2 v, const Tile &t, const uint32_t *__restrict__ chunk_tiles,
+                                            const CheckArgs<CHECK> &ck, const TagRegs &got)
+{
+    if constexpr (CHECK == CHECK_SUMS) chunk_commit(v.s, t.chunk, t.ordinal, chunk_tiles[t.chunk], ck.cx);
+    if constexpr (CHECK == CHECK_TAGS) {
+        TileSpan span{};
+        span.chunk = t.chunk;
+        span.ordinal = t.ordinal;
+        span.expected = chunk_tiles[t.chunk];
+        pair_commit(UNPACK ? SUM2_VERIFY : SUM2_SEAL, ck.g, span, v.s, v.w, ck.out, ck.cx.acc, ck.cx.stride, ck.cx.fan, ck.work, got);
+    }
+}
+
+// Adds an element of 8 bytes or less that starts at byte `pos` of a chunk (or of a tile that starts on a word).
+template <int CHECK, typename E>
+__device__ __forceinline__ void count_elem(Sums2 &acc, E v, uint64_t pos)
+{
+    if constexpr (CHECK != CHECK_NONE) acc.s += elem_weighted(v, pos);
+    if constexpr (CHECK == CHECK_TAGS) {
+        const uint64_t j = pos >> 2;
+        if constexpr (sizeof(E) == 8) acc.w += (j + 1) * uint32_t(v) + (j + 2) * uint32_t(uint64_t(v) >> 32);
+        else acc.w += (j + 1) * (uint64_t(v) << (8 * (pos & 3)));
+    }
+}
+
+// Adds 16 bytes that start at byte `pos` (a multiple of the element size ES) of a chunk.
+template <int CHECK, int ES>
+__device__ __forceinline__ void count_vector(Sums2 &acc, u32x4 v, uint64_t pos)
+{
+    if constexpr (CHECK == CHECK_SUMS) {
+        acc.s += rotated_sum(v, uint32_t(pos));
+    } else if constexpr (CHECK == CHECK_TAGS) {
+        uint32_t w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w, w4 = 0;
+        if constexpr (ES < 4) {                          // a vector that starts inside a word: moved up by its phase, into five words
+            const uint32_t down = 32 - 8 * (uint32_t(pos) & 3u);
+            w4 = uint32_t(uint64_t(v.w) >> down);
+            w3 = uint32_t((uint64_t(v.w) << 32 | v.z) >> down);
+            w2 = uint32_t((uint64_t(v.z) << 32 | v.y) >> down);
+            w1 = uint32_t((uint64_t(v.y) << 32 | v.x) >> down);
+            w0 = uint32_t((uint64_t(v.x) << 32) >> down);
+        }
+        const uint64_t t4 = w4, t3 = t4 + w3, t2 = t3 + w2, t1 = t2 + w1, s = t1 + w0;
+        acc.s += s;
+        acc.w += ((pos >> 2) + 1) * s + (t1 + t2) + (t3 + t4);
+    }
+}
+
+// ---- rows: innermost dimension contiguous, outer dimensions strided -------------
+// A 16-byte vector never straddles a run (run length and strides are multiples of 16; the base need not be).
+// Logical byte -> (row, column) and row -> outer indices use multiply-shift division.
+template <bool UNPACK, int CHECK, bool NTU, bool NTP>
+__device__ __forceinline__ Sums2 rows_tile(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
+{
+    const uint32_t row_bytes = td.row_bytes;
+    const uint64_t row0 = t.src_off / row_bytes;                    // uniform
+    const uint32_t col0 = uint32_t(t.src_off - row0 * row_bytes);
+    const int outer = td.ndim - 1;
+    const uint32_t nvec = t.n0 >> 4;
+    Sums2 acc{0, 0};
+    for (uint32_t v0 = threadIdx.x; v0 < nvec; v0 += kThreads * kUnroll) {
+        u32x4 r[kUnroll];
+        uint64_t off[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const uint32_t v = v0 + u * kThreads;
+            const uint32_t x = col0 + (v << 4);
+            const uint32_t dr = fast_div(x, td.row_div);
+            uint32_t row = uint32_t(row0) + dr;
+            uint64_t o = x - dr * row_bytes;
+            for (int d = outer - 1; d > 0; --d) {
+                const uint32_t q = fast_div(row, td.dim_div[d]);
+                o += uint64_t(row - q * uint32_t(td.shape[d])) * uint64_t(td.stride_b[d]);
+                row = q;
+            }
+            o += uint64_t(row) * uint64_t(td.stride_b[0]);
+            off[u] = o;
+            if (v < nvec) {
+                if constexpr (UNPACK) r[u] = load16<NTP>(reinterpret_cast<const u32x4 *>(pk + (uint64_t(v) << 4)));
+                else r[u] = load16_any<NTU>(user + o);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const uint32_t v = v0 + u * kThreads;
+            if (v < nvec) {
+                if constexpr (UNPACK) store16_any<NTU>(user + off[u], r[u]);
+                else store_packed16<NTP>(reinterpret_cast<u32x4 *>(pk + (uint64_t(v) << 4)), r[u]);
+                count_vector<CHECK, 16>(acc, r[u], t.a + (uint64_t(v) << 4));
+            }
+        }
+    }
+    return acc;
+}
+
+template <bool UNPACK, int CHECK, bool NTU, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_rows(const Tile *__restrict__ tiles,
+                                                   const uint32_t *__restrict__ chunk_tiles,
+                                                   const TensorDev *__restrict__ tensors, uint32_t tensor_base,
+                                                   BasePtrs bases, uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
+{
+    const Tile t = tiles[blockIdx.x];
+    const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
+    const Sums2 acc = rows_tile<UNPACK, CHECK, NTU, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
+}
+
+// ---- rows whose length or pitch is not a multiple of 16 bytes ----------------------
+// Still a gather of contiguous runs (of 16 bytes or more), but a 16-byte vector of the packed stream may end
+// one run and begin the next, and the tensor side is only G-byte aligned (G = 8, 4, 2 or 1).
+// Work is dealt in pieces of G bytes, consecutive lanes taking consecutive pieces of the tile: a wave's access
+// is then contiguous on the packed side and contiguous within each run on the tensor side (64 lanes x 4 bytes
+// = 256 bytes per instruction), whatever the run length; each piece finds its run with one multiply-shift
+// division and the run's storage offset from the outer indices.
+template <int G> struct PieceOf;
+template <> struct PieceOf<8> { using type = uint64_t; };
+template <> struct PieceOf<4> { using type = uint32_t; };
+template <> struct PieceOf<2> { using type = uint16_t; };
+template <> struct PieceOf<1> { using type = uint8_t; };
+
+// TWO_D: the view has two dims (the usual padded-pitch matrix) and needs no index decomposition: run
+// row0 + dr starts (row0 + dr) * pitch into the storage, so byte x of the tile's first run sits at
+// x + dr * (pitch - run length) from that run's start.  Otherwise the run's storage offset comes from
+// its outer indices, divided out with the dims held in registers (the loop stores through byte
+// pointers, which may alias the descriptor, so anything read through it inside the loop would be
+// read again for every piece).  With pieces of 1 or 2 bytes the loads of a round are unconditional
+// (the piece number is clamped into the tile): guarded, the compiler waits for each load before it
+// goes on to the next guard, and 16 loads one after the other cost 1.8-2.4 times the time.  With pieces
+// of 4 or 8 bytes the guarded loads are issued without such waits, interleaved with the address
+// arithmetic, and that order measures 10 % faster than eight loads in one burst.
+template <bool UNPACK, int CHECK, bool NTP, int G, bool TWO_D>
+__device__ __forceinline__ Sums2 rows_split_tile(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
+{
+    using P = typename PieceOf<G>::type;
+    const uint32_t row_bytes = td.row_bytes;
+    const FastDiv row_div = td.row_div;
+    const uint64_t row0 = t.src_off / row_bytes;                    // uniform
+    const uint32_t col0 = uint32_t(t.src_off - row0 * row_bytes);
+    const uint32_t npiece = t.n0 / G;
+    constexpr int U = G == 8 ? 8 : 16;                              // pieces in flight per thread: a 16 KiB tile in one go
+    constexpr int D = TWO_D ? 1 : HXT_MAX_DIMS - 1;                 // dims outside the run
+    const int outer = TWO_D ? 1 : td.ndim - 1;
+    uint32_t shape[D], mul[D], shift[D];
+    uint64_t stride[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        shape[d] = 1, mul[d] = 0, shift[d] = 0, stride[d] = 0;
+        if (d < outer) {
+            shape[d] = uint32_t(td.shape[d]);
+            mul[d] = td.dim_div[d].mul;
+            shift[d] = td.dim_div[d].shift;
+            stride[d] = uint64_t(td.stride_b[d]);
+        }
+    }
+    uint8_t *const first_run = user + row0 * stride[0];             // uniform
+    const int64_t slack = int64_t(stride[0]) - int64_t(row_bytes);
+    auto user_piece = [&](uint32_t i) {                             // piece i of the tile -> its place in storage
+        const uint32_t x = col0 + i * G;
+        const uint32_t dr = fast_div(x, row_div);
+        if constexpr (TWO_D) {
+            return reinterpret_cast<P *>(first_run + (int64_t(x) + int64_t(dr) * slack));
+        } else {
+            uint32_t row = uint32_t(row0) + dr;
+            uint64_t o = 0;
+#pragma unroll
+            for (int d = D - 1; d > 0; --d) {
+                if (d < outer) {
+                    const uint32_t q = fast_div(row, FastDiv{mul[d], shift[d]});
+                    o += uint64_t(row - q * shape[d]) * stride[d];
+                    row = q;
+                }
+            }
+            return reinterpret_cast<P *>(user + o + uint64_t(row) * stride[0] + (x - dr * row_bytes));
+        }
+    };
+    P *pieces = reinterpret_cast<P *>(pk);
+    Sums2 acc{0, 0};
+    const uint32_t last = npiece - 1;
+    for (uint32_t i0 = threadIdx.x; i0 < npiece; i0 += kThreads * U) {
+        P r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (G >= 4) {
+                const uint32_t i = i0 + u * kThreads;
+                r[u] = 0;
+                if (i < npiece) {
+                    if constexpr (UNPACK) r[u] = load_elem<NTP>(pieces + i);
+                    else r[u] = __builtin_nontemporal_load(user_piece(i));
+                }
+            } else {
+                const uint32_t i = min(i0 + u * kThreads, last);
+                if constexpr (UNPACK) r[u] = load_elem<NTP>(pieces + i);
+                else r[u] = __builtin_nontemporal_load(user_piece(i));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = i0 + u * kThreads;
+            if (i < npiece) {
+                if constexpr (UNPACK) __builtin_nontemporal_store(r[u], user_piece(i));
+                else store_packed_elem<NTP>(pieces + i, r[u]);
+                count_elem<CHECK>(acc, r[u], t.a + i * G);
+            }
+        }
+    }
+    return acc;
+}
+
+template <bool UNPACK, int CHECK, bool NTP>
+__device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
+{
+    // widest piece that is naturally aligned everywhere: low bits of the base address, the run length and the pitches
+    const uint32_t low = (uint32_t(reinterpret_cast<uintptr_t>(user)) | td.low_or) & 15u;
+    auto run = [&]<int G>() {
+        return td.ndim == 2 ? rows_split_tile<UNPACK, CHECK, NTP, G, true>(t, td, user, pk)
+                            : rows_split_tile<UNPACK, CHECK, NTP, G, false>(t, td, user, pk);
+    };
+    if ((low & 7u) == 0) return run.template operator()<8>();
+    if ((low & 3u) == 0) return run.template operator()<4>();
+    if ((low & 1u) == 0) return run.template operator()<2>();
+    return run.template operator()<1>();
+}
+
+template <bool UNPACK, int CHECK, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict__ tiles,
+                                                         const uint32_t *__restrict__ chunk_tiles,
+                                                         const TensorDev *__restrict__ tensors, uint32_t tensor_base,
+                                                         BasePtrs bases, uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
+{
+    const Tile t = tiles[blockIdx.x];
+    const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
+    const Sums2 acc = rows_split_any<UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
+}
+
+// ---- transpose: logical inner dimension strided, the one before it contiguous ----
+// A tile is ni x nj elements (at most T x T: 128 x 128 for 1- and 2-byte elements, 64 x 64 otherwise).  The tensor
+// stores nj rows of ni contiguous elements, the packed stream has ni rows of nj.  A thread loads a block of V x V
+// elements (V = 16 bytes' worth: V rows of one vector each), transposes it in registers and leaves V vectors in LDS;
+// after the barrier the tile's rows leave LDS as whole vectors, 16 lanes (256 contiguous bytes) to a row.  So LDS is
+// touched by 16-byte accesses only, once each way; gathering elements out of it instead kept the LDS pipe busy for
+// about 1.7 us of a 14 us launch (64 two-byte reads per thread).  32 MiB of bf16, pack + unpack: 27.3 -> 24.4 us (a plain copy of the same bytes: 24.1).
+// Vectors need no alignment beyond the element's: the hardware takes misaligned 16-byte accesses, and even with both
+// row pitches odd (bf16, pitches of 8198 bytes) they beat element accesses, 30 against 31-38 us per pair.
+template <typename E>
+struct TransposeShape {
+    static constexpr uint32_t T = transpose_tile(sizeof(E)), V = 16 / sizeof(E);
+    static constexpr uint32_t NB = T / V;                        // vectors per tile row, blocks per tile side
+    static constexpr uint32_t BLOCKS = NB * NB;
+};
+
+// x[r] holds V elements of source row r; afterwards x[c] holds the V elements of source column c.
+template <typename E>
+__device__ __forceinline__ void transpose_block(u32x4 (&x)[16 / sizeof(E)])
+{
+    constexpr int V = 16 / sizeof(E);
+    u32x4 y[V];
+    if constexpr (sizeof(E) == 8) {
+        y[0] = u32x4{x[0].x, x[0].y, x[1].x, x[1].y};
+        y[1] = u32x4{x[0].z, x[0].w, x[1].z, x[1].w};
+    } else if constexpr (sizeof(E) == 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y[c] = u32x4{x[0][c], x[1][c], x[2][c], x[3][c]};
+    } else if constexpr (sizeof(E) == 2) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t a = x[2 * q][c], b = x[2 * q + 1][c];
+                y[2 * c][q] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+                y[2 * c + 1][q] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+            }
+    } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t lo01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x05010400u);       // bytes 0 0' 1 1'
+                const uint32_t hi01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x07030602u);       // bytes 2 2' 3 3'
+                const uint32_t lo23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x05010400u);
+                const uint32_t hi23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x07030602u);
+                y[4 * c][q] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+                y[4 * c + 1][q] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+                y[4 * c + 2][q] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+                y[4 * c + 3][q] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i) x[i] = y[i];
+}
+
+// Where the rows of a tile lie on the packed side.
+// PitchRows: a tile inside one chunk, rows a fixed pitch apart, one sum for the tile.
+struct PitchRows {
+    static constexpr bool kSpan = false;
+    uint8_t *base;                 // element (0, 0) of the tile
+    uint64_t pitch;
+    uint64_t pos;                  // its position in the chunk (for the weights of sums)
+    __device__ __forceinline__ uint8_t *at(uint32_t row, uint32_t byte) const { return base + row * pitch + byte; }
+    template <int CHECK>
+    __device__ __forceinline__ uint64_t position(uint32_t row, uint32_t byte) const
+    {
+        if constexpr (CHECK == CHECK_SUMS) return uint32_t(pos) + row * uint32_t(pitch) + byte;
+        return pos + row * pitch + byte;
+    }
+};
+// SpanRows: every row placed on its own (k_transpose_span keeps the placement in LDS): bytes below first[row] lie from
+// p0[row] on in the packed buffer, the rest at p1[row]; sums go to the partial sum of the chunk they fall into.
+struct SpanRows {
+    static constexpr bool kSpan = true;
+    uint8_t *packed;
+    const uint64_t *p0, *p1;
+    const uint16_t *first, *entry;
+    const uint64_t *rem;           // position of the row's first byte in its chunk
+    unsigned long long *part, *wpart;
+    bool may_cross;                // a vector may straddle a chunk border (rows are not 16-byte aligned against it)
+    __device__ __forceinline__ uint8_t *at(uint32_t row, uint32_t byte) const
+    {
+        return packed + (byte < first[row] ? p0[row] : p1[row]) + byte;
+    }
+    // (chunks are multiples of 256 bytes, so the phase in a word, all that plain sums ask for, is the same on both sides)
+    template <int CHECK>
+    __device__ __forceinline__ uint64_t position(uint32_t row, uint32_t byte) const
+    {
+        if constexpr (CHECK == CHECK_SUMS) return uint32_t(rem[row]) + byte;
+        return byte < first[row] ? rem[row] + byte : byte - first[row];
+    }
+    __device__ __forceinline__ bool crosses(uint32_t row, uint32_t byte) const
+    {
+        return may_cross && byte < first[row] && byte + 16 > first[row];
+    }
+    template <int CHECK>
+    __device__ __forceinline__ void count(uint32_t row, bool second, Sums2 v) const
+    {
+        const uint32_t at = entry[row] + (second ? 1u : 0u);
+        __hip_atomic_fetch_add(&part[at], (unsigned long long)v.s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (CHECK == CHECK_TAGS)
+            __hip_atomic_fetch_add(&wpart[at], (unsigned long long)v.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+
+// The elements of a vector on the packed side that straddles a chunk border (bytes below `first` of the row lie from
+// `before` on, the rest from `after` on), one at a time.
+template <typename E, bool NTP>
+__device__ __forceinline__ void store_crossing(uint8_t *before, uint8_t *after, uint32_t first, uint32_t byte, uint32_t n, u32x4 v)
+{
+    constexpr uint32_t ES = sizeof(E);
+#pragma unroll
+    for (uint32_t q = 0; q < 16 / ES; ++q) {
+        const uint32_t at = byte + q * ES;
+        const E e = E(ES == 8 ? uint64_t(v[q * ES / 4]) | uint64_t(v[(q * ES / 4 + 1) & 3]) << 32 : uint64_t(v[q * ES / 4]) >> (8 * (q * ES & 3)));
+        if (q < n) store_packed_elem<NTP>(reinterpret_cast<E *>((at < first ? before : after) + at), e);
+    }
+}
+
+template <typename E>
+__device__ __forceinline__ u32x4 load_crossing(const uint8_t *before, const uint8_t *after, uint32_t first, uint32_t byte)
+{
+    union {
+        E e[16 / sizeof(E)];
+        u32x4 x;
+    } o;
+#pragma unroll
+    for (uint32_t q = 0; q < 16 / sizeof(E); ++q) {
+        const uint32_t at = byte + q * uint32_t(sizeof(E));
+        o.e[q] = *reinterpret_cast<const E *>((at < first ? before : after) + at);
+    }
+    return o.x;
+}
+
+// Adds the sum of a vector of packed bytes (n of them from byte `skip` on count) to the tile's sum, or to the partial sum
+// of its chunk.  SpanRows: called by all lanes of a wave, the 16 lanes of a DPP row holding vectors of one tile row
+// (live: this lane's vector counts); the row is summed across those lanes first, so that one lane goes to LDS.
+template <typename E, int CHECK, class Rows>
+__device__ __forceinline__ void count_packed(const Rows &rows, uint32_t row, uint32_t byte, u32x4 v, uint32_t skip, uint32_t n,
+                                             bool live, Sums2 &acc)
+{
+    const u32x4 kept = live ? keep_bytes(v, skip, n) : u32x4{0, 0, 0, 0};
+    if constexpr (!Rows::kSpan) {
+        count_vector<CHECK, sizeof(E)>(acc, kept, rows.template position<CHECK>(row, byte));
+    } else {
+        const uint32_t border = rows.first[row];
+        const bool crossing = rows.crosses(row, byte);
+        if (crossing && live) {                          // split at the border: rare, and only where rows are misaligned
+            const uint32_t before = border - byte;
+            Sums2 ahead{0, 0}, behind{0, 0};
+            count_vector<CHECK, sizeof(E)>(ahead, keep_bytes(kept, 0, before), rows.template position<CHECK>(row, byte));
+            // (the bytes behind the border start the next chunk: weights counted from its first word)
+#pragma unroll
+            for (uint32_t q = 0; q < 16 / sizeof(E); ++q) {
+                const uint32_t at = q * uint32_t(sizeof(E));
+                const E e = E(sizeof(E) == 8 ? uint64_t(kept[at / 4]) | uint64_t(kept[(at / 4 + 1) & 3]) << 32 : uint64_t(kept[at / 4]) >> (8 * (at & 3)));
+                if (at >= before) count_elem<CHECK>(behind, e, uint64_t(at - before));
+            }
+            rows.template count<CHECK>(row, false, ahead);
+            rows.template count<CHECK>(row, true, behind);
+        }
+        Sums2 v2{0, 0};
+        if (!crossing) count_vector<CHECK, sizeof(E)>(v2, kept, rows.template position<CHECK>(row, byte));
+        constexpr bool kGrouped = TransposeShape<E>::NB % 16 == 0;
+        const bool whole = border >= TransposeShape<E>::T * uint32_t(sizeof(E));     // the row meets no border in this tile
+        if constexpr (kGrouped) {
+            Sums2 total{row16_sum(v2.s), 0};
+            if constexpr (CHECK == CHECK_TAGS) total.w = row16_sum(v2.w);
+            if (whole && (threadIdx.x & 15) == 15) rows.template count<CHECK>(row, false, total);
+            if (!whole && v2.s) rows.template count<CHECK>(row, byte >= border, v2);
+        } else {
+            if (v2.s) rows.template count<CHECK>(row, byte >= border, v2);
+        }
+    }
+}
+
+// Moves one tile.  Source rows are the tensor's (pack) or the packed side's (unpack): nb rows of na elements.
+// place() puts into LDS what `rows` reads there; a pack does that while its loads from the tensor are on their way.
+// fetch() asks for what the caller needs at the end.
+template <typename E, bool UNPACK, int CHECK, bool NTU, bool NTP, bool FULL, class Rows, class Place, class Fetch>
+__device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t user_pitch, uint32_t na_in, uint32_t nb_in,
+                                                           const Rows &rows, u32x4 *lds, Place &&place, Fetch &&fetch)
+{
+    using Sh = TransposeShape<E>;
+    constexpr uint32_t T = Sh::T, V = Sh::V, NB = Sh::NB, ES = sizeof(E);
+    constexpr uint32_t PER = Sh::BLOCKS < uint32_t(kThreads) ? 1 : Sh::BLOCKS / kThreads;      // blocks per thread
+    const uint32_t na = FULL ? T : na_in, nb = FULL ? T : nb_in;
+    auto slot_of = [](uint32_t row, uint32_t slot) { return row * NB + (slot ^ ((row / V) & (NB - 1))); };
+    Sums2 acc{0, 0};
+    if constexpr (Rows::kSpan && UNPACK) {
+        place();
+        __syncthreads();
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t id = threadIdx.x + k * kThreads, la = id & (NB - 1), lb = id / NB;
+        const uint32_t a0 = la * V, b0 = lb * V;
+        constexpr bool kAll = FULL && Sh::BLOCKS >= uint32_t(kThreads);      // every thread has a whole block
+        const bool live = kAll || (id < Sh::BLOCKS && a0 < na && b0 < nb);
+        auto row_of = [&](uint32_t r) { return kAll ? b0 + r : min(b0 + r, nb - 1); };
+        // The last block of a row that is no multiple of V starts early enough to end with it (its first columns are
+        // then moved twice, with the same values); rows beyond the tile repeat the last one.
+        const uint32_t as = FULL || a0 + V <= na ? a0 : (na >= V ? na - V : 0);
+        const bool narrow = !FULL && na < V;
+        u32x4 x[V];
+        if (live && !narrow) {
+#pragma unroll
+            for (uint32_t r = 0; r < V; ++r) {
+                const uint32_t b = row_of(r);
+                if constexpr (!UNPACK) {
+                    x[r] = load16_any<NTU>(user + b * user_pitch + as * ES);
+                } else if constexpr (!Rows::kSpan) {
+                    x[r] = load16_any<NTP>(rows.at(b, as * ES));
+                } else {
+                    // (a vector across a chunk border is read from the 16 bytes that end there, and put right below)
+                    const uint32_t byte = rows.crosses(b, as * ES) ? rows.first[b] - 16u : as * ES;
+                    x[r] = load16_any<NTP>(rows.packed + (as * ES < rows.first[b] ? rows.p0[b] : rows.p1[b]) + int32_t(byte));
+                }
+            }
+            if constexpr (UNPACK && Rows::kSpan) {
+                if (rows.may_cross)
+#pragma unroll
+                    for (uint32_t r = 0; r < V; ++r) {
+                        const uint32_t b = row_of(r);
+                        if (rows.crosses(b, as * ES)) x[r] = load_crossing<E>(rows.packed + rows.p0[b], rows.packed + rows.p1[b], rows.first[b], as * ES);
+                    }
+            }
+        } else if (live) {                               // fewer than V columns in the whole tile
+#pragma unroll
+            for (uint32_t r = 0; r < V; ++r) {
+                const uint32_t b = row_of(r);
+                union {
+                    E e[V];
+                    u32x4 v;
+                } o{};
+#pragma unroll
+                for (uint32_t q = 0; q < V; ++q)
+                    if (q < na) {
+                        if constexpr (!UNPACK) o.e[q] = *reinterpret_cast<const E *>(user + b * user_pitch + q * ES);
+                        else o.e[q] = *reinterpret_cast<const E *>(rows.at(b, q * ES));
+                    }
+                x[r] = o.v;
+            }
+        }
+        if constexpr (CHECK != CHECK_NONE && UNPACK) {
+            const uint32_t skip = (a0 - as) * ES, n = narrow ? na * ES : 16;
+#pragma unroll
+            for (uint32_t r = 0; r < V; ++r)
+                count_packed<E, CHECK>(rows, row_of(r), as * ES, x[r], FULL ? 0 : skip, FULL ? 16 : n,
+                                live && (kAll || b0 + r < nb), acc);
+        }
+        if (k == 0) {
+            if constexpr (!UNPACK) place();
+            fetch();
+        }
+        if (live) {
+            transpose_block<E>(x);
+#pragma unroll
+            for (uint32_t c = 0; c < V; ++c)
+                if (!narrow || c < na) lds[slot_of(as + c, lb)] = x[c];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < T * NB / kThreads; ++k) {
+        const uint32_t id = threadIdx.x + k * kThreads, row = id / NB, slot = id & (NB - 1);
+        const bool live = FULL || (row < na && slot * V < nb);
+        const uint32_t r = FULL ? row : min(row, na - 1), n = FULL ? V : min(V, nb - min(slot * V, nb));
+        const u32x4 v = lds[slot_of(r, slot)];
+        if constexpr (CHECK != CHECK_NONE && !UNPACK) count_packed<E, CHECK>(rows, r, slot * 16, v, 0, n * ES, live, acc);
+        if (!live) continue;
+        if constexpr (UNPACK) {
+            uint8_t *to = user + r * user_pitch + slot * 16;
+            if (FULL || n == V) store16_any<true>(to, v);
+            else store_elems<E>(to, v, n);
+        } else if constexpr (!Rows::kSpan) {
+            uint8_t *to = rows.at(r, slot * 16);
+            if (FULL || n == V) store_packed16<NTP>(reinterpret_cast<u32x4 *>(to), v);
+            else store_elems<E>(to, v, n);
+        } else {
+            if ((FULL || n == V) && !rows.crosses(r, slot * 16)) store_packed16<NTP>(reinterpret_cast<u32x4 *>(rows.at(r, slot * 16)), v);
+            else store_crossing<E, NTP>(rows.packed + rows.p0[r], rows.packed + rows.p1[r], rows.first[r], slot * 16, n, v);
+        }
+    }
+    return acc;
+}
+
+// The tensor's fast direction has a stride of a few elements (es bytes from element to element): element by element,
+// through an LDS tile padded by one element.  Thread (tx, ty) holds elements of packed row tx only while it is on the
+// tensor side and sums them there: sum(row, v, j) for element j of its row.  Eight global loads per thread are issued
+// before the first of them is needed (row and column numbers are clamped into the tile, so the loads need no guard).
+template <typename E, bool UNPACK, bool NTP, class Rows, class Sum>
+__device__ __forceinline__ void transpose_tile_elements(uint8_t *user, uint64_t user_pitch, uint32_t es, uint32_t ni, uint32_t nj,
+                                                        const Rows &rows, uint8_t *lds_raw, Sum &&sum)
+{
+    constexpr uint32_t T = TransposeShape<E>::T, TY = kThreads / T, U = 8;
+    E(*lds)[T + 1] = reinterpret_cast<E(*)[T + 1]>(lds_raw);
+    const uint32_t tx = threadIdx.x & (T - 1), ty = threadIdx.x / T;
+    auto tensor_side = [&]() {
+        if (tx >= ni) return;
+        for (uint32_t j0 = ty; j0 < nj; j0 += TY * U) {
+            E v[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t j = min(j0 + u * TY, nj - 1);
+                if constexpr (!UNPACK) v[u] = __builtin_nontemporal_load(reinterpret_cast<const E *>(user + j * user_pitch + tx * es));
+                else v[u] = lds[j][tx];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t j = j0 + u * TY;
+                if (j < nj) {
+                    if constexpr (!UNPACK) lds[j][tx] = v[u];
+                    else __builtin_nontemporal_store(v[u], reinterpret_cast<E *>(user + j * user_pitch + tx * es));
+                    sum(tx, v[u], j);
+                }
+            }
+        }
+    };
+    auto packed_side = [&]() {
+        const uint32_t txc = min(tx, nj - 1);
+        for (uint32_t i0 = ty; i0 < ni; i0 += TY * U) {
+            E *p[U];
+            E v[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                p[u] = reinterpret_cast<E *>(rows.at(min(i0 + u * TY, ni - 1), txc * uint32_t(sizeof(E))));
+                if constexpr (UNPACK) v[u] = load_elem<NTP>(p[u]);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t i = i0 + u * TY;
+                if (i < ni && tx < nj) {
+                    if constexpr (UNPACK) lds[tx][i] = v[u];
+                    else store_packed_elem<NTP>(p[u], lds[tx][i]);
+                }
+            }
+        }
+    };
+    if constexpr (!UNPACK) {
+        tensor_side();
+        __syncthreads();
+        packed_side();
+    } else {
+        packed_side();
+        __syncthreads();
+        tensor_side();
+    }
+}
+
+template <typename E>
+constexpr uint32_t transpose_lds_bytes() { return TransposeShape<E>::T * (TransposeShape<E>::T + 1) * sizeof(E); }
+
+template <typename E, bool UNPACK, int CHECK, bool NTU, bool NTP>
+__device__ __forceinline__ Sums2 transpose_any(const Tile &t, uint8_t *base, uint8_t *packed, const CheckArgs<CHECK> &ck, uint8_t *lds_raw)
+{
+    constexpr uint32_t T = TransposeShape<E>::T;
+    uint8_t *user = base + t.src_off;
+    const uint32_t ni = t.n0, nj = t.n1;
+    uint64_t in_chunk = t.packed_off & 255u;           // plain sums only need the position within a word
+    if constexpr (CHECK == CHECK_TAGS) in_chunk = t.packed_off - tag_place(ck.g, t.chunk) * ck.g.B;
+    const PitchRows rows{packed + t.packed_off, t.b, in_chunk};
+    u32x4 *lds = reinterpret_cast<u32x4 *>(lds_raw);
+    const uint32_t na = UNPACK ? nj : ni, nb = UNPACK ? ni : nj;
+    Sums2 acc{0, 0};
+    if (t.estep != sizeof(E))
+        transpose_tile_elements<E, UNPACK, NTP>(user, t.a, t.estep, ni, nj, rows, lds_raw, [&](uint32_t i, E v, uint32_t j) {
+            count_elem<CHECK>(acc, v, rows.template position<CHECK>(i, j * sizeof(E)));
+        });
+    else if (ni == T && nj == T)
+        acc = transpose_tile_vectors<E, UNPACK, CHECK, NTU, NTP, true>(user, t.a, na, nb, rows, lds, [] {}, [] {});
+    else
+        acc = transpose_tile_vectors<E, UNPACK, CHECK, NTU, NTP, false>(user, t.a, na, nb, rows, lds, [] {}, [] {});
+    return acc;
+}
+
+template <typename E, bool UNPACK, int CHECK, bool NTU, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__ tiles,
+                                                        const uint32_t *__restrict__ chunk_tiles, BasePtrs bases,
+                                                        uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
+    const Tile t = tiles[blockIdx.x];
+    const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
+    const Sums2 acc = transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, bases.p[t.tensor], packed, ck, lds_raw);
+    commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
+}
+
+// ---- transpose whose tiles span chunks -------------------------------------------
+// For matrices whose packed rows are long against the chunk: a tile is a full block of the logical matrix
+// (so that every memory burst of the tensor side is used whole) and row i of it starts at stream byte
+// s0 + i * b, wherever that falls; a tile row is shorter than a chunk, so it meets at most one chunk
+// border.  Thread i places row i (its chunk, the packed address of its first byte, how many of its
+// bytes lie before the border and where the rest go) and leaves that in LDS, so that the copy only
+// reads it back.  Placing takes no division and no memory access but for rows farther apart than a chunk is long, and
+// what the commit at the end reads is loaded at the start.  Sums go to the tile's per-chunk partial sums in LDS; at the
+// end one thread per chunk touched makes that chunk's arrival (inc holds the tile's chunks, ascending, and the ordinal
+// of each arrival).
+// [256, 65536] bf16 (8 packed rows per 1 MiB chunk), pack + unpack: 33.0 -> 26.0 us.
+
+// What k_transpose_span keeps in LDS beside the tile, for tiles of T rows.  Per row: packed offset of byte x is p0 + x for
+// x < first, p1 + x from there on (first is a whole tile row or more where the row meets no border); at: entry of the
+// row's first chunk; rem: position of its first byte in that chunk (for the weights of the sums).
+template <uint32_t T, int CHECK>
+struct SpanLds {
+    static constexpr uint32_t MAXC = 2 * T + 2;
+    unsigned long long part[MAXC];                      // partial sum per chunk touched
+    unsigned long long wpart[CHECK == CHECK_TAGS ? MAXC : 1];       // and the weighted one
+    uint64_t p0[T], p1[T], rem[T];
+    uint16_t first[T], at[T];                           // (16 bits: four workgroups of bf16 tiles with tags just fit a CU's LDS)
+};
+
+template <typename E, bool UNPACK, int CHECK, bool NTU, bool NTP, class Lds>
+__device__ __forceinline__ void transpose_span_any(const Tile &t, const uint32_t *__restrict__ chunk_tiles,
+                                                   const uint32_t *__restrict__ inc, const ChunkGeom &g, uint8_t *base,
+                                                   uint8_t *packed, const CheckArgs<CHECK> &ck, uint8_t *lds_raw, Lds &sp)
+{
+    constexpr uint32_t T = TransposeShape<E>::T;
+    static_assert(T <= kThreads, "one thread places one row");
+    uint64_t *const row_p0 = sp.p0, *const row_p1 = sp.p1, *const row_rem = sp.rem;
+    uint16_t *const row_first = sp.first, *const row_at = sp.at;
+    unsigned long long *const part = sp.part, *const wpart = sp.wpart;
+    uint8_t *user = base + t.src_off;
+    const uint32_t ni = t.n0, nj = t.n1, n_inc = t.ordinal;
+    const uint32_t *my = inc + 2 * size_t(t.chunk);
+    uint32_t my_chunk = 0, my_ordinal = 0, my_expected = 0;      // this thread's arrival at the end
+    auto fetch = [&]() {                                // asked for behind the tile's own loads, so that it is there then
+        if (CHECK == CHECK_NONE || threadIdx.x >= n_inc) return;
+        my_chunk = my[2 * threadIdx.x];
+        my_ordinal = my[2 * threadIdx.x + 1];
+        my_expected = chunk_tiles[my_chunk];
+    };
+    auto place = [&]() {                                // row threadIdx.x; the partial sums start at zero
+        for (uint32_t i = threadIdx.x; i < n_inc; i += kThreads) {
+            part[i] = 0;
+            if constexpr (CHECK == CHECK_TAGS) wpart[i] = 0;
+        }
+        if (threadIdx.x >= ni) return;
+        // (s / B in units of 256 bytes: tensor starts and chunks are multiples of that, and no message comes near 2^39 bytes)
+        const uint64_t B = g.B, s0 = t.packed_off, s = s0 + uint64_t(threadIdx.x) * t.b;
+        const uint32_t c = fast_div(uint32_t(s >> 8), g.div_b256), c0 = fast_div(uint32_t(s0 >> 8), g.div_b256);
+        const uint64_t rem = s - uint64_t(c) * B;
+        uint32_t at = c - c0;                           // rows no farther apart than a chunk is long meet every chunk in turn
+        if (t.b > B) {                                  // else: look for the entry that names chunk c (it is there)
+            uint32_t lo = 0, hi = n_inc - 1;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) / 2;
+                if (my[2 * mid] < c) lo = mid + 1;
+                else hi = mid;
+            }
+            at = lo;
+        }
+        auto chunk_base = [&](uint32_t ch) {
+            const uint32_t slot = fast_div(ch, g.div_k), lane = ch - slot * g.k;
+            return (uint64_t(lane) * g.q + (lane < g.r ? lane : g.r) + slot) * B;
+        };
+        const uint64_t room = B - rem;                  // bytes of chunk c from the row's start on
+        const bool whole = room >= uint64_t(nj) * sizeof(E);
+        row_at[threadIdx.x] = uint16_t(at);
+        row_first[threadIdx.x] = uint16_t(whole ? T * uint32_t(sizeof(E)) : uint32_t(room));
+        row_rem[threadIdx.x] = rem;
+        row_p0[threadIdx.x] = chunk_base(c) + rem;
+        row_p1[threadIdx.x] = whole ? 0 : chunk_base(c + 1) + rem - B;          // (+ x >= B - rem for those bytes)
+    };
+    const SpanRows rows{packed, row_p0, row_p1, row_first, row_at, row_rem, part, wpart, ((t.packed_off | t.b) & 15u) != 0};
+    u32x4 *lds = reinterpret_cast<u32x4 *>(lds_raw);
+    const uint32_t na = UNPACK ? nj : ni, nb = UNPACK ? ni : nj;
+    if (t.estep != sizeof(E)) {
+        // one thread holds elements of one row: the part before the chunk border and the part after it are summed in
+        // registers and go to LDS once
+        Sums2 a0{0, 0}, a1{0, 0};
+        place();
+        fetch();
+        __syncthreads();
+        transpose_tile_elements<E, UNPACK, NTP>(user, t.a, t.estep, ni, nj, rows, lds_raw, [&](uint32_t i, E v, uint32_t j) {
+            if constexpr (CHECK != CHECK_NONE) {
+                Sums2 x{0, 0};
+                count_elem<CHECK>(x, v, rows.template position<CHECK>(i, j * sizeof(E)));
+                const bool ahead = j * sizeof(E) < row_first[i];
+                a0.s += ahead ? x.s : 0, a0.w += ahead ? x.w : 0;
+                a1.s += ahead ? 0 : x.s, a1.w += ahead ? 0 : x.w;
+            }
+        });
+        if constexpr (CHECK != CHECK_NONE) {
+            const uint32_t tx = threadIdx.x & (T - 1);
+            if (a0.s) rows.template count<CHECK>(tx, false, a0);
+            if (a1.s) rows.template count<CHECK>(tx, true, a1);
+        }
+    } else if (ni == T && nj == T) {
+        transpose_tile_vectors<E, UNPACK, CHECK, NTU, NTP, true>(user, t.a, na, nb, rows, lds, place, fetch);
+    } else {
+        transpose_tile_vectors<E, UNPACK, CHECK, NTU, NTP, false>(user, t.a, na, nb, rows, lds, place, fetch);
+    }
+    if constexpr (CHECK != CHECK_NONE) {
+        __syncthreads();
+        auto arrive = [&](uint32_t i, uint32_t chunk, uint32_t ordinal, uint32_t expected) {
+            if constexpr (CHECK == CHECK_SUMS) commit_total(part[i], chunk, ordinal, expected, ck.cx);
+            else pair_commit_total(UNPACK ? SUM2_VERIFY : SUM2_SEAL, g, chunk, ordinal, expected, part[i], wpart[i], ck.out, ck.cx.acc, ck.cx.stride, ck.cx.fan, ck.work, [&] { return load_tag(g, chunk, ck.work); });
+        };
+        if (threadIdx.x < n_inc) arrive(threadIdx.x, my_chunk, my_ordinal, my_expected);
+        for (uint32_t i = threadIdx.x + kThreads; i < n_inc; i += kThreads) arrive(i, my[2 * i], my[2 * i + 1], chunk_tiles[my[2 * i]]);
+    }
+}
+
+template <typename E, bool UNPACK, int CHECK, bool NTU, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restrict__ tiles,
+                                                             const uint32_t *__restrict__ chunk_tiles,
+                                                             const uint32_t *__restrict__ inc, ChunkGeom g,
+                                                             BasePtrs bases, uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
+    __shared__ SpanLds<TransposeShape<E>::T, CHECK> sp;
+    const Tile t = tiles[blockIdx.x];
+    transpose_span_any<E, UNPACK, CHECK, NTU, NTP>(t, chunk_tiles, inc, g, bases.p[t.tensor], packed, ck, lds_raw, sp);
+}
+
+// ---- generic: any strides, one element at a time -------------------------------
+// Every element's address is recomputed from its logical index.  Only used for views the
+// other kernels do not take (no dimension with stride one, or runs shorter than 16 bytes).
+// The elements [e0, e0 + nel) of one tensor, every dim within reach of the multiply-shift division.
+// ND > 0: the tensor has exactly ND merged dims; ND == 0: any number, read from the descriptor.
+// The dims are copied into registers first: the loop below stores through byte pointers, which
+// may alias anything, so values read through the descriptor inside it would be read again for
+// every element.  Consecutive lanes take consecutive elements, U of them in flight per thread:
+// a wave's access is contiguous on the packed side and as dense on the tensor side as the view
+// allows.  The loads of a round are unconditional (the index is clamped into the tile), so that
+// all of them are issued before the first is waited for; only the stores are guarded.
+template <typename E, bool UNPACK, int CHECK, bool NTP, int ND>
+__device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p, uint64_t in_chunk)
+{
+    constexpr int D = ND ? ND : HXT_MAX_DIMS;
+    const int nd = ND ? ND : td.ndim;
+    uint32_t shape[D], mul[D], shift[D], first[D];
+    uint64_t stride[D];
+    {
+        uint64_t idx = e0;                                  // coordinates of the span's first element
+#pragma unroll
+        for (int d = D - 1; d >= 0; --d) {
+            shape[d] = 1, mul[d] = 0, shift[d] = 0, first[d] = 0, stride[d] = 0;
+            if (d < nd) {
+                shape[d] = uint32_t(td.shape[d]);
+                mul[d] = td.dim_div[d].mul;
+                shift[d] = td.dim_div[d].shift;
+                stride[d] = uint64_t(td.stride_b[d]);
+                const uint64_t q = idx / uint64_t(td.shape[d]);
+                first[d] = uint32_t(idx - q * uint64_t(td.shape[d]));
+                idx = q;
+            }
+        }
+    }
+    // An element's coordinates are the first element's plus its number within the span, carried from
+    // the last dim upwards in 32 bits (a span has fewer than 2^30 elements and so has every dim).
+    auto locate = [&](uint32_t el) -> E * {
+        uint64_t off = 0;
+        uint32_t x = el;
+#pragma unroll
+        for (int d = D - 1; d > 0; --d) {
+            if (d < nd) {
+                x += first[d];
+                const uint32_t q = fast_div(x, FastDiv{mul[d], shift[d]});
+                off += uint64_t(x - q * shape[d]) * stride[d];
+                x = q;
+            }
+        }
+        off += uint64_t(x + first[0]) * stride[0];
+        return reinterpret_cast<E *>(user + off);
+    };
+    constexpr int U = 8;
+    Sums2 acc{0, 0};
+    const uint32_t last = nel - 1;
+    for (uint32_t e1 = threadIdx.x; e1 < nel; e1 += kThreads * U) {
+        E val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t el = min(e1 + u * kThreads, last);
+            if constexpr (UNPACK) val[u] = load_elem<NTP>(p + el);
+            else val[u] = load_elem<true>(locate(el));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t el = e1 + u * kThreads;
+            if (el < nel) {
+                if constexpr (UNPACK) store_elem<true>(locate(el), val[u]);
+                else store_packed_elem<NTP>(p + el, val[u]);
+                count_elem<CHECK>(acc, val[u], in_chunk + uint64_t(el) * sizeof(E));
+            }
+        }
+    }
+    return acc;
+}
+
+// The same for tensors with a dim beyond the reach of the multiply-shift division: every element's
+// index is divided out in 64 bits.
+template <typename E, bool UNPACK, int CHECK, bool NTP>
+__device__ __noinline__ Sums2 generic_span_wide(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p, uint64_t in_chunk)
+{
+    const int nd = td.ndim;
+    Sums2 acc{0, 0};
+    for (uint32_t el = threadIdx.x; el < nel; el += kThreads) {
+        uint64_t idx = e0 + el, off = 0;
+        for (int d = nd - 1; d >= 0; --d) {
+            const uint64_t q = idx / uint64_t(td.shape[d]);
+            off += (idx - q * uint64_t(td.shape[d])) * uint64_t(td.stride_b[d]);
+            idx = q;
+        }
+        E *at = reinterpret_cast<E *>(user + off);
+        E v;
+        if constexpr (UNPACK) {
+            v = load_elem<NTP>(p + el);
+            store_elem<true>(at, v);
+        } else {
+            v = load_elem<true>(at);
+            store_packed_elem<NTP>(p + el, v);
+        }
+        count_elem<CHECK>(acc, v, in_chunk + uint64_t(el) * sizeof(E));
+    }
+    return acc;
+}
+
+template <typename E, bool UNPACK, int CHECK, bool NTP>
+__device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *packed)
+{
+    E *p = reinterpret_cast<E *>(packed + t.packed_off);
+    const uint32_t nel = t.n0 / sizeof(E);
+    const uint64_t e0 = t.src_off / sizeof(E);
+    if (nel == 0) return Sums2{0, 0};
+    if (!td.all_div) return generic_span_wide<E, UNPACK, CHECK, NTP>(td, e0, nel, user, p, t.a);
+    switch (td.ndim) {
+    case 1: return generic_span<E, UNPACK, CHECK, NTP, 1>(td, e0, nel, user, p, t.a);
+    case 2: return generic_span<E, UNPACK, CHECK, NTP, 2>(td, e0, nel, user, p, t.a);
+    case 3: return generic_span<E, UNPACK, CHECK, NTP, 3>(td, e0, nel, user, p, t.a);
+    case 4: return generic_span<E, UNPACK, CHECK, NTP, 4>(td, e0, nel, user, p, t.a);
+    default: return generic_span<E, UNPACK, CHECK, NTP, 0>(td, e0, nel, user, p, t.a);
+    }
+}
+
+template <typename E, bool UNPACK, int CHECK, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_generic(const Tile *__restrict__ tiles,
+                                                      const uint32_t *__restrict__ chunk_tiles,
+                                                      const TensorDev *__restrict__ tensors, uint32_t tensor_base,
+                                                      BasePtrs bases, uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
+{
+    const Tile t = tiles[blockIdx.x];
+    const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
+    const Sums2 acc = generic_any<E, UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed);
+    commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
+}
+
+// ---- a whole message of several kinds of view in one launch --------------------------
+// Messages that mix views (an activation, a mask, a transposed projection, the pads between them) are small more often
+// than not, and one launch per kind then costs more than the bytes: each has to fill the chip and drain it again for a
+// few dozen tiles.  Here every workgroup looks at its tile's kind.  The kernel needs the registers and the LDS of its
+// hungriest branch, which a large message would feel: see kOneLaunchLimit.
+struct MessageArgs {
+    BasePtrs bases;                    // of all tensors of the message
+    uint32_t first[6], base[6];        // per launch group of the plan: its first tile, its first tensor
+    uint32_t n;
+};
+
+template <bool UNPACK, int CHECK>
+__global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ tiles, const uint32_t *__restrict__ chunk_tiles,
+                                                      const TensorDev *__restrict__ tensors, const uint32_t *__restrict__ inc,
+                                                      ChunkGeom g, MessageArgs a, uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
+{
+    constexpr bool NTU = UNPACK, NTP = false;          // the hints of a small message
+    constexpr uint32_t kLds = transpose_lds_bytes<uint64_t>() > transpose_lds_bytes<uint16_t>() ? transpose_lds_bytes<uint64_t>()
+                                                                                                : transpose_lds_bytes<uint16_t>();
+    __shared__ __attribute__((aligned(16))) uint8_t lds_raw[kLds];
+    __shared__ SpanLds<TransposeShape<uint16_t>::T, CHECK> sp;
+    const Tile t = tiles[blockIdx.x];
+    uint32_t first_tensor = a.base[0];
+#pragma unroll
+    for (uint32_t i = 1; i < 6; ++i)
+        if (i < a.n && blockIdx.x >= a.first[i]) first_tensor = a.base[i];
+    const TensorDev &td = tensors[first_tensor + t.tensor];
+    uint8_t *base = a.bases.p[first_tensor + t.tensor], *pk = packed + t.packed_off;
+    auto by_size = [&](auto &&f) {
+        switch (td.esize) {
+        case 1: return f.template operator()<uint8_t>();
+        case 2: return f.template operator()<uint16_t>();
+        case 4: return f.template operator()<uint32_t>();
+        default: return f.template operator()<uint64_t>();
+        }
+    };
+    if (t.kind == K_TRANSPOSE_SPAN) {                  // (its field `chunk` is no chunk; it commits by itself)
+        by_size([&]<typename E>() { transpose_span_any<E, UNPACK, CHECK, NTU, NTP>(t, chunk_tiles, inc, g, base, packed, ck, lds_raw, sp); });
+        return;
+    }
+    const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
+    Sums2 acc{0, 0};
+    switch (t.kind) {
+    case K_ZERO:
+        if constexpr (CHECK == CHECK_TAGS) acc = pad_span2<UNPACK>(pk, t.n0, t.a);
+        else acc.s = pad_span<UNPACK, CHECK == CHECK_SUMS>(pk, t.n0, uint32_t(t.packed_off));
+        break;
+    case K_CONTIG:
+        if constexpr (CHECK == CHECK_TAGS) {
+            acc = copy_span2<UNPACK, NTU, NTP>(base + t.src_off, pk, t.n0);
+            acc.w += (t.a >> 2) * acc.s;
+        } else {
+            acc.s = copy_span<UNPACK, CHECK == CHECK_SUMS, NTU, NTP>(base + t.src_off, pk, t.n0);
+        }
+        break;
+    case K_ROWS: acc = rows_tile<UNPACK, CHECK, NTU, NTP>(t, td, base, pk); break;
+    case K_ROWS_SPLIT: acc = rows_split_any<UNPACK, CHECK, NTP>(t, td, base, pk); break;
+    case K_TRANSPOSE:
+        acc = by_size([&]<typename E>() { return transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, base, packed, ck, lds_raw); });
+        break;
+    default: acc = by_size([&]<typename E>() { return generic_any<E, UNPACK, CHECK, NTP>(t, td, base, packed); }); break;
+    }
+    commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
+}
+
+// ---- stand-alone checksum of packed chunks (closed-form geometry, no table) ----------
+template <bool NTP>
+__global__ __launch_bounds__(kThreads) void k_checksum(ChunkGeom g, const uint8_t *__restrict__ packed, SumCtx cx)
+{
+    const TileSpan t = locate_tile(g, blockIdx.x);
+    const u32x4 *s = reinterpret_cast<const u32x4 *>(packed + t.packed_off);
+    const uint32_t nvec = t.len >> 4;
+    uint64_t acc = 0;
+    for (uint32_t v = threadIdx.x; v < nvec; v += kThreads * kUnroll) {
+        u32x4 r[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+            r[u] = load16_or_zero<NTP>(s, v + u * kThreads, nvec);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) acc += words_sum(r[u]);
+    }
+    chunk_commit(acc, t.chunk, t.ordinal, t.expected, cx);
+}
+
+// ---- stand-alone strong check: the pass over the packed chunks -------------------------
+// Word j of the chunk sits at tile word i = j - j0.  A thread's vectors start at tile words
+// 4 * (tid + 256 * n), n = 0, 1, ...; with S_n the sum of vector n's words and I_n = y + 2z + 3w,
+//   sum (j+1) w_j = (j0 + 4 tid + 1) * sum_n S_n + 1024 * sum_n n S_n + sum_n I_n,
+// so the loop needs additions only (sum_n n S_n is kept as a running suffix sum) and each
+// thread multiplies once.
+template <int MODE, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_checksum2(ChunkGeom g, const uint8_t *__restrict__ packed,
+                                                        void *__restrict__ out, uint8_t *acc, uint32_t stride,
+                                                        uint32_t fan, TagWork work)
+{
+    const TileSpan t = locate_tile(g, blockIdx.x);
+    const TagRegs got = prefetch_tag(MODE, g, t.chunk, work);
+    const u32x4 *s = reinterpret_cast<const u32x4 *>(packed + t.packed_off);
+    const uint64_t j0 = (t.stream_off - uint64_t(t.chunk) * g.B) >> 2;
+    const uint32_t nvec = t.len >> 4;
+    uint64_t S = 0, nS = 0, I = 0;          // sum_n S_n, sum_n n*S_n, sum_n I_n
+    uint64_t n0 = 0;                         // n of the current block of vectors
+    for (uint32_t v = threadIdx.x; v < nvec; v += kThreads * kUnroll, n0 += kUnroll) {
+        u32x4 r[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+            r[u] = load16_or_zero<NTP>(s, v + u * kThreads, nvec);
+        uint64_t blockS = 0, blockN = 0;     // this block's sum_u S_u and sum_u u*S_u
+#pragma unroll
+        for (int u = kUnroll - 1; u >= 0; --u) {
+            const uint64_t zw = uint64_t(r[u].z) + r[u].w;
+            const uint64_t yzw = zw + r[u].y;
+            blockN += blockS;                // after the loop: sum_u u * S_u
+            blockS += yzw + r[u].x;
+            I += yzw + zw + r[u].w;
+        }
+        S += blockS;
+        nS += blockN + n0 * blockS;
+    }
+    pair_commit(MODE, g, t, S, (j0 + 4ull * threadIdx.x + 1) * S + 4ull * kThreads * nS + I, out, acc, stride, fan, work, got);
+}
+
+// ---- pack + seal and unpack + verify in one pass (messages that are one contiguous tensor) ----
+// The copy of k_uniform with both sums of the packed words taken on the way, so that tags cost no
+// extra pass over the message.  Weights are tile-local here (word i of the tile weighs i + 1);
+// the tile's position in its chunk is applied once per workgroup.
 // One launch serves up to kMaxBatch such messages (workgroups [first_tile, first_tile + ntiles) belong to
 // message i), as k_uniform does for the plain sums.
 struct UniformTagItem {
@@ -1662,54 +1878,6 @@ __global__ __launch_bounds__(kThreads) void k_contig_tag(const Tile *__restrict_
         j0 = t.a >> 2;
     }
     pair_commit(MODE, g, span, sums.s, j0 * sums.s + sums.w, out, acc, stride, fan, work, got);
-}
-
-// A few KiB of chunk tags between device memory and pinned host memory (either direction; the pinned
-// buffer is addressed directly over the host link).  A kernel rather than a DMA copy: a launch costs
-// less than the fixed overhead of a copy command, and the DMA queues keep only the large staging copies.
-__global__ __launch_bounds__(kThreads) void k_copy_tags(u32x4 *__restrict__ to, const u32x4 *__restrict__ from, uint32_t nvec)
-{
-    for (uint32_t v = blockIdx.x * kThreads + threadIdx.x; v < nvec; v += gridDim.x * kThreads) to[v] = from[v];
-}
-
-// Plain copy of nvec 16-byte vectors by a small grid (grid-stride), for staging between device memory and
-// pinned host memory over the host link: a few dozen workgroups keep the link busy and leave the rest of the
-// chip to other kernels.  The device side is streamed (non-temporal), four vectors in flight per thread.
-__global__ __launch_bounds__(kThreads) void k_stage_copy(u32x4 *__restrict__ to, const u32x4 *__restrict__ from, uint64_t nvec)
-{
-    const uint64_t step = uint64_t(gridDim.x) * kThreads;
-    uint64_t v = uint64_t(blockIdx.x) * kThreads + threadIdx.x;
-    for (; v + 3 * step < nvec; v += 4 * step) {
-        u32x4 r[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] = __builtin_nontemporal_load(from + v + u * step);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) __builtin_nontemporal_store(r[u], to + v + u * step);
-    }
-    for (; v < nvec; v += step) __builtin_nontemporal_store(__builtin_nontemporal_load(from + v), to + v);
-}
-
-// Zero-fill of nvec 16-byte vectors (a kernel, so that it can be recorded where a memset node cannot).
-__global__ __launch_bounds__(kThreads) void k_fill_zero(u32x4 *__restrict__ p, uint32_t nvec)
-{
-    for (uint32_t v = blockIdx.x * kThreads + threadIdx.x; v < nvec; v += gridDim.x * kThreads) p[v] = u32x4{0, 0, 0, 0};
-}
-
-// status[C] = number of chunks of status[0 .. C) that were rejected.  One workgroup.
-__global__ __launch_bounds__(kThreads) void k_count_rejected(uint32_t *status, uint32_t C)
-{
-    __shared__ uint32_t part[kThreads / 64];
-    uint32_t n = 0;
-    for (uint32_t c = threadIdx.x; c < C; c += kThreads) n += status[c] != 0;
-    for (int o = 32; o > 0; o >>= 1) n += __shfl_down(n, o, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t total = 0;
-#pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) total += part[w];
-        status[C] = total;
-    }
 }
 
 }  // namespace hxt

@@ -418,8 +418,13 @@ int build_plan(const hxt_tensor_desc_t *descs, int n_tensors, int n_lanes, size_
             p.uniform_tensor = uint32_t(i);
         }
     p.uniform = live == 1 && p.tensors[p.uniform_tensor].kind == K_CONTIG;
-    p.all_contig = true;
-    for (const Group &gr : p.groups) p.all_contig = p.all_contig && gr.kernel == K_CONTIG;
+    // a launch per group, for the transposes and the per-element kernel one per element size in it
+    p.launches = uint32_t(p.groups.size());
+    for (const Group &gr : p.groups)
+        if (gr.kernel == K_TRANSPOSE || gr.kernel == K_TRANSPOSE_SPAN || gr.kernel == K_GENERIC)
+            for (uint32_t i = 1; i < gr.count; ++i)
+                p.launches += p.tensors[gr.tensor_base + p.tiles[gr.first + i].tensor].esize !=
+                            p.tensors[gr.tensor_base + p.tiles[gr.first + i - 1].tensor].esize;
     g.N = p.uniform ? p.tensors[p.uniform_tensor].bytes : 0;
     return HXT_OK;
 }

@@ -1,8 +1,12 @@
 """GPU parity at the sizes where a rule of the launch code changes: either side of each limit, against the oracle."""
+import numpy as np
 import pytest
+import torch
 
-from tests.cases import Case, contig, make_storages
-from tests.test_gpu_parity import NT, round_trip_check, say
+from oracle import hxt_oracle as ho
+from paper_2602_18007_amd import hxt
+from tests.cases import SMALL_CASES, Case, contig, make_storages
+from tests.test_gpu_parity import NT, DEV, oracle_msg, round_trip_check, say, to_dev
 
 pytestmark = pytest.mark.gpu
 MiB = 1 << 20
@@ -27,3 +31,65 @@ def test_transpose_tiles_at_their_edges(esize, chunk):
     case = Case("edges_%d_%d" % (esize, chunk), tensors, 3, chunk)
     say("case", case.name, len(tensors), "tensors")
     round_trip_check(case, make_storages(case, 17), nthreads=NT)
+
+
+def tagged_round_trip(case, hint):
+    """pack + seal, then unpack + verify of the intact bytes and of a damaged last chunk, against the oracle."""
+    m = oracle_msg(case)
+    p = hxt.hxt_plan_multi([(s, st, e) for s, st, e in case.tensors], case.k, case.B)
+    hxt.hxt_plan_set_option(p, hxt.HXT_OPT_PACKED_HINT, hint)
+    raws, C = make_storages(case, 23), p.num_chunks
+    want = ho.pack(m, raws, case.B, case.k, fill=0xA5, nthreads=NT)
+    want_tags = ho.seal(m, want, case.B, case.k, 77, 5)
+    packed = torch.full((max(want.size, 16),), 0xA5, dtype=torch.uint8, device=DEV)
+    tags = torch.full((max(C, 1) * 64,), 0xEE, dtype=torch.uint8, device=DEV)
+    hxt.hxt_pack_seal(p, [to_dev(r) for r in raws], packed, 77, 5, tags)
+    assert np.array_equal(packed.cpu().numpy()[:want.size], want)
+    assert np.array_equal(tags.cpu().numpy()[:C * 64].reshape(C, 64), want_tags)
+    if not C or not all(p.tensor_unpack_safe(t) for t in range(len(case.tensors))):
+        return
+    damaged = want.copy()
+    damaged[p.chunk_info(C - 1)["packed_off"] + 5] ^= 0x40
+    for pk in (want, damaged):
+        dst_o = [np.full(r.size, 0x3C, np.uint8) for r in raws]
+        ho.unpack(m, pk, case.B, case.k, dst_o, nthreads=NT)
+        dst = [to_dev(np.full(r.size, 0x3C, np.uint8)) for r in raws]
+        status = torch.full((C + 1,), 0x7FFFFFFF, dtype=torch.int32, device=DEV)
+        hxt.hxt_unpack_verify(p, to_dev(pk), to_dev(want_tags.reshape(-1)), 77, 5, dst, status)
+        assert np.array_equal(status.cpu().numpy().view(np.uint32), ho.verify(m, pk, want_tags, case.B, case.k, 77, 5))
+        for a, b in zip(dst_o, dst):
+            assert np.array_equal(b.cpu().numpy()[:a.size], a)
+
+
+# The packed hint "non-temporal" keeps a message out of the one launch for several kinds, so both routes are compared.
+@pytest.mark.parametrize("hint", [0, 1], ids=["one_launch", "a_launch_per_kind"])
+@pytest.mark.parametrize("case", SMALL_CASES, ids=lambda c: c.name)
+def test_both_routes_of_small_messages(case, hint):
+    say("case", case.name)
+    round_trip_check(case, make_storages(case, 5), hint=hint)
+    tagged_round_trip(case, hint)
+
+
+@pytest.mark.parametrize("hint", [0, 1], ids=["one_launch", "a_launch_per_kind"])
+@pytest.mark.parametrize("chunk", [1024, 1 << 16], ids=lambda b: "chunks_of_%d" % b)
+@pytest.mark.parametrize("esize", [1, 2, 4, 8])
+def test_tags_of_transposes_at_their_edges(esize, chunk, hint):
+    """Weights of vectors that start inside a word or meet a chunk border; 36 matrices, the pads between them and a run
+    of rows whose length is no multiple of 16 bytes."""
+    T, V = (128 if esize <= 2 else 64), 16 // esize
+    sizes = [V + 1, T - 1, T, T + 1, T + V + 1, 2 * T + 3]
+    tensors = tuple(((r, c), (1, r + (r + c) % 3), esize) for r in sizes for c in sizes) + (((37, 2 * V + 1), (2 * V + 4, 1), esize),)
+    case = Case("tagged_edges_%d_%d" % (esize, chunk), tensors, 3, chunk)
+    say("case", case.name)
+    tagged_round_trip(case, hint)
+
+
+@pytest.mark.parametrize("rows", [2054, 2055, 2056, 16430, 16440])
+def test_one_launch_either_side_of_its_limits(rows):
+    """Padded rows of 4082 bytes with pads (limit 8 MiB: 2055 rows), and the same with a mask and a transposed matrix (limit 64 MiB: 16432 rows)."""
+    padded = ((rows, 2041), (2048, 1), 2)
+    for tensors in ((padded,), (padded, contig((rows,), 1), ((64, 40), (1, 64), 4))):
+        case = Case("limit_%d_%d" % (rows, len(tensors)), tensors, 4, MiB)
+        say("case", case.name)
+        round_trip_check(case, make_storages(case, 5), nthreads=NT)
+        tagged_round_trip(case, -1)

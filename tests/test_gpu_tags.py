@@ -149,7 +149,7 @@ def test_full_size_boundary_message_round_trip_with_tags():
 @pytest.mark.parametrize("case", CASES, ids=lambda c: c.name)
 def test_fused_pack_seal_and_unpack_verify_match_the_oracle(case):
     """hxt_pack_seal = pack + seal, hxt_unpack_verify = verify + unpack: same bytes, tags and masks as the oracle's
-    composition, in one pass for single contiguous tensors and in two passes for everything else."""
+    composition, in one pass whatever the views."""
     m = ho.Message([ho.TensorSpec(tuple(s), tuple(st), e) for (s, st, e) in case.tensors])
     p = hxt.hxt_plan_multi([(s, st, e) for (s, st, e) in case.tensors], case.k, case.B)
     raws = make_storages(case, 12)
@@ -353,7 +353,7 @@ def test_tags_on_the_full_size_gradient_buckets():
 
 
 def test_tags_on_a_single_tensor_larger_than_the_cacheable_limit():
-    # one contiguous bf16 tensor of 160 MiB + 4 KiB + 6 bytes (above 128 MiB the packed side is non-temporal),
+    # one contiguous bf16 tensor of 160 MiB + 4 KiB + 6 bytes (above 64 MiB packed loads are non-temporal),
     # 4 lanes, 4 MiB chunks of 256 tiles (fanned-out commits), ragged last chunk
     n = (160 << 20) + 4096 + 6
     t = wl.TensorDesc.contiguous((n // 2,))
