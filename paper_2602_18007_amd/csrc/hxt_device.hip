@@ -398,7 +398,12 @@ int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckAr
         HXT_HIP(hipGetLastError());
         return HXT_OK;
     }
-    for (const Group &g : p.groups) {
+    for (size_t k = p.pads_ride ? 1 : 0; k < p.groups.size(); ++k) {
+        Group g = p.groups[k];
+        if (p.pads_ride) {                                   // from the pads' first tile on
+            g.count += g.first;
+            g.first = 0;
+        }
         BasePtrs b;
         std::memset(&b, 0, sizeof b);
         for (uint32_t i = 0; i < g.n_tensors; ++i) b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
@@ -416,11 +421,12 @@ int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckAr
         } else {
             // The transpose and per-element kernels are instantiated per element size: issue one
             // launch per run of tiles whose tensors share it (host table, same order as on the device).
+            auto esize_at = [&](uint32_t i) { return p.tensors[g.tensor_base + p.tiles[std::max(g.first + i, p.groups[k].first)].tensor].esize; };
             uint32_t i = 0;
             while (i < g.count) {
-                const int es = p.tensors[g.tensor_base + p.tiles[g.first + i].tensor].esize;
+                const int es = esize_at(i);
                 uint32_t j = i + 1;
-                while (j < g.count && p.tensors[g.tensor_base + p.tiles[g.first + j].tensor].esize == es) ++j;
+                while (j < g.count && esize_at(j) == es) ++j;
                 if (g.kernel == K_TRANSPOSE)
                     launch_transpose<UNPACK, CHECK>(hints, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, b, packed, ck, st);
                 else if (g.kernel == K_TRANSPOSE_SPAN)

@@ -167,6 +167,8 @@ struct Plan {
     ChunkGeom geom;                      // closed-form geometry of the packed stream
     bool uniform = false;                // the message is one contiguous tensor: geom alone describes the copy
     uint32_t uniform_tensor = 0;         // index of that tensor
+    bool pads_ride = false;              // the contiguous group holds nothing but pads and there is one other group, of one
+                                         // element size: one launch takes the tiles of both (they lie next to each other)
     uint32_t launches = 0;               // launches the groups take, one per group and element size
 
     uint64_t chunk_padded(uint64_t c) const;

@@ -817,6 +817,15 @@ __device__ __forceinline__ void commit_tile(Sums2 v, const Tile &t, const uint32
     }
 }
 
+// The pads behind a tensor.  Every table-driven kernel takes them, so that they ride in the launch of the tensor's own
+// tiles where the message has no other contiguous piece (see Plan::pads_ride).
+template <bool UNPACK, int CHECK>
+__device__ __forceinline__ Sums2 pad_tile(const Tile &t, uint8_t *packed)
+{
+    if constexpr (CHECK == CHECK_TAGS) return pad_span2<UNPACK>(packed + t.packed_off, t.n0, t.a);
+    else return Sums2{pad_span<UNPACK, CHECK == CHECK_SUMS>(packed + t.packed_off, t.n0, uint32_t(t.packed_off)), 0};
+}
+
 // Adds an element of 8 bytes or less that starts at byte `pos` of a chunk (or of a tile that starts on a word).
 template <int CHECK, typename E>
 __device__ __forceinline__ void count_elem(Sums2 &acc, E v, uint64_t pos)
@@ -906,7 +915,8 @@ __global__ __launch_bounds__(kThreads) void k_rows(const Tile *__restrict__ tile
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = rows_tile<UNPACK, CHECK, NTU, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed)
+                                       : rows_tile<UNPACK, CHECK, NTU, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -1034,7 +1044,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict_
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = rows_split_any<UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -1423,7 +1433,7 @@ __global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__
     __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, bases.p[t.tensor], packed, ck, lds_raw);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, bases.p[t.tensor], packed, ck, lds_raw);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -1552,6 +1562,11 @@ __global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restr
     __shared__ __attribute__((aligned(16))) uint8_t lds_raw[transpose_lds_bytes<E>()];
     __shared__ SpanLds<TransposeShape<E>::T, CHECK> sp;
     const Tile t = tiles[blockIdx.x];
+    if (t.kind == K_ZERO) {
+        const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
+        commit_tile<UNPACK, CHECK>(pad_tile<UNPACK, CHECK>(t, packed), t, chunk_tiles, ck, got);
+        return;
+    }
     transpose_span_any<E, UNPACK, CHECK, NTU, NTP>(t, chunk_tiles, inc, g, bases.p[t.tensor], packed, ck, lds_raw, sp);
 }
 
@@ -1683,7 +1698,7 @@ __global__ __launch_bounds__(kThreads) void k_generic(const Tile *__restrict__ t
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = generic_any<E, UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : generic_any<E, UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -1731,8 +1746,7 @@ __global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ t
     Sums2 acc{0, 0};
     switch (t.kind) {
     case K_ZERO:
-        if constexpr (CHECK == CHECK_TAGS) acc = pad_span2<UNPACK>(pk, t.n0, t.a);
-        else acc.s = pad_span<UNPACK, CHECK == CHECK_SUMS>(pk, t.n0, uint32_t(t.packed_off));
+        acc = pad_tile<UNPACK, CHECK>(t, packed);
         break;
     case K_CONTIG:
         if constexpr (CHECK == CHECK_TAGS) {

@@ -424,7 +424,10 @@ int build_plan(const hxt_tensor_desc_t *descs, int n_tensors, int n_lanes, size_
         if (gr.kernel == K_TRANSPOSE || gr.kernel == K_TRANSPOSE_SPAN || gr.kernel == K_GENERIC)
             for (uint32_t i = 1; i < gr.count; ++i)
                 p.launches += p.tensors[gr.tensor_base + p.tiles[gr.first + i].tensor].esize !=
-                            p.tensors[gr.tensor_base + p.tiles[gr.first + i - 1].tensor].esize;
+                              p.tensors[gr.tensor_base + p.tiles[gr.first + i - 1].tensor].esize;
+    p.pads_ride = p.groups.size() == 2 && p.launches == 2 && p.groups[0].kernel == K_CONTIG;
+    for (uint32_t i = 0; p.pads_ride && i < p.groups[0].count; ++i) p.pads_ride = p.tiles[i].kind == K_ZERO;
+    if (p.pads_ride) p.launches = 1;
     g.N = p.uniform ? p.tensors[p.uniform_tensor].bytes : 0;
     return HXT_OK;
 }
