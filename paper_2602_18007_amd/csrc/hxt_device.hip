@@ -161,9 +161,9 @@ constexpr uint64_t kCacheableTensorLoads = uint64_t(32) << 20;
 
 // Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack +
 // unpack, launches of their own against one launch: bundles of four kinds 0.8 MB 38.7 -> 17.9 us, 7 MB 40.0 -> 18.5 us,
-// with tags 48.5 -> 22.9 us, 17 MB with tags 64.0 -> 40.8 us, 34 MB 46.6 -> 40.9 us.  Where all but one launch is pads
-// the gain is one short launch each way, and k_message's residency (3 or 4 workgroups per CU) costs more than that on
-// large messages: 4.5 MB 23.2 -> 20.0 us, 7.5 MB 26.8 -> 23.6 us, but 17.5 MB 32.4 -> 33.6, 60 MB 102 -> 110 us.
+// with tags 48.5 -> 22.9 us, 17 MB with tags 64.0 -> 40.8 us, 34 MB 46.6 -> 40.9 us.  With two launches
+// the gain is one launch each way, and k_message's residency (3 or 4 workgroups per CU) costs more than that on large
+// messages (measured on strided tensors with their pads in a launch of their own, before these rode along): 4.5 MB 23.2 -> 20.0 us, 7.5 MB 26.8 -> 23.6 us, but 17.5 MB 32.4 -> 33.6, 60 MB 102 -> 110 us.
 constexpr uint64_t kOneLaunchLimit = uint64_t(64) << 20;
 constexpr uint64_t kOneLaunchForTwoLimit = uint64_t(8) << 20;
 
