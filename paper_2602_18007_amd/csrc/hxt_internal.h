@@ -83,7 +83,7 @@ struct ChunkGeom {
     uint32_t ntiles;     // (C - 1) * tpc + tiles of the last chunk
     uint32_t last_tiles; // tiles of the last chunk
     FastDiv div_tpc, div_k;
-    FastDiv div_b256;    // division by B / 256 (of stream offsets / 256, below 2^31)
+    FastDiv div_b256;    // division by B / 256, for chunk_at
 };
 
 struct TileSpan {
@@ -110,6 +110,25 @@ HXT_HD TileSpan locate_tile(const ChunkGeom &g, uint32_t t)
     s.packed_off = (uint64_t(lane) * g.q + (lane < g.r ? lane : g.r) + slot) * g.B + in_chunk;
     s.len = left < g.tile ? uint32_t(left) : g.tile;
     return s;
+}
+
+// Where byte s of the stream (below 2^40, the largest message) lies: its chunk and its position in it.
+struct ChunkAt {
+    uint32_t chunk;
+    uint64_t rem;
+};
+
+HXT_HD ChunkAt chunk_at(const ChunkGeom &g, uint64_t s)
+{
+    // s and B are divided in units of 256 bytes.  The quotient is exact below 2^31 units and at most one too high from
+    // there to 2^32 (the error term of make_fastdiv doubles), which the remainder shows.
+    uint32_t c = fast_div(uint32_t(s >> 8), g.div_b256);
+    uint64_t rem = s - uint64_t(c) * g.B;
+    if (int64_t(rem) < 0) {
+        --c;
+        rem += g.B;
+    }
+    return ChunkAt{c, rem};
 }
 
 // Per-tensor view description for the ROWS and GENERIC kernels (merged dims, logical order).

@@ -1489,10 +1489,9 @@ __device__ __forceinline__ void transpose_span_any(const Tile &t, const uint32_t
             if constexpr (CHECK == CHECK_TAGS) wpart[i] = 0;
         }
         if (threadIdx.x >= ni) return;
-        // (s / B in units of 256 bytes: tensor starts and chunks are multiples of that, and no message comes near 2^39 bytes)
-        const uint64_t B = g.B, s0 = t.packed_off, s = s0 + uint64_t(threadIdx.x) * t.b;
-        const uint32_t c = fast_div(uint32_t(s >> 8), g.div_b256), c0 = fast_div(uint32_t(s0 >> 8), g.div_b256);
-        const uint64_t rem = s - uint64_t(c) * B;
+        const uint64_t B = g.B, s0 = t.packed_off;
+        const auto [c, rem] = chunk_at(g, s0 + uint64_t(threadIdx.x) * t.b);
+        const uint32_t c0 = chunk_at(g, s0).chunk;
         uint32_t at = c - c0;                           // rows no farther apart than a chunk is long meet every chunk in turn
         if (t.b > B) {                                  // else: look for the entry that names chunk c (it is there)
             uint32_t lo = 0, hi = n_inc - 1;

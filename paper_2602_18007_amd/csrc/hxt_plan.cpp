@@ -45,7 +45,7 @@ int make_geom(uint64_t N, uint64_t L, uint64_t B, uint32_t k, uint32_t tile_byte
     g.ntiles = C ? uint32_t((C - 1) * tpc) + g.last_tiles : 0;
     g.div_tpc = make_fastdiv(g.tpc);
     g.div_k = make_fastdiv(g.k);
-    g.div_b256 = make_fastdiv(uint32_t(std::min<uint64_t>(B / HXT_ALIGN, (uint64_t(1) << 31) - 1)));   // larger chunks hold any message
+    g.div_b256 = make_fastdiv(uint32_t(std::min<uint64_t>(B / HXT_ALIGN, ~uint32_t(0))));   // larger chunks hold any message
     return HXT_OK;
 }
 

@@ -243,3 +243,16 @@ extern "C" int fastdiv_check(uint32_t d, const uint32_t *ns, int count)
     }
     return 0;
 }
+
+// The chunk and the position in it that the spanning transposes find for stream bytes of a message of L bytes, against
+// plain 64-bit division.  Returns 0, -1 if the geometry is refused, or 1 + the index of the first wrong one.
+extern "C" int chunk_at_check(uint64_t L, uint64_t B, const uint64_t *at, int count)
+{
+    ChunkGeom g;
+    if (make_geom(0, L, B, 3, 1u << 24, g) != HXT_OK) return -1;
+    for (int i = 0; i < count; ++i) {
+        const ChunkAt c = chunk_at(g, at[i]);
+        if (c.chunk != at[i] / B || c.rem != at[i] % B) return 1 + i;
+    }
+    return 0;
+}

@@ -386,6 +386,18 @@ def test_multiply_shift_division_is_exact(interp):
         assert interp.fastdiv_check(C.c_uint32(d), C.c_void_p(ns.ctypes.data), C.c_int(ns.size)) == 0, d
 
 
+def test_rows_of_spanning_transposes_find_their_chunk_up_to_the_largest_message(interp):
+    """Stream bytes up to 2^40 (the largest message a plan takes), either side of chunk borders, chunks of 1 KiB to 1 TiB."""
+    rng, L = np.random.default_rng(9), 1 << 40
+    for B in [1024, 1280, 3 << 10, 769 * 256, 1 << 20, 25600 << 10, (1 << 20) + 256, 65521 * 256, 1 << 31, (1 << 38) + 256, 1 << 39,
+              (1 << 39) + 256, L - 256, L]:
+        borders = rng.integers(0, L // B + 1, 4000).astype(np.uint64) * np.uint64(B)
+        at = np.concatenate([borders, borders + np.uint64(1), borders + np.uint64(B - 1), borders - np.uint64(1),
+                             rng.integers(0, L, 4000).astype(np.uint64), np.array([0, L // 2 - 1, L // 2, L - 1], np.uint64)])
+        at = np.ascontiguousarray(at[at < L])
+        assert interp.chunk_at_check(C.c_uint64(L), C.c_uint64(B), C.c_void_p(at.ctypes.data), C.c_int(at.size)) == 0, B
+
+
 # ---- randomised views: planner tables vs oracle ------------------------------------
 
 @pytest.mark.parametrize("seed", list(range(12)) + [100, 101, 102, 103])
