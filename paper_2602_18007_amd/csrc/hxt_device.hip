@@ -150,12 +150,17 @@ int env_int(const char *name, int dflt)
 //     (store_packed16).  Better than non-temporal stores up to 1 GiB (pack + unpack with sums: 128 MiB 81 against 92 us,
 //     288 MiB 171 against 197, 512 MiB 338 against 356); above, nothing of the buffer's start is left when it is read
 //     and non-temporal stores are as good or better (1.7 GB pack + accumulate 1407 against 1401 us).
-//   Packed side, loads: cacheable up to 64 MiB, non-temporal above, where keeping what has been read only pushes out
-//     what is still to be read (128 MiB 82.5 -> 80.7 us, 256 MiB 160 -> 152, 288 MiB 219 -> 171; 64 MiB 43.8 against 44.1).
+//   Packed side, loads: cacheable up to 128 MiB, where the buffer still is in the last-level cache when it is read
+//     (unpack of one of two buffers in turn, cacheable against non-temporal: 80 MiB 26.8 against 30.6 us, 96 MiB 31.1
+//     against 35.8, 128 MiB 41.0 against 46.5; accumulated 62.8 against 72.9; rows of 101 bf16 elements 81.9 against 102).
+//     Buffers that have left the cache lose less by it (128 MiB, pack + unpack 82.8 against 81.1).  Non-temporal above:
+//     what has been read only pushes out what is still to be read (pack + unpack 160 MiB 98.8 against 106.4, 256 MiB 153
+//     against 158).  The stand-alone passes, which take nothing but the buffer through the cache, already from 64 MiB on
+//     (pack + hxt_checksum 96 MiB 45.2 against 50.2 us, 128 MiB 57.7 against 67.6).
 //   Tensor side, loads: cacheable while the tensors, the packed buffer and the receiver's tensors fit the 256 MB
 //     last-level cache together (messages up to 32 MiB: 16 MiB 15.1 -> 14.0 us, 32 MiB 24.9 -> 23.4), non-temporal
 //     above (112 MiB 76 -> 71 us).  Stores: non-temporal (a tensor is written once, whole).
-constexpr uint64_t kCacheablePackedLoads = uint64_t(64) << 20;
+constexpr uint64_t kCacheablePackedLoads = uint64_t(128) << 20, kCacheablePackedPasses = uint64_t(64) << 20;
 constexpr uint64_t kWrittenThroughLimit = uint64_t(1) << 30;
 constexpr uint64_t kCacheableTensorLoads = uint64_t(32) << 20;
 
@@ -182,6 +187,8 @@ inline bool packed_nontemporal(int hint, uint64_t bytes, bool load)
 {
     return hint >= 0 ? hint != 0 : bytes > (load ? kCacheablePackedLoads : kWrittenThroughLimit);
 }
+
+inline bool pass_nontemporal(const hxt_plan_t &pl) { return pl.nt_packed >= 0 ? pl.nt_packed != 0 : pl.p.C * pl.p.B > kCacheablePackedPasses; }
 
 inline bool packed_nontemporal(const hxt_plan_t &pl, bool load) { return packed_nontemporal(pl.nt_packed, pl.p.C * pl.p.B, load); }
 
@@ -746,7 +753,7 @@ int run_sum2(const hxt_plan_t *plan, const void *packed, int mode, void *out, co
     SlotsLock lock(pl.slots_mu);
     if ((rc = claim_slots(pl, mode == SUM2_VERIFY ? (chain ? OP_SUM2_RECV_B : OP_SUM2_RECV) : (chain ? OP_SUM2_SEND_B : OP_SUM2_SEND), st, cx, nullptr)) != HXT_OK) return rc;
     const uint8_t *pk = static_cast<const uint8_t *>(packed);
-    const bool ntp = packed_nontemporal(pl, true);
+    const bool ntp = pass_nontemporal(pl);
     auto launch = [&]<int MODE>() {
         TagWork w = work;
         w.sum_bits = pl.sum_bits_geom;
@@ -1496,7 +1503,7 @@ int hxt_checksum(const hxt_plan_t *plan, const void *packed, uint64_t *sums, voi
     if ((rc = claim_slots(pl, OP_CHECKSUM, st, cx, sums)) != HXT_OK) return rc;
     cx.sum_bits = pl.sum_bits_geom;
     const uint8_t *pk = static_cast<const uint8_t *>(packed);
-    if (packed_nontemporal(pl, true))
+    if (pass_nontemporal(pl))
         k_checksum<true><<<pl.p.geom.ntiles, kThreads, 0, st>>>(pl.p.geom, pk, cx);
     else
         k_checksum<false><<<pl.p.geom.ntiles, kThreads, 0, st>>>(pl.p.geom, pk, cx);
