@@ -157,12 +157,12 @@ int env_int(const char *name, int dflt)
 //     what has been read only pushes out what is still to be read (pack + unpack 160 MiB 98.8 against 106.4, 256 MiB 153
 //     against 158).  The stand-alone passes, which take nothing but the buffer through the cache, already from 64 MiB on
 //     (pack + hxt_checksum 96 MiB 45.2 against 50.2 us, 128 MiB 57.7 against 67.6).
-//   Tensor side, loads: cacheable while the tensors, the packed buffer and the receiver's tensors fit the 256 MB
-//     last-level cache together (messages up to 32 MiB: 16 MiB 15.1 -> 14.0 us, 32 MiB 24.9 -> 23.4), non-temporal
-//     above (112 MiB 76 -> 71 us).  Stores: non-temporal (a tensor is written once, whole).
+//   Tensor side, loads and stores: non-temporal.  A message's tensors are new each time: keeping their lines pays only
+//     where the very same tensor is sent again (32 MiB over and over, pack + unpack: 24.8 us non-temporal, 22.6 cacheable;
+//     three in turn 26.4 and 24.7) and costs where it has just been written or has left the cache (through two packed
+//     buffers, 8 MiB 10.4 against 11.5 us, 16 MiB 16.6 against 17.1, a transposed 32 MiB matrix 26.8 against 27.9).
 constexpr uint64_t kCacheablePackedLoads = uint64_t(128) << 20, kCacheablePackedPasses = uint64_t(64) << 20;
 constexpr uint64_t kWrittenThroughLimit = uint64_t(1) << 30;
-constexpr uint64_t kCacheableTensorLoads = uint64_t(32) << 20;
 
 // Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack +
 // unpack, launches of their own against one launch: bundles of four kinds 0.8 MB 38.7 -> 17.9 us, 7 MB 40.0 -> 18.5 us,
@@ -192,12 +192,7 @@ inline bool pass_nontemporal(const hxt_plan_t &pl) { return pl.nt_packed >= 0 ? 
 
 inline bool packed_nontemporal(const hxt_plan_t &pl, bool load) { return packed_nontemporal(pl.nt_packed, pl.p.C * pl.p.B, load); }
 
-// load: the launch reads the tensors and writes the packed buffer.
-inline bool user_nontemporal(uint64_t bytes, bool load)
-{
-    const int o = tuning().nt_user;
-    return o >= 0 ? o != 0 : !load || bytes > kCacheableTensorLoads;
-}
+inline bool user_nontemporal() { return tuning().nt_user != 0; }
 
 using hxt::with_hints;
 
@@ -205,7 +200,7 @@ using hxt::with_hints;
 template <bool UNPACK, typename F>
 void with_hints(const hxt_plan_t &pl, F &&f)
 {
-    with_hints(user_nontemporal(pl.p.C * pl.p.B, !UNPACK), packed_nontemporal(pl, UNPACK), f);
+    with_hints(user_nontemporal(), packed_nontemporal(pl, UNPACK), f);
 }
 
 // The streaming copies are launched with 32 KiB of (unused) dynamic LDS per workgroup, which caps residency at 5
@@ -229,7 +224,7 @@ void launch_uniform(const UniformArgs &a, uint32_t tiles, uint64_t bytes, int hi
 {
     const size_t lds = residency_cap_lds();
     // (a mixed launch has one hint for both directions: as for loads, which it wants cacheable while they are small)
-    with_hints(user_nontemporal(bytes, DIR == DIR_PACK), packed_nontemporal(hint, bytes, DIR != DIR_PACK), [&]<bool NTU, bool NTP>() { k_uniform<DIR, CSUM, NTU, NTP><<<tiles, kThreads, lds, st>>>(a); });
+    with_hints(user_nontemporal(), packed_nontemporal(hint, bytes, DIR != DIR_PACK), [&]<bool NTU, bool NTP>() { k_uniform<DIR, CSUM, NTU, NTP><<<tiles, kThreads, lds, st>>>(a); });
 }
 
 template <bool UNPACK, int CHECK>
@@ -391,8 +386,8 @@ template <bool UNPACK, int CHECK>
 int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckArgs<CHECK> &ck, hipStream_t st)
 {
     const Plan &p = pl.p;
-    const Hints hints{user_nontemporal(p.C * p.B, !UNPACK), packed_nontemporal(pl, UNPACK)};
-    if (p.launches > 1 && p.tensors.size() <= size_t(kMaxGroupTensors) && !hints.packed && tuning().nt_user < 0 &&
+    const bool ntp = packed_nontemporal(pl, UNPACK);
+    if (p.launches > 1 && p.tensors.size() <= size_t(kMaxGroupTensors) && !ntp && tuning().nt_user < 0 &&
         p.L <= (p.launches > 2 ? kOneLaunchLimit : kOneLaunchForTwoLimit)) {
         MessageArgs a;
         std::memset(&a, 0, sizeof a);
@@ -419,7 +414,7 @@ int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckAr
         } else if (g.kernel == K_ROWS) {
             launch_rows<UNPACK, CHECK>(pl, g, b, packed, ck, st);
         } else if (g.kernel == K_ROWS_SPLIT) {
-            if (packed_nontemporal(pl, UNPACK))
+            if (ntp)
                 k_rows_split<UNPACK, CHECK, true><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
                                                                                g.tensor_base, b, packed, ck);
             else
@@ -435,9 +430,9 @@ int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckAr
                 uint32_t j = i + 1;
                 while (j < g.count && esize_at(j) == es) ++j;
                 if (g.kernel == K_TRANSPOSE)
-                    launch_transpose<UNPACK, CHECK>(hints, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, b, packed, ck, st);
+                    launch_transpose<UNPACK, CHECK>(ntp, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, b, packed, ck, st);
                 else if (g.kernel == K_TRANSPOSE_SPAN)
-                    launch_transpose_span<UNPACK, CHECK>(hints, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, pl.d_inc, p.geom, b, packed, ck, st);
+                    launch_transpose_span<UNPACK, CHECK>(ntp, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, pl.d_inc, p.geom, b, packed, ck, st);
                 else
                     launch_generic<UNPACK, CHECK>(pl, g.first + i, j - i, g.tensor_base, es, b, packed, ck, st);
                 i = j;
@@ -870,7 +865,7 @@ int run_tag_batch(int n, const hxt_plan_t *const *plans, void *const *const *ten
             bytes += pj.p.C * pj.p.B;
             ++j;
         }
-        with_hints(user_nontemporal(bytes, !UNPACK), packed_nontemporal(plans[i]->nt_packed, bytes, UNPACK), [&]<bool NTU, bool NTP>() { k_uniform_tag<UNPACK, MODE, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a); });
+        with_hints(user_nontemporal(), packed_nontemporal(plans[i]->nt_packed, bytes, UNPACK), [&]<bool NTU, bool NTP>() { k_uniform_tag<UNPACK, MODE, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a); });
         HXT_HIP(hipGetLastError());
         i = j;
     }
@@ -1309,7 +1304,7 @@ int hxt_unpack_accumulate_batch(int n, const hxt_plan_t *const *plans, const voi
             bytes += pj.p.C * pj.p.B;
             ++j;
         }
-        with_hints(user_nontemporal(bytes, false), packed_nontemporal(plans[i]->nt_packed, bytes, true), [&]<bool NTU, bool NTP>() {
+        with_hints(user_nontemporal(), packed_nontemporal(plans[i]->nt_packed, bytes, true), [&]<bool NTU, bool NTP>() {
             if (sm) k_uniform_accumulate<true, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a);
             else k_uniform_accumulate<false, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a);
         });

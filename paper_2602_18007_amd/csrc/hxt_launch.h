@@ -19,29 +19,13 @@ void with_hints(bool nt_user, bool nt_packed, F &&f)
     }
 }
 
-// Cache hints of a launch: the tensor side's and the packed side's accesses are non-temporal.
-struct Hints {
-    bool user, packed;
-};
-
-// The hints of the strided kernels, whose stores to the tensors are always non-temporal: a receiving launch has one hint.
-template <bool UNPACK, typename F>
-void with_strided_hints(Hints h, F &&f)
-{
-    if constexpr (UNPACK) {
-        if (h.packed) f.template operator()<true, true>();
-        else f.template operator()<true, false>();
-    } else {
-        with_hints(h.user, h.packed, f);
-    }
-}
-
+// (The strided kernels take the packed side's hint alone: ntp.)
 template <bool UNPACK, int CHECK>
-void launch_transpose(Hints h, const Tile *tiles, uint32_t count, int esize, const uint32_t *chunk_tiles, const BasePtrs &b,
+void launch_transpose(bool ntp, const Tile *tiles, uint32_t count, int esize, const uint32_t *chunk_tiles, const BasePtrs &b,
                       uint8_t *packed, const CheckArgs<CHECK> &ck, hipStream_t st);
 
 template <bool UNPACK, int CHECK>
-void launch_transpose_span(Hints h, const Tile *tiles, uint32_t count, int esize, const uint32_t *chunk_tiles,
+void launch_transpose_span(bool ntp, const Tile *tiles, uint32_t count, int esize, const uint32_t *chunk_tiles,
                            const uint32_t *inc, const ChunkGeom &g, const BasePtrs &b, uint8_t *packed,
                            const CheckArgs<CHECK> &ck, hipStream_t st);
 

@@ -14,7 +14,7 @@ MiB = 1 << 20
 
 @pytest.mark.parametrize("nbytes", [32 * MiB, 32 * MiB + 8, 64 * MiB, 64 * MiB + 24, 128 * MiB, 128 * MiB + 24])
 def test_cache_hints_either_side_of_their_limits(nbytes):
-    """Tensor loads stop being cacheable above 32 MiB, packed loads above 128 MiB of packed bytes."""
+    """Packed loads stop being cacheable above 128 MiB of packed bytes."""
     case = Case("contig_%d" % nbytes, (contig((nbytes // 8,), 8),), 3, MiB)
     say("case", case.name)
     round_trip_check(case, make_storages(case, 5), nthreads=NT)
