@@ -136,7 +136,7 @@ int hxt_plan_destroy(hxt_plan_t *plan); /* NULL is allowed */
  * HXT_OPT_PACKED_HINT: cache hint of the packed-buffer side of every copy and pass of this plan.
  *   -1 (default) by size, so that a packed buffer that is re-read soon (by the wire, or by hxt_unpack
  *      on the same GPU) can be served from the 256 MB last-level cache: stores are written through to
- *      it while packed_bytes <= 1 GiB, loads are cacheable up to 128 MiB; non-temporal above;
+ *      it while the message has <= 1 GiB, loads are cacheable up to 128 MiB; non-temporal above;
  *    0 always cacheable;  1 always non-temporal (every byte goes to and comes from HBM).
  *   The environment variable HXT_NT_PACKED (0/1), read when a plan is created, sets the initial value.
  * HXT_OPT_STAGE_D2H: how hxt_stage_d2h* and the CPU-forwarding path of hxt_exchange_stream move

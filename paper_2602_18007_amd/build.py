@@ -11,7 +11,7 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libhxt.so")
 SOURCES = [os.path.join(PKG, "csrc", f) for f in ("hxt_device.hip", "hxt_transpose.hip", "hxt_transpose_span.hip", "hxt_message_pack.hip",
                                                       "hxt_message_unpack.hip", "hxt_plan.cpp")]
-HEADERS = [os.path.join(PKG, "csrc", f) for f in ("hxt_internal.h", "hxt_kernels.h", "hxt_launch.h")] + \
+HEADERS = [os.path.join(PKG, "csrc", f) for f in ("hxt_internal.h", "hxt_kernels.h", "hxt_launch.h", "hxt_rules.h")] + \
           [os.path.join(ROOT, "include", "hxt.h")]
 
 

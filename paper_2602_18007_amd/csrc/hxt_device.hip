@@ -20,6 +20,7 @@
 #include "hxt_internal.h"
 #include "hxt_kernels.h"
 #include "hxt_launch.h"
+#include "hxt_rules.h"
 
 using namespace hxt;
 
@@ -145,33 +146,6 @@ int env_int(const char *name, int dflt)
     return (s && *s) ? std::atoi(s) : dflt;
 }
 
-// Cache hints, chosen per launch from the bytes it moves (HXT_NT_USER / HXT_NT_PACKED, 0 or 1, override).
-//   Packed side, stores: written through to the last-level cache, where the wire or hxt_unpack reads them
-//     (store_packed16).  Better than non-temporal stores up to 1 GiB (pack + unpack with sums: 128 MiB 81 against 92 us,
-//     288 MiB 171 against 197, 512 MiB 338 against 356); above, nothing of the buffer's start is left when it is read
-//     and non-temporal stores are as good or better (1.7 GB pack + accumulate 1407 against 1401 us).
-//   Packed side, loads: cacheable up to 128 MiB, where the buffer still is in the last-level cache when it is read
-//     (unpack of one of two buffers in turn, cacheable against non-temporal: 80 MiB 26.8 against 30.6 us, 96 MiB 31.1
-//     against 35.8, 128 MiB 41.0 against 46.5; accumulated 62.8 against 72.9; rows of 101 bf16 elements 81.9 against 102).
-//     Buffers that have left the cache lose less by it (128 MiB, pack + unpack 82.8 against 81.1).  Non-temporal above:
-//     what has been read only pushes out what is still to be read (pack + unpack 160 MiB 98.8 against 106.4, 256 MiB 153
-//     against 158).  The stand-alone passes, which take nothing but the buffer through the cache, already from 64 MiB on
-//     (pack + hxt_checksum 96 MiB 45.2 against 50.2 us, 128 MiB 57.7 against 67.6).
-//   Tensor side, loads and stores: non-temporal.  A message's tensors are new each time: keeping their lines pays only
-//     where the very same tensor is sent again (32 MiB over and over, pack + unpack: 24.8 us non-temporal, 22.6 cacheable;
-//     three in turn 26.4 and 24.7) and costs where it has just been written or has left the cache (through two packed
-//     buffers, 8 MiB 10.4 against 11.5 us, 16 MiB 16.6 against 17.1, a transposed 32 MiB matrix 26.8 against 27.9).
-constexpr uint64_t kCacheablePackedLoads = uint64_t(128) << 20, kCacheablePackedPasses = uint64_t(64) << 20;
-constexpr uint64_t kWrittenThroughLimit = uint64_t(1) << 30;
-
-// Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack +
-// unpack, launches of their own against one launch: bundles of four kinds 0.8 MB 38.7 -> 17.9 us, 7 MB 40.0 -> 18.5 us,
-// with tags 48.5 -> 22.9 us, 17 MB with tags 64.0 -> 40.8 us, 34 MB 46.6 -> 40.9 us.  With two launches
-// the gain is one launch each way, and k_message's residency (3 or 4 workgroups per CU) costs more than that on large
-// messages (measured on strided tensors with their pads in a launch of their own, before these rode along): 4.5 MB 23.2 -> 20.0 us, 7.5 MB 26.8 -> 23.6 us, but 17.5 MB 32.4 -> 33.6, 60 MB 102 -> 110 us.
-constexpr uint64_t kOneLaunchLimit = uint64_t(64) << 20;
-constexpr uint64_t kOneLaunchForTwoLimit = uint64_t(8) << 20;
-
 struct Tuning {
     int nt_user, nt_packed;        // -1 = automatic
     Tuning() : nt_user(env_int("HXT_NT_USER", -1)), nt_packed(env_int("HXT_NT_PACKED", -1)) {}
@@ -182,19 +156,12 @@ const Tuning &tuning()
     return t;
 }
 
-// hint: HXT_OPT_PACKED_HINT of the plan that decides; bytes: packed bytes of the launch; load: it reads the packed side.
-inline bool packed_nontemporal(int hint, uint64_t bytes, bool load)
-{
-    return hint >= 0 ? hint != 0 : bytes > (load ? kCacheablePackedLoads : kWrittenThroughLimit);
-}
-
-inline bool pass_nontemporal(const hxt_plan_t &pl) { return pl.nt_packed >= 0 ? pl.nt_packed != 0 : pl.p.C * pl.p.B > kCacheablePackedPasses; }
-
-inline bool packed_nontemporal(const hxt_plan_t &pl, bool load) { return packed_nontemporal(pl.nt_packed, pl.p.C * pl.p.B, load); }
-
 inline bool user_nontemporal() { return tuning().nt_user != 0; }
 
+using hxt::packed_nontemporal;
 using hxt::with_hints;
+
+inline bool packed_nontemporal(const hxt_plan_t &pl, bool load) { return packed_nontemporal(pl.nt_packed, launch_bytes(pl.p), load); }
 
 // The hints of one plan's launch.
 template <bool UNPACK, typename F>
@@ -387,8 +354,7 @@ int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckAr
 {
     const Plan &p = pl.p;
     const bool ntp = packed_nontemporal(pl, UNPACK);
-    if (p.launches > 1 && p.tensors.size() <= size_t(kMaxGroupTensors) && !ntp && tuning().nt_user < 0 &&
-        p.L <= (p.launches > 2 ? kOneLaunchLimit : kOneLaunchForTwoLimit)) {
+    if (one_launch(p) && !ntp && tuning().nt_user < 0) {
         MessageArgs a;
         std::memset(&a, 0, sizeof a);
         for (size_t i = 0; i < p.tensors.size(); ++i) a.bases.p[i] = static_cast<uint8_t *>(ptrs[i]);
@@ -463,7 +429,7 @@ int run_copy(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t *sums,
         std::memset(&a, 0, sizeof a);
         a.n = 1;
         a.it[0] = UniformItem{p.geom, base, packed, cx, 0, UNPACK};
-        launch_uniform<UNPACK ? DIR_UNPACK : DIR_PACK, CSUM>(a, p.geom.ntiles, p.C * p.B, pl.nt_packed, st);
+        launch_uniform<UNPACK ? DIR_UNPACK : DIR_PACK, CSUM>(a, p.geom.ntiles, launch_bytes(p), pl.nt_packed, st);
         HXT_HIP(hipGetLastError());
         return HXT_OK;
     }
@@ -719,7 +685,7 @@ int run_batch(int n, const hxt_plan_t *const *plans, void *const *const *tensors
             a.it[a.n++] = UniformItem{pj.p.geom, static_cast<uint8_t *>(tensors[j][pj.p.uniform_tensor]),
                                       static_cast<uint8_t *>(packed[j]), cx, uint32_t(tiles), UNPACK};
             tiles += pj.p.geom.ntiles;
-            bytes += pj.p.C * pj.p.B;
+            bytes += launch_bytes(pj.p);
             ++j;
         }
         constexpr int DIR = UNPACK ? DIR_UNPACK : DIR_PACK;
@@ -748,7 +714,7 @@ int run_sum2(const hxt_plan_t *plan, const void *packed, int mode, void *out, co
     SlotsLock lock(pl.slots_mu);
     if ((rc = claim_slots(pl, mode == SUM2_VERIFY ? (chain ? OP_SUM2_RECV_B : OP_SUM2_RECV) : (chain ? OP_SUM2_SEND_B : OP_SUM2_SEND), st, cx, nullptr)) != HXT_OK) return rc;
     const uint8_t *pk = static_cast<const uint8_t *>(packed);
-    const bool ntp = pass_nontemporal(pl);
+    const bool ntp = pass_nontemporal(pl.nt_packed, launch_bytes(pl.p));
     auto launch = [&]<int MODE>() {
         TagWork w = work;
         w.sum_bits = pl.sum_bits_geom;
@@ -862,7 +828,7 @@ int run_tag_batch(int n, const hxt_plan_t *const *plans, void *const *const *ten
             a.it[a.n++] = UniformTagItem{pj.p.geom, static_cast<uint8_t *>(tensors[j][pj.p.uniform_tensor]),
                                          static_cast<uint8_t *>(packed[j]), outs[j], cx.acc, cx.stride, cx.fan, w, uint32_t(tiles)};
             tiles += pj.p.geom.ntiles;
-            bytes += pj.p.C * pj.p.B;
+            bytes += launch_bytes(pj.p);
             ++j;
         }
         with_hints(user_nontemporal(), packed_nontemporal(plans[i]->nt_packed, bytes, UNPACK), [&]<bool NTU, bool NTP>() { k_uniform_tag<UNPACK, MODE, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a); });
@@ -939,8 +905,8 @@ int fused_direct_stream(hxt_plan_t &pl, const hxt_exchange_t &x, hipStream_t sp,
         if (k > 0) rc = add(k - 1, true);
         if (rc == HXT_OK && k < x.n_messages) rc = add(k, false);
         if (rc != HXT_OK) return rc;
-        if (x.send_sums) launch_uniform<DIR_MIXED, true>(a, tiles, p.C * p.B, pl.nt_packed, sp);
-        else launch_uniform<DIR_MIXED, false>(a, tiles, p.C * p.B, pl.nt_packed, sp);
+        if (x.send_sums) launch_uniform<DIR_MIXED, true>(a, tiles, launch_bytes(p), pl.nt_packed, sp);
+        else launch_uniform<DIR_MIXED, false>(a, tiles, launch_bytes(p), pl.nt_packed, sp);
         HXT_HIP(hipGetLastError());
     }
     if (su != sp || ss != sp) {
@@ -1301,7 +1267,7 @@ int hxt_unpack_accumulate_batch(int n, const hxt_plan_t *const *plans, const voi
                                       const_cast<uint8_t *>(static_cast<const uint8_t *>(packed[j])), cx, uint32_t(tiles),
                                       tp.dtype == HXT_F32 ? 1u : 0u};
             tiles += pj.p.geom.ntiles;
-            bytes += pj.p.C * pj.p.B;
+            bytes += launch_bytes(pj.p);
             ++j;
         }
         with_hints(user_nontemporal(), packed_nontemporal(plans[i]->nt_packed, bytes, true), [&]<bool NTU, bool NTP>() {
@@ -1479,9 +1445,8 @@ int hxt_pack_noalloc(const void *src, size_t message_bytes, int n_lanes, size_t 
     a.it[0].cx = cx;
     a.it[0].first_tile = 0;
     a.it[0].unpack = 0;
-    const uint64_t bytes = uint64_t(g.C) * g.B;
-    if (sums) launch_uniform<DIR_PACK, true>(a, g.ntiles, bytes, tuning().nt_packed, st);
-    else launch_uniform<DIR_PACK, false>(a, g.ntiles, bytes, tuning().nt_packed, st);
+    if (sums) launch_uniform<DIR_PACK, true>(a, g.ntiles, L, tuning().nt_packed, st);
+    else launch_uniform<DIR_PACK, false>(a, g.ntiles, L, tuning().nt_packed, st);
     HXT_HIP(hipGetLastError());
     return HXT_OK;
 }
@@ -1498,7 +1463,7 @@ int hxt_checksum(const hxt_plan_t *plan, const void *packed, uint64_t *sums, voi
     if ((rc = claim_slots(pl, OP_CHECKSUM, st, cx, sums)) != HXT_OK) return rc;
     cx.sum_bits = pl.sum_bits_geom;
     const uint8_t *pk = static_cast<const uint8_t *>(packed);
-    if (pass_nontemporal(pl))
+    if (pass_nontemporal(pl.nt_packed, launch_bytes(pl.p)))
         k_checksum<true><<<pl.p.geom.ntiles, kThreads, 0, st>>>(pl.p.geom, pk, cx);
     else
         k_checksum<false><<<pl.p.geom.ntiles, kThreads, 0, st>>>(pl.p.geom, pk, cx);

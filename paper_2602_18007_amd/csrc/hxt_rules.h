@@ -1,0 +1,56 @@
+// Rules of the launch code that only look at sizes: no HIP, so that they can be tested without a GPU.
+#ifndef HXT_RULES_H
+#define HXT_RULES_H
+
+#include "hxt_internal.h"
+
+namespace hxt {
+
+// Cache hints, chosen per launch from the stream bytes it moves, whatever chunks they are cut into (HXT_NT_USER /
+// HXT_NT_PACKED, 0 or 1, override).
+//   Packed side, stores: written through to the last-level cache, where the wire or hxt_unpack reads them
+//     (store_packed16).  Better than non-temporal stores up to 1 GiB (pack + unpack with sums: 128 MiB 81 against 92 us,
+//     288 MiB 171 against 197, 512 MiB 338 against 356); above, nothing of the buffer's start is left when it is read
+//     and non-temporal stores are as good or better (1.7 GB pack + accumulate 1407 against 1401 us).
+//   Packed side, loads: cacheable up to 128 MiB, where the buffer still is in the last-level cache when it is read
+//     (unpack of one of two buffers in turn, cacheable against non-temporal: 80 MiB 26.8 against 30.6 us, 96 MiB 31.1
+//     against 35.8, 128 MiB 41.0 against 46.5; accumulated 62.8 against 72.9; rows of 101 bf16 elements 81.9 against 102).
+//     Buffers that have left the cache lose less by it (128 MiB, pack + unpack 82.8 against 81.1).  Non-temporal above:
+//     what has been read only pushes out what is still to be read (pack + unpack 160 MiB 98.8 against 106.4, 256 MiB 153
+//     against 158).  The stand-alone passes, which take nothing but the buffer through the cache, already from 64 MiB on
+//     (pack + hxt_checksum 96 MiB 45.2 against 50.2 us, 128 MiB 57.7 against 67.6).
+//   Tensor side, loads and stores: non-temporal.  A message's tensors are new each time: keeping their lines pays only
+//     where the very same tensor is sent again (32 MiB over and over, pack + unpack: 24.8 us non-temporal, 22.6 cacheable;
+//     three in turn 26.4 and 24.7) and costs where it has just been written or has left the cache (through two packed
+//     buffers, 8 MiB 10.4 against 11.5 us, 16 MiB 16.6 against 17.1, a transposed 32 MiB matrix 26.8 against 27.9).
+constexpr uint64_t kCacheablePackedLoads = uint64_t(128) << 20, kCacheablePackedPasses = uint64_t(64) << 20;
+constexpr uint64_t kWrittenThroughLimit = uint64_t(1) << 30;
+
+// Bytes a launch over the message moves on the packed side (its packed buffer, whole chunks, can be much longer).
+inline uint64_t launch_bytes(const Plan &p) { return p.L; }
+
+// hint: HXT_OPT_PACKED_HINT of the plan that decides; bytes: those of the launch; load: it reads the packed side.
+inline bool packed_nontemporal(int hint, uint64_t bytes, bool load)
+{
+    return hint >= 0 ? hint != 0 : bytes > (load ? kCacheablePackedLoads : kWrittenThroughLimit);
+}
+
+inline bool pass_nontemporal(int hint, uint64_t bytes) { return hint >= 0 ? hint != 0 : bytes > kCacheablePackedPasses; }
+
+// Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack +
+// unpack, launches of their own against one launch: bundles of four kinds 0.8 MB 38.7 -> 17.9 us, 7 MB 40.0 -> 18.5 us,
+// with tags 48.5 -> 22.9 us, 17 MB with tags 64.0 -> 40.8 us, 34 MB 46.6 -> 40.9 us.  With two launches
+// the gain is one launch each way, and k_message's residency (3 or 4 workgroups per CU) costs more than that on large
+// messages (measured on strided tensors with their pads in a launch of their own, before these rode along): 4.5 MB 23.2 -> 20.0 us, 7.5 MB 26.8 -> 23.6 us, but 17.5 MB 32.4 -> 33.6, 60 MB 102 -> 110 us.
+constexpr uint64_t kOneLaunchLimit = uint64_t(64) << 20;
+constexpr uint64_t kOneLaunchForTwoLimit = uint64_t(8) << 20;
+
+inline bool one_launch(const Plan &p)
+{
+    return p.launches > 1 && p.tensors.size() <= size_t(kMaxGroupTensors) &&
+           launch_bytes(p) <= (p.launches > 2 ? kOneLaunchLimit : kOneLaunchForTwoLimit);
+}
+
+}  // namespace hxt
+
+#endif

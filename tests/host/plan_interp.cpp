@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "hxt_internal.h"
+#include "hxt_rules.h"
 
 using namespace hxt;
 
@@ -255,4 +256,18 @@ extern "C" int chunk_at_check(uint64_t L, uint64_t B, const uint64_t *at, int co
         if (c.chunk != at[i] / B || c.rem != at[i] % B) return 1 + i;
     }
     return 0;
+}
+
+// How a message goes out: launches of a kind's own it takes, whether they become one, and the packed side's hints by size
+// (bit 0: stores, bit 1: loads, bit 2: stand-alone passes non-temporal).  Returns an hxt_status.
+extern "C" int launch_rules(const hxt_tensor_desc_t *descs, int n_tensors, int n_lanes, uint64_t chunk_bytes, uint32_t *launches,
+                            uint32_t *one, uint32_t *hints)
+{
+    Plan p;
+    if (int rc = build_plan(descs, n_tensors, n_lanes, chunk_bytes, kDefaultTileBytes, p); rc != HXT_OK) return rc;
+    *launches = p.uniform ? 1 : p.launches;
+    *one = !p.uniform && one_launch(p);
+    *hints = (packed_nontemporal(-1, launch_bytes(p), false) ? 1u : 0u) | (packed_nontemporal(-1, launch_bytes(p), true) ? 2u : 0u) |
+             (pass_nontemporal(-1, launch_bytes(p)) ? 4u : 0u);
+    return HXT_OK;
 }

@@ -288,7 +288,8 @@ def interp():
     src = os.path.join(ROOT, "tests", "host", "plan_interp.cpp")
     out = os.path.join(ROOT, "tests", "host", "libplan_interp.so")
     csrc = os.path.join(ROOT, "paper_2602_18007_amd", "csrc")
-    deps = [src, os.path.join(csrc, "hxt_plan.cpp"), os.path.join(csrc, "hxt_internal.h")]
+    deps = [src, os.path.join(csrc, "hxt_plan.cpp"), os.path.join(csrc, "hxt_internal.h"),
+            os.path.join(csrc, "hxt_rules.h")]
     if not os.path.exists(out) or any(os.path.getmtime(d) > os.path.getmtime(out) for d in deps):
         subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-shared", "-fPIC", "-Wall", "-Wextra",
                         "-fsanitize=undefined", "-fno-sanitize-recover=all",
@@ -300,16 +301,41 @@ def interp():
     return L
 
 
-def run_interp(L, case, storages, packed, direction, tile_bytes):
+def describe(case):
+    """The case's tensors as the C ABI takes them, and what has to stay alive while they are used."""
     n = len(case.tensors)
-    descs = (_Desc * max(n, 1))()
-    keep = []
+    descs, keep = (_Desc * max(n, 1))(), []
     size_code = {1: 1, 2: 3, 4: 4, 8: 5}
     for j, (shape, strides, e) in enumerate(case.tensors):
         shp = (C.c_int64 * max(len(shape), 1))(*shape)
         st = (C.c_int64 * max(len(shape), 1))(*strides)
         keep += [shp, st]
         descs[j].ndim, descs[j].shape, descs[j].strides, descs[j].dtype = len(shape), shp, st, size_code[e]
+    return descs, keep
+
+
+def launch_rules(L, case):
+    """(launches of a kind's own, whether they go out as one, non-temporal hints: 1 stores, 2 loads, 4 passes)"""
+    descs, keep = describe(case)
+    out = [C.c_uint32(0) for _ in range(3)]
+    assert L.launch_rules(descs, len(case.tensors), case.k, C.c_uint64(case.B), *[C.byref(x) for x in out]) == 0
+    return out[0].value, bool(out[1].value), out[2].value
+
+
+def test_launch_rules_go_by_the_bytes_a_message_moves(interp):
+    """Not by its packed buffer, which a last chunk can make much longer: one MiB in a chunk of 2 GiB is a small message,
+    two kinds of view in it still go out in one launch, and either side of each line of the hints."""
+    MiB = 1 << 20
+    for chunk in (MiB, 2048 * MiB):
+        for nbytes, hints in ((MiB, 0), (64 * MiB, 0), (64 * MiB + 256, 4), (128 * MiB, 4), (128 * MiB + 256, 6), (1024 * MiB, 6), (1024 * MiB + 256, 7)):
+            assert launch_rules(interp, Case("contig", (contig((nbytes,), 1),), 4, chunk)) == (1, False, hints), (chunk, nbytes)
+        two = (((1024, 500), (512, 1), 2), contig((1024,), 1))
+        assert launch_rules(interp, Case("two", two, 4, chunk)) == (2, True, 0), chunk
+
+
+def run_interp(L, case, storages, packed, direction, tile_bytes):
+    n = len(case.tensors)
+    descs, keep = describe(case)
     bases = (C.c_void_p * max(n, 1))(*[s.ctypes.data for s in storages])
     sizes = (C.c_uint64 * max(n, 1))(*[s.size for s in storages])
     written = np.zeros(max(packed.size, 1), np.uint8)
