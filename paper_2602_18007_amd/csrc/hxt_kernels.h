@@ -172,7 +172,8 @@ __device__ __forceinline__ u32x4 keep_bytes(u32x4 v, uint32_t from, uint32_t to)
                  v.z & below(2, to) & ~below(2, from), v.w & below(3, to) & ~below(3, from)};
 }
 
-// Sum over the 16 lanes of a DPP row, in its last lane (the others hold partial sums).  Inactive lanes count as zero.
+// Sum over every LANES lanes in a DPP row of 16, in the last of them (the others hold partial sums).  Inactive lanes count
+// as zero.
 template <int CTRL, int ROWS = 0xF>
 __device__ __forceinline__ uint64_t dpp_plus(uint64_t v)
 {
@@ -181,12 +182,14 @@ __device__ __forceinline__ uint64_t dpp_plus(uint64_t v)
     return v + (uint64_t(hi) << 32 | lo);
 }
 
-__device__ __forceinline__ uint64_t row16_sum(uint64_t v)
+template <uint32_t LANES>
+__device__ __forceinline__ uint64_t lanes_sum(uint64_t v)
 {
+    static_assert(LANES == 8 || LANES == 16);
     v = dpp_plus<0x111>(v);                              // row_shr 1, 2, 4, 8
     v = dpp_plus<0x112>(v);
     v = dpp_plus<0x114>(v);
-    return dpp_plus<0x118>(v);
+    return LANES == 16 ? dpp_plus<0x118>(v) : v;
 }
 
 // One arrival at an accumulator slot that expects `expected` of them: adds `value` and reports
@@ -1062,15 +1065,20 @@ __global__ __launch_bounds__(kThreads, UNPACK && CHECK != CHECK_TAGS ? 7 : 1) vo
 template <typename E>
 struct TransposeShape {
     static constexpr uint32_t T = transpose_tile(sizeof(E)), V = 16 / sizeof(E);
-    static constexpr uint32_t NB = T / V;                        // vectors per tile row, blocks per tile side
-    static constexpr uint32_t BLOCKS = NB * NB;
+    static constexpr uint32_t NB = T / V;                        // vectors per tile row
+    // Source rows of a thread's block: as many as a vector has elements, so that LDS takes whole vectors.  Not for bytes:
+    // 64 such blocks make up a tile, three waves of four would have none and the fourth all the sums to take; a block is 4
+    // rows, LDS takes words.  32 MiB of bytes, receiving: 13.8 -> 11.9 us, with tags 25.3 -> 14.0, across chunks 22.2 -> 14.5.
+    static constexpr uint32_t R = sizeof(E) == 1 ? 4 : V;
+    static constexpr uint32_t BLOCKS = NB * (T / R);
 };
 
-// x[r] holds V elements of source row r; afterwards x[c] holds the V elements of source column c.
+// x[r] holds V elements of source row r; afterwards x[c] holds the V elements of source column c (bytes: word c & 3 of
+// x[c / 4] holds the 4 elements of source column c).
 template <typename E>
-__device__ __forceinline__ void transpose_block(u32x4 (&x)[16 / sizeof(E)])
+__device__ __forceinline__ void transpose_block(u32x4 (&x)[TransposeShape<E>::R])
 {
-    constexpr int V = 16 / sizeof(E);
+    constexpr int V = TransposeShape<E>::R;
     u32x4 y[V];
     if constexpr (sizeof(E) == 8) {
         y[0] = u32x4{x[0].x, x[0].y, x[1].x, x[1].y};
@@ -1089,18 +1097,14 @@ __device__ __forceinline__ void transpose_block(u32x4 (&x)[16 / sizeof(E)])
             }
     } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t lo01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x05010400u);       // bytes 0 0' 1 1'
-                const uint32_t hi01 = __builtin_amdgcn_perm(x[4 * q + 1][c], x[4 * q][c], 0x07030602u);       // bytes 2 2' 3 3'
-                const uint32_t lo23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x05010400u);
-                const uint32_t hi23 = __builtin_amdgcn_perm(x[4 * q + 3][c], x[4 * q + 2][c], 0x07030602u);
-                y[4 * c][q] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
-                y[4 * c + 1][q] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
-                y[4 * c + 2][q] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
-                y[4 * c + 3][q] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-            }
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t lo01 = __builtin_amdgcn_perm(x[1][c], x[0][c], 0x05010400u);       // bytes 0 0' 1 1'
+            const uint32_t hi01 = __builtin_amdgcn_perm(x[1][c], x[0][c], 0x07030602u);       // bytes 2 2' 3 3'
+            const uint32_t lo23 = __builtin_amdgcn_perm(x[3][c], x[2][c], 0x05010400u);
+            const uint32_t hi23 = __builtin_amdgcn_perm(x[3][c], x[2][c], 0x07030602u);
+            y[c] = u32x4{__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                         __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+        }
     }
 #pragma unroll
     for (int i = 0; i < V; ++i) x[i] = y[i];
@@ -1186,8 +1190,9 @@ __device__ __forceinline__ u32x4 load_crossing(const uint8_t *before, const uint
 }
 
 // Adds the sum of a vector of packed bytes (n of them from byte `skip` on count) to the tile's sum, or to the partial sum
-// of its chunk.  SpanRows: called by all lanes of a wave, the 16 lanes of a DPP row holding vectors of one tile row
-// (live: this lane's vector counts); the row is summed across those lanes first, so that one lane goes to LDS.
+// of its chunk.  SpanRows: called by all lanes of a wave, 16 lanes next to each other (8 for bytes) holding
+// vectors of one tile row (live: this lane's vector counts); the row is summed across those lanes first, so that one lane
+// goes to LDS.
 template <typename E, int CHECK, class Rows>
 __device__ __forceinline__ void count_packed(const Rows &rows, uint32_t row, uint32_t byte, u32x4 v, uint32_t skip, uint32_t n,
                                              bool live, Sums2 &acc)
@@ -1214,16 +1219,12 @@ __device__ __forceinline__ void count_packed(const Rows &rows, uint32_t row, uin
         }
         Sums2 v2{0, 0};
         if (!crossing) count_vector<CHECK, sizeof(E)>(v2, kept, rows.template position<CHECK>(row, byte));
-        constexpr bool kGrouped = TransposeShape<E>::NB % 16 == 0;
+        constexpr uint32_t LANES = TransposeShape<E>::NB < 16 ? TransposeShape<E>::NB : 16;     // of a DPP row that hold one tile row
         const bool whole = border >= TransposeShape<E>::T * uint32_t(sizeof(E));     // the row meets no border in this tile
-        if constexpr (kGrouped) {
-            Sums2 total{row16_sum(v2.s), 0};
-            if constexpr (CHECK == CHECK_TAGS) total.w = row16_sum(v2.w);
-            if (whole && (threadIdx.x & 15) == 15) rows.template count<CHECK>(row, false, total);
-            if (!whole && v2.s) rows.template count<CHECK>(row, byte >= border, v2);
-        } else {
-            if (v2.s) rows.template count<CHECK>(row, byte >= border, v2);
-        }
+        Sums2 total{lanes_sum<LANES>(v2.s), 0};
+        if constexpr (CHECK == CHECK_TAGS) total.w = lanes_sum<LANES>(v2.w);
+        if (whole && (threadIdx.x & (LANES - 1)) == LANES - 1) rows.template count<CHECK>(row, false, total);
+        if (!whole && v2.s) rows.template count<CHECK>(row, byte >= border, v2);
     }
 }
 
@@ -1235,7 +1236,7 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
                                                            const Rows &rows, u32x4 *lds, Place &&place, Fetch &&fetch)
 {
     using Sh = TransposeShape<E>;
-    constexpr uint32_t T = Sh::T, V = Sh::V, NB = Sh::NB, ES = sizeof(E);
+    constexpr uint32_t T = Sh::T, V = Sh::V, R = Sh::R, NB = Sh::NB, ES = sizeof(E);
     constexpr uint32_t PER = Sh::BLOCKS < uint32_t(kThreads) ? 1 : Sh::BLOCKS / kThreads;      // blocks per thread
     const uint32_t na = FULL ? T : na_in, nb = FULL ? T : nb_in;
     auto slot_of = [](uint32_t row, uint32_t slot) { return row * NB + (slot ^ ((row / V) & (NB - 1))); };
@@ -1247,7 +1248,7 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
 #pragma unroll
     for (uint32_t k = 0; k < PER; ++k) {
         const uint32_t id = threadIdx.x + k * kThreads, la = id & (NB - 1), lb = id / NB;
-        const uint32_t a0 = la * V, b0 = lb * V;
+        const uint32_t a0 = la * V, b0 = lb * R;
         constexpr bool kAll = FULL && Sh::BLOCKS >= uint32_t(kThreads);      // every thread has a whole block
         const bool live = kAll || (id < Sh::BLOCKS && a0 < na && b0 < nb);
         auto row_of = [&](uint32_t r) { return kAll ? b0 + r : min(b0 + r, nb - 1); };
@@ -1255,10 +1256,10 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
         // then moved twice, with the same values); rows beyond the tile repeat the last one.
         const uint32_t as = FULL || a0 + V <= na ? a0 : (na >= V ? na - V : 0);
         const bool narrow = !FULL && na < V;
-        u32x4 x[V];
+        u32x4 x[R];
         if (live && !narrow) {
 #pragma unroll
-            for (uint32_t r = 0; r < V; ++r) {
+            for (uint32_t r = 0; r < R; ++r) {
                 const uint32_t b = row_of(r);
                 if constexpr (!UNPACK) {
                     x[r] = load16_any<NTU>(user + b * user_pitch + as * ES);
@@ -1273,14 +1274,14 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
             if constexpr (UNPACK && Rows::kSpan) {
                 if (rows.may_cross)
 #pragma unroll
-                    for (uint32_t r = 0; r < V; ++r) {
+                    for (uint32_t r = 0; r < R; ++r) {
                         const uint32_t b = row_of(r);
                         if (rows.crosses(b, as * ES)) x[r] = load_crossing<E>(rows.packed + rows.p0[b], rows.packed + rows.p1[b], rows.first[b], as * ES);
                     }
             }
         } else if (live) {                               // fewer than V columns in the whole tile
 #pragma unroll
-            for (uint32_t r = 0; r < V; ++r) {
+            for (uint32_t r = 0; r < R; ++r) {
                 const uint32_t b = row_of(r);
                 union {
                     E e[V];
@@ -1298,7 +1299,7 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
         if constexpr (CHECK != CHECK_NONE && UNPACK) {
             const uint32_t skip = (a0 - as) * ES, n = narrow ? na * ES : 16;
 #pragma unroll
-            for (uint32_t r = 0; r < V; ++r)
+            for (uint32_t r = 0; r < R; ++r)
                 count_packed<E, CHECK>(rows, row_of(r), as * ES, x[r], FULL ? 0 : skip, FULL ? 16 : n,
                                 live && (kAll || b0 + r < nb), acc);
         }
@@ -1310,7 +1311,10 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
             transpose_block<E>(x);
 #pragma unroll
             for (uint32_t c = 0; c < V; ++c)
-                if (!narrow || c < na) lds[slot_of(as + c, lb)] = x[c];
+                if (!narrow || c < na) {
+                    if constexpr (R == V) lds[slot_of(as + c, lb)] = x[c];
+                    else reinterpret_cast<uint32_t *>(lds + slot_of(as + c, lb / (V / R)))[lb % (V / R)] = x[c / R][c % R];
+                }
         }
     }
     __syncthreads();
