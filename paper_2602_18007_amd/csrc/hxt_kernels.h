@@ -124,6 +124,12 @@ __device__ __forceinline__ void store16_any(uint8_t *p, u32x4 v)
     else *reinterpret_cast<u32x4_any *>(p) = v;
 }
 
+// The same, cacheable, for one side of a branch whose other side is non-temporal (as one store the hint would be lost).
+__device__ __forceinline__ void store16_cached(uint8_t *p, u32x4 v)
+{
+    __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u32x4 *)reinterpret_cast<u32x4 *>(p), v, "wavefront");
+}
+
 // The first n elements of a vector, one at a time.
 template <typename E>
 __device__ __forceinline__ void store_elems(uint8_t *p, u32x4 v, uint32_t n)
@@ -1318,6 +1324,14 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
         }
     }
     __syncthreads();
+    // Receiving, rows that do not start on 16 bytes are left in the cache: non-temporal, the bursts they share with their
+    // neighbours go out in parts.  A base one element off, 32 MiB: bytes 27.2 -> 13.7 us, two bytes 16.6 -> 13.0, four
+    // 17.7 -> 12.1, across chunks 30 -> 17.4, 22.8 -> 16.0, 22.5 -> 14.9; 96 MiB of bytes 110 -> 71.  Not in launches of up
+    // to 24 MiB of wider elements, which would have it all to write back at their end (two bytes, 8 MiB 5.0 against 5.7 us,
+    // 12 MiB 8.9 against 11.8; 24 MiB even; bytes, 8 MiB 6.6 against 5.8), and not of eight bytes, whose rows of 512 bytes
+    // have few such bursts (96 MiB across chunks 54.6 against 57.1).
+    const bool large = ES == 1 || (ES < 8 && uint64_t(gridDim.x) * (T * T * ES) > (24u << 20));
+    const bool cached = large && ((uint32_t(reinterpret_cast<uintptr_t>(user)) | uint32_t(user_pitch)) & 15u) != 0;
 #pragma unroll
     for (uint32_t k = 0; k < T * NB / kThreads; ++k) {
         const uint32_t id = threadIdx.x + k * kThreads, row = id / NB, slot = id & (NB - 1);
@@ -1328,8 +1342,9 @@ __device__ __forceinline__ Sums2 transpose_tile_vectors(uint8_t *user, uint64_t 
         if (!live) continue;
         if constexpr (UNPACK) {
             uint8_t *to = user + r * user_pitch + slot * 16;
-            if (FULL || n == V) store16_any<true>(to, v);
-            else store_elems<E>(to, v, n);
+            if (!(FULL || n == V)) store_elems<E>(to, v, n);
+            else if (cached) store16_cached(to, v);
+            else store16_any<true>(to, v);
         } else if constexpr (!Rows::kSpan) {
             uint8_t *to = rows.at(r, slot * 16);
             if (FULL || n == V) store_packed16<NTP>(reinterpret_cast<u32x4 *>(to), v);
