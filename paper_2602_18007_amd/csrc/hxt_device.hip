@@ -225,16 +225,17 @@ void launch_generic(const hxt_plan_t &pl, uint32_t first, uint32_t count, uint32
     const Tile *tiles = pl.d_tiles + first;
     const uint32_t *ct = pl.d_chunk_tiles;
     const TensorDev *td = pl.d_tensors;
-    auto go = [&]<bool NTP>() {
+    auto go = [&]<bool NTP, bool THROUGH>() {
         switch (esize) {
-        case 1: k_generic<uint8_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
-        case 2: k_generic<uint16_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
-        case 4: k_generic<uint32_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
-        default: k_generic<uint64_t, UNPACK, CHECK, NTP><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
+        case 1: k_generic<uint8_t, UNPACK, CHECK, NTP, THROUGH><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
+        case 2: k_generic<uint16_t, UNPACK, CHECK, NTP, THROUGH><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
+        case 4: k_generic<uint32_t, UNPACK, CHECK, NTP, THROUGH><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
+        default: k_generic<uint64_t, UNPACK, CHECK, NTP, false><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
         }
     };
-    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
-    else go.template operator()<false>();
+    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true, false>();
+    else if (!UNPACK && elements_through(esize, launch_bytes(pl.p))) go.template operator()<false, !UNPACK>();
+    else go.template operator()<false, false>();
 }
 
 // The accumulator slots of an operation are shared by all calls of that operation on this

@@ -99,11 +99,13 @@ __device__ __forceinline__ void store_packed16(u32x4 *p, u32x4 v)
     else __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u32x4 *)p, v, "agent");
 }
 
-template <bool NT, typename E>
+// THROUGH = false: element by element, where writing through does not pay, and left to the L2.
+template <bool NT, bool THROUGH = true, typename E>
 __device__ __forceinline__ void store_packed_elem(E *p, E v)
 {
     if constexpr (NT) __builtin_nontemporal_store(v, p);
-    else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else if constexpr (THROUGH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
 }
 
 // 16 bytes at any address: the hardware takes misaligned vector accesses, and 64 lanes of them next to each other
@@ -951,7 +953,9 @@ template <> struct PieceOf<1> { using type = uint8_t; };
 // (the piece number is clamped into the tile): guarded, the compiler waits for each load before it
 // goes on to the next guard, and 16 loads one after the other cost 1.8-2.4 times the time.  With pieces
 // of 4 or 8 bytes the guarded loads are issued without such waits, interleaved with the address
-// arithmetic, and that order measures 10 % faster than eight loads in one burst.
+// arithmetic, and that order measures 10 % faster than eight loads in one burst.  Pieces of 1 or 2 bytes, 64 or 128
+// bytes per instruction, are not written through (rows of 101 elements, pack of 32 MiB, written through against left to
+// the L2: bytes 36.6 and 32.2 us, two bytes 24.1 and 22.9, but four bytes 14.7 and 15.5).
 template <bool UNPACK, int CHECK, bool NTP, int G, bool TWO_D>
 __device__ __forceinline__ Sums2 rows_split_tile(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
@@ -1022,7 +1026,7 @@ __device__ __forceinline__ Sums2 rows_split_tile(const Tile &t, const TensorDev 
             const uint32_t i = i0 + u * kThreads;
             if (i < npiece) {
                 if constexpr (UNPACK) __builtin_nontemporal_store(r[u], user_piece(i));
-                else store_packed_elem<NTP>(pieces + i, r[u]);
+                else store_packed_elem<NTP, (G >= 4)>(pieces + i, r[u]);
                 count_elem<CHECK>(acc, r[u], t.a + i * G);
             }
         }
@@ -1601,7 +1605,7 @@ __global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restr
 // a wave's access is contiguous on the packed side and as dense on the tensor side as the view
 // allows.  The loads of a round are unconditional (the index is clamped into the tile), so that
 // all of them are issued before the first is waited for; only the stores are guarded.
-template <typename E, bool UNPACK, int CHECK, bool NTP, int ND>
+template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH, int ND>
 __device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p, uint64_t in_chunk)
 {
     constexpr int D = ND ? ND : HXT_MAX_DIMS;
@@ -1657,7 +1661,7 @@ __device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, 
             const uint32_t el = e1 + u * kThreads;
             if (el < nel) {
                 if constexpr (UNPACK) store_elem<true>(locate(el), val[u]);
-                else store_packed_elem<NTP>(p + el, val[u]);
+                else store_packed_elem<NTP, THROUGH>(p + el, val[u]);
                 count_elem<CHECK>(acc, val[u], in_chunk + uint64_t(el) * sizeof(E));
             }
         }
@@ -1667,7 +1671,7 @@ __device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, 
 
 // The same for tensors with a dim beyond the reach of the multiply-shift division: every element's
 // index is divided out in 64 bits.
-template <typename E, bool UNPACK, int CHECK, bool NTP>
+template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH>
 __device__ __noinline__ Sums2 generic_span_wide(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p, uint64_t in_chunk)
 {
     const int nd = td.ndim;
@@ -1686,31 +1690,31 @@ __device__ __noinline__ Sums2 generic_span_wide(const TensorDev &td, uint64_t e0
             store_elem<true>(at, v);
         } else {
             v = load_elem<true>(at);
-            store_packed_elem<NTP>(p + el, v);
+            store_packed_elem<NTP, THROUGH>(p + el, v);
         }
         count_elem<CHECK>(acc, v, in_chunk + uint64_t(el) * sizeof(E));
     }
     return acc;
 }
 
-template <typename E, bool UNPACK, int CHECK, bool NTP>
+template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH>
 __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *packed)
 {
     E *p = reinterpret_cast<E *>(packed + t.packed_off);
     const uint32_t nel = t.n0 / sizeof(E);
     const uint64_t e0 = t.src_off / sizeof(E);
     if (nel == 0) return Sums2{0, 0};
-    if (!td.all_div) return generic_span_wide<E, UNPACK, CHECK, NTP>(td, e0, nel, user, p, t.a);
+    if (!td.all_div) return generic_span_wide<E, UNPACK, CHECK, NTP, THROUGH>(td, e0, nel, user, p, t.a);
     switch (td.ndim) {
-    case 1: return generic_span<E, UNPACK, CHECK, NTP, 1>(td, e0, nel, user, p, t.a);
-    case 2: return generic_span<E, UNPACK, CHECK, NTP, 2>(td, e0, nel, user, p, t.a);
-    case 3: return generic_span<E, UNPACK, CHECK, NTP, 3>(td, e0, nel, user, p, t.a);
-    case 4: return generic_span<E, UNPACK, CHECK, NTP, 4>(td, e0, nel, user, p, t.a);
-    default: return generic_span<E, UNPACK, CHECK, NTP, 0>(td, e0, nel, user, p, t.a);
+    case 1: return generic_span<E, UNPACK, CHECK, NTP, THROUGH, 1>(td, e0, nel, user, p, t.a);
+    case 2: return generic_span<E, UNPACK, CHECK, NTP, THROUGH, 2>(td, e0, nel, user, p, t.a);
+    case 3: return generic_span<E, UNPACK, CHECK, NTP, THROUGH, 3>(td, e0, nel, user, p, t.a);
+    case 4: return generic_span<E, UNPACK, CHECK, NTP, THROUGH, 4>(td, e0, nel, user, p, t.a);
+    default: return generic_span<E, UNPACK, CHECK, NTP, THROUGH, 0>(td, e0, nel, user, p, t.a);
     }
 }
 
-template <typename E, bool UNPACK, int CHECK, bool NTP>
+template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH>
 __global__ __launch_bounds__(kThreads) void k_generic(const Tile *__restrict__ tiles,
                                                       const uint32_t *__restrict__ chunk_tiles,
                                                       const TensorDev *__restrict__ tensors, uint32_t tensor_base,
@@ -1718,7 +1722,7 @@ __global__ __launch_bounds__(kThreads) void k_generic(const Tile *__restrict__ t
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : generic_any<E, UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : generic_any<E, UNPACK, CHECK, NTP, THROUGH>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -1784,7 +1788,7 @@ __global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ t
     case K_TRANSPOSE:
         acc = by_size([&]<typename E>() { return transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, base, packed, ck, lds_raw); });
         break;
-    default: acc = by_size([&]<typename E>() { return generic_any<E, UNPACK, CHECK, NTP>(t, td, base, packed); }); break;
+    default: acc = by_size([&]<typename E>() { return generic_any<E, UNPACK, CHECK, NTP, false>(t, td, base, packed); }); break;
     }
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }

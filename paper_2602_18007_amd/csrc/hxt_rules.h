@@ -37,6 +37,18 @@ inline bool packed_nontemporal(int hint, uint64_t bytes, bool load)
 
 inline bool pass_nontemporal(int hint, uint64_t bytes) { return hint >= 0 ? hint != 0 : bytes > kCacheablePackedPasses; }
 
+// Packed elements of the per-element kernel: written through in messages of more than 12 MiB (of bytes: up to 64); smaller
+// ones find them in the L2 when they are unpacked here, and those of 8 bytes are left there always.  Every other column,
+// pack + unpack, through against not: bf16 4 MiB 17.0 and 14.3 us, 8 MiB 20.9 and 19.2, 16 MiB 32.0 and 34.2, 32 MiB 56.3
+// and 59.8; f32 8 MiB 18.2 and 16.6, 32 MiB 53.0 and 54.8; bytes 4 MiB 24.3 and 19.9, 32 MiB 74.2 and 76.2, 96 MiB just
+// written 215 and 207; f64 16 MiB 30.3 and 29.0.
+constexpr uint64_t kElementsThrough = uint64_t(12) << 20, kBytesThrough = uint64_t(64) << 20;
+
+inline bool elements_through(int esize, uint64_t bytes)
+{
+    return esize < 8 && bytes > kElementsThrough && (esize > 1 || bytes <= kBytesThrough);
+}
+
 // Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack +
 // unpack, launches of their own against one launch: bundles of four kinds 0.8 MB 38.7 -> 17.9 us, 7 MB 40.0 -> 18.5 us,
 // with tags 48.5 -> 22.9 us, 17 MB with tags 64.0 -> 40.8 us, 34 MB 46.6 -> 40.9 us.  With two launches

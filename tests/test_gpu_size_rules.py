@@ -20,6 +20,43 @@ def test_cache_hints_either_side_of_their_limits(nbytes):
     round_trip_check(case, make_storages(case, 5), nthreads=NT)
 
 
+@pytest.mark.parametrize("nbytes", [12 * MiB, 12 * MiB + 4096, 64 * MiB, 64 * MiB + 4096])
+@pytest.mark.parametrize("esize", [1, 2, 4, 8])
+def test_elements_written_through_either_side_of_their_limits(esize, nbytes):
+    """Every other element of rows: packed elements are written through above 12 MiB, single bytes up to 64 MiB."""
+    cols = 4096 // esize
+    case = Case("columns_%d_%d" % (esize, nbytes), (((nbytes // 4096, cols), (2 * cols, 2), esize),), 3, MiB)
+    say("case", case.name)
+    round_trip_check(case, make_storages(case, 5), nthreads=NT)
+
+
+@pytest.mark.parametrize("esize", [1, 2, 4, 8])
+@pytest.mark.parametrize("nbytes", [8 * MiB, 25 * MiB])
+def test_transposed_tensors_at_any_base(esize, nbytes):
+    """Receiving transposes store rows that do not start on 16 bytes cacheable, by size of element and launch: bases one
+    element off, pitches of whole vectors and not, against the oracle."""
+    rows = 1021
+    cols = nbytes // (rows * esize)
+    for pitch in (rows + 3, rows + 6):                   # 1024 elements, and an odd number of elements to a vector
+        base, ends = 1, (cols - 1) * pitch + rows
+        m = ho.Message([ho.TensorSpec((rows, cols), (1, pitch), esize)])
+        raw = np.random.default_rng(3).integers(0, 256, size=ends * esize, dtype=np.uint8)
+        p = hxt.hxt_plan_multi([((rows, cols), (1, pitch), esize)], 4, MiB)
+        assert p.tensor_kind(0).startswith("transpose")
+        at = torch.empty(ends * esize + 64, dtype=torch.uint8, device=DEV)[base * esize:]
+        at[:raw.size] = torch.from_numpy(raw).to(DEV)
+        want = ho.pack(m, [raw], MiB, 4, fill=0xA5, nthreads=NT)
+        packed = torch.full((want.size,), 0xA5, dtype=torch.uint8, device=DEV)
+        say("pitch", pitch)
+        hxt.hxt_pack(p, [at], packed)
+        assert np.array_equal(packed.cpu().numpy(), want)
+        dst_o = [np.full(raw.size, 0x3C, np.uint8)]
+        ho.unpack(m, want, MiB, 4, dst_o, nthreads=NT)
+        at.fill_(0x3C)
+        hxt.hxt_unpack(p, packed, [at])
+        assert np.array_equal(at.cpu().numpy()[:raw.size], dst_o[0])
+
+
 @pytest.mark.parametrize("chunk", [1024, 1 << 16, 1 << 20], ids=lambda b: "chunks_of_%d" % b)
 @pytest.mark.parametrize("esize", [1, 2, 4, 8])
 def test_transpose_tiles_at_their_edges(esize, chunk):
