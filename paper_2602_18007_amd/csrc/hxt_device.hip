@@ -219,6 +219,29 @@ void launch_rows(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_
 }
 
 template <bool UNPACK, int CHECK>
+void launch_rows_split(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck,
+                       hipStream_t st)
+{
+    uint32_t wide = 0;                                       // some tensor is accessed in pieces of 4 bytes or more
+    for (uint32_t i = 0; i < g.n_tensors; ++i)
+        if (pl.p.tensors[g.tensor_base + i].kind == K_ROWS_SPLIT)
+            wide |= ((uint32_t(reinterpret_cast<uintptr_t>(b.p[i])) | pl.p.tdev[g.tensor_base + i].low_or) & 3u) == 0;
+    auto go = [&]<bool NTP, bool NARROW>() {
+        k_rows_split<UNPACK, CHECK, NTP, NARROW><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
+                                                                               g.tensor_base, b, packed, ck);
+    };
+    constexpr bool kNarrow = !UNPACK && CHECK != CHECK_TAGS;
+    const bool ntp = packed_nontemporal(pl, UNPACK);
+    if (kNarrow && !wide) {
+        if (ntp) go.template operator()<true, kNarrow>();
+        else go.template operator()<false, kNarrow>();
+    } else {
+        if (ntp) go.template operator()<true, false>();
+        else go.template operator()<false, false>();
+    }
+}
+
+template <bool UNPACK, int CHECK>
 void launch_generic(const hxt_plan_t &pl, uint32_t first, uint32_t count, uint32_t tensor_base, int esize,
                     const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck, hipStream_t st)
 {
@@ -381,12 +404,7 @@ int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckAr
         } else if (g.kernel == K_ROWS) {
             launch_rows<UNPACK, CHECK>(pl, g, b, packed, ck, st);
         } else if (g.kernel == K_ROWS_SPLIT) {
-            if (ntp)
-                k_rows_split<UNPACK, CHECK, true><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                               g.tensor_base, b, packed, ck);
-            else
-                k_rows_split<UNPACK, CHECK, false><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                                g.tensor_base, b, packed, ck);
+            launch_rows_split<UNPACK, CHECK>(pl, g, b, packed, ck, st);
         } else {
             // The transpose and per-element kernels are instantiated per element size: issue one
             // launch per run of tiles whose tensors share it (host table, same order as on the device).

@@ -1034,7 +1034,8 @@ __device__ __forceinline__ Sums2 rows_split_tile(const Tile &t, const TensorDev 
     return acc;
 }
 
-template <bool UNPACK, int CHECK, bool NTP>
+// NARROW: pieces of 1 or 2 bytes only.
+template <bool UNPACK, int CHECK, bool NTP, bool NARROW>
 __device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
     // widest piece that is naturally aligned everywhere: low bits of the base address, the run length and the pitches
@@ -1043,23 +1044,28 @@ __device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &
         return td.ndim == 2 ? rows_split_tile<UNPACK, CHECK, NTP, G, true>(t, td, user, pk)
                             : rows_split_tile<UNPACK, CHECK, NTP, G, false>(t, td, user, pk);
     };
-    if ((low & 7u) == 0) return run.template operator()<8>();
-    if ((low & 3u) == 0) return run.template operator()<4>();
+    if constexpr (!NARROW) {
+        if ((low & 7u) == 0) return run.template operator()<8>();
+        if ((low & 3u) == 0) return run.template operator()<4>();
+    }
     if ((low & 1u) == 0) return run.template operator()<2>();
     return run.template operator()<1>();
 }
 
 // (Receiving with plain sums or none, 7 waves per SIMD are asked for: the compiler takes 75 registers otherwise, 6 waves:
-// [327680, 100] bf16 at a pitch of 128, pack + unpack, 58.2 -> 56.9 us.)
-template <bool UNPACK, int CHECK, bool NTP>
-__global__ __launch_bounds__(kThreads, UNPACK && CHECK != CHECK_TAGS ? 7 : 1) void k_rows_split(const Tile *__restrict__ tiles,
+// [327680, 100] bf16 at a pitch of 128, pack + unpack, 58.2 -> 56.9 us.  Sends of runs that all go in pieces of 1 or 2
+// bytes have a kernel of their own with 8 waves: they live on loads in flight, and the registers of the wider pieces leave
+// 6.  Rows of 101 elements, pack with sums, 32 MiB: bytes 32.5 -> 27.3 us, two bytes 22.9 -> 17.4; four bytes lose by such
+// a bound, 13.6 -> 15.2.)
+template <bool UNPACK, int CHECK, bool NTP, bool NARROW>
+__global__ __launch_bounds__(kThreads, NARROW ? 8 : UNPACK && CHECK != CHECK_TAGS ? 7 : 1) void k_rows_split(const Tile *__restrict__ tiles,
                                                          const uint32_t *__restrict__ chunk_tiles,
                                                          const TensorDev *__restrict__ tensors, uint32_t tensor_base,
                                                          BasePtrs bases, uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP, NARROW>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -1784,7 +1790,7 @@ __global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ t
         }
         break;
     case K_ROWS: acc = rows_tile<UNPACK, CHECK, NTU, NTP>(t, td, base, pk); break;
-    case K_ROWS_SPLIT: acc = rows_split_any<UNPACK, CHECK, NTP>(t, td, base, pk); break;
+    case K_ROWS_SPLIT: acc = rows_split_any<UNPACK, CHECK, NTP, false>(t, td, base, pk); break;
     case K_TRANSPOSE:
         acc = by_size([&]<typename E>() { return transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, base, packed, ck, lds_raw); });
         break;
