@@ -49,13 +49,16 @@ inline bool elements_through(int esize, uint64_t bytes)
     return esize < 8 && bytes > kElementsThrough && (esize > 1 || bytes <= kBytesThrough);
 }
 
-// Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack +
-// unpack, launches of their own against one launch: bundles of four kinds 0.8 MB 38.7 -> 17.9 us, 7 MB 40.0 -> 18.5 us,
-// with tags 48.5 -> 22.9 us, 17 MB with tags 64.0 -> 40.8 us, 34 MB 46.6 -> 40.9 us.  With two launches
-// the gain is one launch each way, and k_message's residency (3 or 4 workgroups per CU) costs more than that on large
-// messages (measured on strided tensors with their pads in a launch of their own, before these rode along): 4.5 MB 23.2 -> 20.0 us, 7.5 MB 26.8 -> 23.6 us, but 17.5 MB 32.4 -> 33.6, 60 MB 102 -> 110 us.
+// Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack + unpack
+// with sums, launches of their own against one:
+//   three launches or more: six tensors of five kinds 4 MiB 33 -> 14 us, 16 MiB 46 -> 25, 48 MiB 64 -> 50, 64 MiB 75 -> 64,
+//     80 MiB 84 -> 76; three transposes of different element sizes 4 MiB 30 -> 16, 48 MiB 53 -> 48, 64 MiB 77 -> 77, but
+//     80 MiB 90 -> 94.
+//   two, where the gain is one launch each way and k_message's residency (3 or 4 workgroups per CU) soon costs more: padded
+//     rows and a mask 4 MiB 16 -> 11, 12 MiB 23 -> 17; two transposes 12 MiB 27 -> 19; every other column and a mask 12 MiB
+//     34 -> 28 (with tags 39 -> 34), but its pack alone 16 MiB with tags 20.4 -> 22.5 and 24 MiB 21.4 -> 24.7.
 constexpr uint64_t kOneLaunchLimit = uint64_t(64) << 20;
-constexpr uint64_t kOneLaunchForTwoLimit = uint64_t(8) << 20;
+constexpr uint64_t kOneLaunchForTwoLimit = uint64_t(12) << 20;
 
 inline bool one_launch(const Plan &p)
 {

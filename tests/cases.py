@@ -94,6 +94,22 @@ def case_by_name(name: str) -> Case:
     raise KeyError(name)
 
 
+def two_launch_case(stream_bytes: int) -> Case:
+    """A message of padded rows and a byte mask, without pads between them: two launches of a kind's own."""
+    rows = stream_bytes * 4 // 5 // 51200 * 256              # 200 bytes each: whole multiples of 256
+    return Case("two_launches_%d" % stream_bytes, (((rows, 100), (128, 1), 2), contig((stream_bytes - 200 * rows,), 1)), 4, 1 << 20)
+
+
+def three_launch_case(stream_bytes: int) -> Case:
+    """The same with a transposed matrix of 4-byte elements."""
+    rows = stream_bytes * 4 // 5 // 51200 * 256
+    return Case("three_launches_%d" % stream_bytes, (((rows, 100), (128, 1), 2), contig((stream_bytes - 200 * rows - 65536,), 1),
+                                                     ((128, 128), (1, 128), 4)), 4, 1 << 20)
+
+
+ONE_LAUNCH_LIMITS = {two_launch_case: 12 << 20, three_launch_case: 64 << 20}     # of messages of two launches, of more
+
+
 def make_storages(case: Case, seed: int) -> List[np.ndarray]:
     rng = np.random.default_rng(seed)
     return [rng.integers(0, 256, size=storage_bytes(*t), dtype=np.uint8) for t in case.tensors]

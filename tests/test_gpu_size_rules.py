@@ -5,7 +5,7 @@ import torch
 
 from oracle import hxt_oracle as ho
 from paper_2602_18007_amd import hxt
-from tests.cases import SMALL_CASES, Case, contig, make_storages
+from tests.cases import ONE_LAUNCH_LIMITS, SMALL_CASES, Case, contig, make_storages
 from tests.test_gpu_parity import NT, DEV, oracle_msg, round_trip_check, say, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -134,10 +134,21 @@ def test_tags_of_transposes_at_their_edges(esize, chunk, hint):
 
 @pytest.mark.parametrize("rows", [2054, 2055, 2056, 16430, 16440])
 def test_one_launch_either_side_of_its_limits(rows):
-    """Padded rows of 4082 bytes with pads (limit 8 MiB: 2055 rows), and the same with a mask and a transposed matrix (limit 64 MiB: 16432 rows)."""
+    """Padded rows of 4082 bytes with pads, which ride in the launch of the rows at any size, and the same with a mask and a
+    transposed matrix (three launches: one up to 64 MiB, 16432 rows)."""
     padded = ((rows, 2041), (2048, 1), 2)
     for tensors in ((padded,), (padded, contig((rows,), 1), ((64, 40), (1, 64), 4))):
         case = Case("limit_%d_%d" % (rows, len(tensors)), tensors, 4, MiB)
         say("case", case.name)
         round_trip_check(case, make_storages(case, 5), nthreads=NT)
         tagged_round_trip(case, -1)
+
+
+@pytest.mark.parametrize("over", [0, 256])
+@pytest.mark.parametrize("make", list(ONE_LAUNCH_LIMITS), ids=["two_launches", "three_launches"])
+def test_messages_of_several_kinds_either_side_of_their_limit(make, over):
+    """The planner's tests check that these take one launch up to the limit and one per kind beyond it."""
+    case = make(ONE_LAUNCH_LIMITS[make] + over)
+    say("case", case.name)
+    round_trip_check(case, make_storages(case, 5), nthreads=NT)
+    tagged_round_trip(case, -1)

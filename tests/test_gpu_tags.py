@@ -217,10 +217,10 @@ BATCH_MESSAGES = [
 @pytest.mark.parametrize("offset", [0, 4])
 def test_batched_fused_tag_calls_match_the_oracle(offset):
     """hxt_pack_seal_batch / hxt_unpack_verify_batch over a mixed set of messages (single tensors that share
-    launches, a bucket of contiguous tensors served by the table-driven fused kernel, a strided message that
-    takes two passes, an empty one): tags, packed bytes, destinations and masks against the oracle, with one
-    message's sequence number stale and one message damaged on the host.  offset 4: bases that are only
-    element aligned (every message falls back to its own call)."""
+    launches, a bucket of contiguous tensors served by the table-driven fused kernel, a strided message, an
+    empty one): tags, packed bytes, destinations and masks against the oracle, with one message's sequence number
+    stale and one message damaged on the host.  offset 4: bases that are only element aligned (the same kernels
+    and launches)."""
     cases = BATCH_MESSAGES
     n = len(cases)
     ms = [ho.Message([ho.TensorSpec(tuple(s), tuple(st), e) for (s, st, e) in c.tensors]) for c in cases]

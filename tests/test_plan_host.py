@@ -14,7 +14,7 @@ from oracle import hxt_oracle as ho
 from paper_2602_18007_amd import build as hxt_build
 from paper_2602_18007_amd import hxt
 from paper_2602_18007_amd import workloads as wl
-from tests.cases import SMALL_CASES, Case, contig, make_storages, random_view, storage_bytes
+from tests.cases import ONE_LAUNCH_LIMITS, SMALL_CASES, Case, contig, make_storages, random_view, storage_bytes
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -331,6 +331,15 @@ def test_launch_rules_go_by_the_bytes_a_message_moves(interp):
             assert launch_rules(interp, Case("contig", (contig((nbytes,), 1),), 4, chunk)) == (1, False, hints), (chunk, nbytes)
         two = (((1024, 500), (512, 1), 2), contig((1024,), 1))
         assert launch_rules(interp, Case("two", two, 4, chunk)) == (2, True, 0), chunk
+
+
+@pytest.mark.parametrize("make,launches", zip(ONE_LAUNCH_LIMITS, (2, 3)), ids=["two", "three"])
+def test_messages_of_several_kinds_go_out_in_one_launch_up_to_their_limit(interp, make, launches):
+    limit = ONE_LAUNCH_LIMITS[make]
+    assert launch_rules(interp, make(limit)) == (launches, True, 0)
+    assert launch_rules(interp, make(limit + 256))[:2] == (launches, False)
+    # pads behind a single strided tensor ride in its own launch: nothing to put together
+    assert launch_rules(interp, Case("pads_ride", (((2055, 2041), (2048, 1), 2),), 4, 1 << 20))[:2] == (1, False)
 
 
 def run_interp(L, case, storages, packed, direction, tile_bytes):
