@@ -156,18 +156,33 @@ const Tuning &tuning()
     return t;
 }
 
-inline bool user_nontemporal() { return tuning().nt_user != 0; }
-
 using hxt::packed_nontemporal;
 using hxt::with_hints;
 
 inline bool packed_nontemporal(const hxt_plan_t &pl, bool load) { return packed_nontemporal(pl.nt_packed, launch_bytes(pl.p), load); }
 
-// The hints of one plan's launch.
-template <bool UNPACK, typename F>
-void with_hints(const hxt_plan_t &pl, F &&f)
+inline uintptr_t low_bits(const void *p) { return reinterpret_cast<uintptr_t>(p) & 255u; }
+
+inline uintptr_t low_bits(const BasePtrs &b, uint32_t n)
 {
-    with_hints(user_nontemporal(), packed_nontemporal(pl, UNPACK), f);
+    uintptr_t low = 0;
+    for (uint32_t i = 0; i < n; ++i) low |= low_bits(b.p[i]);
+    return low;
+}
+
+template <class Args>
+uintptr_t launch_low_bits(const Args &a)                 // of a uniform launch's messages
+{
+    uintptr_t low = 0;
+    for (uint32_t i = 0; i < a.n; ++i) low |= low_bits(a.it[i].user);
+    return low;
+}
+
+// The hints of one plan's launch; low: the low bits of its tensors' bases.
+template <bool UNPACK, typename F>
+void with_hints(const hxt_plan_t &pl, uintptr_t low, F &&f)
+{
+    with_hints(user_nontemporal(tuning().nt_user, !UNPACK, low, launch_bytes(pl.p)), packed_nontemporal(pl, UNPACK), f);
 }
 
 // The streaming copies are launched with 32 KiB of (unused) dynamic LDS per workgroup, which caps residency at 5
@@ -191,14 +206,14 @@ void launch_uniform(const UniformArgs &a, uint32_t tiles, uint64_t bytes, int hi
 {
     const size_t lds = residency_cap_lds();
     // (a mixed launch has one hint for both directions: as for loads, which it wants cacheable while they are small)
-    with_hints(user_nontemporal(), packed_nontemporal(hint, bytes, DIR != DIR_PACK), [&]<bool NTU, bool NTP>() { k_uniform<DIR, CSUM, NTU, NTP><<<tiles, kThreads, lds, st>>>(a); });
+    with_hints(user_nontemporal(tuning().nt_user, DIR == DIR_PACK, launch_low_bits(a), bytes), packed_nontemporal(hint, bytes, DIR != DIR_PACK), [&]<bool NTU, bool NTP>() { k_uniform<DIR, CSUM, NTU, NTP><<<tiles, kThreads, lds, st>>>(a); });
 }
 
 template <bool UNPACK, int CHECK>
 void launch_contig(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck,
                    hipStream_t st)
 {
-    with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
+    with_hints<UNPACK>(pl, low_bits(b, g.n_tensors), [&]<bool NTU, bool NTP>() {
         if constexpr (CHECK == CHECK_TAGS)
             k_contig_tag<UNPACK, UNPACK ? SUM2_VERIFY : SUM2_SEAL, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(
                 pl.d_tiles + g.first, pl.d_chunk_tiles, b, packed, ck.g, ck.out, ck.cx.acc, ck.cx.stride, ck.cx.fan, ck.work);
@@ -212,7 +227,7 @@ template <bool UNPACK, int CHECK>
 void launch_rows(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck,
                  hipStream_t st)
 {
-    with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
+    with_hints<UNPACK>(pl, low_bits(b, g.n_tensors), [&]<bool NTU, bool NTP>() {
         k_rows<UNPACK, CHECK, NTU, NTP><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
                                                                      g.tensor_base, b, packed, ck);
     });
@@ -477,7 +492,7 @@ int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t 
         // `unpack` carries the element kind here: 1 = f32, 0 = bf16
         a.it[0] = UniformItem{p.geom, static_cast<uint8_t *>(ptrs[p.uniform_tensor]), packed, cx, 0,
                               tp.dtype == HXT_F32 ? 1u : 0u};
-        with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
+        with_hints<true>(pl, 0, [&]<bool NTU, bool NTP>() {
             k_uniform_accumulate<CSUM, NTU, NTP><<<p.geom.ntiles, kThreads, 0, st>>>(a);
         });
         HXT_HIP(hipGetLastError());
@@ -492,7 +507,7 @@ int run_accumulate(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, uint64_t 
             b.p[i] = static_cast<uint8_t *>(ptrs[g.tensor_base + i]);
             kinds.f32[i] = p.tensors[g.tensor_base + i].dtype == HXT_F32;
         }
-        with_hints<true>(pl, [&]<bool NTU, bool NTP>() {
+        with_hints<true>(pl, 0, [&]<bool NTU, bool NTP>() {
             k_contig_accumulate<CSUM, NTU, NTP><<<g.count, kThreads, residency_cap_lds(), st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles,
                                                                               b, kinds, packed, cx);
         });
@@ -776,7 +791,7 @@ int run_copy_tag(const hxt_plan_t *plan, void *const *ptrs, void *packed, void *
         std::memset(&a, 0, sizeof a);
         a.n = 1;
         a.it[0] = UniformTagItem{p.geom, base, pk, out, cx.acc, cx.stride, cx.fan, w, 0};
-        with_hints<UNPACK>(pl, [&]<bool NTU, bool NTP>() {
+        with_hints<UNPACK>(pl, launch_low_bits(a), [&]<bool NTU, bool NTP>() {
             k_uniform_tag<UNPACK, MODE, NTU, NTP><<<p.geom.ntiles, kThreads, 0, st>>>(a);
         });
         HXT_HIP(hipGetLastError());
@@ -850,7 +865,7 @@ int run_tag_batch(int n, const hxt_plan_t *const *plans, void *const *const *ten
             bytes += launch_bytes(pj.p);
             ++j;
         }
-        with_hints(user_nontemporal(), packed_nontemporal(plans[i]->nt_packed, bytes, UNPACK), [&]<bool NTU, bool NTP>() { k_uniform_tag<UNPACK, MODE, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a); });
+        with_hints(user_nontemporal(tuning().nt_user, !UNPACK, launch_low_bits(a), bytes), packed_nontemporal(plans[i]->nt_packed, bytes, UNPACK), [&]<bool NTU, bool NTP>() { k_uniform_tag<UNPACK, MODE, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a); });
         HXT_HIP(hipGetLastError());
         i = j;
     }
@@ -1289,7 +1304,7 @@ int hxt_unpack_accumulate_batch(int n, const hxt_plan_t *const *plans, const voi
             bytes += launch_bytes(pj.p);
             ++j;
         }
-        with_hints(user_nontemporal(), packed_nontemporal(plans[i]->nt_packed, bytes, true), [&]<bool NTU, bool NTP>() {
+        with_hints(user_nontemporal(tuning().nt_user, false, 0, bytes), packed_nontemporal(plans[i]->nt_packed, bytes, true), [&]<bool NTU, bool NTP>() {
             if (sm) k_uniform_accumulate<true, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a);
             else k_uniform_accumulate<false, NTU, NTP><<<uint32_t(tiles), kThreads, 0, st>>>(a);
         });

@@ -23,6 +23,10 @@ namespace hxt {
 //     where the very same tensor is sent again (32 MiB over and over, pack + unpack: 24.8 us non-temporal, 22.6 cacheable;
 //     three in turn 26.4 and 24.7) and costs where it has just been written or has left the cache (through two packed
 //     buffers, 8 MiB 10.4 against 11.5 us, 16 MiB 16.6 against 17.1, a transposed 32 MiB matrix 26.8 against 27.9).
+//   But loads from tensors at bases that are not multiples of 16 bytes are cacheable up to 64 MiB: neighbouring vectors
+//     share bursts there (base one element off, tensor just written, pack + unpack: 32 MiB 36.1 us non-temporal, 32.7
+//     cacheable; 64 MiB 63.6 and 56.6; but pack of a 128 MiB tensor that is not in the cache 43.5 and 49.4).
+constexpr uint64_t kCacheableMisalignedLoads = uint64_t(64) << 20;
 constexpr uint64_t kCacheablePackedLoads = uint64_t(128) << 20, kCacheablePackedPasses = uint64_t(64) << 20;
 constexpr uint64_t kWrittenThroughLimit = uint64_t(1) << 30;
 
@@ -33,6 +37,12 @@ inline uint64_t launch_bytes(const Plan &p) { return p.L; }
 inline bool packed_nontemporal(int hint, uint64_t bytes, bool load)
 {
     return hint >= 0 ? hint != 0 : bytes > (load ? kCacheablePackedLoads : kWrittenThroughLimit);
+}
+
+// forced: HXT_NT_USER; send: the launch reads tensors; low: all their base addresses ORed.
+inline bool user_nontemporal(int forced, bool send, uintptr_t low, uint64_t bytes)
+{
+    return forced >= 0 ? forced != 0 : !(send && low % 16 != 0 && bytes <= kCacheableMisalignedLoads);
 }
 
 inline bool pass_nontemporal(int hint, uint64_t bytes) { return hint >= 0 ? hint != 0 : bytes > kCacheablePackedPasses; }

@@ -20,6 +20,42 @@ def test_cache_hints_either_side_of_their_limits(nbytes):
     round_trip_check(case, make_storages(case, 5), nthreads=NT)
 
 
+@pytest.mark.parametrize("nbytes", [64 * MiB, 64 * MiB + 256])
+@pytest.mark.parametrize("view", ["contig", "rows", "two_contig"])
+def test_sends_from_bases_off_by_an_element(view, nbytes):
+    """Loads from tensors that do not start on 16 bytes are cacheable up to 64 MiB, non-temporal above: plain sums and tags,
+    one tensor, rows and a message of two tensors of which one is aligned."""
+    n = nbytes // 2
+    if view == "rows":
+        tensors, off = [((n // 4096, 4096), (4104, 1), 2)] + ([((n % 4096,), (1,), 2)] if n % 4096 else []), [2, 0]
+    elif view == "two_contig":
+        tensors, off = [((n // 2,), (1,), 2), ((n - n // 2,), (1,), 2)], [0, 2]
+    else:
+        tensors, off = [((n,), (1,), 2)], [2]
+    case = Case(view, tuple(tensors), 4, MiB)
+    m, raws = oracle_msg(case), make_storages(case, 5)
+    p = hxt.hxt_plan_multi(tensors, 4, MiB)
+    C = p.num_chunks
+    want = ho.pack(m, raws, MiB, 4, fill=0xA5, nthreads=NT)
+    src = []
+    for r, o in zip(raws, off):
+        t = torch.empty(r.size + 64, dtype=torch.uint8, device=DEV)[o:]
+        t[:r.size] = torch.from_numpy(r).to(DEV)
+        src.append(t)
+    say(view, nbytes)
+    for tagged in (False, True):
+        packed = torch.full((want.size,), 0xA5, dtype=torch.uint8, device=DEV)
+        if tagged:
+            tags = torch.zeros(64 * C, dtype=torch.uint8, device=DEV)
+            hxt.hxt_pack_seal(p, src, packed, 7, 1, tags)
+            assert np.array_equal(tags.cpu().numpy().reshape(C, 64), ho.seal(m, want, MiB, 4, 7, 1))
+        else:
+            sums = torch.zeros(C, dtype=torch.int64, device=DEV)
+            hxt.hxt_pack(p, src, packed, sums)
+            assert np.array_equal(sums.cpu().numpy().view(np.uint64), ho.checksum(m, want, MiB, 4))
+        assert np.array_equal(packed.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("nbytes", [12 * MiB, 12 * MiB + 4096, 64 * MiB, 64 * MiB + 4096])
 @pytest.mark.parametrize("esize", [1, 2, 4, 8])
 def test_elements_written_through_either_side_of_their_limits(esize, nbytes):
