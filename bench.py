@@ -614,6 +614,35 @@ def config_entries(torch, hxt, wl, a, link, headline_regions):
     return out
 
 
+# What the output line says of every further message; the rest of its record goes to stderr with the whole record.
+ENTRY_KEYS = ("workload", "path", "checks", "cache_state", "gbps", "ms_per_step", "us_per_micro_batch", "pct_hbm_peak",
+              "pct_host_link", "bound_pct", "cpu_oracle_gbps")
+USUAL_CHECKS = "fused send+receive checksums"           # not repeated for every message
+PROSE_KEYS = ("note", "region_is", "traffic_is", "issue", "timing", "cpu_oracle_sample")
+
+
+def short_line(out):
+    """The record without its prose and with the further messages' figures only: consumers keep the last 8000 characters of
+    what is printed, and the whole record is longer than that."""
+    def trim(v):
+        return {k: trim(x) for k, x in v.items() if k not in PROSE_KEYS} if isinstance(v, dict) else v
+
+    def entry(e):
+        e = {k: e[k].split(" (")[0] if isinstance(e[k], str) else e[k] for k in ENTRY_KEYS if k in e}
+        if e.get("checks") == USUAL_CHECKS:
+            del e["checks"]
+        if "cache_state" in e and not e["cache_state"].startswith("all-cold"):
+            e["cache_state"] = "packed cached"
+        return e
+
+    line = {k: trim(v) for k, v in out.items() if k not in ("configs", "paper_context")}
+    for region in list(line.get("regions", {}).values()) + [line.get("roofline_llc_assisted", {})]:
+        region.pop("cache_state", None)                 # the region's name says it
+    if "configs" in out:
+        line["configs"] = [entry(e) for e in out["configs"]]
+    return line
+
+
 def main():
     a = parse()
     if a.gpus != 1:
@@ -754,7 +783,8 @@ def main():
                     seen[name] = cpu_baseline(wc, budget_s=1.5, max_tensors=9 if big else None, one_core=False)
                 e["cpu_oracle_gbps"] = seen[name]["value"]
                 e["cpu_oracle_sample"] = seen[name]["sample"]
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stderr)
+    print(json.dumps(short_line(out)))
 
 
 if __name__ == "__main__":

@@ -31,6 +31,18 @@ def test_traffic_figure_is_readable_for_this_build():
     assert bench.traffic_from_profile("some other build") is None
 
 
+def test_the_line_stays_short_however_long_the_record():
+    sys.path.insert(0, ROOT)
+    import bench
+    entry = {"workload": "w" * 20, "path": "device_direct", "checks": "fused send+receive checksums", "cache_state": "all-cold (" + "x" * 60 + ")",
+             "gbps": 6149.51, "ms_per_step": 1.13498, "pct_hbm_peak": 76.87, "frac": 0.7716, "cpu_oracle_gbps": 6.282, "issue": "y" * 80,
+             "cpu_oracle_sample": "z" * 150, "kernel": "k", "timed_steps": 36}
+    out = {"value": 1.0, "config": {"workload": "w", "note": "n" * 500, "cache_state": "all-cold"}, "configs": [entry] * 25, "paper_context": "p" * 999}
+    line = bench.short_line(out)
+    assert len(json.dumps(line)) < 7500 and line["config"] == {"workload": "w", "cache_state": "all-cold"}
+    assert len(line["configs"]) == 25 and line["configs"][0]["cache_state"] == "all-cold" and line["configs"][0]["gbps"] == 6149.51
+
+
 def one_line(r):
     assert r.returncode == 0, r.stderr[-2000:]
     lines = [ln for ln in r.stdout.splitlines() if ln.startswith("{")]
@@ -73,7 +85,9 @@ def test_default_workload_line_has_the_contract_keys():
 
 @pytest.mark.gpu
 def test_default_run_lists_every_benchmark_message():
-    out = one_line(run_bench("--steps", "20", "--warmup", "5", timeout=900))
+    r = run_bench("--steps", "20", "--warmup", "5", timeout=900)
+    out = one_line(r)
+    assert len(r.stdout) < 7500                            # a consumer that keeps the last 8000 characters keeps the line
     check_contract(out, 20, 5)
     cb = out["cpu_baseline"]
     assert cb["kind"] == "oracle" and cb["cores"] >= 1 and cb["value"] > 0 and cb["sample"]
