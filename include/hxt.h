@@ -137,7 +137,8 @@ int hxt_plan_destroy(hxt_plan_t *plan); /* NULL is allowed */
  *   -1 (default) by size, so that a packed buffer that is re-read soon (by the wire, or by hxt_unpack
  *      on the same GPU) can be served from the 256 MB last-level cache: stores are written through to
  *      it while the message has <= 1 GiB, loads are cacheable up to 128 MiB; non-temporal above;
- *    0 always cacheable;  1 always non-temporal (every byte goes to and comes from HBM).
+ *    0 always cacheable (stores written through or left to the L2);
+ *    1 always non-temporal (every byte goes to and comes from HBM).
  *   The environment variable HXT_NT_PACKED (0/1), read when a plan is created, sets the initial value.
  * HXT_OPT_STAGE_D2H: how hxt_stage_d2h* and the CPU-forwarding path of hxt_exchange_stream move
  *   the packed buffer to pinned host memory.

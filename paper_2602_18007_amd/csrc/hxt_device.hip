@@ -1354,6 +1354,7 @@ int hxt_exchange_stream(const hxt_plan_t *plan, const hxt_exchange_t *x)
     if (!fwd) {
         const bool chains_ok = x->n_buffers % 2 == 0 && sp != su;
         bool fused_ok = !tagged && x->n_buffers >= 2 && p.uniform && !x->send_sums == !x->recv_sums;
+        // (the kernel takes any base; the mode is documented for 16-byte aligned messages and refuses others as it always has)
         for (int i = 0; fused_ok && i < x->n_messages; ++i)
             fused_ok = reinterpret_cast<uintptr_t>(x->src[i * T + p.uniform_tensor]) % 16 == 0 &&
                        reinterpret_cast<uintptr_t>(x->dst[i * T + p.uniform_tensor]) % 16 == 0;

@@ -11,7 +11,9 @@ namespace hxt {
 //   Packed side, stores: written through to the last-level cache, where the wire or hxt_unpack reads them
 //     (store_packed16).  Better than non-temporal stores up to 1 GiB (pack + unpack with sums: 128 MiB 81 against 92 us,
 //     288 MiB 171 against 197, 512 MiB 338 against 356); above, nothing of the buffer's start is left when it is read
-//     and non-temporal stores are as good or better (1.7 GB pack + accumulate 1407 against 1401 us).
+//     and non-temporal stores are as good or better (1.7 GB pack + accumulate 1407 against 1401 us).  Buffers of 8 to
+//     16 MiB that are unpacked right away on the same GPU would be faster left in the L2s (8 MiB 9.9 against 10.4 us, 16 MiB
+//     16.0 against 16.6), which no wire reads; after the kernel that writes the tensor even those are not (16.5 against 15.8).
 //   Packed side, loads: cacheable up to 128 MiB, where the buffer still is in the last-level cache when it is read
 //     (unpack of one of two buffers in turn, cacheable against non-temporal: 80 MiB 26.8 against 30.6 us, 96 MiB 31.1
 //     against 35.8, 128 MiB 41.0 against 46.5; accumulated 62.8 against 72.9; rows of 101 bf16 elements 81.9 against 102).
