@@ -269,8 +269,8 @@ __device__ __forceinline__ void chunk_commit(uint64_t acc, uint32_t chunk, uint3
 // packed, unpack: packed -> user) in 16-byte vectors, UNROLL independent loads in flight per
 // thread before the first store; a last partial vector goes byte by byte.  NTU / NTP mark
 // the user-side / packed-side accesses non-temporal.  The tensor may start at any address: with a base that is only
-// element aligned the same instructions cost 4 % (32 MiB, pack + unpack: 20.9 us aligned, 21.7 us one or two bytes
-// off; putting vectors together from narrower aligned accesses took 24.0).
+// element aligned the same instructions cost up to 8 % (32 MiB, pack + unpack, all buffers cold: 27.0 us aligned, 29.1 two
+// bytes off; putting vectors together from narrower aligned accesses took 31.0).
 template <bool UNPACK, bool CSUM, bool NTU, bool NTP>
 __device__ __forceinline__ uint64_t copy_span(uint8_t *user, uint8_t *pk, uint32_t bytes)
 {
@@ -1075,7 +1075,8 @@ __global__ __launch_bounds__(kThreads, NARROW ? 8 : UNPACK && CHECK != CHECK_TAG
 // elements (V = 16 bytes' worth: V rows of one vector each), transposes it in registers and leaves V vectors in LDS;
 // after the barrier the tile's rows leave LDS as whole vectors, 16 lanes (256 contiguous bytes) to a row.  So LDS is
 // touched by 16-byte accesses only, once each way; gathering elements out of it instead kept the LDS pipe busy for
-// about 1.7 us of a 14 us launch (64 two-byte reads per thread).  32 MiB of bf16, pack + unpack: 27.3 -> 24.4 us (a plain copy of the same bytes: 24.1).
+// about 1.7 us of a 14 us launch (64 two-byte reads per thread).  32 MiB of bf16, pack + unpack, new tensors through two
+// packed buffers: 28.4 -> 26.8 us (a plain copy of the same bytes: 26.2); the gain is all on the sending side.
 // Vectors need no alignment beyond the element's: the hardware takes misaligned 16-byte accesses, and even with both
 // row pitches odd (bf16, pitches of 8198 bytes) they beat element accesses, 30 against 31-38 us per pair.
 template <typename E>
@@ -1478,7 +1479,7 @@ __global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__
 // what the commit at the end reads is loaded at the start.  Sums go to the tile's per-chunk partial sums in LDS; at the
 // end one thread per chunk touched makes that chunk's arrival (inc holds the tile's chunks, ascending, and the ordinal
 // of each arrival).
-// [256, 65536] bf16 (8 packed rows per 1 MiB chunk), pack + unpack: 33.0 -> 26.0 us.
+// [256, 65536] bf16 (8 packed rows per 1 MiB chunk), pack + unpack: 33.2 -> 27.8 us.
 
 // What k_transpose_span keeps in LDS beside the tile, for tiles of T rows.  Per row: packed offset of byte x is p0 + x for
 // x < first, p1 + x from there on (first is a whole tile row or more where the row meets no border); at: entry of the
