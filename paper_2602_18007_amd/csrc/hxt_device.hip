@@ -237,23 +237,12 @@ template <bool UNPACK, int CHECK>
 void launch_rows_split(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck,
                        hipStream_t st)
 {
-    uint32_t wide = 0;                                       // some tensor is accessed in pieces of 4 bytes or more
-    for (uint32_t i = 0; i < g.n_tensors; ++i)
-        if (pl.p.tensors[g.tensor_base + i].kind == K_ROWS_SPLIT)
-            wide |= ((uint32_t(reinterpret_cast<uintptr_t>(b.p[i])) | pl.p.tdev[g.tensor_base + i].low_or) & 3u) == 0;
-    auto go = [&]<bool NTP, bool NARROW>() {
-        k_rows_split<UNPACK, CHECK, NTP, NARROW><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                               g.tensor_base, b, packed, ck);
+    auto go = [&]<bool NTP>() {
+        k_rows_split<UNPACK, CHECK, NTP><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
+                                                                       g.tensor_base, b, packed, ck);
     };
-    constexpr bool kNarrow = !UNPACK && CHECK != CHECK_TAGS;
-    const bool ntp = packed_nontemporal(pl, UNPACK);
-    if (kNarrow && !wide) {
-        if (ntp) go.template operator()<true, kNarrow>();
-        else go.template operator()<false, kNarrow>();
-    } else {
-        if (ntp) go.template operator()<true, false>();
-        else go.template operator()<false, false>();
-    }
+    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
+    else go.template operator()<false>();
 }
 
 template <bool UNPACK, int CHECK>

@@ -141,6 +141,7 @@ struct TensorDev {
                                        // give the widest naturally aligned piece the tensor side can be accessed in)
     uint32_t reserved;
     FastDiv row_div;                   // ROWS: division by row_bytes
+    FastDiv lane_div;                  // ROWS_SPLIT: division by the 16-byte vectors begun in a run
     FastDiv dim_div[HXT_MAX_DIMS];     // division by shape[d]: for the outer dims of a ROWS tensor, for all dims if all_div
     int64_t shape[HXT_MAX_DIMS];
     int64_t stride_b[HXT_MAX_DIMS];    // bytes

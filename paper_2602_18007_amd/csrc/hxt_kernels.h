@@ -180,6 +180,18 @@ __device__ __forceinline__ u32x4 keep_bytes(u32x4 v, uint32_t from, uint32_t to)
                  v.z & below(2, to) & ~below(2, from), v.w & below(3, to) & ~below(3, from)};
 }
 
+__device__ __forceinline__ u32x4 shift_bytes_down(u32x4 v, uint32_t by)         // by < 16: byte k of the result is byte k + by
+{
+    const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v) >> (8 * by);
+    return __builtin_bit_cast(u32x4, x);
+}
+
+__device__ __forceinline__ u32x4 shift_bytes_up(u32x4 v, uint32_t by)
+{
+    const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v) << (8 * by);
+    return __builtin_bit_cast(u32x4, x);
+}
+
 // Sum over every LANES lanes in a DPP row of 16, in the last of them (the others hold partial sums).  Inactive lanes count
 // as zero.
 template <int CTRL, int ROWS = 0xF>
@@ -849,12 +861,12 @@ __device__ __forceinline__ void count_elem(Sums2 &acc, E v, uint64_t pos)
     }
 }
 
-// Adds 16 bytes that start at byte `pos` (a multiple of the element size ES) of a chunk.
+// Adds 16 bytes that start at byte `pos` (a multiple of the element size ES; ES = 16: any vector of the packed side's own) of a chunk.
 template <int CHECK, int ES>
 __device__ __forceinline__ void count_vector(Sums2 &acc, u32x4 v, uint64_t pos)
 {
     if constexpr (CHECK == CHECK_SUMS) {
-        acc.s += rotated_sum(v, uint32_t(pos));
+        acc.s += ES == 16 ? words_sum(v) : rotated_sum(v, uint32_t(pos));
     } else if constexpr (CHECK == CHECK_TAGS) {
         uint32_t w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w, w4 = 0;
         if constexpr (ES < 4) {                          // a vector that starts inside a word: moved up by its phase, into five words
@@ -932,91 +944,96 @@ __global__ __launch_bounds__(kThreads) void k_rows(const Tile *__restrict__ tile
 }
 
 // ---- rows whose length or pitch is not a multiple of 16 bytes ----------------------
-// Still a gather of contiguous runs (of 16 bytes or more), but a 16-byte vector of the packed stream may end
-// one run and begin the next, and the tensor side is only G-byte aligned (G = 8, 4, 2 or 1).
-// Work is dealt in pieces of G bytes, consecutive lanes taking consecutive pieces of the tile: a wave's access
-// is then contiguous on the packed side and contiguous within each run on the tensor side (64 lanes x 4 bytes
-// = 256 bytes per instruction), whatever the run length; each piece finds its run with one multiply-shift
-// division and the run's storage offset from the outer indices.
+// Still a gather of contiguous runs (of 16 bytes or more), but a 16-byte vector of the packed stream may end one run and
+// begin the next.  A byte finds its run with one multiply-shift division and the run's storage offset from the outer
+// indices.
+// TWO_D: the view has two dims (the usual padded-pitch matrix) and needs no index decomposition.  Otherwise the outer dims
+// are held in registers (the loops store through byte pointers, which may alias the descriptor, so anything read through it
+// inside them would be read again every time).
+template <bool TWO_D>
+struct RunsOf {
+    static constexpr int D = TWO_D ? 1 : HXT_MAX_DIMS - 1;          // dims outside the run
+    uint32_t shape[D], mul[D], shift[D];
+    uint64_t stride[D];
+    uint32_t row_bytes, row0, col0;                                 // the tile starts at byte col0 of run row0
+    int outer;
+    FastDiv row_div;
+    __device__ __forceinline__ RunsOf(const Tile &t, const TensorDev &td)
+        : row_bytes(td.row_bytes), outer(TWO_D ? 1 : td.ndim - 1), row_div(td.row_div)
+    {
+        const uint64_t r = t.src_off / row_bytes;                   // uniform
+        row0 = uint32_t(r);
+        col0 = uint32_t(t.src_off - r * row_bytes);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            shape[d] = 1, mul[d] = 0, shift[d] = 0, stride[d] = 0;
+            if (d < outer) {
+                shape[d] = uint32_t(td.shape[d]);
+                mul[d] = td.dim_div[d].mul;
+                shift[d] = td.dim_div[d].shift;
+                stride[d] = uint64_t(td.stride_b[d]);
+            }
+        }
+    }
+    // Storage offset of run row0 + dr.
+    __device__ __forceinline__ uint64_t run(uint32_t dr) const
+    {
+        uint32_t row = row0 + dr;
+        uint64_t o = 0;
+#pragma unroll
+        for (int d = D - 1; d > 0; --d) {
+            if (d < outer) {
+                const uint32_t q = fast_div(row, FastDiv{mul[d], shift[d]});
+                o += uint64_t(row - q * shape[d]) * stride[d];
+                row = q;
+            }
+        }
+        return o + uint64_t(row) * stride[0];
+    }
+    // Storage offset of byte x of run row0 (x counted on into run row0 + dr, where it lies).
+    __device__ __forceinline__ uint64_t place(uint32_t x, uint32_t dr) const
+    {
+        if constexpr (TWO_D) return uint64_t(row0) * stride[0] + x + uint64_t(dr) * (stride[0] - row_bytes);      // (modulo 2^64)
+        else return run(dr) + uint64_t(int64_t(int32_t(x - dr * row_bytes)));
+    }
+    // Bytes from the first to the last byte of the view.
+    __device__ __forceinline__ uint64_t extent() const
+    {
+        uint64_t e = row_bytes;
+#pragma unroll
+        for (int d = 0; d < D; ++d) e += uint64_t(shape[d] - 1) * stride[d];
+        return e;
+    }
+};
+
 template <int G> struct PieceOf;
 template <> struct PieceOf<8> { using type = uint64_t; };
 template <> struct PieceOf<4> { using type = uint32_t; };
-template <> struct PieceOf<2> { using type = uint16_t; };
-template <> struct PieceOf<1> { using type = uint8_t; };
 
-// TWO_D: the view has two dims (the usual padded-pitch matrix) and needs no index decomposition: run
-// row0 + dr starts (row0 + dr) * pitch into the storage, so byte x of the tile's first run sits at
-// x + dr * (pitch - run length) from that run's start.  Otherwise the run's storage offset comes from
-// its outer indices, divided out with the dims held in registers (the loop stores through byte
-// pointers, which may alias the descriptor, so anything read through it inside the loop would be
-// read again for every piece).  With pieces of 1 or 2 bytes the loads of a round are unconditional
-// (the piece number is clamped into the tile): guarded, the compiler waits for each load before it
-// goes on to the next guard, and 16 loads one after the other cost 1.8-2.4 times the time.  With pieces
-// of 4 or 8 bytes the guarded loads are issued without such waits, interleaved with the address
-// arithmetic, and that order measures 10 % faster than eight loads in one burst.  Pieces of 1 or 2 bytes, 64 or 128
-// bytes per instruction, are not written through (rows of 101 elements, pack of 32 MiB, written through against left to
-// the L2: bytes 36.6 and 32.2 us, two bytes 24.1 and 22.9, but four bytes 14.7 and 15.5).
+// In pieces of G bytes, naturally aligned on both sides, consecutive lanes taking consecutive pieces of the tile: a wave's
+// access is contiguous on the packed side and contiguous within each run on the tensor side (64 lanes x 8 bytes = 512 bytes
+// per instruction).  Guarded loads are issued without waits here, interleaved with the address arithmetic, and that order
+// measures 10 % faster than eight loads in one burst.
 template <bool UNPACK, int CHECK, bool NTP, int G, bool TWO_D>
-__device__ __forceinline__ Sums2 rows_split_tile(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
+__device__ __forceinline__ Sums2 rows_split_pieces(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
     using P = typename PieceOf<G>::type;
-    const uint32_t row_bytes = td.row_bytes;
-    const FastDiv row_div = td.row_div;
-    const uint64_t row0 = t.src_off / row_bytes;                    // uniform
-    const uint32_t col0 = uint32_t(t.src_off - row0 * row_bytes);
+    const RunsOf<TWO_D> runs(t, td);
     const uint32_t npiece = t.n0 / G;
     constexpr int U = G == 8 ? 8 : 16;                              // pieces in flight per thread: a 16 KiB tile in one go
-    constexpr int D = TWO_D ? 1 : HXT_MAX_DIMS - 1;                 // dims outside the run
-    const int outer = TWO_D ? 1 : td.ndim - 1;
-    uint32_t shape[D], mul[D], shift[D];
-    uint64_t stride[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        shape[d] = 1, mul[d] = 0, shift[d] = 0, stride[d] = 0;
-        if (d < outer) {
-            shape[d] = uint32_t(td.shape[d]);
-            mul[d] = td.dim_div[d].mul;
-            shift[d] = td.dim_div[d].shift;
-            stride[d] = uint64_t(td.stride_b[d]);
-        }
-    }
-    uint8_t *const first_run = user + row0 * stride[0];             // uniform
-    const int64_t slack = int64_t(stride[0]) - int64_t(row_bytes);
     auto user_piece = [&](uint32_t i) {                             // piece i of the tile -> its place in storage
-        const uint32_t x = col0 + i * G;
-        const uint32_t dr = fast_div(x, row_div);
-        if constexpr (TWO_D) {
-            return reinterpret_cast<P *>(first_run + (int64_t(x) + int64_t(dr) * slack));
-        } else {
-            uint32_t row = uint32_t(row0) + dr;
-            uint64_t o = 0;
-#pragma unroll
-            for (int d = D - 1; d > 0; --d) {
-                if (d < outer) {
-                    const uint32_t q = fast_div(row, FastDiv{mul[d], shift[d]});
-                    o += uint64_t(row - q * shape[d]) * stride[d];
-                    row = q;
-                }
-            }
-            return reinterpret_cast<P *>(user + o + uint64_t(row) * stride[0] + (x - dr * row_bytes));
-        }
+        const uint32_t x = runs.col0 + i * G, dr = fast_div(x, runs.row_div);
+        return reinterpret_cast<P *>(user + runs.place(x, dr));
     };
     P *pieces = reinterpret_cast<P *>(pk);
     Sums2 acc{0, 0};
-    const uint32_t last = npiece - 1;
     for (uint32_t i0 = threadIdx.x; i0 < npiece; i0 += kThreads * U) {
         P r[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if constexpr (G >= 4) {
-                const uint32_t i = i0 + u * kThreads;
-                r[u] = 0;
-                if (i < npiece) {
-                    if constexpr (UNPACK) r[u] = load_elem<NTP>(pieces + i);
-                    else r[u] = __builtin_nontemporal_load(user_piece(i));
-                }
-            } else {
-                const uint32_t i = min(i0 + u * kThreads, last);
+            const uint32_t i = i0 + u * kThreads;
+            r[u] = 0;
+            if (i < npiece) {
                 if constexpr (UNPACK) r[u] = load_elem<NTP>(pieces + i);
                 else r[u] = __builtin_nontemporal_load(user_piece(i));
             }
@@ -1026,7 +1043,7 @@ __device__ __forceinline__ Sums2 rows_split_tile(const Tile &t, const TensorDev 
             const uint32_t i = i0 + u * kThreads;
             if (i < npiece) {
                 if constexpr (UNPACK) __builtin_nontemporal_store(r[u], user_piece(i));
-                else store_packed_elem<NTP, (G >= 4)>(pieces + i, r[u]);
+                else store_packed_elem<NTP>(pieces + i, r[u]);
                 count_elem<CHECK>(acc, r[u], t.a + i * G);
             }
         }
@@ -1034,38 +1051,132 @@ __device__ __forceinline__ Sums2 rows_split_tile(const Tile &t, const TensorDev 
     return acc;
 }
 
-// NARROW: pieces of 1 or 2 bytes only.
-template <bool UNPACK, int CHECK, bool NTP, bool NARROW>
+// In 16-byte vectors.
+// Sending, a vector of the packed side that ends one run and begins the next is put together from two loads, one where it
+// would lie if its first run went on and one where it would lie if its second run had begun earlier.  Both stay within the
+// view's extent unless the second run lies below the first one (or over it) in storage; the loads are then taken from within
+// the runs and shifted.
+// Receiving, every run (the part of it that is in this tile) gets as many lanes as it has vectors begun; the last of them
+// ends with the run, so that it stores some bytes a second time, with the same values, and a wave's store covers every run
+// whole: each burst of the tensor side is written once, which counts as much as the width (stored with their last pieces
+// apart, 32 MiB of rows of 37 elements took 109 us instead of 27).  Only what a tile holds of its first or last run can be
+// shorter than a vector and goes byte by byte.
+// Rows of bf16 at odd pitches, 32 MiB, pack / unpack, in pieces of 2 bytes against vectors (tensors of three messages in
+// turn): 37 elements 18.8 / 36.8 -> 18.6 / 27.0 us, 101 elements 17.3 / 24.5 -> 16.3 / 20.4, 1003 elements 17.5 / 19.3 ->
+// 15.1 / 15.2.  Pieces of 4 bytes (101 f32) 15.0 / 17.8 against 16.0 / 16.6; of 8 bytes (100 bf16) 15.1 / 17.2 against 16.1 /
+// 18.8: sending, pieces of 4 and 8 bytes are the faster ones, receiving, those of 8.
+template <bool UNPACK, int CHECK, bool NTP, bool TWO_D>
+__device__ __forceinline__ Sums2 rows_split_vectors(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
+{
+    const RunsOf<TWO_D> runs(t, td);
+    const uint32_t rb = runs.row_bytes, n = t.n0;
+    Sums2 acc{0, 0};
+    constexpr uint32_t U = kUnroll;
+    auto byte = [&](uint32_t i) {                                   // byte i of the tile alone
+        const uint32_t x = runs.col0 + i, dr = fast_div(x, runs.row_div);
+        uint8_t *at = user + runs.place(x, dr);
+        const uint8_t v = UNPACK ? pk[i] : *at;
+        if constexpr (UNPACK) *at = v;
+        else pk[i] = v;
+        count_elem<CHECK>(acc, v, t.a + i);
+    };
+    if constexpr (!UNPACK) {
+        const uint32_t nvec = n >> 4;
+        const uint64_t extent = runs.extent();
+        for (uint32_t v0 = threadIdx.x; v0 < nvec; v0 += kThreads * U) {
+            u32x4 r[U], s[U];
+            uint32_t k[U];
+            bool apart[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t x = runs.col0 + (min(v0 + u * kThreads, nvec - 1) << 4);
+                const uint32_t dr = fast_div(x, runs.row_div);
+                uint64_t o = runs.place(x, dr);
+                k[u] = rb - (x - dr * rb);                                      // bytes of the run from here on
+                s[u] = u32x4{0, 0, 0, 0};
+                apart[u] = false;
+                if (k[u] < 16) {
+                    uint64_t o2 = runs.place(x, dr + 1);                 // (below run dr + 1 by k)
+                    apart[u] = o + 16 > extent || int64_t(o2) < 0;
+                    if (apart[u]) o -= 16 - k[u], o2 += k[u];       // the run's last bytes, the next one's first
+                    s[u] = load16_any<true>(user + o2);
+                }
+                r[u] = load16_any<true>(user + o);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t v = v0 + u * kThreads;
+                if (v < nvec) {
+                    if (apart[u]) {
+                        r[u] = shift_bytes_down(r[u], 16 - k[u]);
+                        s[u] = shift_bytes_up(s[u], k[u]);
+                    }
+                    const u32x4 w = k[u] < 16 ? keep_bytes(r[u], 0, k[u]) | keep_bytes(s[u], k[u], 16) : r[u];
+                    store_packed16<NTP>(reinterpret_cast<u32x4 *>(pk) + v, w);
+                    count_vector<CHECK, 16>(acc, w, t.a + (uint64_t(v) << 4));
+                }
+            }
+        }
+        if (threadIdx.x < (n & 15u)) byte((nvec << 4) + threadIdx.x);            // only at the very end of the tensor
+    } else {
+        const uint32_t last = fast_div(runs.col0 + n - 1, runs.row_div);         // the tile meets runs row0 .. row0 + last
+        const uint32_t lanes = (rb + 15) >> 4, all = (last + 1) * lanes;
+        for (uint32_t i0 = threadIdx.x; i0 < all; i0 += kThreads * U) {
+            u32x4 r[U];
+            uint32_t at[U], skip[U];                                // byte of the tile; bytes that the lane before has too (16: nothing to do)
+            uint8_t *to[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+                const uint32_t i = min(i0 + u * kThreads, all - 1);
+                const uint32_t dr = fast_div(i, td.lane_div), start = dr * rb - runs.col0;       // (below zero, wrapped, for the first run)
+                const uint32_t lo = dr ? start : 0, hi = min(start + rb, n), y = lo + 16 * (i - dr * lanes);
+                const bool live = i0 + u * kThreads < all && y < hi && hi - lo >= 16;
+                at[u] = live ? min(y, hi - 16) : 0;
+                skip[u] = live ? y - at[u] : 16;
+                to[u] = user + runs.place(at[u] + runs.col0, dr);
+                r[u] = load16_any<NTP>(pk + at[u]);
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u)
+                if (skip[u] < 16) {
+                    store16_any<true>(to[u], r[u]);
+                    count_vector<CHECK, 1>(acc, keep_bytes(r[u], skip[u], 16), t.a + at[u]);
+                }
+        }
+        auto piece = [&](uint32_t lo, uint32_t hi) {
+            if (hi - lo < 16 && threadIdx.x < hi - lo) byte(lo + threadIdx.x);
+        };
+        piece(0, min(rb - runs.col0, n));
+        if (last) piece(last * rb - runs.col0, n);
+    }
+    return acc;
+}
+
+template <bool UNPACK, int CHECK, bool NTP>
 __device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
     // widest piece that is naturally aligned everywhere: low bits of the base address, the run length and the pitches
-    const uint32_t low = (uint32_t(reinterpret_cast<uintptr_t>(user)) | td.low_or) & 15u;
-    auto run = [&]<int G>() {
-        return td.ndim == 2 ? rows_split_tile<UNPACK, CHECK, NTP, G, true>(t, td, user, pk)
-                            : rows_split_tile<UNPACK, CHECK, NTP, G, false>(t, td, user, pk);
+    const uint32_t low = (uint32_t(reinterpret_cast<uintptr_t>(user)) | td.low_or) & 7u;
+    auto pieces = [&]<int G>() {
+        return td.ndim == 2 ? rows_split_pieces<UNPACK, CHECK, NTP, G, true>(t, td, user, pk)
+                            : rows_split_pieces<UNPACK, CHECK, NTP, G, false>(t, td, user, pk);
     };
-    if constexpr (!NARROW) {
-        if ((low & 7u) == 0) return run.template operator()<8>();
-        if ((low & 3u) == 0) return run.template operator()<4>();
-    }
-    if ((low & 1u) == 0) return run.template operator()<2>();
-    return run.template operator()<1>();
+    if (low == 0) return pieces.template operator()<8>();
+    if constexpr (!UNPACK)
+        if ((low & 3u) == 0) return pieces.template operator()<4>();
+    return td.ndim == 2 ? rows_split_vectors<UNPACK, CHECK, NTP, true>(t, td, user, pk)
+                        : rows_split_vectors<UNPACK, CHECK, NTP, false>(t, td, user, pk);
 }
 
-// (Receiving with plain sums or none, 7 waves per SIMD are asked for: the compiler takes 75 registers otherwise, 6 waves:
-// [327680, 100] bf16 at a pitch of 128, pack + unpack, 58.2 -> 56.9 us.  Sends of runs that all go in pieces of 1 or 2
-// bytes have a kernel of their own with 8 waves: they live on loads in flight, and the registers of the wider pieces leave
-// 6.  Rows of 101 elements, pack with sums, 32 MiB: bytes 32.5 -> 27.3 us, two bytes 22.9 -> 17.4; four bytes lose by such
-// a bound, 13.6 -> 15.2.)
-template <bool UNPACK, int CHECK, bool NTP, bool NARROW>
-__global__ __launch_bounds__(kThreads, NARROW ? 8 : UNPACK && CHECK != CHECK_TAGS ? 7 : 1) void k_rows_split(const Tile *__restrict__ tiles,
+template <bool UNPACK, int CHECK, bool NTP>
+__global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict__ tiles,
                                                          const uint32_t *__restrict__ chunk_tiles,
                                                          const TensorDev *__restrict__ tensors, uint32_t tensor_base,
                                                          BasePtrs bases, uint8_t *__restrict__ packed, CheckArgs<CHECK> ck)
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP, NARROW>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -1791,7 +1902,7 @@ __global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ t
         }
         break;
     case K_ROWS: acc = rows_tile<UNPACK, CHECK, NTU, NTP>(t, td, base, pk); break;
-    case K_ROWS_SPLIT: acc = rows_split_any<UNPACK, CHECK, NTP, false>(t, td, base, pk); break;
+    case K_ROWS_SPLIT: acc = rows_split_any<UNPACK, CHECK, NTP>(t, td, base, pk); break;
     case K_TRANSPOSE:
         acc = by_size([&]<typename E>() { return transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, base, packed, ck, lds_raw); });
         break;

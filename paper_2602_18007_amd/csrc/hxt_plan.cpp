@@ -166,6 +166,7 @@ static TensorDev make_tensor_dev(const TensorPlan &t)
         d.low_or = d.row_bytes;
         for (int i = 0; i < t.ndim - 1; ++i) d.low_or |= uint32_t(uint64_t(d.stride_b[i]) & 0xFFu);
         d.row_div = make_fastdiv(d.row_bytes);
+        d.lane_div = make_fastdiv((d.row_bytes + 15) / 16);
         for (int i = 0; i < t.ndim - 1; ++i) d.dim_div[i] = make_fastdiv(uint32_t(t.shape[i]));
     }
     // For the per-element kernel: all_div says that dim_div is valid for every dim, with room for a carry.

@@ -1,0 +1,56 @@
+"""GPU parity of the strided copy kernels at the shapes where their work is split: edges of vectors, runs and tiles, plain
+sums and tags, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import hxt_oracle as ho
+from paper_2602_18007_amd import hxt
+from tests.cases import Case, make_storages
+from tests.test_gpu_parity import DEV, oracle_msg, plan_of, round_trip_check, say, to_dev
+
+pytestmark = pytest.mark.gpu
+KiB = 1 << 10
+
+
+def check(shape, strides, esize, lanes, chunk, base_offset=0):
+    """Plain sums (round_trip_check) and tags, both directions."""
+    case = Case("view", ((shape, strides, esize),), lanes, chunk)
+    raws = make_storages(case, 11)
+    say(shape, strides, esize, lanes, chunk, base_offset)
+    round_trip_check(case, raws, base_offset=base_offset)
+    m, p = oracle_msg(case), plan_of(case)
+    C = p.num_chunks
+    want = ho.pack(m, raws, chunk, lanes, fill=0xA5)
+    src = [to_dev(r, base_offset) for r in raws]
+    packed = torch.full((want.size,), 0xA5, dtype=torch.uint8, device=DEV)
+    tags = torch.zeros(64 * C, dtype=torch.uint8, device=DEV)
+    hxt.hxt_pack_seal(p, src, packed, 5, 2, tags)
+    assert np.array_equal(packed.cpu().numpy(), want)
+    assert np.array_equal(tags.cpu().numpy().reshape(C, 64), ho.seal(m, want, chunk, lanes, 5, 2))
+    if not p.tensor_unpack_safe(0):
+        return
+    dst_o = [np.full(r.size, 0x3C, np.uint8) for r in raws]
+    ho.unpack(m, want, chunk, lanes, dst_o)
+    dst = [to_dev(d * 0 + 0x3C, base_offset) for d in dst_o]
+    status = torch.full((C + 1,), 7, dtype=torch.int32, device=DEV)
+    hxt.hxt_unpack_verify(p, packed, tags, 5, 2, dst, status)
+    assert np.array_equal(dst[0].cpu().numpy(), dst_o[0])
+    assert not status.any()
+
+
+# (run length in elements, gap behind it, element size, base off by): one vector and its neighbours, runs that end anywhere
+# in a vector, pieces of 8 and 4 bytes and vectors, each side of the rule between them.
+RUNS = [(16, 1, 1, 0), (17, 0, 1, 1), (31, 9, 1, 0), (8, 1, 2, 0), (9, 4, 2, 2), (100, 28, 2, 0), (100, 28, 2, 2), (101, 3, 2, 0),
+        (102, 2, 2, 0), (1003, 1, 2, 0), (5, 1, 4, 0), (6, 2, 4, 4), (101, 19, 4, 0), (3, 1, 8, 0), (4099, 5, 1, 3)]
+
+
+@pytest.mark.parametrize("run,gap,esize,off", RUNS)
+def test_rows_that_are_no_multiple_of_a_vector(run, gap, esize, off):
+    pitch = run + gap
+    rows = 70 * KiB // (run * esize) + 3
+    check((rows, run), (pitch, 1), esize, 3, 8 * KiB + 256, off)
+    check((rows // 4, 4, run), (pitch, (rows // 4) * pitch + 1, 1), esize, 2, 64 * KiB, off)       # neighbours far apart in storage
+    check((4, rows // 4, run), ((rows // 4) * pitch + 3, pitch, 1), esize, 2, 64 * KiB, off)
+    check((rows, run), (max(run - 3, 0), 1), esize, 2, 16 * KiB, off)                              # runs that overlap: a source only
+    check((7, run), (0, 1), esize, 1, 512, off)                                                    # the same run over and over
