@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "hxt_internal.h"
 
@@ -1723,13 +1724,13 @@ __global__ __launch_bounds__(kThreads) void k_transpose_span(const Tile *__restr
 // a wave's access is contiguous on the packed side and as dense on the tensor side as the view
 // allows.  The loads of a round are unconditional (the index is clamped into the tile), so that
 // all of them are issued before the first is waited for; only the stores are guarded.
-template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH, int ND>
-__device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p, uint64_t in_chunk)
-{
-    constexpr int D = ND ? ND : HXT_MAX_DIMS;
-    const int nd = ND ? ND : td.ndim;
+template <int ND>
+struct ElementsOf {
+    static constexpr int D = ND ? ND : HXT_MAX_DIMS;
+    int nd;
     uint32_t shape[D], mul[D], shift[D], first[D];
     uint64_t stride[D];
+    __device__ __forceinline__ ElementsOf(const TensorDev &td, uint64_t e0) : nd(ND ? ND : td.ndim)
     {
         uint64_t idx = e0;                                  // coordinates of the span's first element
 #pragma unroll
@@ -1746,23 +1747,33 @@ __device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, 
             }
         }
     }
-    // An element's coordinates are the first element's plus its number within the span, carried from
-    // the last dim upwards in 32 bits (a span has fewer than 2^30 elements and so has every dim).
-    auto locate = [&](uint32_t el) -> E * {
+    // Storage offset of element el of the span.  An element's coordinates are the first element's plus its number within
+    // the span, carried from the last dim upwards in 32 bits (a span has fewer than 2^30 elements and so has every dim).
+    // left: elements of the last dim from this one to its end.
+    __device__ __forceinline__ uint64_t at(uint32_t el, uint32_t *left = nullptr) const
+    {
         uint64_t off = 0;
         uint32_t x = el;
+        if (left && nd == 1) *left = shape[0] - (first[0] + el);
 #pragma unroll
         for (int d = D - 1; d > 0; --d) {
             if (d < nd) {
                 x += first[d];
                 const uint32_t q = fast_div(x, FastDiv{mul[d], shift[d]});
+                if (left && d == nd - 1) *left = shape[d] - (x - q * shape[d]);
                 off += uint64_t(x - q * shape[d]) * stride[d];
                 x = q;
             }
         }
-        off += uint64_t(x + first[0]) * stride[0];
-        return reinterpret_cast<E *>(user + off);
-    };
+        return off + uint64_t(x + first[0]) * stride[0];
+    }
+};
+
+template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH, int ND>
+__device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, uint32_t nel, uint8_t *user, E *p, uint64_t in_chunk)
+{
+    const ElementsOf<ND> els(td, e0);
+    auto locate = [&](uint32_t el) { return reinterpret_cast<E *>(user + els.at(el)); };
     constexpr int U = 8;
     Sums2 acc{0, 0};
     const uint32_t last = nel - 1;
@@ -1783,6 +1794,92 @@ __device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, 
                 count_elem<CHECK>(acc, val[u], in_chunk + uint64_t(el) * sizeof(E));
             }
         }
+    }
+    return acc;
+}
+
+// Sending elements that lie S = 2 or 4 apart: M = 16 / (S * element size) neighbours of a run are read as one vector, so that
+// a wave's load is contiguous, picked out of the registers and stored side by side, 16 / S bytes.  The vector starts with the
+// first of them; where they are the last of their run it ends with the last of them instead (what lies behind need not be
+// the view's); neighbours that are not of one run are read one by one.
+// What it saves is instructions, a load of 2 bytes for every element.  Pack alone with sums, element by element against this:
+// every other of 16.8 M bf16 25.5 -> 21.3 us (tensors not in the cache 27.5 -> 24.1), of 8 M 15.3 -> 11.3, of 6 M with tags
+// 14.4 -> 9.9, of 33.5 M bytes 42.0 -> 21.2; every fourth of 4 M bf16 11.4 -> 10.1, of 16.8 M 33.0 -> 32.6, of 33.5 M bytes
+// 44.1 -> 33.0.  Not for elements of 4 bytes, whose own loads are wide enough (every other of 8.4 M f32 21.4 -> 23.0, every
+// fourth 33.2 -> 37.9).  Every third goes element by element: read as whole vectors, lanes 48 bytes apart, 29.3 -> 33.5.
+template <typename E, uint32_t S>
+struct Apart {
+    static constexpr uint32_t ES = sizeof(E), M = 16 / (S * ES), BYTES = M * ES, BEHIND = (S - 1) * ES;
+    using P = std::conditional_t<BYTES == 8, uint64_t, uint32_t>;
+    static_assert(BYTES == sizeof(P));
+    // The elements at bytes 0, S * ES, 2 * S * ES ... of a vector.
+    static __device__ __forceinline__ P pick(u32x4 v)
+    {
+        auto two = [](uint32_t a, uint32_t b) {             // the elements that start in each of two words, side by side
+            if constexpr (ES == 2) return __builtin_amdgcn_perm(b, a, 0x05040100u);
+            else return S == 2 ? __builtin_amdgcn_perm(b, a, 0x06040200u) : __builtin_amdgcn_perm(b, a, 0x0C0C0400u);      // (0x0C: zero)
+        };
+        if constexpr (ES == 4) {
+            if constexpr (S == 2) return uint64_t(v.z) << 32 | v.x;
+            else return v.x;
+        } else if constexpr (ES == 2) {
+            if constexpr (S == 2) return uint64_t(two(v.z, v.w)) << 32 | two(v.x, v.y);
+            else return two(v.x, v.z);
+        } else {
+            if constexpr (S == 2) return uint64_t(two(v.z, v.w)) << 32 | two(v.x, v.y);
+            else return two(v.x, v.y) | two(v.z, v.w) << 16;
+        }
+    }
+};
+
+// Runs of fewer elements have too many neighbours that are not of one run (4 M bf16 in runs of 9: 11.0 -> 16.3 us; of 32:
+// 10.7 -> 8.8).
+constexpr int64_t kApartRun = 32;
+
+template <typename E, uint32_t S, int CHECK, bool NTP, int ND>
+__device__ __forceinline__ Sums2 send_apart(const TensorDev &td, uint64_t e0, uint32_t nel, const uint8_t *user, E *p, uint64_t in_chunk)
+{
+    using A = Apart<E, S>;
+    using P = typename A::P;
+    constexpr uint32_t ES = sizeof(E), M = A::M, U = 8;
+    const ElementsOf<ND> els(td, e0);
+    const uint32_t groups = nel / M;
+    P *const out = reinterpret_cast<P *>(p);
+    Sums2 acc{0, 0};
+    for (uint32_t g0 = threadIdx.x; g0 < groups; g0 += kThreads * U) {
+        u32x4 r[U];
+        uint32_t left[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            // (of two runs: what the first run ends with is read, which is not used)
+            uint64_t off = els.at(min(g0 + u * kThreads, groups - 1) * M, &left[u]);
+            if (left[u] <= M) off -= A::BEHIND + (M - left[u]) * (S * ES);
+            r[u] = load16_any<true>(user + off);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t g = g0 + u * kThreads;
+            if (g >= groups) continue;
+            if (left[u] == M) r[u] = shift_bytes_down(r[u], A::BEHIND);
+            P v = A::pick(r[u]);
+            if (left[u] < M) {
+                union {
+                    E e[M];
+                    P x;
+                } o;
+#pragma unroll
+                for (uint32_t q = 0; q < M; ++q) o.e[q] = *reinterpret_cast<const E *>(user + els.at(g * M + q));
+                v = o.x;
+            }
+            store_packed_elem<NTP>(out + g, v);
+            count_elem<CHECK>(acc, v, in_chunk + uint64_t(g) * A::BYTES);
+        }
+    }
+    if (threadIdx.x < nel - groups * M) {                   // only at the very end of the tensor
+        const uint32_t el = groups * M + threadIdx.x;
+        const E v = *reinterpret_cast<const E *>(user + els.at(el));
+        p[el] = v;
+        count_elem<CHECK>(acc, v, in_chunk + uint64_t(el) * ES);
     }
     return acc;
 }
@@ -1823,6 +1920,17 @@ __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td,
     const uint64_t e0 = t.src_off / sizeof(E);
     if (nel == 0) return Sums2{0, 0};
     if (!td.all_div) return generic_span_wide<E, UNPACK, CHECK, NTP, THROUGH>(td, e0, nel, user, p, t.a);
+    if constexpr (!UNPACK && sizeof(E) <= 2) {
+        const uint64_t step = uint64_t(td.stride_b[td.ndim - 1]);
+        auto apart = [&]<uint32_t S>() {
+            return td.ndim == 1 ? send_apart<E, S, CHECK, NTP, 1>(td, e0, nel, user, p, t.a)
+                                : send_apart<E, S, CHECK, NTP, 0>(td, e0, nel, user, p, t.a);
+        };
+        if (td.shape[td.ndim - 1] >= kApartRun) {
+            if (step == 2 * sizeof(E)) return apart.template operator()<2>();
+            if (step == 4 * sizeof(E)) return apart.template operator()<4>();
+        }
+    }
     switch (td.ndim) {
     case 1: return generic_span<E, UNPACK, CHECK, NTP, THROUGH, 1>(td, e0, nel, user, p, t.a);
     case 2: return generic_span<E, UNPACK, CHECK, NTP, THROUGH, 2>(td, e0, nel, user, p, t.a);

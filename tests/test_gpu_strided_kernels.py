@@ -54,3 +54,18 @@ def test_rows_that_are_no_multiple_of_a_vector(run, gap, esize, off):
     check((4, rows // 4, run), ((rows // 4) * pitch + 3, pitch, 1), esize, 2, 64 * KiB, off)
     check((rows, run), (max(run - 3, 0), 1), esize, 2, 16 * KiB, off)                              # runs that overlap: a source only
     check((7, run), (0, 1), esize, 1, 512, off)                                                    # the same run over and over
+
+
+# (elements of a run, distance between them, element size, base off by): runs either side of 32 elements, whole numbers of
+# groups and not, distances with a path of their own (2 and 4, of 1 and 2 bytes) and without.
+APART = [(31, 2, 2, 0), (32, 2, 2, 0), (33, 2, 2, 2), (101, 2, 2, 0), (67, 4, 2, 6), (128, 4, 2, 0), (100, 3, 2, 0), (45, 2, 1, 1),
+         (77, 4, 1, 3), (64, 5, 1, 0), (50, 2, 4, 4), (40, 4, 4, 0), (37, 2, 8, 8)]
+
+
+@pytest.mark.parametrize("run,step,esize,off", APART)
+def test_elements_a_few_apart(run, step, esize, off):
+    n = 70 * KiB // (run * esize) + 3
+    check((n * run + 5,), (step,), esize, 3, 8 * KiB + 256, off)
+    check((n, run), (run * step + 1, step), esize, 2, 64 * KiB, off)
+    check((n // 3, 3, run), (run * step, (n // 3) * run * step + 3, step), esize, 2, 64 * KiB, off)
+    check((n, run), (step, step), esize, 2, 16 * KiB, off)             # runs over each other: a source only
