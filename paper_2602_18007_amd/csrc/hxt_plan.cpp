@@ -115,6 +115,33 @@ static bool view_is_injective(const TensorPlan &t)
     return true;
 }
 
+// Tiles of a transpose (a view whose last two dims are I and J) that stay inside one chunk: every chunk holds the end of a row
+// of the packed side, a block of whole rows and the beginning of a row.
+static uint64_t tiles_inside_chunks(const TensorPlan &t, uint64_t chunk_bytes)
+{
+    const uint64_t e = t.esize, I = t.shape[t.ndim - 2], J = t.shape[t.ndim - 1], T = transpose_tile(uint32_t(e));
+    auto up = [](uint64_t x, uint64_t a) { return (x + a - 1) / a; };
+    uint64_t n = 0;
+    for (uint64_t s = t.stream_off, end = t.stream_off + t.bytes; s < end;) {
+        const uint64_t stop = std::min((s / chunk_bytes + 1) * chunk_bytes, end);
+        const uint64_t ea = (s - t.stream_off) / e, eb = (stop - t.stream_off) / e;
+        uint64_t r0 = ea / J, r1 = eb / J;
+        if (r0 == r1) {
+            n += up(eb - ea, T);
+        } else {
+            if (ea % J) n += up((r0 + 1) * J - ea, T), ++r0;
+            if (eb % J) n += up(eb % J, T);
+            while (r0 < r1) {                              // whole rows, a batch at a time
+                const uint64_t rows = std::min(r1 - r0, I - r0 % I);
+                n += up(rows, T) * up(J, T);
+                r0 += rows;
+            }
+        }
+        s = stop;
+    }
+    return n;
+}
+
 static Kind classify(const TensorPlan &t, uint64_t chunk_bytes)
 {
     if (t.elems == 0) return K_NONE;
@@ -136,15 +163,25 @@ static Kind classify(const TensorPlan &t, uint64_t chunk_bytes)
     }
     // The dim before the last runs along the storage (stride one, or a few elements: at most 16 bytes, so that
     // neighbouring elements still share memory bursts) and the last dim jumps further: a transpose through LDS.
-    // Tiles stay inside one chunk when a chunk holds at least a tile's height of rows of the packed side, so that
-    // all but the tiles at chunk borders are full; flatter chunks get tiles that span chunks (chunks of at least
+    // Tiles stay inside one chunk when a chunk holds at least a tile's height of rows of the packed side and all but the
+    // tiles at chunk borders are full; flatter chunks get tiles that span chunks (chunks of at least
     // 1 KiB, so that a tile row meets at most one chunk border).
     const bool classic = t.ndim >= 2 && t.stride[last] > 1 && t.stride[last - 1] == 1;
     const bool strided = t.ndim >= 2 && t.stride[last - 1] > 1 && t.stride[last] > t.stride[last - 1] &&
                          uint64_t(t.stride[last - 1]) * t.esize <= 16;
     if (classic || strided) {
         const bool tall = uint64_t(t.shape[last]) * t.esize * transpose_tile(uint32_t(t.esize)) <= chunk_bytes;
-        if (tall) return K_TRANSPOSE;
+        // Chunks that do not hold whole numbers of tile rows clip the tiles at their borders, down to single rows, and a
+        // clipped tile takes as long as a full one.  Tensors of more than 10 MiB, where tiles wait for their turn on the
+        // chip, get tiles that span chunks if that leaves out a fifth of them or more.  bf16 [4000, 4000], pack + unpack:
+        // chunks of 1 MiB 48.7 -> 31.4 us (with tags 56.3 -> 35.2), 4 MiB 35.4 -> 32.4, 8 MiB (22 % more tiles) 32.9 either
+        // way, one chunk 29.2 inside and 31.9 spanning; f32 [4, 1000, 1500] with 1 MiB 26.8 -> 24.9.  Smaller tensors are
+        // all on the chip at once, and smaller tiles are then done sooner: [2100, 2104] bf16 (8.4 MiB) 19.9 inside, 21.8
+        // spanning, [2500, 2504] (11.9 MiB) 24.7 and 22.7; f32 [2100, 1050] 16.4 and 16.8, [2500, 1250] 22.3 and 18.8.
+        const uint64_t T = transpose_tile(uint32_t(t.esize));
+        const uint64_t I = t.shape[last - 1], J = t.shape[last], whole = t.elems / (I * J) * ((I + T - 1) / T) * ((J + T - 1) / T);
+        const bool clipped = t.bytes > (uint64_t(10) << 20) && 4 * tiles_inside_chunks(t, chunk_bytes) > 5 * whole;
+        if (tall && !(clipped && chunk_bytes >= 1024)) return K_TRANSPOSE;
         if (chunk_bytes >= 1024) return K_TRANSPOSE_SPAN;
         if (classic) return K_TRANSPOSE;
     }

@@ -6,7 +6,7 @@ import torch
 
 from oracle import hxt_oracle as ho
 from paper_2602_18007_amd import hxt
-from tests.cases import Case, make_storages
+from tests.cases import CLIPPED_TRANSPOSES as CLIPPED, Case, make_storages
 from tests.test_gpu_parity import DEV, oracle_msg, plan_of, round_trip_check, say, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -69,3 +69,9 @@ def test_elements_a_few_apart(run, step, esize, off):
     check((n, run), (run * step + 1, step), esize, 2, 64 * KiB, off)
     check((n // 3, 3, run), (run * step, (n // 3) * run * step + 3, step), esize, 2, 64 * KiB, off)
     check((n, run), (step, step), esize, 2, 16 * KiB, off)             # runs over each other: a source only
+
+
+# Either side of 10 MiB, chunks that hold whole numbers of tile rows and not: tiles inside chunks or across them.
+@pytest.mark.parametrize("shape,strides,esize,chunk", CLIPPED)
+def test_transposes_that_chunks_would_clip(shape, strides, esize, chunk):
+    check(shape, strides, esize, 3, chunk)
