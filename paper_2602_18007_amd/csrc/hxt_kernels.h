@@ -1806,7 +1806,8 @@ __device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, 
 // every other of 16.8 M bf16 25.5 -> 21.3 us (tensors not in the cache 27.5 -> 24.1), of 8 M 15.3 -> 11.3, of 6 M with tags
 // 14.4 -> 9.9, of 33.5 M bytes 42.0 -> 21.2; every fourth of 4 M bf16 11.4 -> 10.1, of 16.8 M 33.0 -> 32.6, of 33.5 M bytes
 // 44.1 -> 33.0.  Not for elements of 4 bytes, whose own loads are wide enough (every other of 8.4 M f32 21.4 -> 23.0, every
-// fourth 33.2 -> 37.9).  Every third goes element by element: read as whole vectors, lanes 48 bytes apart, 29.3 -> 33.5.
+// fourth 33.2 -> 37.9).  The packed side is written through by the rule for single elements (every fourth of 1.2 M bf16, pack +
+// unpack, 14.2 us through, 12.6 not; 14.0 element by element).  Every third goes element by element: read as whole vectors, lanes 48 bytes apart, 29.3 -> 33.5.
 template <typename E, uint32_t S>
 struct Apart {
     static constexpr uint32_t ES = sizeof(E), M = 16 / (S * ES), BYTES = M * ES, BEHIND = (S - 1) * ES;
@@ -1836,7 +1837,7 @@ struct Apart {
 // 10.7 -> 8.8).
 constexpr int64_t kApartRun = 32;
 
-template <typename E, uint32_t S, int CHECK, bool NTP, int ND>
+template <typename E, uint32_t S, int CHECK, bool NTP, bool THROUGH, int ND>
 __device__ __forceinline__ Sums2 send_apart(const TensorDev &td, uint64_t e0, uint32_t nel, const uint8_t *user, E *p, uint64_t in_chunk)
 {
     using A = Apart<E, S>;
@@ -1871,7 +1872,7 @@ __device__ __forceinline__ Sums2 send_apart(const TensorDev &td, uint64_t e0, ui
                 for (uint32_t q = 0; q < M; ++q) o.e[q] = *reinterpret_cast<const E *>(user + els.at(g * M + q));
                 v = o.x;
             }
-            store_packed_elem<NTP>(out + g, v);
+            store_packed_elem<NTP, THROUGH>(out + g, v);
             count_elem<CHECK>(acc, v, in_chunk + uint64_t(g) * A::BYTES);
         }
     }
@@ -1925,8 +1926,8 @@ __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td,
     if constexpr (!UNPACK && APART && sizeof(E) <= 2) {
         const uint64_t step = uint64_t(td.stride_b[td.ndim - 1]);
         auto apart = [&]<uint32_t S>() {
-            return td.ndim == 1 ? send_apart<E, S, CHECK, NTP, 1>(td, e0, nel, user, p, t.a)
-                                : send_apart<E, S, CHECK, NTP, 0>(td, e0, nel, user, p, t.a);
+            return td.ndim == 1 ? send_apart<E, S, CHECK, NTP, THROUGH, 1>(td, e0, nel, user, p, t.a)
+                                : send_apart<E, S, CHECK, NTP, THROUGH, 0>(td, e0, nel, user, p, t.a);
         };
         if (td.shape[td.ndim - 1] >= kApartRun) {
             if (step == 2 * sizeof(E)) return apart.template operator()<2>();
