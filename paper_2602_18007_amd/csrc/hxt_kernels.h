@@ -673,13 +673,14 @@ __device__ __forceinline__ void pair_commit_total(int mode, const ChunkGeom &g, 
     if (last) finish_chunk(mode, g, chunk, a, b, out, work, tag(), acc, stride, fan);
 }
 
+using PairParts = uint64_t[2][kThreads / 64];          // in LDS
+
 // Workgroup-wide: reduces every thread's (a, b), adds the pair to the chunk's accumulators (two-level
 // fan-out as in chunk_commit); the workgroup that completes the chunk finishes it.
 __device__ __forceinline__ void pair_commit(int mode, const ChunkGeom &g, const TileSpan &t, unsigned long long a,
                                             unsigned long long b, void *out, uint8_t *acc, uint32_t stride,
-                                            uint32_t fan, const TagWork &work, const TagRegs &got)
+                                            uint32_t fan, const TagWork &work, const TagRegs &got, PairParts &part)
 {
-    __shared__ uint64_t part[2][kThreads / 64];
     for (int o = 32; o > 0; o >>= 1) {
         a += __shfl_down(a, o, 64);
         b += __shfl_down(b, o, 64);
@@ -826,6 +827,17 @@ __device__ __forceinline__ TagRegs prefetch_check(const CheckArgs<CHECK> &ck, ui
     else return TagRegs{};
 }
 
+template <bool UNPACK>
+__device__ __forceinline__ void commit_tags(Sums2 v, const Tile &t, const uint32_t *__restrict__ chunk_tiles,
+                                            const CheckArgs<CHECK_TAGS> &ck, const TagRegs &got, PairParts &part)
+{
+    TileSpan span{};
+    span.chunk = t.chunk;
+    span.ordinal = t.ordinal;
+    span.expected = chunk_tiles[t.chunk];
+    pair_commit(UNPACK ? SUM2_VERIFY : SUM2_SEAL, ck.g, span, v.s, v.w, ck.out, ck.cx.acc, ck.cx.stride, ck.cx.fan, ck.work, got, part);
+}
+
 // Workgroup-wide: the tile's sums (weights counted from the chunk's first word) go to its chunk.
 template <bool UNPACK, int CHECK>
 __device__ __forceinline__ void commit_tile(Sums2 v, const Tile &t, const uint32_t *__restrict__ chunk_tiles,
@@ -833,11 +845,8 @@ __device__ __forceinline__ void commit_tile(Sums2 v, const Tile &t, const uint32
 {
     if constexpr (CHECK == CHECK_SUMS) chunk_commit(v.s, t.chunk, t.ordinal, chunk_tiles[t.chunk], ck.cx);
     if constexpr (CHECK == CHECK_TAGS) {
-        TileSpan span{};
-        span.chunk = t.chunk;
-        span.ordinal = t.ordinal;
-        span.expected = chunk_tiles[t.chunk];
-        pair_commit(UNPACK ? SUM2_VERIFY : SUM2_SEAL, ck.g, span, v.s, v.w, ck.out, ck.cx.acc, ck.cx.stride, ck.cx.fan, ck.work, got);
+        __shared__ PairParts part;
+        commit_tags<UNPACK>(v, t, chunk_tiles, ck, got, part);
     }
 }
 
@@ -1598,7 +1607,7 @@ __global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__
 // row's first chunk; rem: position of its first byte in that chunk (for the weights of the sums).
 template <uint32_t T, int CHECK>
 struct SpanLds {
-    static constexpr uint32_t MAXC = 2 * T + 2;
+    static constexpr uint32_t MAXC = 2 * T;             // a row meets at most two chunks
     unsigned long long part[MAXC];                      // partial sum per chunk touched
     unsigned long long wpart[CHECK == CHECK_TAGS ? MAXC : 1];       // and the weighted one
     uint64_t p0[T], p1[T], rem[T];
@@ -2019,7 +2028,11 @@ __global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ t
         break;
     default: acc = by_size([&]<typename E>() { return generic_any<E, UNPACK, CHECK, NTP, false, false>(t, td, base, packed); }); break;
     }
-    commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
+    // (with tags, what the sums are reduced in lies where a spanning tile keeps its own: 40960 bytes of LDS are four
+    // workgroups per CU, 64 more were three.  Pack + unpack with
+    // tags of bundles of four kinds: 24 MB 41.7 -> 39.0 us, 31 MB 44.1 -> 40.8; 7 MB, one round of tiles, 22.9 and 23.1)
+    if constexpr (CHECK == CHECK_TAGS) commit_tags<UNPACK>(acc, t, chunk_tiles, ck, got, reinterpret_cast<PairParts &>(sp.part));
+    else commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
 // ---- stand-alone checksum of packed chunks (closed-form geometry, no table) ----------
@@ -2076,7 +2089,8 @@ __global__ __launch_bounds__(kThreads) void k_checksum2(ChunkGeom g, const uint8
         S += blockS;
         nS += blockN + n0 * blockS;
     }
-    pair_commit(MODE, g, t, S, (j0 + 4ull * threadIdx.x + 1) * S + 4ull * kThreads * nS + I, out, acc, stride, fan, work, got);
+    __shared__ PairParts part;
+    pair_commit(MODE, g, t, S, (j0 + 4ull * threadIdx.x + 1) * S + 4ull * kThreads * nS + I, out, acc, stride, fan, work, got, part);
 }
 
 // ---- pack + seal and unpack + verify in one pass (messages that are one contiguous tensor) ----
@@ -2122,7 +2136,8 @@ __global__ __launch_bounds__(kThreads) void k_uniform_tag(UniformTagArgs a)
         sums.w += pad.w;
     }
     const uint64_t j0 = (t.stream_off - uint64_t(t.chunk) * g.B) >> 2;       // the tile's first word in its chunk
-    pair_commit(MODE, g, t, sums.s, j0 * sums.s + sums.w, it.out, it.acc, it.stride, it.fan, it.work, got);
+    __shared__ PairParts part;
+    pair_commit(MODE, g, t, sums.s, j0 * sums.s + sums.w, it.out, it.acc, it.stride, it.fan, it.work, got, part);
 }
 
 // The same for the contiguous tensors of a multi-tensor message (gradient buckets): the table-driven copy
@@ -2147,7 +2162,8 @@ __global__ __launch_bounds__(kThreads) void k_contig_tag(const Tile *__restrict_
         sums = copy_span2<UNPACK, NTU, NTP>(bases.p[t.tensor] + t.src_off, packed + t.packed_off, t.n0);
         j0 = t.a >> 2;
     }
-    pair_commit(MODE, g, span, sums.s, j0 * sums.s + sums.w, out, acc, stride, fan, work, got);
+    __shared__ PairParts part;
+    pair_commit(MODE, g, span, sums.s, j0 * sums.s + sums.w, out, acc, stride, fan, work, got, part);
 }
 
 }  // namespace hxt
