@@ -168,9 +168,10 @@ int hxt_plan_lane_info(const hxt_plan_t *plan, int lane, hxt_lane_info_t *out);
 /* 1 if hxt_unpack may write through tensor t's view (no two elements alias), else 0 */
 int hxt_plan_tensor_unpack_safe(const hxt_plan_t *plan, int t);
 /* which kernel family serves tensor t: 0 none (empty), 1 contiguous copy, 2 row gather (runs and
- * pitches that are multiples of 16 bytes), 3 LDS transpose, 4 per-element, 6 row gather in narrower
- * pieces (runs of 16 bytes or more whose length or pitch is not a multiple of 16), 7 LDS transpose
- * whose tiles span chunks (a chunk holds fewer rows of the packed side than a tile is high) */
+ * pitches that are multiples of 16 bytes), 3 LDS transpose, 4 per-element, 6 row gather in
+ * pieces or across runs (runs of 16 bytes or more whose length or pitch is not a multiple of 16), 7 LDS
+ * transpose whose tiles span chunks (a chunk holds fewer rows of the packed side than a tile is high, or
+ * chunk borders would clip the tiles of a large tensor) */
 int hxt_plan_tensor_kind(const hxt_plan_t *plan, int t);
 
 /* ---- step 2: pack (Section 2.2: user buffer -> chunk buffer, device to device)

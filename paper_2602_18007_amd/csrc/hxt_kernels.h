@@ -1842,9 +1842,12 @@ struct Apart {
     }
 };
 
-// Runs of fewer elements have too many neighbours that are not of one run (4 M bf16 in runs of 9: 11.0 -> 16.3 us; of 32:
-// 10.7 -> 8.8).
-constexpr int64_t kApartRun = 32;
+// Runs of fewer than 32 elements have too many neighbours that are not of one run (4 M bf16 in runs of 9: 11.0 -> 16.3 us;
+// of 32: 10.7 -> 8.8).
+HXT_HD bool takes_apart(size_t esize, int64_t run, uint64_t step)
+{
+    return esize <= 2 && run >= 32 && (step == 2 * esize || step == 4 * esize);
+}
 
 template <typename E, uint32_t S, int CHECK, bool NTP, bool THROUGH, int ND>
 __device__ __forceinline__ Sums2 send_apart(const TensorDev &td, uint64_t e0, uint32_t nel, const uint8_t *user, E *p, uint64_t in_chunk)
@@ -1922,8 +1925,9 @@ __device__ __noinline__ Sums2 generic_span_wide(const TensorDev &td, uint64_t e0
     return acc;
 }
 
-// APART: with send_apart.  (k_message goes without: its code, every branch of which costs the others a little, would be 0.3 MB
-// longer; a bundle of 7 MB with tags, pack + unpack, 24.4 us with it and 23.0 without.)
+// APART: with send_apart, where takes_apart finds use for it.  (Elsewhere its registers and code only slow the others down: every
+// third column of a 1.1 MB matrix, pack + unpack, 13.75 us with it and 13.54 without; a bundle of 7 MB with tags in k_message,
+// which has no room for it, 24.4 and 23.0.)
 template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH, bool APART>
 __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *packed)
 {
@@ -1938,9 +1942,9 @@ __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td,
             return td.ndim == 1 ? send_apart<E, S, CHECK, NTP, THROUGH, 1>(td, e0, nel, user, p, t.a)
                                 : send_apart<E, S, CHECK, NTP, THROUGH, 0>(td, e0, nel, user, p, t.a);
         };
-        if (td.shape[td.ndim - 1] >= kApartRun) {
+        if (takes_apart(sizeof(E), td.shape[td.ndim - 1], step)) {
             if (step == 2 * sizeof(E)) return apart.template operator()<2>();
-            if (step == 4 * sizeof(E)) return apart.template operator()<4>();
+            return apart.template operator()<4>();
         }
     }
     switch (td.ndim) {
@@ -1952,7 +1956,7 @@ __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td,
     }
 }
 
-template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH>
+template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH, bool APART>
 __global__ __launch_bounds__(kThreads) void k_generic(const Tile *__restrict__ tiles,
                                                       const uint32_t *__restrict__ chunk_tiles,
                                                       const TensorDev *__restrict__ tensors, uint32_t tensor_base,
@@ -1960,7 +1964,7 @@ __global__ __launch_bounds__(kThreads) void k_generic(const Tile *__restrict__ t
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : generic_any<E, UNPACK, CHECK, NTP, THROUGH, true>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : generic_any<E, UNPACK, CHECK, NTP, THROUGH, APART>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
