@@ -1605,9 +1605,11 @@ __global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__
 // What k_transpose_span keeps in LDS beside the tile, for tiles of T rows.  Per row: packed offset of byte x is p0 + x for
 // x < first, p1 + x from there on (first is a whole tile row or more where the row meets no border); at: entry of the
 // row's first chunk; rem: position of its first byte in that chunk (for the weights of the sums).
-template <uint32_t T, int CHECK>
+// A tile's rows meet at most 2 T chunks; SPARE entries more change nothing but where the rest lies (k_message has no room for
+// them; here, without them, [143, 96522] of two bytes with tags took 53.6 us a pair instead of 52.4).
+template <uint32_t T, int CHECK, uint32_t SPARE = 2>
 struct SpanLds {
-    static constexpr uint32_t MAXC = 2 * T;             // a row meets at most two chunks
+    static constexpr uint32_t MAXC = 2 * T + SPARE;
     unsigned long long part[MAXC];                      // partial sum per chunk touched
     unsigned long long wpart[CHECK == CHECK_TAGS ? MAXC : 1];       // and the weighted one
     uint64_t p0[T], p1[T], rem[T];
@@ -1991,7 +1993,7 @@ __global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ t
     constexpr uint32_t kLds = transpose_lds_bytes<uint64_t>() > transpose_lds_bytes<uint16_t>() ? transpose_lds_bytes<uint64_t>()
                                                                                                 : transpose_lds_bytes<uint16_t>();
     __shared__ __attribute__((aligned(16))) uint8_t lds_raw[kLds];
-    __shared__ SpanLds<TransposeShape<uint16_t>::T, CHECK> sp;
+    __shared__ SpanLds<TransposeShape<uint16_t>::T, CHECK, 0> sp;
     const Tile t = tiles[blockIdx.x];
     uint32_t first_tensor = a.base[0];
 #pragma unroll
