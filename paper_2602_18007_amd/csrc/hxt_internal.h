@@ -147,6 +147,34 @@ struct TensorDev {
     int64_t stride_b[HXT_MAX_DIMS];    // bytes
 };
 
+// Receiving rows in 16-byte vectors: a tile of n bytes that starts at byte col0 of a run of rb bytes deals lanes over the part
+// of every run that lies in it, as many as the part has vectors begun; the last one of a part ends with it.  By run, not by
+// tile, because a run's store must not be split into bursts; by the part, because a run can be much longer than a tile.
+struct RunLanes {
+    uint32_t rb, col0, n, first, lanes, all;           // lanes of the first run's part, of a whole run, of the tile
+    FastDiv div;                                       // by lanes
+    struct Lane {
+        uint32_t dr, at, skip;     // run (counted from the tile's first), the vector's byte of the tile, its bytes that the lane
+    };                             // before has too (16: nothing to move, the part is shorter than a vector)
+    // runs: those the tile meets
+    HXT_HD RunLanes(uint32_t rb_, uint32_t col0_, uint32_t n_, uint32_t runs, FastDiv by_lanes) : rb(rb_), col0(col0_), n(n_), div(by_lanes)
+    {
+        const uint32_t part = rb - col0 < n ? rb - col0 : n;
+        lanes = (rb + 15) >> 4;
+        first = (part + 15) >> 4;
+        all = first + (runs > 1 ? (runs - 2) * lanes + ((n - ((runs - 1) * rb - col0) + 15) >> 4) : 0);
+    }
+    HXT_HD Lane lane(uint32_t i) const
+    {
+        const uint32_t q = i < first ? 0 : fast_div(i - first, div), dr = i < first ? 0 : q + 1;
+        const uint32_t k = i < first ? i : i - first - q * lanes;
+        const uint32_t start = dr * rb - col0;         // (below zero, wrapped, for the first run)
+        const uint32_t lo = dr ? start : 0, hi = start + rb < n ? start + rb : n, y = lo + 16 * k;
+        const uint32_t at = y + 16 < hi ? y : hi - 16;
+        return hi - lo < 16 ? Lane{dr, 0, 16} : Lane{dr, at, y - at};
+    }
+};
+
 constexpr int kMaxGroupTensors = 64;   // base pointers passed by value per launch
 
 struct TensorPlan {

@@ -1066,15 +1066,17 @@ __device__ __forceinline__ Sums2 rows_split_pieces(const Tile &t, const TensorDe
 // would lie if its first run went on and one where it would lie if its second run had begun earlier.  Both stay within the
 // view's extent unless the second run lies below the first one (or over it) in storage; the loads are then taken from within
 // the runs and shifted.
-// Receiving, every run (the part of it that is in this tile) gets as many lanes as it has vectors begun; the last of them
-// ends with the run, so that it stores some bytes a second time, with the same values, and a wave's store covers every run
+// Receiving, every run (the part of it that is in this tile) gets as many lanes as it has vectors begun (RunLanes); the last of
+// them ends with the run, so that it stores some bytes a second time, with the same values, and a wave's store covers every run
 // whole: each burst of the tensor side is written once, which counts as much as the width (stored with their last pieces
 // apart, 32 MiB of rows of 37 elements took 109 us instead of 27).  Only what a tile holds of its first or last run can be
 // shorter than a vector and goes byte by byte.
 // Rows of bf16 at odd pitches, 32 MiB, pack / unpack, in pieces of 2 bytes against vectors (tensors of three messages in
 // turn): 37 elements 18.8 / 36.8 -> 18.6 / 27.0 us, 101 elements 17.3 / 24.5 -> 16.3 / 20.4, 1003 elements 17.5 / 19.3 ->
 // 15.1 / 15.2.  Pieces of 4 bytes (101 f32) 15.0 / 17.8 against 16.0 / 16.6; of 8 bytes (100 bf16) 15.1 / 17.2 against 16.1 /
-// 18.8: sending, pieces of 4 and 8 bytes are the faster ones, receiving, those of 8.
+// 18.8: sending, pieces of 4 and 8 bytes are the faster ones, receiving, those of 8.  Rows much longer than a tile, 66 MB of
+// bf16 at odd pitches, unpack in pieces of 2 bytes against vectors: 50257 elements 29.6 -> 23.9 us, 151643 30.4 -> 23.6, a
+// million 30.2 -> 23.1 (with tags 36.6 -> 25.3, 36.2 -> 25.5, 36.7 -> 24.9).
 template <bool UNPACK, int CHECK, bool NTP, bool TWO_D>
 __device__ __forceinline__ Sums2 rows_split_vectors(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
@@ -1130,20 +1132,18 @@ __device__ __forceinline__ Sums2 rows_split_vectors(const Tile &t, const TensorD
         if (threadIdx.x < (n & 15u)) byte((nvec << 4) + threadIdx.x);            // only at the very end of the tensor
     } else {
         const uint32_t last = fast_div(runs.col0 + n - 1, runs.row_div);         // the tile meets runs row0 .. row0 + last
-        const uint32_t lanes = (rb + 15) >> 4, all = (last + 1) * lanes;
-        for (uint32_t i0 = threadIdx.x; i0 < all; i0 += kThreads * U) {
+        const RunLanes deal(rb, runs.col0, n, last + 1, td.lane_div);
+        for (uint32_t i0 = threadIdx.x; i0 < deal.all; i0 += kThreads * U) {
             u32x4 r[U];
-            uint32_t at[U], skip[U];                                // byte of the tile; bytes that the lane before has too (16: nothing to do)
+            uint32_t at[U], skip[U];
             uint8_t *to[U];
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u) {
-                const uint32_t i = min(i0 + u * kThreads, all - 1);
-                const uint32_t dr = fast_div(i, td.lane_div), start = dr * rb - runs.col0;       // (below zero, wrapped, for the first run)
-                const uint32_t lo = dr ? start : 0, hi = min(start + rb, n), y = lo + 16 * (i - dr * lanes);
-                const bool live = i0 + u * kThreads < all && y < hi && hi - lo >= 16;
-                at[u] = live ? min(y, hi - 16) : 0;
-                skip[u] = live ? y - at[u] : 16;
-                to[u] = user + runs.place(at[u] + runs.col0, dr);
+                const uint32_t i = i0 + u * kThreads;
+                const RunLanes::Lane l = deal.lane(min(i, deal.all - 1));
+                at[u] = l.at;
+                skip[u] = i < deal.all ? l.skip : 16;
+                to[u] = user + runs.place(at[u] + runs.col0, l.dr);
                 r[u] = load16_any<NTP>(pk + at[u]);
             }
 #pragma unroll

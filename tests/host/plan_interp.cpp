@@ -3,6 +3,7 @@
 // host planner (tile offsets, clipping at chunk borders, launch groups) before anything
 // runs on a GPU; it is compiled together with the planner source only, never with the
 // kernels, and is not part of the product.
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <vector>
@@ -270,4 +271,39 @@ extern "C" int launch_rules(const hxt_tensor_desc_t *descs, int n_tensors, int n
     *hints = (packed_nontemporal(-1, launch_bytes(p), false) ? 1u : 0u) | (packed_nontemporal(-1, launch_bytes(p), true) ? 2u : 0u) |
              (pass_nontemporal(-1, launch_bytes(p)) ? 4u : 0u);
     return HXT_OK;
+}
+
+// The lanes that a receiving tile of n bytes, which starts at byte col0 of a run of rb bytes, deals over the runs it meets:
+// every byte of a part of 16 bytes or more must be counted by exactly one lane, the vectors must stay inside their part, and
+// there may be no more lanes than the parts have vectors begun.  Returns the number of lanes, or -1.
+extern "C" int64_t run_lanes_check(uint32_t rb, uint32_t col0, uint32_t n)
+{
+    const uint32_t runs = uint32_t((uint64_t(col0) + n - 1) / rb) + 1;
+    const RunLanes d(rb, col0, n, runs, make_fastdiv((rb + 15) / 16));
+    std::vector<uint8_t> counted(n, 0);
+    uint64_t most = 0;
+    auto part = [&](uint64_t dr, int64_t &lo, int64_t &hi) {
+        lo = std::max<int64_t>(int64_t(dr * rb) - col0, 0);
+        hi = std::min<int64_t>(int64_t((dr + 1) * rb) - col0, n);
+    };
+    int64_t lo, hi;
+    for (uint64_t dr = 0; dr < runs; ++dr) {
+        part(dr, lo, hi);
+        most += uint64_t(hi - lo + 15) / 16;
+    }
+    if (d.all != most) return -1;
+    for (uint32_t i = 0; i < d.all; ++i) {
+        const RunLanes::Lane l = d.lane(i);
+        if (l.dr >= runs) return -1;
+        part(l.dr, lo, hi);
+        if (l.skip == 16 && hi - lo < 16 && l.at == 0) continue;
+        if (l.skip > 15 || l.at < lo || l.at + 16 > hi) return -1;
+        for (uint32_t b = l.skip; b < 16; ++b) ++counted[l.at + b];
+    }
+    for (uint64_t dr = 0; dr < runs; ++dr) {
+        part(dr, lo, hi);
+        for (int64_t b = lo; b < hi; ++b)
+            if (counted[b] != (hi - lo >= 16)) return -1;
+    }
+    return d.all;
 }

@@ -56,6 +56,17 @@ def test_rows_that_are_no_multiple_of_a_vector(run, gap, esize, off):
     check((7, run), (0, 1), esize, 1, 512, off)                                                    # the same run over and over
 
 
+# Runs longer than a tile of 16 KiB (bytes, gap): tiles inside one run, over the end of one with less and more than a vector
+# on either side.
+@pytest.mark.parametrize("run,gap,off", [(16385, 1, 0), (16399, 4, 1), (16401, 2, 0), (40001, 10, 3), (300007, 57, 0)])
+def test_rows_longer_than_a_tile(run, gap, off):
+    pitch = run + gap
+    for chunk in (256 * KiB, 40 * KiB + 256):
+        check((4, run), (pitch, 1), 1, 3, chunk, off)
+        check((2, 2, run), (pitch, 2 * pitch + 1, 1), 1, 2, chunk, off)       # the next run below this one in storage
+    check((3, run // 2), (pitch, 1), 2, 2, 64 * KiB, 2 * off)
+
+
 # (elements of a run, distance between them, element size, base off by): runs either side of 32 elements, whole numbers of
 # groups and not, distances with a path of their own (2 and 4, of 1 and 2 bytes) and without.
 APART = [(31, 2, 2, 0), (32, 2, 2, 0), (33, 2, 2, 2), (101, 2, 2, 0), (67, 4, 2, 6), (128, 4, 2, 0), (100, 3, 2, 0), (45, 2, 1, 1),

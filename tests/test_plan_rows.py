@@ -1,0 +1,27 @@
+"""Rows that are no multiple of 16 bytes, receiving: how a tile's lanes are dealt over the runs it meets, on the CPU."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from tests.test_plan_host import interp  # noqa: F401
+
+
+def lanes(interp, rb, col0, n):  # noqa: F811
+    interp.run_lanes_check.restype = C.c_int64
+    return interp.run_lanes_check(C.c_uint32(rb), C.c_uint32(col0), C.c_uint32(n))
+
+
+@pytest.mark.parametrize("rb", [16, 17, 31, 32, 33, 202, 4099, 16383, 16384, 16385, 40001, 300007, (1 << 30) - 1])
+def test_lanes_of_a_tile_are_those_of_its_bytes(interp, rb):  # noqa: F811
+    """Inside one run, over the end of one and over many; parts of less than a vector, of whole vectors and not.  No more
+    lanes than the parts have vectors begun (one a part beyond the tile's own), however long the runs are."""
+    rng = np.random.default_rng(rb)
+    starts = {0, 1, 15, 16, rb - 1, rb - 15, rb - 16, rb - 17, rb // 2, rb // 3} | {int(x) for x in rng.integers(0, rb, 6)}
+    for col0 in sorted(c for c in starts if 0 <= c < rb):
+        left = rb - col0
+        for n in sorted({1, 15, 16, 17, 256, 8448, 16384, left, left - 1, left + 1, left + 15, left + 16, left + 17}):
+            if 0 < n <= 1 << 16:
+                runs = (col0 + n - 1) // rb + 1
+                got = lanes(interp, rb, col0, n)
+                assert 0 < got <= n // 16 + runs, (rb, col0, n, got)
