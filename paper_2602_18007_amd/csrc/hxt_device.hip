@@ -592,35 +592,6 @@ int upload(hxt_plan_t &pl)
     return HXT_OK;
 }
 
-// Byte ranges of the packed buffer that staging moves for a lane selection.
-int stage_ranges(const Plan &p, int lane, uint64_t (*r)[2])
-{
-    auto used = [&](int l) -> uint64_t {
-        uint64_t n = p.lane_chunks[l];
-        if (n == 0) return 0;
-        return (n - 1) * p.B + p.chunk_padded((n - 1) * p.k + l);
-    };
-    if (lane >= 0) {
-        r[0][0] = p.lane_off[lane];
-        r[0][1] = used(lane);
-        return r[0][1] ? 1 : 0;
-    }
-    // all lanes: regions are adjacent; only the lane holding the last chunk can end short
-    if (p.C == 0) return 0;
-    const int ls = int((p.C - 1) % p.k);
-    const uint64_t cut = p.lane_off[ls] + used(ls), total = p.lane_off[p.k];
-    r[0][0] = 0;
-    if (cut == p.lane_off[ls + 1]) {
-        r[0][1] = total;
-        return 1;
-    }
-    r[0][1] = cut;
-    if (p.lane_off[ls + 1] == total) return 1;
-    r[1][0] = p.lane_off[ls + 1];
-    r[1][1] = total - p.lane_off[ls + 1];
-    return 2;
-}
-
 // Workgroups of the staging copy kernel: enough to keep the host link busy (it needs about 100 KB in flight;
 // measured 55 GB/s with 16 workgroups and with 4096), few enough to leave the chip to the kernels beside it.
 constexpr uint32_t kStageCopyGroups = 64;
@@ -663,29 +634,6 @@ int stage(const hxt_plan_t *plan, int lane, int64_t first_slot, int64_t n_slots,
         if (rc != HXT_OK) return rc;
     }
     return HXT_OK;
-}
-
-// The byte ranges of the packed buffer that the CPU-forwarding stream stages, in pieces: the host-to-device copy of a piece
-// starts when that piece is on the host, so that fewer bytes go with the other direction idle when a window of messages
-// (drain_every, or all of them) begins and ends.  8 x 56 MiB in windows of 4: 11.84 ms whole, 11.07 in 2 pieces, 10.87 in 3,
-// 10.86 in 4; 8 x 28 MiB 6.11, 5.74, 5.63, 5.71; 7 x 8 MiB 1.77, 1.70, 1.85, 2.21.  No more than 16 copies a direction and
-// window: with more outstanding the runtime stops overlapping the two directions (see drain_every).
-constexpr int kMostPieces = 3;
-int staging_pieces(const Plan &p, int window, uint64_t (*piece)[2])
-{
-    uint64_t r[2][2];
-    const int n = stage_ranges(p, -1, r);
-    int m = 0;
-    for (int i = 0; i < n; ++i) {
-        const int by_size = r[i][1] >= (uint64_t(24) << 20) ? 3 : (r[i][1] >= (uint64_t(8) << 20) ? 2 : 1);
-        const int cuts = std::max(1, std::min({by_size, kMostPieces, 16 / window}));
-        const uint64_t step = (r[i][1] / uint64_t(cuts) + HXT_ALIGN - 1) / HXT_ALIGN * HXT_ALIGN;
-        for (uint64_t o = 0; o < r[i][1]; o += step, ++m) {
-            piece[m][0] = r[i][0] + o;
-            piece[m][1] = std::min(step, r[i][1] - o);
-        }
-    }
-    return m;
 }
 
 // Batch: the messages that the uniform kernel can take (one contiguous tensor,
@@ -1392,9 +1340,9 @@ int hxt_exchange_stream(const hxt_plan_t *plan, const hxt_exchange_t *x)
     }
     const int nb = x->n_buffers;
     hxt_plan_t &pl = *const_cast<hxt_plan_t *>(plan);
-    uint64_t piece[2 * kMostPieces][2];
+    StagedCopy copy[kMostCopies];
     const int window = x->drain_every > 0 ? std::min(x->drain_every, x->n_messages) : x->n_messages;
-    const int n_pieces = fwd ? staging_pieces(p, window, piece) : 0;
+    const int n_copies = fwd ? staging_copies(p, window, copy) : 0, n_pieces = n_copies ? copy[n_copies - 1].piece + 1 : 0;
     // per buffer set: packed (pack done), drained (send buffer may be rewritten), landed (host buffer may be rewritten),
     // tags read (pinned tag buffer may be rewritten), staged (host copy of a piece complete; of the last one: drained too)
     enum { PACKED, DRAINED, LANDED, TAGS_READ, STAGED };
@@ -1435,11 +1383,13 @@ int hxt_exchange_stream(const hxt_plan_t *plan, const hxt_exchange_t *x)
         if (fwd) {
             if (!hip(hipStreamWaitEvent(ss, at(PACKED, b), 0))) break;
             if (i >= nb && !hip(hipStreamWaitEvent(ss, at(LANDED, b), 0))) break;
-            for (int q = 0; q < n_pieces && rc == HXT_OK; ++q) {
-                rc = copy_range(x->packed_send[b], x->host_pinned[b], piece[q][0], piece[q][1], hipMemcpyDeviceToHost,
-                                pl.stage_d2h_kernel > 0, ss);
+            for (int first = 0, end; first < n_copies && rc == HXT_OK; first = end) {        // a piece
+                const int q = copy[first].piece;
+                for (end = first; end < n_copies && copy[end].piece == q && rc == HXT_OK; ++end)
+                    rc = copy_range(x->packed_send[b], x->host_pinned[b], copy[end].off, copy[end].bytes, hipMemcpyDeviceToHost, pl.stage_d2h_kernel > 0, ss);
                 if (rc != HXT_OK || !hip(hipEventRecord(at(STAGED + q, b), ss)) || !hip(hipStreamWaitEvent(su, at(STAGED + q, b), 0))) break;
-                rc = copy_range(x->host_pinned[b], x->packed_recv[b], piece[q][0], piece[q][1], hipMemcpyHostToDevice, false, su);
+                for (int k = first; k < end && rc == HXT_OK; ++k)
+                    rc = copy_range(x->host_pinned[b], x->packed_recv[b], copy[k].off, copy[k].bytes, hipMemcpyHostToDevice, false, su);
             }
             if (rc != HXT_OK) break;
             if (!hip(hipEventRecord(at(LANDED, b), su))) break;       // straight after the copy: the next device-to-host copy waits on it

@@ -2,6 +2,8 @@
 #ifndef HXT_RULES_H
 #define HXT_RULES_H
 
+#include <algorithm>
+
 #include "hxt_internal.h"
 
 namespace hxt {
@@ -76,6 +78,75 @@ inline bool one_launch(const Plan &p)
 {
     return p.launches > 1 && p.tensors.size() <= size_t(kMaxGroupTensors) &&
            launch_bytes(p) <= (p.launches > 2 ? kOneLaunchLimit : kOneLaunchForTwoLimit);
+}
+
+// Byte ranges of the packed buffer that staging moves for a lane selection.
+inline int stage_ranges(const Plan &p, int lane, uint64_t (*r)[2])
+{
+    auto used = [&](int l) -> uint64_t {
+        uint64_t n = p.lane_chunks[l];
+        if (n == 0) return 0;
+        return (n - 1) * p.B + p.chunk_padded((n - 1) * p.k + l);
+    };
+    if (lane >= 0) {
+        r[0][0] = p.lane_off[lane];
+        r[0][1] = used(lane);
+        return r[0][1] ? 1 : 0;
+    }
+    // all lanes: regions are adjacent; only the lane holding the last chunk can end short
+    if (p.C == 0) return 0;
+    const int ls = int((p.C - 1) % p.k);
+    const uint64_t cut = p.lane_off[ls] + used(ls), total = p.lane_off[p.k];
+    r[0][0] = 0;
+    if (cut == p.lane_off[ls + 1]) {
+        r[0][1] = total;
+        return 1;
+    }
+    r[0][1] = cut;
+    if (p.lane_off[ls + 1] == total) return 1;
+    r[1][0] = p.lane_off[ls + 1];
+    r[1][1] = total - p.lane_off[ls + 1];
+    return 2;
+}
+
+// The copies in which the CPU-forwarding stream stages a message, in pieces of equal bytes: the host-to-device copies of a
+// piece start when that piece is on the host, so that fewer bytes go with the other direction idle when a window of messages
+// (drain_every, or all of them) begins and ends.  Whole against in pieces, windows of 4: 8 x 56 MiB in three 11.91 -> 10.92 ms,
+// 16 x 24 MiB in three 10.63 -> 9.81, 16 x 19 MiB in three 8.65 -> 8.08 (in two 8.20), 8 x 12 MiB in two 2.79 -> 2.66 (in three
+// 2.73), 16 x 10 MiB in two 4.73 -> 4.55; 8 MiB in two 3.93 -> 3.83, but also 4.07 -> 4.26 and 1.97 -> 2.19.
+// Cut only as far as the runtime still overlaps the two directions: with more outstanding a stream takes up to twice as long,
+// now and then or always.  No more than 16 copies a direction and window (a piece that lies in both ranges of the packed
+// buffer is two; 20 to 32: 13 MiB 5.65 -> 11.2 ms, 17 MiB 7.15 -> 13.3, 25 MiB 10.2 -> 11.4), and windows of more than 4
+// messages only from 24 MiB on (two pieces in windows of 8: 24 MiB 9.74 -> 9.33; of 5 to 8: 10 MiB 5.71 -> 5.99, 6.70 -> 8.54,
+// 7.66 -> 10.9, 4.36 -> 7.41, 16 MiB 8.81 -> 8.40 and 10.3 -> 9.93, but 11.7 -> 14.0 and 6.62 -> 8.54).
+constexpr int kMostPieces = 3, kMostCopies = kMostPieces + 1, kShortWindow = 4;
+constexpr uint64_t kTwoPieces = uint64_t(10) << 20, kThreePieces = uint64_t(14) << 20, kPiecesInLongWindows = uint64_t(24) << 20;
+
+struct StagedCopy {
+    uint64_t off, bytes;
+    int piece;
+};
+
+inline int staging_copies(const Plan &p, int window, StagedCopy *out)
+{
+    uint64_t r[2][2];
+    const int n = stage_ranges(p, -1, r);
+    if (n == 0) return 0;
+    const uint64_t total = r[0][1] + (n > 1 ? r[1][1] : 0);
+    int pieces = total >= kThreePieces ? kMostPieces : (total >= kTwoPieces ? 2 : 1);
+    if (window > kShortWindow) pieces = total >= kPiecesInLongWindows ? std::max(1, std::min(kMostPieces, 16 / window - (n - 1))) : 1;
+    const uint64_t step = (total / uint64_t(pieces) + HXT_ALIGN - 1) / HXT_ALIGN * HXT_ALIGN;
+    int m = 0;
+    uint64_t before = 0;                                   // bytes of the ranges ahead
+    for (int i = 0; i < n; ++i) {
+        for (uint64_t o = 0; o < r[i][1]; ++m) {
+            const uint64_t piece = (before + o) / step, end = std::min(r[i][1], (piece + 1) * step - before);
+            out[m] = StagedCopy{r[i][0] + o, end - o, int(piece)};
+            o = end;
+        }
+        before += r[i][1];
+    }
+    return m;
 }
 
 }  // namespace hxt

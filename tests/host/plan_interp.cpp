@@ -307,3 +307,18 @@ extern "C" int64_t run_lanes_check(uint32_t rb, uint32_t col0, uint32_t n)
     }
     return d.all;
 }
+
+// The copies in which the CPU-forwarding stream stages the message, as (offset, bytes, piece); ranges: how many the packed
+// buffer has.  Returns their number, or a negative hxt_status.
+extern "C" int staging_copies_of(const hxt_tensor_desc_t *descs, int n_tensors, int n_lanes, uint64_t chunk_bytes, int window,
+                                 uint64_t *out, int *ranges)
+{
+    Plan p;
+    if (int rc = build_plan(descs, n_tensors, n_lanes, chunk_bytes, kDefaultTileBytes, p); rc != HXT_OK) return rc;
+    uint64_t r[2][2];
+    StagedCopy copy[kMostCopies];
+    *ranges = stage_ranges(p, -1, r);
+    const int n = staging_copies(p, window, copy);
+    for (int i = 0; i < n; ++i) out[3 * i] = copy[i].off, out[3 * i + 1] = copy[i].bytes, out[3 * i + 2] = uint64_t(copy[i].piece);
+    return n;
+}

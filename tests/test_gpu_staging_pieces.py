@@ -11,9 +11,10 @@ MiB = 1 << 20
 
 
 @pytest.mark.parametrize("nbytes,messages,how", [
-    (8 * MiB - 256, 3, {}), (8 * MiB, 3, {}), (24 * MiB, 3, {}),                      # 1, 2 and 3 pieces
-    (25 * MiB + 300, 5, {"drain_every": 2}),                                          # pieces of unequal lengths, windows
-    (8 * MiB, 9, {}), (8 * MiB, 9, {"drain_every": 8}),                               # 16 copies a window at most
+    (10 * MiB - 256, 3, {}), (10 * MiB, 3, {}), (14 * MiB, 3, {}),                    # 1, 2 and 3 pieces (the planner's tests count them)
+    (25 * MiB + 300, 5, {"drain_every": 2}),                                          # 3 pieces, 4 copies: one piece lies in both ranges
+    (10 * MiB, 9, {"drain_every": 4}), (10 * MiB, 9, {}),                             # 2 pieces, and 1 in a window that is too long
+    (24 * MiB, 9, {"drain_every": 8}),                                                # 2 pieces, 16 copies a window
 ])
 @pytest.mark.parametrize("n_buffers", [1, 2])
 def test_messages_staged_in_pieces(nbytes, messages, how, n_buffers):
