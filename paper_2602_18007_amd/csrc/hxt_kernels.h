@@ -1072,18 +1072,18 @@ __device__ __forceinline__ Sums2 rows_split_pieces(const Tile &t, const TensorDe
 // apart, 32 MiB of rows of 37 elements took 109 us instead of 27).  Only what a tile holds of its first or last run can be
 // shorter than a vector and goes byte by byte.
 // Rows of bf16 at odd pitches, 32 MiB, pack / unpack, in pieces of 2 bytes against vectors (tensors of three messages in
-// turn): 37 elements 18.8 / 36.8 -> 18.6 / 27.0 us, 101 elements 17.3 / 24.5 -> 16.3 / 20.4, 1003 elements 17.5 / 19.3 ->
-// 15.1 / 15.2.  Pieces of 4 bytes (101 f32) 15.0 / 17.8 against 16.0 / 16.6; of 8 bytes (100 bf16) 15.1 / 17.2 against 16.1 /
-// 18.8: sending, pieces of 4 and 8 bytes are the faster ones, receiving, those of 8.  Rows much longer than a tile, 66 MB of
-// bf16 at odd pitches, unpack in pieces of 2 bytes against vectors: 50257 elements 29.6 -> 23.9 us, 151643 30.4 -> 23.6, a
-// million 30.2 -> 23.1 (with tags 36.6 -> 25.3, 36.2 -> 25.5, 36.7 -> 24.9).
+// turn): 37 elements 18.8 / 36.8 -> 18.9 / 24.8 us, 101 elements 17.3 / 24.2 -> 16.1 / 18.5, 1003 elements 17.3 / 19.3 ->
+// 15.4 / 14.8.  Pieces of 4 bytes: 101 f32 15.0 / 18.2 against 16.0 / 15.7, 102 bf16 unpack 21.2 against 18.6 (8 MiB 6.4 and
+// 6.5); of 8 bytes: 100 bf16 15.1 / 17.2 against 16.1 / 18.8: sending, pieces of 4 and 8 bytes are the faster ones, receiving,
+// those of 8.  Rows much longer than a tile, 66 MB of bf16 at odd pitches, unpack in pieces of 2 bytes against vectors: 50257
+// elements 29.6 -> 23.6 us, 151643 30.4 -> 23.6, a million 30.2 -> 23.0 (with tags 36.6 -> 25.3, 36.2 -> 25.5, 36.7 -> 24.9).
 template <bool UNPACK, int CHECK, bool NTP, bool TWO_D>
 __device__ __forceinline__ Sums2 rows_split_vectors(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
     const RunsOf<TWO_D> runs(t, td);
     const uint32_t rb = runs.row_bytes, n = t.n0;
     Sums2 acc{0, 0};
-    constexpr uint32_t U = kUnroll;
+    constexpr uint32_t U = UNPACK ? RunLanes::PER_THREAD : kUnroll;
     auto byte = [&](uint32_t i) {                                   // byte i of the tile alone
         const uint32_t x = runs.col0 + i, dr = fast_div(x, runs.row_div);
         uint8_t *at = user + runs.place(x, dr);
@@ -1162,7 +1162,7 @@ __device__ __forceinline__ Sums2 rows_split_vectors(const Tile &t, const TensorD
     return acc;
 }
 
-template <bool UNPACK, int CHECK, bool NTP>
+template <bool UNPACK, int CHECK, bool NTP, bool PIECES_LIKELY>
 __device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
     // widest piece that is naturally aligned everywhere: low bits of the base address, the run length and the pitches
@@ -1171,7 +1171,7 @@ __device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &
         return td.ndim == 2 ? rows_split_pieces<UNPACK, CHECK, NTP, G, true>(t, td, user, pk)
                             : rows_split_pieces<UNPACK, CHECK, NTP, G, false>(t, td, user, pk);
     };
-    if (low == 0) return pieces.template operator()<8>();
+    if (PIECES_LIKELY ? __builtin_expect(low == 0, 1) : low == 0) return pieces.template operator()<8>();
     if constexpr (!UNPACK)
         if ((low & 3u) == 0) return pieces.template operator()<4>();
     return td.ndim == 2 ? rows_split_vectors<UNPACK, CHECK, NTP, true>(t, td, user, pk)
@@ -1186,7 +1186,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict_
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP, false>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 
@@ -2028,7 +2028,11 @@ __global__ __launch_bounds__(kThreads) void k_message(const Tile *__restrict__ t
         }
         break;
     case K_ROWS: acc = rows_tile<UNPACK, CHECK, NTU, NTP>(t, td, base, pk); break;
-    case K_ROWS_SPLIT: acc = rows_split_any<UNPACK, CHECK, NTP>(t, td, base, pk); break;
+    case K_ROWS_SPLIT:
+        // (receiving, pieces are named as the likely way, or the code of the vectors around them slows them down: 7 MB in four
+        // kinds of view with tags, unpack 10.7 us against 10.2; sending it is the other way round, 10.5 against 11.1)
+        acc = rows_split_any<UNPACK, CHECK, NTP, UNPACK>(t, td, base, pk);
+        break;
     case K_TRANSPOSE:
         acc = by_size([&]<typename E>() { return transpose_any<E, UNPACK, CHECK, NTU, NTP>(t, base, packed, ck, lds_raw); });
         break;

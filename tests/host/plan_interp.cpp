@@ -275,12 +275,13 @@ extern "C" int launch_rules(const hxt_tensor_desc_t *descs, int n_tensors, int n
 
 // The lanes that a receiving tile of n bytes, which starts at byte col0 of a run of rb bytes, deals over the runs it meets:
 // every byte of a part of 16 bytes or more must be counted by exactly one lane, the vectors must stay inside their part, and
-// there may be no more lanes than the parts have vectors begun.  Returns the number of lanes, or -1.
-extern "C" int64_t run_lanes_check(uint32_t rb, uint32_t col0, uint32_t n)
+// there may be no more lanes than the parts have vectors begun.  Returns the number of lanes, or -1; rounds: of the kernel.
+extern "C" int64_t run_lanes_check(uint32_t rb, uint32_t col0, uint32_t n, uint32_t *rounds)
 {
     const uint32_t runs = uint32_t((uint64_t(col0) + n - 1) / rb) + 1;
     const RunLanes d(rb, col0, n, runs, make_fastdiv((rb + 15) / 16));
     std::vector<uint8_t> counted(n, 0);
+    *rounds = (d.all + 256 * RunLanes::PER_THREAD - 1) / (256 * RunLanes::PER_THREAD);
     uint64_t most = 0;
     auto part = [&](uint64_t dr, int64_t &lo, int64_t &hi) {
         lo = std::max<int64_t>(int64_t(dr * rb) - col0, 0);

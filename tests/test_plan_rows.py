@@ -8,8 +8,10 @@ from tests.test_plan_host import interp  # noqa: F401
 
 
 def lanes(interp, rb, col0, n):  # noqa: F811
+    """(lanes, rounds of the kernel)"""
     interp.run_lanes_check.restype = C.c_int64
-    return interp.run_lanes_check(C.c_uint32(rb), C.c_uint32(col0), C.c_uint32(n))
+    rounds = C.c_uint32(0)
+    return interp.run_lanes_check(C.c_uint32(rb), C.c_uint32(col0), C.c_uint32(n), C.byref(rounds)), rounds.value
 
 
 @pytest.mark.parametrize("rb", [16, 17, 31, 32, 33, 202, 4099, 16383, 16384, 16385, 40001, 300007, (1 << 30) - 1])
@@ -23,5 +25,12 @@ def test_lanes_of_a_tile_are_those_of_its_bytes(interp, rb):  # noqa: F811
         for n in sorted({1, 15, 16, 17, 256, 8448, 16384, left, left - 1, left + 1, left + 15, left + 16, left + 17}):
             if 0 < n <= 1 << 16:
                 runs = (col0 + n - 1) // rb + 1
-                got = lanes(interp, rb, col0, n)
+                got = lanes(interp, rb, col0, n)[0]
                 assert 0 < got <= n // 16 + runs, (rb, col0, n, got)
+
+
+@pytest.mark.parametrize("rb", [64, 65, 79, 101, 202, 204, 404, 2006, 4099, 8193, 16385, 100514])
+def test_a_whole_tile_takes_one_round(interp, rb):  # noqa: F811
+    """However it lies in its runs, a tile of 16 KiB: a second round would be for a few dozen lanes alone."""
+    for col0 in range(0, rb, max(1, rb // 97)):
+        assert lanes(interp, rb, col0, 16384)[1] == 1, (rb, col0)
