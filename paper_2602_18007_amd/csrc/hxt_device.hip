@@ -237,12 +237,22 @@ template <bool UNPACK, int CHECK>
 void launch_rows_split(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck,
                        hipStream_t st)
 {
-    auto go = [&]<bool NTP>() {
-        k_rows_split<UNPACK, CHECK, NTP><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
-                                                                       g.tensor_base, b, packed, ck);
+    bool pieces = true;                                      // of all tensors
+    for (uint32_t i = 0; i < g.n_tensors; ++i)
+        if (pl.p.tensors[g.tensor_base + i].kind == K_ROWS_SPLIT)
+            pieces = pieces && in_pieces<UNPACK>(uint32_t(reinterpret_cast<uintptr_t>(b.p[i])) | pl.p.tdev[g.tensor_base + i].low_or);
+    auto go = [&]<bool NTP, bool ALL_PIECES>() {
+        k_rows_split<UNPACK, CHECK, NTP, ALL_PIECES><<<g.count, kThreads, 0, st>>>(pl.d_tiles + g.first, pl.d_chunk_tiles, pl.d_tensors,
+                                                                                   g.tensor_base, b, packed, ck);
     };
-    if (packed_nontemporal(pl, UNPACK)) go.template operator()<true>();
-    else go.template operator()<false>();
+    const bool ntp = packed_nontemporal(pl, UNPACK);
+    if (pieces) {
+        if (ntp) go.template operator()<true, true>();
+        else go.template operator()<false, true>();
+    } else {
+        if (ntp) go.template operator()<true, false>();
+        else go.template operator()<false, false>();
+    }
 }
 
 template <bool UNPACK, int CHECK>

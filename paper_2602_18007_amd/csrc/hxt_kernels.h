@@ -1162,7 +1162,11 @@ __device__ __forceinline__ Sums2 rows_split_vectors(const Tile &t, const TensorD
     return acc;
 }
 
-template <bool UNPACK, int CHECK, bool NTP, bool PIECES_LIKELY>
+// Whether a tensor goes in pieces: low is its base address and TensorDev::low_or ORed.
+template <bool UNPACK>
+HXT_HD bool in_pieces(uint32_t low) { return (low & (UNPACK ? 7u : 3u)) == 0; }
+
+template <bool UNPACK, int CHECK, bool NTP, bool PIECES_LIKELY, bool ALL_PIECES = false>
 __device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *pk)
 {
     // widest piece that is naturally aligned everywhere: low bits of the base address, the run length and the pitches
@@ -1171,14 +1175,19 @@ __device__ __forceinline__ Sums2 rows_split_any(const Tile &t, const TensorDev &
         return td.ndim == 2 ? rows_split_pieces<UNPACK, CHECK, NTP, G, true>(t, td, user, pk)
                             : rows_split_pieces<UNPACK, CHECK, NTP, G, false>(t, td, user, pk);
     };
+    if constexpr (ALL_PIECES && UNPACK) return pieces.template operator()<8>();
     if (PIECES_LIKELY ? __builtin_expect(low == 0, 1) : low == 0) return pieces.template operator()<8>();
+    if constexpr (ALL_PIECES) return pieces.template operator()<4>();
     if constexpr (!UNPACK)
-        if ((low & 3u) == 0) return pieces.template operator()<4>();
+        if (in_pieces<UNPACK>(low)) return pieces.template operator()<4>();
     return td.ndim == 2 ? rows_split_vectors<UNPACK, CHECK, NTP, true>(t, td, user, pk)
                         : rows_split_vectors<UNPACK, CHECK, NTP, false>(t, td, user, pk);
 }
 
-template <bool UNPACK, int CHECK, bool NTP>
+// ALL_PIECES: every tensor of the launch goes in pieces.  (A kernel of their own, as the code of the vectors beside them slows
+// them down: rows of 200 bytes, 8 MB, pack / unpack, 6.00 / 6.18 -> 5.81 / 5.95 us; with tags 16 MB 10.37 / 12.68 -> 9.97 /
+// 12.41; in three dims 4 MB 5.54 / 6.03 -> 5.41 / 5.56.)
+template <bool UNPACK, int CHECK, bool NTP, bool ALL_PIECES>
 __global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict__ tiles,
                                                          const uint32_t *__restrict__ chunk_tiles,
                                                          const TensorDev *__restrict__ tensors, uint32_t tensor_base,
@@ -1186,7 +1195,7 @@ __global__ __launch_bounds__(kThreads) void k_rows_split(const Tile *__restrict_
 {
     const Tile t = tiles[blockIdx.x];
     const TagRegs got = prefetch_check<UNPACK, CHECK>(ck, t.chunk);
-    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP, false>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
+    const Sums2 acc = t.kind == K_ZERO ? pad_tile<UNPACK, CHECK>(t, packed) : rows_split_any<UNPACK, CHECK, NTP, false, ALL_PIECES>(t, tensors[tensor_base + t.tensor], bases.p[t.tensor], packed + t.packed_off);
     commit_tile<UNPACK, CHECK>(acc, t, chunk_tiles, ck, got);
 }
 

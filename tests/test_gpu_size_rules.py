@@ -68,9 +68,11 @@ def test_elements_written_through_either_side_of_their_limits(esize, nbytes):
 
 @pytest.mark.parametrize("hint", [0, 1])
 @pytest.mark.parametrize("rows", [((300, 101, 107, 1),), ((300, 101, 107, 2), (70, 33, 40, 2)), ((300, 101, 107, 1), (70, 101, 107, 4)),
-                                  ((300, 102, 106, 2), (41, 35, 36, 1)), ((300, 102, 106, 8),)], ids=lambda r: "esizes_" + "_".join(str(x[3]) for x in r))
+                                  ((300, 102, 106, 2), (41, 35, 36, 1)), ((300, 102, 106, 8),),
+                                  ((300, 100, 104, 2), (41, 35, 36, 1)), ((300, 100, 104, 2), (70, 102, 106, 2))], ids=lambda r: "rows_of_" + "_".join(str(x[1] * x[3]) for x in r))
 def test_rows_of_odd_lengths_by_the_pieces_they_go_in(rows, hint):
-    """Sends whose runs all go in pieces of 1 or 2 bytes have a kernel of their own; with a wider one among them they don't."""
+    """Runs go in pieces of 8 bytes (sending, of 4 too) or in vectors; messages whose runs all go in pieces have a kernel of
+    their own, and with others among them they don't."""
     case = Case("odd_rows", tuple(((n, c), (p, 1), e) for n, c, p, e in rows), 3, 1 << 16)
     say("case", rows)
     round_trip_check(case, make_storages(case, 5), hint=hint)
