@@ -256,17 +256,12 @@ void launch_rows_split(const hxt_plan_t &pl, const Group &g, const BasePtrs &b, 
 }
 
 template <bool UNPACK, int CHECK>
-void launch_generic(const hxt_plan_t &pl, uint32_t first, uint32_t count, uint32_t tensor_base, uint32_t n_tensors, int esize,
+void launch_generic(const hxt_plan_t &pl, uint32_t first, uint32_t count, uint32_t tensor_base, bool apart, int esize,
                     const BasePtrs &b, uint8_t *packed, const CheckArgs<CHECK> &ck, hipStream_t st)
 {
     const Tile *tiles = pl.d_tiles + first;
     const uint32_t *ct = pl.d_chunk_tiles;
     const TensorDev *td = pl.d_tensors;
-    bool apart = false;
-    for (uint32_t i = tensor_base; !UNPACK && i < tensor_base + n_tensors; ++i) {
-        const TensorPlan &t = pl.p.tensors[i];
-        apart |= t.kind == K_GENERIC && t.esize == esize && takes_apart(size_t(esize), t.shape[t.ndim - 1], uint64_t(t.stride[t.ndim - 1]) * uint64_t(esize));
-    }
     auto go = [&]<bool NTP, bool THROUGH, bool APART>() {
         switch (esize) {
         case 1: k_generic<uint8_t, UNPACK, CHECK, NTP, THROUGH, APART><<<count, kThreads, 0, st>>>(tiles, ct, td, tensor_base, b, packed, ck); break;
@@ -442,7 +437,7 @@ int run_groups(hxt_plan_t &pl, void *const *ptrs, uint8_t *packed, const CheckAr
                 else if (g.kernel == K_TRANSPOSE_SPAN)
                     launch_transpose_span<UNPACK, CHECK>(ntp, pl.d_tiles + g.first + i, j - i, es, pl.d_chunk_tiles, pl.d_inc, p.geom, b, packed, ck, st);
                 else
-                    launch_generic<UNPACK, CHECK>(pl, g.first + i, j - i, g.tensor_base, g.n_tensors, es, b, packed, ck, st);
+                    launch_generic<UNPACK, CHECK>(pl, g.first + i, j - i, g.tensor_base, (g.apart & uint32_t(es)) != 0, es, b, packed, ck, st);
                 i = j;
             }
         }

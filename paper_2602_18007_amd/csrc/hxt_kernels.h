@@ -1853,13 +1853,6 @@ struct Apart {
     }
 };
 
-// Runs of fewer than 32 elements have too many neighbours that are not of one run (4 M bf16 in runs of 9: 11.0 -> 16.3 us;
-// of 32: 10.7 -> 8.8).
-HXT_HD bool takes_apart(size_t esize, int64_t run, uint64_t step)
-{
-    return esize <= 2 && run >= 32 && (step == 2 * esize || step == 4 * esize);
-}
-
 template <typename E, uint32_t S, int CHECK, bool NTP, bool THROUGH, int ND>
 __device__ __forceinline__ Sums2 send_apart(const TensorDev &td, uint64_t e0, uint32_t nel, const uint8_t *user, E *p, uint64_t in_chunk)
 {

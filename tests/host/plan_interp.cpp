@@ -323,3 +323,14 @@ extern "C" int staging_copies_of(const hxt_tensor_desc_t *descs, int n_tensors, 
     for (int i = 0; i < n; ++i) out[3 * i] = copy[i].off, out[3 * i + 1] = copy[i].bytes, out[3 * i + 2] = uint64_t(copy[i].piece);
     return n;
 }
+
+// The element sizes whose tensors are sent as elements a few apart, ORed over the launches of the message's per-element
+// tensors (a bit a size).  Returns them, or a negative hxt_status.
+extern "C" int apart_sizes(const hxt_tensor_desc_t *descs, int n_tensors, int n_lanes, uint64_t chunk_bytes)
+{
+    Plan p;
+    if (int rc = build_plan(descs, n_tensors, n_lanes, chunk_bytes, kDefaultTileBytes, p); rc != HXT_OK) return rc;
+    uint32_t sizes = 0;
+    for (const Group &g : p.groups) sizes |= g.apart;
+    return int(sizes);
+}

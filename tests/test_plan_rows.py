@@ -1,10 +1,12 @@
-"""Rows that are no multiple of 16 bytes, receiving: how a tile's lanes are dealt over the runs it meets, on the CPU."""
+"""What the planner lays down for rows that are no multiple of 16 bytes (how a receiving tile's lanes are dealt over the runs it
+meets) and for elements a few apart, on the CPU."""
 import ctypes as C
 
 import numpy as np
 import pytest
 
-from tests.test_plan_host import interp  # noqa: F401
+from tests.cases import Case, contig
+from tests.test_plan_host import describe, interp  # noqa: F401
 
 
 def lanes(interp, rb, col0, n):  # noqa: F811
@@ -34,3 +36,16 @@ def test_a_whole_tile_takes_one_round(interp, rb):  # noqa: F811
     """However it lies in its runs, a tile of 16 KiB: a second round would be for a few dozen lanes alone."""
     for col0 in range(0, rb, max(1, rb // 97)):
         assert lanes(interp, rb, col0, 16384)[1] == 1, (rb, col0)
+
+
+# (elements of a run, distance between them, element size): the ones sent as elements a few apart
+@pytest.mark.parametrize("views,sizes", [
+    (((32, 2, 2),), 2), (((32, 4, 1),), 1), (((32, 2, 2), (32, 2, 1)), 3),
+    (((31, 2, 2),), 0), (((32, 3, 2),), 0), (((32, 2, 4),), 0), (((32, 8, 1),), 0),
+    (((31, 2, 2), (40, 4, 1)), 1),                           # of one size, a launch of the other has none
+    (((31, 2, 2), (100, 2, 2)), 2),                          # one of them is enough for a launch
+])
+def test_the_plan_says_which_launches_have_elements_a_few_apart(interp, views, sizes):  # noqa: F811
+    case = Case("apart", tuple(((9, n), (n * step + 5, step), es) for n, step, es in views) + (contig((100,), 2),), 3, 4096)
+    descs, keep = describe(case)
+    assert interp.apart_sizes(descs, len(case.tensors), case.k, C.c_uint64(case.B)) == sizes
