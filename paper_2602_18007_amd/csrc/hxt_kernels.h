@@ -1818,7 +1818,7 @@ __device__ __forceinline__ Sums2 generic_span(const TensorDev &td, uint64_t e0, 
     return acc;
 }
 
-// Sending elements that lie S = 2 or 4 apart: M = 16 / (S * element size) neighbours of a run are read as one vector, so that
+// Sending elements (of 1 or 2 bytes) that lie S = 2 or 4 apart: M = 16 / (S * element size) neighbours of a run are read as one vector, so that
 // a wave's load is contiguous, picked out of the registers and stored side by side, 16 / S bytes.  The vector starts with the
 // first of them; where they are the last of their run it ends with the last of them instead (what lies behind need not be
 // the view's); neighbours that are not of one run are read one by one.
@@ -1832,7 +1832,7 @@ template <typename E, uint32_t S>
 struct Apart {
     static constexpr uint32_t ES = sizeof(E), M = 16 / (S * ES), BYTES = M * ES, BEHIND = (S - 1) * ES;
     using P = std::conditional_t<BYTES == 8, uint64_t, uint32_t>;
-    static_assert(BYTES == sizeof(P));
+    static_assert(ES <= 2 && BYTES == sizeof(P));
     // The elements at bytes 0, S * ES, 2 * S * ES ... of a vector.
     static __device__ __forceinline__ P pick(u32x4 v)
     {
@@ -1840,10 +1840,7 @@ struct Apart {
             if constexpr (ES == 2) return __builtin_amdgcn_perm(b, a, 0x05040100u);
             else return S == 2 ? __builtin_amdgcn_perm(b, a, 0x06040200u) : __builtin_amdgcn_perm(b, a, 0x0C0C0400u);      // (0x0C: zero)
         };
-        if constexpr (ES == 4) {
-            if constexpr (S == 2) return uint64_t(v.z) << 32 | v.x;
-            else return v.x;
-        } else if constexpr (ES == 2) {
+        if constexpr (ES == 2) {
             if constexpr (S == 2) return uint64_t(two(v.z, v.w)) << 32 | two(v.x, v.y);
             else return two(v.x, v.z);
         } else {

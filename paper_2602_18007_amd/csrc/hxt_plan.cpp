@@ -155,8 +155,8 @@ static Kind classify(const TensorPlan &t, uint64_t chunk_bytes)
         for (int d = 0; d < last; ++d)
             ok = ok && (uint64_t(t.stride[d]) * t.esize) % 16 == 0 && t.shape[d] < (int64_t(1) << 31);
         if (ok) return K_ROWS;
-        // runs or pitches that are not multiples of 16 bytes: still a gather of runs, with the tensor side
-        // accessed in narrower pieces, as long as a 16-byte vector meets at most one run boundary
+        // runs or pitches that are not multiples of 16 bytes: still a gather of runs, in narrower pieces or in vectors put
+        // together across runs, as long as a 16-byte vector meets at most one run boundary
         bool split = row_bytes >= 16 && row_bytes < (1u << 30) && rows < (1u << 31);
         for (int d = 0; d < last; ++d) split = split && t.shape[d] < (int64_t(1) << 31);
         return split ? K_ROWS_SPLIT : K_GENERIC;
