@@ -172,15 +172,22 @@ static Kind classify(const TensorPlan &t, uint64_t chunk_bytes)
     if (classic || strided) {
         const bool tall = uint64_t(t.shape[last]) * t.esize * transpose_tile(uint32_t(t.esize)) <= chunk_bytes;
         // Chunks that do not hold whole numbers of tile rows clip the tiles at their borders, down to single rows, and a
-        // clipped tile takes as long as a full one.  Tensors of more than 10 MiB, where tiles wait for their turn on the
-        // chip, get tiles that span chunks if that leaves out a fifth of them or more.  bf16 [4000, 4000], pack + unpack:
+        // clipped tile takes as long as a full one.  Tensors of more than 10 MiB (some 14 or 18, below), where tiles
+        // wait for their turn on the chip, get tiles that span chunks if that leaves out a fifth of them or more.  bf16 [4000, 4000], pack + unpack:
         // chunks of 1 MiB 48.7 -> 31.4 us (with tags 56.3 -> 35.2), 4 MiB 35.4 -> 32.4, 8 MiB (22 % more tiles) 32.9 either
         // way, one chunk 29.2 inside and 31.9 spanning; f32 [4, 1000, 1500] with 1 MiB 26.8 -> 24.9.  Smaller tensors are
         // all on the chip at once, and smaller tiles are then done sooner: [2100, 2104] bf16 (8.4 MiB) 19.9 inside, 21.8
-        // spanning, [2500, 2504] (11.9 MiB) 24.7 and 22.7; f32 [2100, 1050] 16.4 and 16.8, [2500, 1250] 22.3 and 18.8.
+        // spanning, [2500, 2504] (11.9 MiB) 24.7 and 22.7; f32 [2100, 1050] 16.4 and 16.8, [2500, 1250] 22.3 and 18.8; bytes [3400,
+        // 3404] (11.0 MiB) 30.7 and 23.1.  Tiles of 8-byte elements wait from 18 MiB on (chunks of 1 MiB, inside and spanning, sums
+        // / tags: 10 MiB 17.8 / 19.5 and 22.4 / 26.3 us, 15 MiB 21.2 / 23.2 and 22.5 / 27.0, 17.2 MiB 23.4 / 27.0 and 23.0 / 27.1,
+        // 18.4 MiB 1.07 / 1.02 times faster spanning, 19.6 MiB 29.2 / 31.9 and 21.1 / 25.5); bytes a few apart, whose tiles go element
+        // by element and look for the chunk border at each, from 14 MiB on (every other: 11 MiB 49.3 and 51.6, 13.8 MiB 6 % slower
+        // spanning, 15.3 MiB 70.4 and 55.8, 47 MiB 189 and 148; 16.8 MiB 2 to 6 % slower, as its tiles fall).  Larger tensors lose
+        // now and then by the tiles of their last round (f32 34 MiB 5 %, but 30 MiB gain 20 % and 52 MiB 10 %).
         const uint64_t T = transpose_tile(uint32_t(t.esize));
         const uint64_t I = t.shape[last - 1], J = t.shape[last], whole = t.elems / (I * J) * ((I + T - 1) / T) * ((J + T - 1) / T);
-        const bool clipped = t.bytes > (uint64_t(10) << 20) && 4 * tiles_inside_chunks(t, chunk_bytes) > 5 * whole;
+        const uint64_t wait_from = uint64_t(t.esize == 8 && classic ? 18 : (t.esize == 1 && strided ? 14 : 10)) << 20;
+        const bool clipped = t.bytes > wait_from && 4 * tiles_inside_chunks(t, chunk_bytes) > 5 * whole;
         if (tall && !(clipped && chunk_bytes >= 1024)) return K_TRANSPOSE;
         if (chunk_bytes >= 1024) return K_TRANSPOSE_SPAN;
         if (classic) return K_TRANSPOSE;

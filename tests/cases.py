@@ -107,11 +107,14 @@ def three_launch_case(stream_bytes: int) -> Case:
                                                      ((128, 128), (1, 128), 4)), 4, 1 << 20)
 
 
-# Transposes of more than 10 MiB with clipped tiles and without, and one below: (shape, strides, element size, chunk bytes).
+# Transposes of more than 10 MiB with clipped tiles and without, and one below; either side of 18 MiB for 8-byte elements and of
+# 14 for bytes a few apart: (shape, strides, element size, chunk bytes).
 CLIPPED_TRANSPOSES = [
     ((2290, 2293), (1, 2290), 2, 640 << 10), ((2288, 2290), (1, 2288), 2, 640 << 10),      # 14 KB above 10 MiB, 7 KB below
     ((2, 1300, 1100), (1100 * 1301 + 5, 1, 1301), 4, 700 << 10), ((2560, 2560), (1, 2560), 2, 640 << 10),
     ((3500, 3100), (1, 3503), 1, 500 << 10), ((1200, 1200), (2, 2403), 8, 1 << 20),
+    ((1535, 1536), (1, 1536), 8, 1 << 20), ((1536, 1537), (1, 1536), 8, 1 << 20),
+    ((3830, 3830), (2, 7661), 1, 1 << 20), ((3832, 3832), (2, 7665), 1, 1 << 20),
 ]
 
 ONE_LAUNCH_LIMITS = {two_launch_case: 12 << 20, three_launch_case: 64 << 20}     # of messages of two launches, of more

@@ -10,7 +10,7 @@ from tests.test_plan_host import interp, oracle_msg, run_interp  # noqa: F401
 INSIDE, ACROSS = 3, 7
 
 
-@pytest.mark.parametrize("view,kind", list(zip(CLIPPED_TRANSPOSES, [ACROSS, INSIDE, ACROSS, INSIDE, ACROSS, ACROSS])))
+@pytest.mark.parametrize("view,kind", list(zip(CLIPPED_TRANSPOSES, [ACROSS, INSIDE, ACROSS, INSIDE, ACROSS, ACROSS, INSIDE, ACROSS, INSIDE, ACROSS])))
 def test_large_transposes(interp, view, kind):  # noqa: F811
     shape, strides, esize, chunk = view
     case = Case("transpose", ((shape, strides, esize),), 3, chunk)
