@@ -180,12 +180,24 @@ struct RunLanes {
     }
 };
 
-// Whether a tensor of the per-element kernel whose last dim has `run` elements `step` bytes apart is sent by send_apart.
-// Runs of fewer than 32 elements have too many neighbours that are not of one run (4 M bf16 in runs of 9: 11.0 -> 16.3 us;
-// of 32: 10.7 -> 8.8).
-HXT_HD bool takes_apart(size_t esize, int64_t run, uint64_t step)
+// Whether a tensor of the per-element kernel whose last dim has `run` elements `step` bytes apart is sent by send_apart, which
+// takes 16 / step neighbours at a time.  Where these are not all of one run it reads them one by one, and a wave with one
+// such lane waits for all of them: views of several dims go this way if runs are whole numbers of neighbours, or so long
+// that few waves meet the end of one.  Sends of 2, 8 and 32 MiB element by element against this, pitches 3 elements more:
+//   whole numbers: bytes every other, runs of 16 9.7 -> 7.2, 15.8 -> 9.1, 44 -> 24 us, every fourth, of 12 11.6 -> 9.4, 16.8 -> 13.1,
+//     48 -> 38; bf16 every other, of 12 7.2 -> 7.3, 10.5 -> 9.0, 27 -> 24, of 200 7.1 -> 7.1, 10.3 -> 8.4, 27 -> 22 (runs of 8 were not
+//     measured);
+//   others: bytes every other, runs of 101 11.2 -> 17.9, 15.6 -> 20.3, 44 -> 43, of 1002 10.6 -> 15.0, 15.4 -> 17.3, 44 -> 39, of 4098
+//     10.9 -> 9.8, 15.4 -> 11.4, 44 -> 28; every fourth, of 101 12.1 -> 20.0, 16.8 -> 25.7, 47 -> 58, of 4098 11.5 -> 10.3, 16.4 -> 13.5, 46
+//     -> 37; bf16 every other, of 101 7.7 -> 12.0, 10.4 -> 14.9, 27 -> 34, of 2002 7.3 -> 7.5, 10.3 -> 8.9, 26 -> 23, of 4098 7.5 -> 7.3,
+//     10.3 -> 8.6, 26 -> 22;
+//   two neighbours at a time (bf16 every fourth) do not pay in several dims: runs of 1024 7.9 -> 9.2, 11.8 -> 11.4, 34.2 -> 34.2.
+HXT_HD bool takes_apart(size_t esize, int ndim, int64_t run, uint64_t step)
 {
-    return esize <= 2 && run >= 32 && (step == 2 * esize || step == 4 * esize);
+    if (esize > 2 || (step != 2 * esize && step != 4 * esize)) return false;
+    if (ndim == 1) return run >= 32;
+    const int64_t m = int64_t(16 / step);
+    return m > 2 && ((run >= 12 && run % m == 0) || run >= 4096);
 }
 
 constexpr int kMaxGroupTensors = 64;   // base pointers passed by value per launch

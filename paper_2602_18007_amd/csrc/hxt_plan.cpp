@@ -438,7 +438,7 @@ int build_plan(const hxt_tensor_desc_t *descs, int n_tensors, int n_lanes, size_
                 Tile t = v[i].t;
                 t.tensor = v[i].tensor_abs - g.tensor_base;
                 g.n_tensors = std::max(g.n_tensors, t.tensor + 1);
-                if (const TensorPlan &tp = p.tensors[v[i].tensor_abs]; t.kind == K_GENERIC && takes_apart(tp.esize, tp.shape[tp.ndim - 1], uint64_t(tp.stride[tp.ndim - 1]) * tp.esize))
+                if (const TensorPlan &tp = p.tensors[v[i].tensor_abs]; t.kind == K_GENERIC && takes_apart(tp.esize, tp.ndim, tp.shape[tp.ndim - 1], uint64_t(tp.stride[tp.ndim - 1]) * tp.esize))
                     g.apart |= uint32_t(tp.esize);
                 if (kern == K_TRANSPOSE_SPAN) {              // one arrival at every chunk the tile touches
                     for (uint32_t e = 0; e < t.ordinal; ++e) {

@@ -67,10 +67,11 @@ def test_rows_longer_than_a_tile(run, gap, off):
     check((3, run // 2), (pitch, 1), 2, 2, 64 * KiB, 2 * off)
 
 
-# (elements of a run, distance between them, element size, base off by): runs either side of 32 elements, whole numbers of
-# groups and not, distances with a path of their own (2 and 4, of 1 and 2 bytes) and without.
+# (elements of a run, distance between them, element size, base off by): runs either side of 32 elements, the shortest and
+# the long ones, whole numbers of groups and not, distances with a path of their own (2 and 4, of 1 and 2 bytes) and without.
 APART = [(31, 2, 2, 0), (32, 2, 2, 0), (33, 2, 2, 2), (101, 2, 2, 0), (67, 4, 2, 6), (128, 4, 2, 0), (100, 3, 2, 0), (45, 2, 1, 1),
-         (77, 4, 1, 3), (64, 5, 1, 0), (50, 2, 4, 4), (40, 4, 4, 0), (37, 2, 8, 8)]
+         (77, 4, 1, 3), (64, 5, 1, 0), (50, 2, 4, 4), (40, 4, 4, 0), (37, 2, 8, 8),
+         (16, 2, 1, 1), (24, 2, 1, 0), (12, 4, 1, 3), (12, 2, 2, 2), (4097, 2, 2, 2), (4099, 2, 1, 1), (4098, 4, 1, 0)]
 
 
 @pytest.mark.parametrize("run,step,esize,off", APART)

@@ -38,14 +38,25 @@ def test_a_whole_tile_takes_one_round(interp, rb):  # noqa: F811
         assert lanes(interp, rb, col0, 16384)[1] == 1, (rb, col0)
 
 
-# (elements of a run, distance between them, element size): the ones sent as elements a few apart
+# (elements of a run, distance between them, element size): the ones sent as elements a few apart.  Runs that are not whole
+# numbers of the neighbours read at once only if they are long: a wave with such a group reads its elements one by one.
 @pytest.mark.parametrize("views,sizes", [
     (((32, 2, 2),), 2), (((32, 4, 1),), 1), (((32, 2, 2), (32, 2, 1)), 3),
     (((31, 2, 2),), 0), (((32, 3, 2),), 0), (((32, 2, 4),), 0), (((32, 8, 1),), 0),
     (((31, 2, 2), (40, 4, 1)), 1),                           # of one size, a launch of the other has none
     (((31, 2, 2), (100, 2, 2)), 2),                          # one of them is enough for a launch
+    (((33, 2, 2),), 0), (((101, 2, 2),), 0), (((4095, 2, 2),), 0), (((4097, 2, 2),), 2),
+    (((36, 2, 1),), 0), (((1004, 2, 1),), 0), (((4097, 2, 1),), 1), (((102, 4, 1),), 0), (((4097, 4, 1),), 1),
+    (((8, 2, 2),), 0), (((12, 2, 2),), 2), (((8, 2, 1),), 0), (((16, 2, 1),), 1), (((12, 4, 1),), 1),
+    (((1024, 4, 2),), 0), (((5000, 4, 2),), 0),              # two at a time
 ])
 def test_the_plan_says_which_launches_have_elements_a_few_apart(interp, views, sizes):  # noqa: F811
     case = Case("apart", tuple(((9, n), (n * step + 5, step), es) for n, step, es in views) + (contig((100,), 2),), 3, 4096)
     descs, keep = describe(case)
     assert interp.apart_sizes(descs, len(case.tensors), case.k, C.c_uint64(case.B)) == sizes
+
+
+@pytest.mark.parametrize("n,step,es,sizes", [(31, 2, 2, 0), (33, 2, 2, 2), (35, 4, 2, 2), (101, 2, 1, 1), (1 << 20, 4, 1, 1), (101, 3, 1, 0)])
+def test_one_run_of_elements_a_few_apart(interp, n, step, es, sizes):  # noqa: F811
+    descs, keep = describe(Case("run", (((n,), (step,), es),), 3, 4096))
+    assert interp.apart_sizes(descs, 1, 3, C.c_uint64(4096)) == sizes
