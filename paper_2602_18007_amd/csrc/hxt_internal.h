@@ -139,7 +139,7 @@ struct TensorDev {
     uint32_t all_div;                  // 1: dim_div is valid for every dim and every shape[d] <= 2^30
     uint32_t low_or;                   // ROWS_SPLIT: OR of the run length and the outer strides in bytes (their low bits
                                        // give the widest naturally aligned piece the tensor side can be accessed in)
-    uint32_t reserved;
+    uint32_t apart;                    // GENERIC: takes_apart is true for it
     FastDiv row_div;                   // ROWS: division by row_bytes
     FastDiv lane_div;                  // ROWS_SPLIT: division by the 16-byte vectors begun in a run
     FastDiv dim_div[HXT_MAX_DIMS];     // division by shape[d]: for the outer dims of a ROWS tensor, for all dims if all_div
@@ -180,26 +180,6 @@ struct RunLanes {
     }
 };
 
-// Whether a tensor of the per-element kernel whose last dim has `run` elements `step` bytes apart is sent by send_apart, which
-// takes 16 / step neighbours at a time.  Where these are not all of one run it reads them one by one, and a wave with one
-// such lane waits for all of them: views of several dims go this way if runs are whole numbers of neighbours, or so long
-// that few waves meet the end of one.  Sends of 2, 8 and 32 MiB element by element against this, pitches 3 elements more:
-//   whole numbers: bytes every other, runs of 16 9.7 -> 7.2, 15.8 -> 9.1, 44 -> 24 us, every fourth, of 12 11.6 -> 9.4, 16.8 -> 13.1,
-//     48 -> 38; bf16 every other, of 12 7.2 -> 7.3, 10.5 -> 9.0, 27 -> 24, of 200 7.1 -> 7.1, 10.3 -> 8.4, 27 -> 22 (runs of 8 were not
-//     measured);
-//   others: bytes every other, runs of 101 11.2 -> 17.9, 15.6 -> 20.3, 44 -> 43, of 1002 10.6 -> 15.0, 15.4 -> 17.3, 44 -> 39, of 4098
-//     10.9 -> 9.8, 15.4 -> 11.4, 44 -> 28; every fourth, of 101 12.1 -> 20.0, 16.8 -> 25.7, 47 -> 58, of 4098 11.5 -> 10.3, 16.4 -> 13.5, 46
-//     -> 37; bf16 every other, of 101 7.7 -> 12.0, 10.4 -> 14.9, 27 -> 34, of 2002 7.3 -> 7.5, 10.3 -> 8.9, 26 -> 23, of 4098 7.5 -> 7.3,
-//     10.3 -> 8.6, 26 -> 22;
-//   two neighbours at a time (bf16 every fourth) do not pay in several dims: runs of 1024 7.9 -> 9.2, 11.8 -> 11.4, 34.2 -> 34.2.
-HXT_HD bool takes_apart(size_t esize, int ndim, int64_t run, uint64_t step)
-{
-    if (esize > 2 || (step != 2 * esize && step != 4 * esize)) return false;
-    if (ndim == 1) return run >= 32;
-    const int64_t m = int64_t(16 / step);
-    return m > 2 && ((run >= 12 && run % m == 0) || run >= 4096);
-}
-
 constexpr int kMaxGroupTensors = 64;   // base pointers passed by value per launch
 
 struct TensorPlan {
@@ -212,6 +192,31 @@ struct TensorPlan {
     Kind kind = K_NONE;
     bool unpack_safe = true;
 };
+
+// Whether a tensor of the per-element kernel is sent by send_apart, which takes 16 / step neighbours of the last dim, `step` bytes
+// apart, at a time.  Where these are not all of one run it reads them one by one, and a wave with one such lane waits for all
+// of them: views of several dims go this way if runs are whole numbers of neighbours, or so long that few waves meet the end of
+// one, which matters the less the more tiles there are.  Sends of 2, 8 and 32 MiB element by element against this, pitches 3
+// elements more:
+//   whole numbers: bytes every other, runs of 16 9.7 -> 7.2, 15.8 -> 9.1, 44 -> 24 us, every fourth, of 12 11.6 -> 9.4, 16.8 -> 13.1,
+//     48 -> 38; bf16 every other, of 12 7.2 -> 7.3, 10.5 -> 9.0, 27 -> 24, of 200 7.1 -> 7.1, 10.3 -> 8.4, 27 -> 22 (runs of 8 were not
+//     measured); every fourth, of 1024 7.9 -> 9.2, 11.8 -> 11.4, 34.2 -> 34.2;
+//   others: bytes every other, runs of 101 11.2 -> 17.9, 15.6 -> 20.3, 44 -> 43, of 404 10.6 -> 15.0, 15.7 -> 16.7, 46 -> 37, of 1501
+//     10.2 -> 10.4, 15.4 -> 12.1, 44 -> 29, of 2002 11.0 -> 12.6, 15.5 -> 14.5, 44 -> 34, of 4098 10.9 -> 9.8, 15.4 -> 11.4, 44 -> 28; every
+//     fourth, of 101 12.1 -> 20.0, 16.8 -> 25.7, 47 -> 58, of 403 11.8 -> 15.4, 16.5 -> 18.9, 46.8 -> 46.4, of 1501 11.8 -> 11.7, 16.4 -> 14.7,
+//     47 -> 39; bf16 every other, of 101 7.7 -> 12.0, 10.4 -> 14.9, 27 -> 34, of 403 7.4 -> 9.8, 10.5 -> 11.4, 29.0 -> 28.9, of 1501 7.1 -> 8.0,
+//     10.3 -> 9.6, 26 -> 25, of 4098 7.5 -> 7.3, 10.3 -> 8.6, 26 -> 22; every fourth, of 4097 and more, never (30001 7.6 -> 8.8, 11.7 -> 12.3,
+//     34 -> 35).
+inline bool takes_apart(const TensorPlan &t)
+{
+    const int64_t run = t.shape[t.ndim - 1], step = t.stride[t.ndim - 1] * t.esize;
+    if (t.esize > 2 || (step != 2 * t.esize && step != 4 * t.esize)) return false;
+    if (t.ndim == 1) return run >= 32;
+    const int64_t m = 16 / step;
+    const bool some = t.bytes >= (uint64_t(6) << 20), many = t.bytes >= (uint64_t(24) << 20);       // tiles
+    if (run >= 12 && run % m == 0) return m > 2 || some;
+    return m > 2 && run >= (many ? 400 : (some ? 1500 : 4096));
+}
 
 struct Group {          // one kernel launch
     Kind kernel;        // K_CONTIG (serves ZERO tiles too), K_ROWS, K_ROWS_SPLIT, K_TRANSPOSE, K_GENERIC

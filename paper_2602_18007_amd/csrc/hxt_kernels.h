@@ -1943,7 +1943,7 @@ __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td,
             return td.ndim == 1 ? send_apart<E, S, CHECK, NTP, THROUGH, 1>(td, e0, nel, user, p, t.a)
                                 : send_apart<E, S, CHECK, NTP, THROUGH, 0>(td, e0, nel, user, p, t.a);
         };
-        if (takes_apart(sizeof(E), td.ndim, td.shape[td.ndim - 1], step)) {
+        if (td.apart) {
             if (step == 2 * sizeof(E)) return apart.template operator()<2>();
             return apart.template operator()<4>();
         }

@@ -213,6 +213,7 @@ static TensorDev make_tensor_dev(const TensorPlan &t)
         d.lane_div = make_fastdiv((d.row_bytes + 15) / 16);
         for (int i = 0; i < t.ndim - 1; ++i) d.dim_div[i] = make_fastdiv(uint32_t(t.shape[i]));
     }
+    d.apart = t.kind == K_GENERIC && takes_apart(t) ? 1u : 0u;
     // For the per-element kernel: all_div says that dim_div is valid for every dim, with room for a carry.
     bool small = t.ndim > 0;
     for (int i = 0; i < t.ndim; ++i) small = small && t.shape[i] >= 1 && t.shape[i] <= (int64_t(1) << 30);
@@ -438,8 +439,7 @@ int build_plan(const hxt_tensor_desc_t *descs, int n_tensors, int n_lanes, size_
                 Tile t = v[i].t;
                 t.tensor = v[i].tensor_abs - g.tensor_base;
                 g.n_tensors = std::max(g.n_tensors, t.tensor + 1);
-                if (const TensorPlan &tp = p.tensors[v[i].tensor_abs]; t.kind == K_GENERIC && takes_apart(tp.esize, tp.ndim, tp.shape[tp.ndim - 1], uint64_t(tp.stride[tp.ndim - 1]) * tp.esize))
-                    g.apart |= uint32_t(tp.esize);
+                if (t.kind == K_GENERIC && p.tdev[v[i].tensor_abs].apart) g.apart |= uint32_t(p.tensors[v[i].tensor_abs].esize);
                 if (kern == K_TRANSPOSE_SPAN) {              // one arrival at every chunk the tile touches
                     for (uint32_t e = 0; e < t.ordinal; ++e) {
                         const size_t at = 2 * (size_t(t.chunk) + e);

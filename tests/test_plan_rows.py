@@ -38,7 +38,7 @@ def test_a_whole_tile_takes_one_round(interp, rb):  # noqa: F811
         assert lanes(interp, rb, col0, 16384)[1] == 1, (rb, col0)
 
 
-# (elements of a run, distance between them, element size): the ones sent as elements a few apart.  Runs that are not whole
+# (elements of a run, distance between them, element size, runs): the ones sent as elements a few apart.  Runs that are not whole
 # numbers of the neighbours read at once only if they are long: a wave with such a group reads its elements one by one.
 @pytest.mark.parametrize("views,sizes", [
     (((32, 2, 2),), 2), (((32, 4, 1),), 1), (((32, 2, 2), (32, 2, 1)), 3),
@@ -49,9 +49,12 @@ def test_a_whole_tile_takes_one_round(interp, rb):  # noqa: F811
     (((36, 2, 1),), 0), (((1004, 2, 1),), 0), (((4097, 2, 1),), 1), (((102, 4, 1),), 0), (((4097, 4, 1),), 1),
     (((8, 2, 2),), 0), (((12, 2, 2),), 2), (((8, 2, 1),), 0), (((16, 2, 1),), 1), (((12, 4, 1),), 1),
     (((1024, 4, 2),), 0), (((5000, 4, 2),), 0),              # two at a time
+    (((1499, 2, 2, 2200),), 0), (((1501, 2, 2, 2090),), 0), (((1501, 2, 2, 2100),), 2),        # either side of 6 MiB
+    (((1501, 2, 1, 4190),), 0), (((1501, 2, 1, 4200),), 1), (((1024, 4, 2, 3071),), 0), (((1024, 4, 2, 3072),), 2), (((5001, 4, 2, 700),), 0),
+    (((401, 2, 2, 31370),), 0), (((401, 2, 2, 31390),), 2), (((399, 2, 2, 32000),), 0),        # of 24 MiB
 ])
 def test_the_plan_says_which_launches_have_elements_a_few_apart(interp, views, sizes):  # noqa: F811
-    case = Case("apart", tuple(((9, n), (n * step + 5, step), es) for n, step, es in views) + (contig((100,), 2),), 3, 4096)
+    case = Case("apart", tuple(((rows[0] if rows else 9, n), (n * step + 5, step), es) for n, step, es, *rows in views) + (contig((100,), 2),), 3, 4096)
     descs, keep = describe(case)
     assert interp.apart_sizes(descs, len(case.tensors), case.k, C.c_uint64(case.B)) == sizes
 
