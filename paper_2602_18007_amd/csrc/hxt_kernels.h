@@ -1074,7 +1074,8 @@ __device__ __forceinline__ Sums2 rows_split_pieces(const Tile &t, const TensorDe
 // Rows of bf16 at odd pitches, 32 MiB, pack / unpack, in pieces of 2 bytes against vectors (tensors of three messages in
 // turn): 37 elements 18.8 / 36.8 -> 18.9 / 24.8 us, 101 elements 17.3 / 24.2 -> 16.1 / 18.5, 1003 elements 17.3 / 19.3 ->
 // 15.4 / 14.8.  Pieces of 4 bytes: 101 f32 15.0 / 18.2 against 16.0 / 15.7, 102 bf16 unpack 21.2 against 18.6 (8 MiB 6.4 and
-// 6.5); of 8 bytes: 100 bf16 15.1 / 17.2 against 16.1 / 18.8: sending, pieces of 4 and 8 bytes are the faster ones, receiving,
+// 6.5; short runs lose at small sizes, 5 f32 8 MiB 8.4 and 9.1, 9 f32 7.8 and 8.2, and gain from there on, 32 MiB 30.6 and 28.6, 27.2
+// and 24.7); of 8 bytes: 100 bf16 15.1 / 17.2 against 16.1 / 18.8: sending, pieces of 4 and 8 bytes are the faster ones, receiving,
 // those of 8.  Rows much longer than a tile, 66 MB of bf16 at odd pitches, unpack in pieces of 2 bytes against vectors: 50257
 // elements 29.6 -> 23.6 us, 151643 30.4 -> 23.6, a million 30.2 -> 23.0 (with tags 36.6 -> 25.3, 36.2 -> 25.5, 36.7 -> 24.9).
 template <bool UNPACK, int CHECK, bool NTP, bool TWO_D>
@@ -1614,8 +1615,10 @@ __global__ __launch_bounds__(kThreads) void k_transpose(const Tile *__restrict__
 // What k_transpose_span keeps in LDS beside the tile, for tiles of T rows.  Per row: packed offset of byte x is p0 + x for
 // x < first, p1 + x from there on (first is a whole tile row or more where the row meets no border); at: entry of the
 // row's first chunk; rem: position of its first byte in that chunk (for the weights of the sums).
-// A tile's rows meet at most 2 T chunks; SPARE entries more change nothing but where the rest lies (k_message has no room for
-// them; here, without them, [143, 96522] of two bytes with tags took 53.6 us a pair instead of 52.4).
+// A tile's rows meet at most 2 T chunks.  SPARE entries more change nothing but where the rest lies, and no reason is known for
+// what that does to transposes with tags (sums do not change): pack + unpack of two bytes, without them against with them, [143,
+// 96522] 54.1 and 52.7 us, [500, 33000] 52.3 and 51.7, [256, 65536] 34.6 and 35.2, [4000, 4000] 34.3 and 34.7; of one byte [256,
+// 65536] 23.6 and 23.3.  k_transpose_span keeps the layout that it has always had; k_message has no room for them.
 template <uint32_t T, int CHECK, uint32_t SPARE = 2>
 struct SpanLds {
     static constexpr uint32_t MAXC = 2 * T + SPARE;
@@ -1926,9 +1929,11 @@ __device__ __noinline__ Sums2 generic_span_wide(const TensorDev &td, uint64_t e0
     return acc;
 }
 
-// APART: with send_apart, where takes_apart finds use for it.  (Elsewhere its registers and code only slow the others down: every
-// third column of a 1.1 MB matrix, pack + unpack, 13.75 us with it and 13.54 without; a bundle of 7 MB with tags in k_message,
-// which has no room for it, 24.4 and 23.0.)
+// APART: with send_apart, where takes_apart finds use for it.  Elsewhere its registers (65 to 79 instead of 44 to 51: 6 or 7 waves
+// per SIMD instead of 8) only slow the others down: sends of every third and fifth element, without it and with it, bytes with
+// tags 1 MB 10.6 -> 11.1, 11.2 -> 11.8, 11.5 -> 12.0, 4 MB 13.6 -> 14.0, 13.4 -> 13.8, 14.1 -> 14.5, bf16 1 MB 7.1 -> 7.3, with tags
+// 8.1 -> 8.3; from 16 MB on there is no difference.  A bundle of 7 MB with tags in k_message, which has no room for it, 23.0 ->
+// 24.4 a pair.
 template <typename E, bool UNPACK, int CHECK, bool NTP, bool THROUGH, bool APART>
 __device__ __forceinline__ Sums2 generic_any(const Tile &t, const TensorDev &td, uint8_t *user, uint8_t *packed)
 {

@@ -63,14 +63,17 @@ inline bool elements_through(int esize, uint64_t bytes)
     return esize < 8 && bytes > kElementsThrough && (esize > 1 || bytes <= kBytesThrough);
 }
 
-// Stream bytes up to which a message that would take several launches goes out in one (k_message).  Measured, pack + unpack
-// with sums, launches of their own against one:
-//   three launches or more: six tensors of five kinds 4 MiB 33 -> 14 us, 16 MiB 46 -> 25, 48 MiB 64 -> 50, 64 MiB 75 -> 64,
-//     80 MiB 84 -> 76; three transposes of different element sizes 4 MiB 30 -> 16, 48 MiB 53 -> 48, 64 MiB 77 -> 77, but
-//     80 MiB 90 -> 94.
-//   two, where the gain is one launch each way and k_message's residency (3 or 4 workgroups per CU) soon costs more: padded
-//     rows and a mask 4 MiB 16 -> 11, 12 MiB 23 -> 17; two transposes 12 MiB 27 -> 19; every other column and a mask 12 MiB
-//     34 -> 28 (with tags 39 -> 34), but its pack alone 16 MiB with tags 20.4 -> 22.5 and 24 MiB 21.4 -> 24.7.
+// Stream bytes up to which a message that would take several launches goes out in one (k_message, 4 workgroups per CU).
+// Measured, pack + unpack with sums, launches of their own against one:
+//   three launches or more: six tensors of five kinds 16 MiB 64 -> 28 us, 48 MiB 92 -> 59, 64 MiB 105 -> 70 (with tags 128 ->
+//     79), 80 MiB 121 -> 86; three transposes of different element sizes 4 MiB 33 -> 15, 48 MiB 76 -> 63, 64 MiB 90 -> 78, 80 MiB
+//     112 -> 95; every other column, odd rows and a mask 16 MiB 40 -> 27, 64 MiB 83 -> 75, but the pack alone 38.3 -> 38.4 there
+//     and 43.9 -> 48.0 at 80 MiB (98 -> 90 a pair): the line lies where sending alone would lose.
+//   two, where the gain is one launch each way: odd rows and a mask 8 MiB 19 -> 15, 12 MiB 22 -> 17; two transposes 12 MiB 28 ->
+//     18; every third column and a mask 12 MiB 38 -> 33.  Every other column and a mask, where k_message goes without send_apart:
+//     4 MiB 18.2 -> 16.0, 12 MiB 28.9 -> 27.4 (with tags 33.4 -> 30.7) with the pack alone 12.1 -> 13.2, 16 MiB 35.4 -> 33.7 and
+//     14.6 -> 15.7, 24 MiB 45.0 -> 48.2 and 18.4 -> 23.9.  Other pairs would gain beyond the line too (16 MiB: odd rows and a mask
+//     28 -> 21, two transposes 25 -> 17).
 constexpr uint64_t kOneLaunchLimit = uint64_t(64) << 20;
 constexpr uint64_t kOneLaunchForTwoLimit = uint64_t(12) << 20;
 
